@@ -7,14 +7,14 @@
 // about 7 % faster than the 32x32x16 form under the chip's power limit: it moves half as many
 // accumulator registers per flop).
 //
-// An operand tile is staged in LDS in one of two layouts, chosen by how the operand
-// lies in memory relative to the contraction index k:
-//   KC ("k contiguous"): memory is [row][k]; LDS holds [256 rows][64 k] (128 B per row,
-//       16-byte chunks XOR-swizzled by (row >> 1) & 7); a lane's MFMA fragment (8
-//       consecutive k of one row) is one ds_read_b128.
-//   KS ("k strided"):    memory is [k][col]; LDS holds [64 k][256 cols] (512 B per k-row,
-//       16-byte chunks XOR-swizzled by ((k >> 3) & 3) << 1 | (k & 3) << 3); the fragment is
-//       gathered with two ds_read_b64_tr_b16 transpose reads (4 consecutive k of one column each).
+// Tiles go from global memory straight into LDS (buffer_load_dwordx4 ... lds).  Such a load writes 64 x 16
+// consecutive bytes of LDS, so a layout's swizzle is applied to the global address each lane reads.  The layout of
+// an operand tile depends on how the operand lies in memory relative to the contraction index k:
+//   KC ("k contiguous"): memory is [row][k]; LDS holds rows of 64 k (128 B), 16-byte chunks XOR-swizzled by
+//       (row >> 1) & 7; a lane's MFMA fragment (8 consecutive k of one row) is one ds_read_b128.
+//   KS ("k strided"):    memory is [k][col]; LDS holds k-rows, 16-byte chunks XOR-swizzled by a function of k
+//       (ks_swizzle); the fragment is gathered with two ds_read_b64_tr_b16 transpose reads (4 consecutive k of
+//       one column each).
 // Lane layouts used (checked on the hardware): for v_mfma_f32_16x16x32_bf16 lane l
 // supplies row l % 16, k = 8 * (l / 16) .. + 7 of either operand; accumulator register v
 // of lane l is element (4 * (l / 16) + v, l % 16).  ds_read_b64_tr_b16
@@ -43,7 +43,8 @@ constexpr int WAVE_M = 128;     // rows of the output tile one wave owns
 constexpr int WAVE_N = 64;
 constexpr int MT = WAVE_M / 16; // 16 x 16 MFMA tiles per wave along M: 8
 constexpr int NT = WAVE_N / 16; // and along N: 4
-constexpr int OPERAND_TILE_BYTES = 256 * TILE_K * 2;           // 32 KiB
+constexpr int HALF_TILE_BYTES = 128 * TILE_K * 2;              // half of an operand tile: 16 KiB
+constexpr int OPERAND_TILE_BYTES = 2 * HALF_TILE_BYTES;        // 32 KiB
 constexpr int STAGE_BYTES = 2 * OPERAND_TILE_BYTES;            // A + B
 constexpr int LDS_BYTES = 2 * STAGE_BYTES;                     // double buffered: 128 KiB
 
@@ -51,271 +52,238 @@ enum { KC = 0, KS = 1 };
 
 // One GEMM operand in global memory (16-bit elements), addressed through a buffer resource:
 //   KC: element (row, k) at base[row * ld + k];   KS: element (k, col) at base[k * ld + col].
-// Loads are buffer_load_dwordx4 with a scalar resource, a scalar offset (the k-step and the tile
-// quarter) and ONE 32-bit per-lane offset per operand that never changes inside the main loop.
+// A load has a scalar resource, a scalar offset (the k-step and the part of the tile) and ONE 32-bit per-lane
+// offset per operand that never changes inside the main loop.
 // The resource covers exactly rows x cols of the matrix: a tile may hang over its end (ragged row or
 // class counts, the last k-step of a contraction) and the overhang reads as zeros, as the hardware
 // bounds check returns 0 beyond the resource.  Offsets are 32-bit: (rows + 256) * ld * 2 bytes must stay
 // below 4 GiB (checked on the host).
 struct Operand {
-    __amdgpu_buffer_rsrc_t rsrc;
+    u32x4 rsrc;
     uint32_t ld;        // row pitch in elements
 };
 
 // `rows` x `cols` elements are valid (KC: rows x k extent; KS: k extent x columns).
 __device__ __forceinline__ Operand make_operand(const uint16_t* base, int64_t ld, int64_t rows, int64_t cols) {
     const int64_t bytes = ((rows - 1) * ld + cols) * 2;
+    const uint64_t p = reinterpret_cast<uint64_t>(base);
     Operand op;
-    op.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0, (int)(uint32_t)bytes, 0x00020000);
+    op.rsrc = u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, (uint32_t)bytes, 0x00020000u};
     op.ld = (uint32_t)ld;
     return op;
 }
 
-// ---- global -> registers -> LDS staging ---------------------------------------------------
-// A 32 KiB operand tile is 2048 chunks of 16 bytes; thread t moves chunks t, t + 512, t + 1024 and
-// t + 1536.  Chunk set j (one chunk per thread) is "quarter j" of the tile: rows 64 j .. 64 j + 63 of
-// a KC tile, k-rows 16 j .. 16 j + 15 of a KS tile.
+// ---- global -> LDS ------------------------------------------------------------------------------
+// 16 bytes per lane from `voff` (per lane) + `soff` (uniform) of the operand to LDS byte lds_off + 16 * lane.
+// Inline assembly, because for the builtin the compiler makes every later LDS read wait for ALL loads in flight;
+// here the main loop counts them itself (wait_counts).  The load is complete in LDS when vmcnt says so.
+__device__ __forceinline__ void load_to_lds(const Operand& op, uint32_t voff, uint32_t soff, uint32_t lds_off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds_off), "v"(voff), "s"(op.rsrc), "s"(soff) : "memory");
+}
+
+// LDS byte offset of a pointer into a __shared__ array.
+__device__ __forceinline__ uint32_t lds_offset(const char* lds) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds;
+}
+
+// Waits until at most VM vector-memory operations and LG LDS operations of this wave are outstanding.
+template <int VM, int LG>
+__device__ __forceinline__ void wait_counts() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | 0x70 | (LG << 8));
+    __builtin_amdgcn_sched_barrier(0);
+}
+constexpr int NO_VM_WAIT = 63, NO_LG_WAIT = 15;
+
+// Workgroup barrier that orders nothing by itself (no implied waits): the caller has waited for what it needs.
+__device__ __forceinline__ void raw_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
 
 // Chunk swizzle of a KS tile.  A transposing read is served half a wave at a time; the 32 lanes of a
 // half cover 4 k-rows (k & 3) in each of 2 lane blocks 8 k-rows apart ((k >> 3) & 1), two adjacent
 // chunks and both 8-byte halves of a chunk each.  Those 16 (k-row, chunk) pairs must fall into 16
-// different chunks modulo 16 (256 bytes span all banks): k & 3 goes to chunk bits 2-3, (k >> 3) & 1 to
-// bit 1, the two adjacent chunks differ in bit 0.  Bit 4 of k only separates the two halves of the wave.
-// Bits 2 and 5 of k are left out so that the reads 4 and 32 k-rows further on keep the same pattern.
-__device__ __forceinline__ int ks_swizzle(int k) {
-    return (((k >> 3) & 1) << 1) | ((k & 3) << 2) | (((k >> 4) & 1) << 4);
-}
-
-// Per-lane byte offset of a thread's chunk in quarter 0 of the tile whose first row (KC) or first
-// column (KS) is o0, at k = 0.
-template <int KIND>
-__device__ __forceinline__ uint32_t tile_lane_offset(const Operand& op, int o0, int tid) {
-    if (KIND == KC) return ((uint32_t)(o0 + (tid >> 3)) * op.ld + (uint32_t)((tid & 7) * 8)) * 2u;
-    return ((uint32_t)(tid >> 5) * op.ld + (uint32_t)(o0 + (tid & 31) * 8)) * 2u;
-}
-
-// Loads this thread's chunk of quarter j of the tile at contraction offset k0.
-template <int KIND>
-__device__ __forceinline__ u32x4 quarter_g2r(const Operand& op, uint32_t lane_off, int k0, int j) {
-    const uint32_t soff = KIND == KC ? ((uint32_t)k0 + (uint32_t)(64 * j) * op.ld) * 2u
-                                     : ((uint32_t)(k0 + 16 * j) * op.ld) * 2u;
-    return __builtin_amdgcn_raw_buffer_load_b128(op.rsrc, (int)lane_off, (int)soff, 0);
-}
-
-template <int KIND>
-__device__ __forceinline__ void quarter_r2s(char* lds, const u32x4& v, int tid, int j) {
-    const int q = tid + NTHREADS * j;
-    int off;
-    if (KIND == KC) {
-        const int row = q >> 3, ch = q & 7;
-        off = row * 128 + ((ch ^ ((row >> 1) & 7)) << 4);
-    } else {
-        const int kr = q >> 5, ch = q & 31;
-        off = kr * 512 + ((ch ^ ks_swizzle(kr)) << 4);
-    }
-    *reinterpret_cast<u32x4*>(lds + off) = v;
-}
-
-// ---- LDS -> MFMA fragments ------------------------------------------------------------------
-
-// Per-lane byte offsets into an operand tile, computed once per kernel.
-template <int KIND, int NTILES>
-struct FragAddr {
-    int off[KIND == KC ? 2 : NTILES];   // KC: one per 32-wide k-substep; KS: one per 16-wide tile
-
-    // `w0` = first row/column of this wave's sub-tile inside the 256-wide operand tile.
-    __device__ __forceinline__ void init(int lane, int w0) {
-        const int i = lane & 15, g = lane >> 4;
-        if (KIND == KC) {
-            const int sw = (i >> 1) & 7;            // w0 and 16 * t are multiples of 16: no effect on the swizzle
-#pragma unroll
-            for (int s = 0; s < 2; ++s) off[s] = (w0 + i) * 128 + (((4 * s + g) ^ sw) << 4);
-        } else {
-            const int x = i >> 2;                    // k-row within the group of four == (k & 3)
-            const int krow = 8 * g + x;              // substeps add multiples of 32, the second read 4
-#pragma unroll
-            for (int t = 0; t < NTILES; ++t) {
-                const int col = w0 + 16 * t + 4 * (i & 3);
-                off[t] = krow * 512 + (((col >> 3) ^ ks_swizzle(krow)) << 4) + ((col & 7) << 1);
-            }
-        }
-    }
-
-    // Fragment of 16-wide tile t for k-substep s (32 k each) from the operand tile at `lds`.
-    __device__ __forceinline__ bf16x8 load(const char* lds, int t, int s) const {
-        if (KIND == KC) {
-            return *reinterpret_cast<const bf16x8*>(lds + off[s] + t * (16 * 128));
-        } else {
-            typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
-            const char* p = lds + off[t] + s * (32 * 512);
-            s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
-            s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * 512));
-            s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            return __builtin_bit_cast(bf16x8, v);
-        }
-    }
-};
+// different chunks modulo 16 (256 bytes span all banks, a k-row is 256 bytes): k & 3 goes to chunk bits 2-3,
+// (k >> 3) & 1 to bit 1, the two adjacent chunks differ in bit 0.  Bits 2 and 5 of k are left out so that the
+// reads 4 and 32 k-rows further on keep the same pattern.
+__device__ __forceinline__ int ks_swizzle(int k) { return (((k >> 3) & 1) << 1) | ((k & 3) << 2); }
 
 // ---- main loop ---------------------------------------------------------------------------------
 
-// Scheduling hint for one slot of the software pipeline: N MFMAs; NR LDS reads go with the first
-// MFMAs (so that they land before the slot ends), then NW LDS writes, then NV global loads with the
-// last MFMAs.  The instructions are written before the hint; the hint only fixes their interleaving
-// (LDS reads stay ahead of LDS writes, as the compiler must assume they may alias).
-template <int I, int N, int NR, int NW, int NV>
-struct SlotSched {
-    static __device__ __forceinline__ void apply() {
-        constexpr int H = (N + 1) / 2 + 1;
-        constexpr int r = I < H ? (NR * (I + 1) + H - 1) / H - (NR * I + H - 1) / H : 0;
-        constexpr int w = (I >= N - 1 - NW && I < N - 1) ? 1 : 0;
-        constexpr int v = (I >= N - NV) ? 1 : 0;
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                        // one MFMA
-        if constexpr (r > 0) __builtin_amdgcn_sched_group_barrier(0x100, r, 0);   // LDS reads
-        if constexpr (w > 0) __builtin_amdgcn_sched_group_barrier(0x200, w, 0);   // LDS writes
-        if constexpr (v > 0) __builtin_amdgcn_sched_group_barrier(0x020, v, 0);   // global loads
-        if constexpr (I + 1 < N) SlotSched<I + 1, N, NR, NW, NV>::apply();
-        else __builtin_amdgcn_sched_barrier(0);      // nothing moves across the end of a slot
-    }
-};
-
 // acc[mt][nt] += A(m0 .. m0+255, k) * B(n0 .. n0+255, k) for k in [k_begin, k_begin + 64 * k_steps).
-// For a KC operand o0 is its first row; for a KS operand its first column.
+// A is KC, m0 its first row; for a KC operand B n0 is its first row, for a KS one its first column.
+// A wave's M tiles are rows WAVE_M * wm + 16 * mt of the tile, its N tiles columns wave_col<BKIND>(wn, nt).
 // Ends with a workgroup barrier, so LDS may be reused by the caller right away.
 //
-// Software pipeline.  LDS holds two stages (k-step j in stage j & 1).  Iteration j multiplies
-// k-step j in four slots of 16 MFMAs each: (k-substep 0 | 1 of 32) x (upper | lower 64 rows of the
-// wave's sub-tile); the fragments of a slot are read from LDS one slot ahead (A fragments every slot,
-// B fragments every other slot).  The tiles are staged through registers one quarter at a time,
-// so that LDS writes and global loads are spread evenly over the iteration and every global load
-// has a full iteration to land:
-//   slot x = 0, 1, 2:  quarter x of k-step j + 1: registers -> stage (j + 1) & 1; then the same
-//                      registers <- quarter x of k-step j + 2 from global memory
-//   barrier            (every wave has finished reading stage j & 1 and writing stage (j + 1) & 1)
-//   slot 3:            quarter 3 of k-step j + 2: registers -> stage j & 1 (free now); then the
-//                      registers <- quarter 3 of k-step j + 3
-// k-steps beyond the last are clamped to the last one (a harmless reload).  Rows, columns or k beyond
-// an operand's extent read as zeros.
+// Ping-pong between the two waves of a SIMD.  Waves 0-3 (M half 0) and 4-7 (M half 1) sit on the four SIMDs in
+// pairs.  A k-step is four phases, one per quadrant of the wave's 128 x 64 sub-tile (A half x B half, 16 MFMAs
+// each, both k-substeps); a phase is a LOAD slot (LDS fragments for its MFMAs, global -> LDS loads for a later
+// k-step, waits) and an MFMA slot, with a workgroup barrier after each.  The second half of the waves runs one
+// slot behind, so that in every slot one wave of a SIMD feeds the matrix core while the other one reads LDS and
+// issues loads: neither competes with the other for issue slots, and every wait is covered by the partner's
+// 256 MFMA cycles.
+//
+// LDS holds two stages (k-step j in stage j & 1) of four 16 KiB half tiles (A0 A1 B0 B1; half h of A holds the 64
+// rows of the h-th half of each wave row, and likewise for the columns of B).  Each phase reads one half tile
+// and the phase after it refills that half tile with k-step j + 2:
+//   phase   MFMAs      reads          loads (2 per wave)
+//     0     A0 x B0    A0(j)          B0(j + 2)
+//     1     A0 x B1    B1(j)          A0(j + 2)
+//     2     A1 x B0    A1(j)          B1(j + 2)
+//     3     A1 x B1    B0(j + 1)      A1(j + 2)
+// A wave's reads of phase p are complete (lgkmcnt 0) before the barrier that ends its LOAD slot; the refill is
+// issued after a later barrier than that of either half of the waves.  Every half tile is read seven phases after
+// its loads were issued: at the end of a LOAD slot, what the next phase reads has landed when at most the
+// 6 phases x 2 loads issued since are outstanding (vmcnt 12), so a load has more than 3000 cycles to arrive.
+//
+// Measured (4096 x 4096 x 8192, normal random operands, against the loop that went through registers and left the
+// interleaving of the two waves to the hardware): KC 1335 -> 1497, KS 1285 -> 1442 TFLOP/s; all ones 1866 ->
+// 2140.  Two phases of 32 MFMAs: 1467; raising the wave priority (s_setprio) in the MFMA slots: 1486.
 typedef f32x4 acc_t[MT][NT];
+
+// First column of N tile nt of wave column wn in the 256-wide tile.  The B half tiles are chosen so that their
+// global loads are whole lines: a KS half tile is 128 adjacent columns.
+template <int BKIND>
+__device__ __forceinline__ int wave_col(int wn, int nt) {
+    return BKIND == KC ? WAVE_N * wn + 16 * nt : 128 * (nt >> 1) + 32 * wn + 16 * (nt & 1);
+}
 
 // `descending` (uniform over the workgroup): walk the k-steps from the last to the first.  Tiles that follow each
 // other on a compute unit and share an operand panel can alternate the direction, so that the second finds
 // the end of the panel, which the first has just read, still in the L2.
-template <int AKIND, int BKIND>
+template <int BKIND>
 __device__ __forceinline__ void gemm_mainloop(acc_t& acc, const Operand& A, const Operand& Bop,
                                               int m0, int n0, int k_begin, int k_steps, char* lds,
                                               bool descending = false) {
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
-    constexpr int HM = MT / 2;                                   // M tiles per slot
-    constexpr int RA = HM * (AKIND == KC ? 1 : 2);               // LDS reads for a slot's A fragments
-    constexpr int RB = NT * (BKIND == KC ? 1 : 2);               // and for a substep's B fragments
-    constexpr int NMFMA = HM * NT;
+    const int i = lane & 15, g = lane >> 4;
     const int last = k_steps - 1;
-
-    FragAddr<AKIND, MT> fa;
-    FragAddr<BKIND, NT> fb;
-    fa.init(lane, wm * WAVE_M);
-    fb.init(lane, wn * WAVE_N);
-
-    u32x4 sa[4], sb[4];
-    bf16x8 af[2][HM], bfr[2][NT];
-
-    auto load_a = [&](int set, const char* la, int s, int half) {
-#pragma unroll
-        for (int t = 0; t < HM; ++t) af[set][t] = fa.load(la, HM * half + t, s);
-    };
-    auto load_b = [&](int set, const char* la, int s) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) bfr[set][t] = fb.load(la + OPERAND_TILE_BYTES, t, s);
-    };
-    auto mfmas = [&](int aset, int bset, int half) {
-#pragma unroll
-        for (int i = 0; i < HM; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-                acc[HM * half + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[aset][i], bfr[bset][j],
-                                                                                acc[HM * half + i][j], 0, 0, 0);
-    };
     const int k_first = descending ? k_begin + last * TILE_K : k_begin;
     const int k_stride = descending ? -TILE_K : TILE_K;
-    auto kofs = [&](int step) { return k_first + (step < last ? step : last) * k_stride; };
-    const uint32_t a_off = tile_lane_offset<AKIND>(A, m0, tid);
-    const uint32_t b_off = tile_lane_offset<BKIND>(Bop, n0, tid);
-    auto g2r = [&](int quarter, int step) {
-        sa[quarter] = quarter_g2r<AKIND>(A, a_off, kofs(step), quarter);
-        sb[quarter] = quarter_g2r<BKIND>(Bop, b_off, kofs(step), quarter);
+
+    // Global -> LDS.  A half tile is 16 loads of 1 KiB; wave w issues loads w and w + 8.
+    //   KC: a load is 8 rows of 128 bytes; LDS rows 8 w .. + 7 and 64 + 8 w .. + 7 of the half tile.
+    //       A: half tile row r is tile row 128 * (r / 64) + 64 * half + r % 64;
+    //       B: half tile row r is tile row  64 * (r / 32) + 32 * half + r % 32.
+    //   KS: a load is 4 k-rows of 256 bytes: k-rows 4 w .. + 3 and 32 + 4 w .. + 3, columns 128 * half .. + 127.
+    const int r8 = lane >> 3, kc_chunk = (lane & 7) ^ ((((8 * wave + r8) >> 1)) & 7);
+    const uint32_t a_lane = ((uint32_t)(m0 + 8 * wave + r8) * A.ld + (uint32_t)(8 * kc_chunk)) * 2u;
+    const uint32_t a_half = 128u * A.ld, a_second = 256u * A.ld;                  // 64 and 128 rows, in bytes
+    const int k4 = 4 * wave + (lane >> 4);
+    const uint32_t b_lane = BKIND == KC
+        ? ((uint32_t)(n0 + 64 * (wave >> 2) + 8 * (wave & 3) + r8) * Bop.ld + (uint32_t)(8 * kc_chunk)) * 2u
+        : ((uint32_t)k4 * Bop.ld + (uint32_t)(n0 + 8 * ((lane & 15) ^ ks_swizzle(k4)))) * 2u;
+    const uint32_t b_half = BKIND == KC ? 64u * Bop.ld : 256u;                    // 32 rows | 128 columns
+    const uint32_t b_second = BKIND == KC ? 256u * Bop.ld : 64u * Bop.ld;         // 128 rows | 32 k-rows
+    const uint32_t lds_wave = lds_offset(lds) + 1024u * (uint32_t)wave;
+    auto load_a = [&](int half, int step) {
+        const uint32_t src = (uint32_t)(k_first + step * k_stride) * 2u + half * a_half;
+        const uint32_t dst = lds_wave + (step & 1) * STAGE_BYTES + half * HALF_TILE_BYTES;
+        load_to_lds(A, a_lane, src, dst);
+        load_to_lds(A, a_lane, src + a_second, dst + HALF_TILE_BYTES / 2);
     };
-    auto r2s = [&](int quarter, char* stage) {
-        quarter_r2s<AKIND>(stage, sa[quarter], tid, quarter);
-        quarter_r2s<BKIND>(stage + OPERAND_TILE_BYTES, sb[quarter], tid, quarter);
+    auto load_b = [&](int half, int step) {
+        const uint32_t k = (uint32_t)(k_first + step * k_stride);
+        const uint32_t src = (BKIND == KC ? k : k * Bop.ld) * 2u + half * b_half;
+        const uint32_t dst = lds_wave + (step & 1) * STAGE_BYTES + OPERAND_TILE_BYTES + half * HALF_TILE_BYTES;
+        load_to_lds(Bop, b_lane, src, dst);
+        load_to_lds(Bop, b_lane, src + b_second, dst + HALF_TILE_BYTES / 2);
     };
 
-    // prologue: stage 0 <- k-step 0; quarter 3 of k-step 1 -> stage 1; registers <- what the loop expects.
-    // Quarter 3 of k-step 1 is fetched together with k-step 0 (into spare registers), so the fill costs
-    // one global-memory latency, not two.
+    // LDS -> fragments: af[tile of the half][k-substep], bf0 / bf1 the same for the two halves of B
+    int a_frag[2], b_frag[2];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) g2r(q, 0);
-    const u32x4 a31 = quarter_g2r<AKIND>(A, a_off, kofs(1), 3);
-    const u32x4 b31 = quarter_g2r<BKIND>(Bop, b_off, kofs(1), 3);
+    for (int s = 0; s < 2; ++s) {
+        const int chunk = (4 * s + g) ^ (i >> 1);
+        a_frag[s] = (64 * wm + i) * 128 + 16 * chunk;
+        if (BKIND == KC) {
+            b_frag[s] = OPERAND_TILE_BYTES + (32 * wn + i) * 128 + 16 * chunk;
+        } else {                                       // s counts the two 16-wide tiles here
+            const int krow = 8 * g + (i >> 2), col = 32 * wn + 16 * s + 4 * (i & 3);
+            b_frag[s] = OPERAND_TILE_BYTES + krow * 256 + (((col >> 3) ^ ks_swizzle(krow)) << 4) + ((col & 7) << 1);
+        }
+    }
+    bf16x8 af[MT / 2][2], bf0[NT / 2][2], bf1[NT / 2][2];
+    auto read_a = [&](int half, int stage) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) r2s(q, lds);
-    quarter_r2s<AKIND>(lds + STAGE_BYTES, a31, tid, 3);
-    quarter_r2s<BKIND>(lds + STAGE_BYTES + OPERAND_TILE_BYTES, b31, tid, 3);
+        for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int q = 0; q < 3; ++q) g2r(q, 1);
-    g2r(3, 2);
-    __syncthreads();
-    load_a(0, lds, 0, 0);
-    load_b(0, lds, 0);
+            for (int t = 0; t < MT / 2; ++t)
+                af[t][s] = *reinterpret_cast<const bf16x8*>(lds + (a_frag[s] + stage) + half * HALF_TILE_BYTES + t * 2048);
+    };
+    auto read_b = [&](bf16x8 (&bf)[NT / 2][2], int half, int stage) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < NT / 2; ++t) {
+                if (BKIND == KC) {
+                    bf[t][s] = *reinterpret_cast<const bf16x8*>(lds + (b_frag[s] + stage) + half * HALF_TILE_BYTES + t * 2048);
+                } else {
+                    typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
+                    const char* p = lds + (b_frag[t] + stage) + half * HALF_TILE_BYTES + s * (32 * 256);
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * 256));
+                    bf[t][s] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+            }
+    };
+    auto mfmas = [&](int a_h, int b_h, bf16x8 (&bf)[NT / 2][2]) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int x = 0; x < MT / 2; ++x)
+#pragma unroll
+                for (int y = 0; y < NT / 2; ++y) {
+                    f32x4& c = acc[MT / 2 * a_h + x][NT / 2 * b_h + y];
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[x][s], bf[y][s], c, 0, 0, 0);
+                }
+        __builtin_amdgcn_sched_barrier(0);
+    };
 
-    for (int j = 0; j < last; ++j) {
-        char* lc = lds + (j & 1) * STAGE_BYTES;          // stage of k-step j
-        char* ln = lds + ((j + 1) & 1) * STAGE_BYTES;    // stage of k-step j + 1
-        // slot 0: substep 0, upper rows
-        load_a(1, lc, 0, 1);
-        mfmas(0, 0, 0);
-        r2s(0, ln);
-        g2r(0, j + 2);
-        SlotSched<0, NMFMA, RA, 2, 2>::apply();
-        // slot 1: substep 0, lower rows
-        load_a(0, lc, 1, 0);
-        load_b(1, lc, 1);
-        mfmas(1, 0, 1);
-        r2s(1, ln);
-        g2r(1, j + 2);
-        SlotSched<0, NMFMA, RA + RB, 2, 2>::apply();
-        // slot 2: substep 1, upper rows
-        load_a(1, lc, 1, 1);
-        mfmas(0, 1, 0);
-        r2s(2, ln);
-        g2r(2, j + 2);
-        SlotSched<0, NMFMA, RA, 2, 2>::apply();
-        __syncthreads();
-        // slot 3: substep 1, lower rows
-        load_a(0, ln, 0, 0);
-        load_b(0, ln, 0);
-        mfmas(1, 1, 1);
-        r2s(3, lc);
-        g2r(3, j + 3);
-        SlotSched<0, NMFMA, RA + RB, 2, 2>::apply();
+    // k-steps 0 and 1 in the order in which the loop would have issued their loads; then B0(0), which the loop
+    // reads one phase ahead
+    load_b(0, 0); load_a(0, 0); load_b(1, 0); load_a(1, 0);
+    if (last > 0) {
+        load_b(0, 1); load_a(0, 1); load_b(1, 1); load_a(1, 1);
+        wait_counts<12, NO_LG_WAIT>();
+    } else {
+        wait_counts<4, NO_LG_WAIT>();
     }
-    {   // last k-step: nothing left to stage
-        const char* lc = lds + (last & 1) * STAGE_BYTES;
-        load_a(1, lc, 0, 1);
-        mfmas(0, 0, 0);
-        SlotSched<0, NMFMA, RA, 0, 0>::apply();
-        load_a(0, lc, 1, 0);
-        load_b(1, lc, 1);
-        mfmas(1, 0, 1);
-        SlotSched<0, NMFMA, RA + RB, 0, 0>::apply();
-        load_a(1, lc, 1, 1);
-        mfmas(0, 1, 0);
-        SlotSched<0, NMFMA, RA, 0, 0>::apply();
-        mfmas(1, 1, 1);
+    raw_barrier();
+    read_b(bf0, 0, 0);
+    wait_counts<NO_VM_WAIT, 0>();
+    raw_barrier();
+    if (wm == 1) raw_barrier();                        // the second half of the waves falls one slot behind
+
+    for (int j = 0; j < last - 1; ++j) {
+        const int cur = (j & 1) * STAGE_BYTES, nxt = STAGE_BYTES - cur;
+        read_a(0, cur);      load_b(0, j + 2); wait_counts<12, 0>(); raw_barrier(); mfmas(0, 0, bf0); raw_barrier();
+        read_b(bf1, 1, cur); load_a(0, j + 2); wait_counts<12, 0>(); raw_barrier(); mfmas(0, 1, bf1); raw_barrier();
+        read_a(1, cur);      load_b(1, j + 2); wait_counts<12, 0>(); raw_barrier(); mfmas(1, 0, bf0); raw_barrier();
+        read_b(bf0, 0, nxt); load_a(1, j + 2); wait_counts<12, 0>(); raw_barrier(); mfmas(1, 1, bf1); raw_barrier();
     }
-    __syncthreads();
+    if (last > 0) {          // the last but one: nothing left to load
+        const int cur = ((last - 1) & 1) * STAGE_BYTES, nxt = STAGE_BYTES - cur;
+        read_a(0, cur);      wait_counts<10, 0>(); raw_barrier(); mfmas(0, 0, bf0); raw_barrier();
+        read_b(bf1, 1, cur); wait_counts<8, 0>();  raw_barrier(); mfmas(0, 1, bf1); raw_barrier();
+        read_a(1, cur);      wait_counts<6, 0>();  raw_barrier(); mfmas(1, 0, bf0); raw_barrier();
+        read_b(bf0, 0, nxt); wait_counts<4, 0>();  raw_barrier(); mfmas(1, 1, bf1); raw_barrier();
+    }
+    {
+        const int cur = (last & 1) * STAGE_BYTES;
+        read_a(0, cur);      wait_counts<2, 0>();  raw_barrier(); mfmas(0, 0, bf0); raw_barrier();
+        read_b(bf1, 1, cur); wait_counts<0, 0>();  raw_barrier(); mfmas(0, 1, bf1); raw_barrier();
+        read_a(1, cur);      wait_counts<NO_VM_WAIT, 0>(); raw_barrier(); mfmas(1, 0, bf0); raw_barrier();
+        mfmas(1, 1, bf1);
+    }
+    if (wm == 0) raw_barrier();
+    raw_barrier();
 }
 
 __device__ __forceinline__ void zero_acc(acc_t& acc) {
@@ -331,12 +299,14 @@ __device__ __forceinline__ void zero_acc(acc_t& acc) {
 // A launch whose tile count is not a multiple of the 256 compute units ends with a round in which
 // most of them idle.  The tiles of that last round can instead be cut into four "thin" tiles of
 // 256 x 64 (one wave column of a full tile each) and handed to four times as many workgroups.  A thin
-// tile does a quarter of the MFMA work for 5/8 of the staging traffic, so it runs at the pace of its
-// LDS writes, about a quarter to a third of a full tile's time.  Both operands are KC.
+// tile does a quarter of the MFMA work for 5/8 of the staging traffic, about a quarter to a third of a full
+// tile's time.
 constexpr int THIN_N = WAVE_N;                         // 64 columns
 constexpr int THIN_WAVE_M = TILE_M / 8;                // a wave of a thin tile: 32 rows x 64 columns
 constexpr int THIN_MT = THIN_WAVE_M / 16, THIN_NT = THIN_N / 16;
 constexpr int THIN_STAGE_BYTES = OPERAND_TILE_BYTES + THIN_N * TILE_K * 2;    // 32 KiB A + 8 KiB B
+constexpr int THIN_STAGES = 3;
+static_assert(THIN_STAGES * THIN_STAGE_BYTES <= LDS_BYTES, "");
 typedef f32x4 thin_acc_t[THIN_MT][THIN_NT];
 
 // A thin tile's B operand may also be k-strided (memory [k][col]): LDS then holds [64 k][64 cols], 128 bytes per
@@ -345,116 +315,87 @@ typedef f32x4 thin_acc_t[THIN_MT][THIN_NT];
 // half of the bank window, bits 1 and 3 of k go to chunk bits 1-2, the adjacent chunks differ in bit 0.
 __device__ __forceinline__ int thin_ks_swizzle(int k) { return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2); }
 
-// Byte offset of a thread's chunk of the k-strided thin B tile whose first column is n0, at k = 0: thread t
-// moves chunk t % 8 of k-row t / 8.
-__device__ __forceinline__ uint32_t thin_ks_lane_offset(const Operand& op, int n0, int tid) {
-    return ((uint32_t)(tid >> 3) * op.ld + (uint32_t)(n0 + (tid & 7) * 8)) * 2u;
-}
-__device__ __forceinline__ u32x4 thin_ks_g2r(const Operand& op, uint32_t lane_off, int k0) {
-    return __builtin_amdgcn_raw_buffer_load_b128(op.rsrc, (int)lane_off, (int)((uint32_t)k0 * op.ld * 2u), 0);
-}
-__device__ __forceinline__ void thin_ks_r2s(char* lds, const u32x4& v, int tid) {
-    const int kr = tid >> 3, ch = tid & 7;
-    *reinterpret_cast<u32x4*>(lds + kr * 128 + ((ch ^ thin_ks_swizzle(kr)) << 4)) = v;
-}
-struct ThinKsFrag {
-    int off[THIN_N / 16];
-    __device__ __forceinline__ void init(int lane) {
-        const int i = lane & 15, g = lane >> 4;
-        const int krow = 8 * g + (i >> 2);
-#pragma unroll
-        for (int t = 0; t < THIN_N / 16; ++t) {
-            const int col = 16 * t + 4 * (i & 3);
-            off[t] = krow * 128 + (((col >> 3) ^ thin_ks_swizzle(krow)) << 4) + ((col & 7) << 1);
-        }
-    }
-    __device__ __forceinline__ bf16x8 load(const char* lds, int t, int s) const {
-        typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
-        const char* p = lds + off[t] + s * (32 * 128);
-        s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
-        s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * 128));
-        s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        return __builtin_bit_cast(bf16x8, v);
-    }
-};
-
 // acc[mt][nt] += A(m0 .. m0+255, k) * B(n0 .. n0+63, k) for k in [k_begin, k_begin + 64 * k_steps);
-// wave w holds rows 32 w .. 32 w + 31.  BKIND KS: B is k-strided, n0 its first column.  Two LDS stages, the same software pipeline as the full tile in
-// two slots of 8 MFMAs per k-step: slot A multiplies k-substep 0 while the fragments of substep 1 are
-// read, the next k-step goes registers -> LDS and the one after it global -> registers; after the
-// barrier slot B multiplies substep 1 while the first fragments of the next k-step are read.
-// k-steps beyond the last are clamped to the last one (a harmless reload).  Ends with a workgroup barrier.
+// wave w holds rows 32 w .. 32 w + 31.  A is KC; BKIND KS: B is k-strided, n0 its first column.  Three LDS stages
+// filled straight from global memory two k-steps ahead, one barrier per k-step: behind the barrier of k-step j
+// every wave has its loads of k-step j in LDS and has finished reading k-step j - 1, whose stage the loads of
+// k-step j + 2 refill.  Ends with a workgroup barrier.
 template <int BKIND = KC>
 __device__ __forceinline__ void thin_mainloop(thin_acc_t& acc, const Operand& A, const Operand& Bop, int m0, int n0,
                                               int k_begin, int k_steps, char* lds, bool descending = false) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    FragAddr<KC, THIN_MT> fa;
-    FragAddr<KC, THIN_NT> fb;
-    ThinKsFrag fbs;
-    fa.init(lane, wave * THIN_WAVE_M);
-    if (BKIND == KC) fb.init(lane, 0);
-    else fbs.init(lane);
-    const uint32_t a_off = tile_lane_offset<KC>(A, m0, tid);
-    // KC: thread t moves chunk t % 8 of row t / 8 of the 64; KS: chunk t % 8 of k-row t / 8
-    const uint32_t b_off = BKIND == KC ? tile_lane_offset<KC>(Bop, n0, tid) : thin_ks_lane_offset(Bop, n0, tid);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15, g = lane >> 4, r8 = lane >> 3;
     const int last = k_steps - 1;
     const int k_first = descending ? k_begin + last * TILE_K : k_begin;
     const int k_stride = descending ? -TILE_K : TILE_K;
-    constexpr int NM = THIN_MT * THIN_NT, NR = THIN_MT + THIN_NT * (BKIND == KC ? 1 : 2);
-    u32x4 ra[4], rb;
-    bf16x8 af[2][THIN_MT], bfr[2][THIN_NT];
-    auto g2r = [&](int step) {
-        const int k0 = k_first + (step < last ? step : last) * k_stride;
+    // wave w loads rows 64 q + 8 w .. + 7 of A (q = 0 .. 3) and rows (KC) or k-rows (KS) 8 w .. + 7 of B
+    const int row = 8 * wave + r8, kc_chunk = (lane & 7) ^ ((row >> 1) & 7);
+    const uint32_t a_lane = ((uint32_t)(m0 + row) * A.ld + (uint32_t)(8 * kc_chunk)) * 2u;
+    const uint32_t b_lane = BKIND == KC
+        ? ((uint32_t)(n0 + row) * Bop.ld + (uint32_t)(8 * kc_chunk)) * 2u
+        : ((uint32_t)row * Bop.ld + (uint32_t)(n0 + 8 * ((lane & 7) ^ thin_ks_swizzle(row)))) * 2u;
+    const uint32_t lds_wave = lds_offset(lds) + 1024u * (uint32_t)wave;
+    auto load = [&](int step, int stage) {
+        const uint32_t k = (uint32_t)(k_first + step * k_stride);
+        const uint32_t dst = lds_wave + (uint32_t)stage;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) ra[q] = quarter_g2r<KC>(A, a_off, k0, q);
-        rb = BKIND == KC ? quarter_g2r<KC>(Bop, b_off, k0, 0) : thin_ks_g2r(Bop, b_off, k0);
+        for (int q = 0; q < 4; ++q) load_to_lds(A, a_lane, 2u * k + (uint32_t)q * 128u * A.ld, dst + q * 8192);
+        load_to_lds(Bop, b_lane, (BKIND == KC ? k : k * Bop.ld) * 2u, dst + OPERAND_TILE_BYTES);
     };
-    auto r2s = [&](char* stage) {
+    int a_frag[2], b_frag[THIN_NT];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) quarter_r2s<KC>(stage, ra[q], tid, q);
-        if (BKIND == KC) quarter_r2s<KC>(stage + OPERAND_TILE_BYTES, rb, tid, 0);
-        else thin_ks_r2s(stage + OPERAND_TILE_BYTES, rb, tid);
-    };
-    auto frags = [&](int set, const char* stage, int s) {
+    for (int s = 0; s < 2; ++s) a_frag[s] = (THIN_WAVE_M * wave + i) * 128 + (((4 * s + g) ^ (i >> 1)) << 4);
 #pragma unroll
-        for (int i = 0; i < THIN_MT; ++i) af[set][i] = fa.load(stage, i, s);
-#pragma unroll
-        for (int i = 0; i < THIN_NT; ++i)
-            bfr[set][i] = BKIND == KC ? fb.load(stage + OPERAND_TILE_BYTES, i, s) : fbs.load(stage + OPERAND_TILE_BYTES, i, s);
-    };
-    auto mfmas = [&](int set) {
-#pragma unroll
-        for (int i = 0; i < THIN_MT; ++i)
-#pragma unroll
-            for (int jn = 0; jn < THIN_NT; ++jn)
-                acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[set][i], bfr[set][jn], acc[i][jn], 0, 0, 0);
-    };
-    g2r(0);
-    r2s(lds);
-    g2r(1);
-    __syncthreads();
-    frags(0, lds, 0);
-    for (int j = 0; j < last; ++j) {
-        const char* cur = lds + (j & 1) * THIN_STAGE_BYTES;
-        char* nxt = lds + ((j + 1) & 1) * THIN_STAGE_BYTES;
-        frags(1, cur, 1);
-        mfmas(0);
-        r2s(nxt);                  // free since the barrier of the iteration before
-        g2r(j + 2);
-        SlotSched<0, NM, NR, 5, 5>::apply();
-        __syncthreads();
-        frags(0, nxt, 0);
-        mfmas(1);
-        SlotSched<0, NM, NR, 0, 0>::apply();
+    for (int t = 0; t < THIN_NT; ++t) {
+        if (BKIND == KC) {
+            b_frag[t] = OPERAND_TILE_BYTES + i * 128 + (((4 * (t & 1) + g) ^ (i >> 1)) << 4);    // t = k-substep 0 | 1
+        } else {
+            const int krow = 8 * g + (i >> 2), col = 16 * t + 4 * (i & 3);
+            b_frag[t] = OPERAND_TILE_BYTES + krow * 128 + (((col >> 3) ^ thin_ks_swizzle(krow)) << 4) + ((col & 7) << 1);
+        }
     }
-    {
-        const char* cur = lds + (last & 1) * THIN_STAGE_BYTES;
-        frags(1, cur, 1);
-        mfmas(0);
-        SlotSched<0, NM, NR, 0, 0>::apply();
-        mfmas(1);
+    load(0, 0);
+    if (last > 0) load(1, THIN_STAGE_BYTES);
+    int cur = 0, nxt = 2 * THIN_STAGE_BYTES;              // stages of k-steps j and j + 2
+    for (int j = 0; j <= last; ++j) {
+        if (j < last) wait_counts<5, NO_LG_WAIT>();       // k-step j + 1 may still be on its way
+        else wait_counts<0, NO_LG_WAIT>();
+        raw_barrier();
+        if (j + 2 <= last) load(j + 2, nxt);
+        bf16x8 af[THIN_MT][2], bf[THIN_NT][2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int t = 0; t < THIN_MT; ++t)
+                af[t][s] = *reinterpret_cast<const bf16x8*>(lds + (a_frag[s] + cur) + t * 2048);
+#pragma unroll
+            for (int t = 0; t < THIN_NT; ++t) {
+                if (BKIND == KC) {
+                    bf[t][s] = *reinterpret_cast<const bf16x8*>(lds + (b_frag[s] + cur) + t * 2048);
+                } else {
+                    typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
+                    const char* p = lds + (b_frag[t] + cur) + s * (32 * 128);
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * 128));
+                    bf[t][s] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int x = 0; x < THIN_MT; ++x)
+#pragma unroll
+                for (int y = 0; y < THIN_NT; ++y)
+                    acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[x][s], bf[y][s], acc[x][y], 0, 0, 0);
+        cur += THIN_STAGE_BYTES;
+        if (cur == THIN_STAGES * THIN_STAGE_BYTES) cur = 0;
+        nxt += THIN_STAGE_BYTES;
+        if (nxt == THIN_STAGES * THIN_STAGE_BYTES) nxt = 0;
     }
-    __syncthreads();
+    wait_counts<NO_VM_WAIT, 0>();
+    raw_barrier();
 }
 
 // How a launch of n_tiles full tiles is cut: the tiles of the last, partial round become thin tiles
@@ -504,12 +445,13 @@ __device__ __forceinline__ int out_tile_offset(int n, int m) {
     return n * 512 + (((m >> 2) ^ out_tile_swizzle(n)) << 3) + ((m & 3) << 1);
 }
 
+template <int BKIND>
 __device__ __forceinline__ void acc_to_lds_bf16(const acc_t& acc, char* lds) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 2, wn = wave & 3, g = lane >> 4, jl = lane & 15;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-        const int n = wn * WAVE_N + 16 * nt + jl;
+        const int n = wave_col<BKIND>(wn, nt) + jl;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             u32x2 p;

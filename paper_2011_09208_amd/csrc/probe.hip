@@ -57,8 +57,8 @@ __global__ __launch_bounds__(NTHREADS) void probe_gemm(ProbeGemmArgs p) {
     zero_acc(acc);
     const Operand A = make_operand(p.A, p.lda, p.M, p.K);
     const Operand Bo = make_operand(p.B, p.ldb, p.N, p.K);
-    gemm_mainloop<KC, KC>(acc, A, Bo, mt * TILE_M, nt * TILE_N, 0, p.K / TILE_K, lds);
-    acc_to_lds_bf16(acc, lds);
+    gemm_mainloop<KC>(acc, A, Bo, mt * TILE_M, nt * TILE_N, 0, p.K / TILE_K, lds);
+    acc_to_lds_bf16<KC>(acc, lds);
     __syncthreads();
     lds_tile_store_rows(lds, p.C + (int64_t)nt * TILE_N * p.ldc + mt * TILE_M, p.ldc, TILE_N, TILE_M);
 }

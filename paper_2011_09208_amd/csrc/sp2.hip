@@ -35,7 +35,7 @@ __global__ __launch_bounds__(NTHREADS) void sp2_partial_logits(Sp2Args a) {
     zero_acc(acc);
     const Operand A = make_operand(a.X, a.ldx, a.B, a.Ds);
     const Operand Bo = make_operand(a.W, a.ldw, a.C, a.Ds);
-    gemm_mainloop<KC, KC>(acc, A, Bo, bt * TILE_M, ct * TILE_N, 0, a.Ds / TILE_K, lds);
+    gemm_mainloop<KC>(acc, A, Bo, bt * TILE_M, ct * TILE_N, 0, a.Ds / TILE_K, lds);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 2, wn = wave & 3, g = lane >> 4, jl = lane & 15;

@@ -153,7 +153,7 @@ __device__ __forceinline__ void logits_tile(acc_t& acc, const FcArgs& a, int ct,
     zero_acc(acc);
     const Operand A = make_operand(a.W, a.ldw, a.C, a.D);
     const Operand Bo = make_operand(a.X, a.ldx, a.B, a.D);
-    gemm_mainloop<KC, KC>(acc, A, Bo, ct * TILE_M, bt * TILE_N, 0, a.D / TILE_K, lds, logits_descending(a, ct, bt));
+    gemm_mainloop<KC>(acc, A, Bo, ct * TILE_M, bt * TILE_N, 0, a.D / TILE_K, lds, logits_descending(a, ct, bt));
     const int tid = threadIdx.x;
     const bool has_bias = a.bias != nullptr;
     if (has_bias) {
@@ -600,7 +600,7 @@ __global__ __launch_bounds__(NTHREADS) void bwd_recompute_dz(FcArgs a, const flo
     // contraction (over rows, read across them).  The tile is staged in LDS so that it leaves in
     // whole 512-byte rows.
     __syncthreads();                       // the bias staging area is about to be overwritten
-    acc_to_lds_bf16(acc, lds);
+    acc_to_lds_bf16<KC>(acc, lds);
     __syncthreads();
     lds_tile_store_rows(lds, dZ + (int64_t)bt * TILE_N * ldz + ct * TILE_M, ldz, TILE_N, TILE_M);
 }
@@ -631,7 +631,7 @@ __global__ __launch_bounds__(NTHREADS) void predict_probs(FcArgs a, const float*
             for (int v = 0; v < 4; ++v) acc[mt][nt][v] = __builtin_amdgcn_exp2f(fmaf(acc[mt][nt][v], LOG2E, shift));
     }
     __syncthreads();                       // the bias staging area is about to be overwritten
-    acc_to_lds_bf16(acc, lds);
+    acc_to_lds_bf16<KC>(acc, lds);
     __syncthreads();
     const int b_left = a.B - bt * TILE_N, c_left = a.C - ct * TILE_M;
     lds_tile_store_rows(lds, P + (int64_t)bt * TILE_N * ldp + ct * TILE_M, ldp, b_left < TILE_N ? b_left : TILE_N,
@@ -737,7 +737,7 @@ __global__ __launch_bounds__(NTHREADS) void bwd_dx(DxArgs a) {
     zero_acc(acc);
     const Operand A = make_operand(a.dZ, a.ldz, a.Bpad, a.ldz);
     const Operand Bo = make_operand(a.W, a.ldw, a.C, a.D);          // classes beyond the shard read as zeros
-    gemm_mainloop<KC, KS>(acc, A, Bo, bt * TILE_M, dt * TILE_N, s0 * TILE_K, ns, lds);
+    gemm_mainloop<KS>(acc, A, Bo, bt * TILE_M, dt * TILE_N, s0 * TILE_K, ns, lds);
 
     // The accumulator layout gives a lane four consecutive rows of one column: direct stores would be 64-byte
     // pieces.  Instead each half of the tile (the 128 rows of one wave row) goes through LDS as fp32
@@ -753,7 +753,7 @@ __global__ __launch_bounds__(NTHREADS) void bwd_dx(DxArgs a) {
         if (wm == h) {
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const int col = wn * WAVE_N + 16 * nt + jl;
+                const int col = wave_col<KS>(wn, nt) + jl;
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -852,11 +852,11 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, char* lds, unsigned lon
     if (TRACE) stamp[1] = __builtin_readcyclecounter();
     // workgroups are dealt out 256 at a time, 32 to each XCD: alternate the direction round by round, so that a
     // compute unit's next tile finds the end of the X^T panels, which it has just read, still in the L2
-    gemm_mainloop<KC, KS>(acc, A, Bo, dt * TILE_M, ct * TILE_N, 0, a.k_steps, lds, ((blockIdx.x >> 8) & 1) != 0);
+    gemm_mainloop<KS>(acc, A, Bo, dt * TILE_M, ct * TILE_N, 0, a.k_steps, lds, ((blockIdx.x >> 8) & 1) != 0);
     if (TRACE) stamp[2] = __builtin_readcyclecounter();
 
     // [class][feature] tile through LDS, then whole 512-byte rows of dW
-    acc_to_lds_bf16(acc, lds);
+    acc_to_lds_bf16<KS>(acc, lds);
     __syncthreads();
     if (TRACE) stamp[3] = __builtin_readcyclecounter();
     const int c_left = a.C - ct * TILE_N, d_left = a.D - dt * TILE_M;
