@@ -23,6 +23,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace ws {
 
@@ -151,6 +152,65 @@ __device__ __forceinline__ int wave_col(int wn, int nt) {
     return BKIND == KC ? WAVE_N * wn + 16 * nt : 128 * (nt >> 1) + 32 * wn + 16 * (nt & 1);
 }
 
+// LDS -> fragments: af[tile of the half][k-substep], bf the same for half a B.
+template <int BKIND>
+struct FragReader {
+    int a_frag[2], b_frag[2];
+    __device__ __forceinline__ FragReader(int wm, int wn, int i, int g) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int chunk = (4 * s + g) ^ (i >> 1);
+            a_frag[s] = (64 * wm + i) * 128 + 16 * chunk;
+            if (BKIND == KC) {
+                b_frag[s] = OPERAND_TILE_BYTES + (32 * wn + i) * 128 + 16 * chunk;
+            } else {                                       // s counts the two 16-wide tiles here
+                const int krow = 8 * g + (i >> 2), col = 32 * wn + 16 * s + 4 * (i & 3);
+                b_frag[s] = OPERAND_TILE_BYTES + krow * 256 + (((col >> 3) ^ ks_swizzle(krow)) << 4) + ((col & 7) << 1);
+            }
+        }
+    }
+    __device__ __forceinline__ void read_a(bf16x8 (&af)[MT / 2][2], const char* lds, int half, int stage) const {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < MT / 2; ++t)
+                af[t][s] = *reinterpret_cast<const bf16x8*>(lds + (a_frag[s] + stage) + half * HALF_TILE_BYTES + t * 2048);
+    }
+    __device__ __forceinline__ void read_b(bf16x8 (&bf)[NT / 2][2], const char* lds, int half, int stage) const {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < NT / 2; ++t) {
+                if (BKIND == KC) {
+                    bf[t][s] = *reinterpret_cast<const bf16x8*>(lds + (b_frag[s] + stage) + half * HALF_TILE_BYTES + t * 2048);
+                } else {
+                    typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
+                    const char* p = lds + (b_frag[t] + stage) + half * HALF_TILE_BYTES + s * (32 * 256);
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * 256));
+                    bf[t][s] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+            }
+    }
+};
+
+// The 16 MFMAs of quadrant Q = 2 * (A half) + (B half).  FIRST: the accumulators start from zero.
+template <int Q, bool FIRST = false>
+__device__ __forceinline__ void quadrant_mfmas(acc_t& acc, const bf16x8 (&af)[MT / 2][2], const bf16x8 (&bf)[NT / 2][2]) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int x = 0; x < MT / 2; ++x)
+#pragma unroll
+            for (int y = 0; y < NT / 2; ++y) {
+                f32x4& c = acc[MT / 2 * (Q >> 1) + x][NT / 2 * (Q & 1) + y];
+                const f32x4 from = FIRST && s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : c;
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[x][s], bf[y][s], from, 0, 0, 0);
+            }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // `descending` (uniform over the workgroup): walk the k-steps from the last to the first.  Tiles that follow each
 // other on a compute unit and share an operand panel can alternate the direction, so that the second finds
 // the end of the panel, which the first has just read, still in the L2.
@@ -195,56 +255,10 @@ __device__ __forceinline__ void gemm_mainloop(acc_t& acc, const Operand& A, cons
         load_to_lds(Bop, b_lane, src + b_second, dst + HALF_TILE_BYTES / 2);
     };
 
-    // LDS -> fragments: af[tile of the half][k-substep], bf0 / bf1 the same for the two halves of B
-    int a_frag[2], b_frag[2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int chunk = (4 * s + g) ^ (i >> 1);
-        a_frag[s] = (64 * wm + i) * 128 + 16 * chunk;
-        if (BKIND == KC) {
-            b_frag[s] = OPERAND_TILE_BYTES + (32 * wn + i) * 128 + 16 * chunk;
-        } else {                                       // s counts the two 16-wide tiles here
-            const int krow = 8 * g + (i >> 2), col = 32 * wn + 16 * s + 4 * (i & 3);
-            b_frag[s] = OPERAND_TILE_BYTES + krow * 256 + (((col >> 3) ^ ks_swizzle(krow)) << 4) + ((col & 7) << 1);
-        }
-    }
+    const FragReader<BKIND> frag(wm, wn, i, g);
     bf16x8 af[MT / 2][2], bf0[NT / 2][2], bf1[NT / 2][2];
-    auto read_a = [&](int half, int stage) {
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int t = 0; t < MT / 2; ++t)
-                af[t][s] = *reinterpret_cast<const bf16x8*>(lds + (a_frag[s] + stage) + half * HALF_TILE_BYTES + t * 2048);
-    };
-    auto read_b = [&](bf16x8 (&bf)[NT / 2][2], int half, int stage) {
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int t = 0; t < NT / 2; ++t) {
-                if (BKIND == KC) {
-                    bf[t][s] = *reinterpret_cast<const bf16x8*>(lds + (b_frag[s] + stage) + half * HALF_TILE_BYTES + t * 2048);
-                } else {
-                    typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
-                    const char* p = lds + (b_frag[t] + stage) + half * HALF_TILE_BYTES + s * (32 * 256);
-                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
-                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * 256));
-                    bf[t][s] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                }
-            }
-    };
-    auto mfmas = [&](int a_h, int b_h, bf16x8 (&bf)[NT / 2][2]) {
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int x = 0; x < MT / 2; ++x)
-#pragma unroll
-                for (int y = 0; y < NT / 2; ++y) {
-                    f32x4& c = acc[MT / 2 * a_h + x][NT / 2 * b_h + y];
-                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[x][s], bf[y][s], c, 0, 0, 0);
-                }
-        __builtin_amdgcn_sched_barrier(0);
-    };
+    auto read_a = [&](int half, int stage) { frag.read_a(af, lds, half, stage); };
+    auto read_b = [&](bf16x8 (&bf)[NT / 2][2], int half, int stage) { frag.read_b(bf, lds, half, stage); };
 
     // k-steps 0 and 1 in the order in which the loop would have issued their loads; then B0(0), which the loop
     // reads one phase ahead
@@ -263,24 +277,35 @@ __device__ __forceinline__ void gemm_mainloop(acc_t& acc, const Operand& A, cons
 
     for (int j = 0; j < last - 1; ++j) {
         const int cur = (j & 1) * STAGE_BYTES, nxt = STAGE_BYTES - cur;
-        read_a(0, cur);      load_b(0, j + 2); wait_counts<12, 0>(); raw_barrier(); mfmas(0, 0, bf0); raw_barrier();
-        read_b(bf1, 1, cur); load_a(0, j + 2); wait_counts<12, 0>(); raw_barrier(); mfmas(0, 1, bf1); raw_barrier();
-        read_a(1, cur);      load_b(1, j + 2); wait_counts<12, 0>(); raw_barrier(); mfmas(1, 0, bf0); raw_barrier();
-        read_b(bf0, 0, nxt); load_a(1, j + 2); wait_counts<12, 0>(); raw_barrier(); mfmas(1, 1, bf1); raw_barrier();
+        read_a(0, cur);      load_b(0, j + 2); wait_counts<12, 0>(); raw_barrier();
+        quadrant_mfmas<0>(acc, af, bf0); raw_barrier();
+        read_b(bf1, 1, cur); load_a(0, j + 2); wait_counts<12, 0>(); raw_barrier();
+        quadrant_mfmas<1>(acc, af, bf1); raw_barrier();
+        read_a(1, cur);      load_b(1, j + 2); wait_counts<12, 0>(); raw_barrier();
+        quadrant_mfmas<2>(acc, af, bf0); raw_barrier();
+        read_b(bf0, 0, nxt); load_a(1, j + 2); wait_counts<12, 0>(); raw_barrier();
+        quadrant_mfmas<3>(acc, af, bf1); raw_barrier();
     }
     if (last > 0) {          // the last but one: nothing left to load
         const int cur = ((last - 1) & 1) * STAGE_BYTES, nxt = STAGE_BYTES - cur;
-        read_a(0, cur);      wait_counts<10, 0>(); raw_barrier(); mfmas(0, 0, bf0); raw_barrier();
-        read_b(bf1, 1, cur); wait_counts<8, 0>();  raw_barrier(); mfmas(0, 1, bf1); raw_barrier();
-        read_a(1, cur);      wait_counts<6, 0>();  raw_barrier(); mfmas(1, 0, bf0); raw_barrier();
-        read_b(bf0, 0, nxt); wait_counts<4, 0>();  raw_barrier(); mfmas(1, 1, bf1); raw_barrier();
+        read_a(0, cur);      wait_counts<10, 0>(); raw_barrier();
+        quadrant_mfmas<0>(acc, af, bf0); raw_barrier();
+        read_b(bf1, 1, cur); wait_counts<8, 0>(); raw_barrier();
+        quadrant_mfmas<1>(acc, af, bf1); raw_barrier();
+        read_a(1, cur);      wait_counts<6, 0>(); raw_barrier();
+        quadrant_mfmas<2>(acc, af, bf0); raw_barrier();
+        read_b(bf0, 0, nxt); wait_counts<4, 0>(); raw_barrier();
+        quadrant_mfmas<3>(acc, af, bf1); raw_barrier();
     }
     {
         const int cur = (last & 1) * STAGE_BYTES;
-        read_a(0, cur);      wait_counts<2, 0>();  raw_barrier(); mfmas(0, 0, bf0); raw_barrier();
-        read_b(bf1, 1, cur); wait_counts<0, 0>();  raw_barrier(); mfmas(0, 1, bf1); raw_barrier();
-        read_a(1, cur);      wait_counts<NO_VM_WAIT, 0>(); raw_barrier(); mfmas(1, 0, bf0); raw_barrier();
-        mfmas(1, 1, bf1);
+        read_a(0, cur);      wait_counts<2, 0>(); raw_barrier();
+        quadrant_mfmas<0>(acc, af, bf0); raw_barrier();
+        read_b(bf1, 1, cur); wait_counts<0, 0>(); raw_barrier();
+        quadrant_mfmas<1>(acc, af, bf1); raw_barrier();
+        read_a(1, cur);      wait_counts<NO_VM_WAIT, 0>(); raw_barrier();
+        quadrant_mfmas<2>(acc, af, bf0); raw_barrier();
+        quadrant_mfmas<3>(acc, af, bf1);
     }
     if (wm == 0) raw_barrier();
     raw_barrier();

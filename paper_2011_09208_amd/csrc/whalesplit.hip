@@ -15,7 +15,8 @@
 //                      (optionally accumulating into the caller's dX) and the db partials
 // fwd_logits_stats and bwd_recompute_dz run the tiles of a ragged last round (256 compute units) as
 // four thin 256 x 64 tiles each (logits_thin, fwd_stats_thin, dz_thin; plan_tiles on the host); bwd_dw
-// does the same where the contraction is long (dw_thin).
+// does the same where the contraction is long (dw_thin).  From four k-steps on dW runs as a stream of tiles per
+// compute unit (bwd_dw_stream, gemm_stream.h), except where it updates the weights in place or is traced.
 // Tile orders and cache reuse: each XCD walks a contiguous range of tiles whose neighbours share operand
 // panels (logits_tile_coords, bwd_dx, dw_tile); every other round of tiles walks the contraction backwards
 // (logits_descending, dw_tile) and bwd_recompute_dz starts with the tiles that fwd_logits_stats ended on.
@@ -28,6 +29,7 @@
 
 #include "../../include/whalesplit.h"
 #include "gemm_core.h"
+#include "gemm_stream.h"
 
 namespace ws {
 
@@ -930,6 +932,58 @@ __global__ __launch_bounds__(NTHREADS) void bwd_dw(DwArgs a, FinishArgs fin) {
     dw_tile<false>(a, lds, nullptr);
 }
 
+// The same tiles as a stream (gemm_stream.h): nothing waits for the 128 KiB that leave a compute unit per tile, and no
+// tile for its first loads.  B = 1024, D = 2048, C = 100 000: 380 -> 345 us; B = 256: 181 -> 141 us; B = 1024, C = 12 500:
+// 69 -> 67 us (1.5 tiles per compute unit).  Feature tiles fastest and the direction of the contraction
+// alternating round by round as in dw_tile.
+template <int RATE>
+struct DwEpilogue : RowStore<KS, RATE> {
+    const DwArgs& a;
+    const StreamShare& share;
+    int round = -1;
+    static constexpr int LOADS = 0;
+    __device__ __forceinline__ DwEpilogue(const DwArgs& args, const StreamShare& s, char* lds) : a(args), share(s) {
+        this->init(a.lddw, lds);
+    }
+    __device__ __forceinline__ void begin_next() { ++round; }
+    __device__ __forceinline__ void load_extra() {}
+    template <int Q>
+    __device__ __forceinline__ void finish(const acc_t& acc) {
+        if (Q == 0) {
+            const int tile = share.tile(round), dt = tile % a.nDT, ct = tile / a.nDT;
+            const int64_t off = (int64_t)ct * TILE_N * a.lddw + dt * TILE_M;
+            const int64_t bytes = (((int64_t)a.C - 1) * a.lddw + a.D - off) * 2;
+            this->at.base = a.dW + off;
+            this->at.records = bytes < 0xfffffff0ll ? (uint32_t)bytes : 0xfffffff0u;
+            this->at.m_valid = a.D - dt * TILE_M;
+        }
+        this->template put<Q>(acc);
+    }
+};
+
+template <int RATE, int PREFETCH>
+__global__ __launch_bounds__(NTHREADS) void bwd_dw_stream(DwArgs a, FinishArgs fin) {
+    __shared__ __attribute__((aligned(16))) char lds[STREAM_LDS_BYTES];
+    if ((int)blockIdx.x >= fin.first_block) {
+        finish_bwd(fin, (int)blockIdx.x - fin.first_block);
+        return;
+    }
+    if ((int)blockIdx.x >= a.plan.thin_first) {
+        dw_thin(a, (int)blockIdx.x - a.plan.thin_first, lds);
+        return;
+    }
+    const StreamShare share(a.plan.n_full, blockIdx.x);
+    if (share.count == 0) return;
+    DwEpilogue<RATE> epi(a, share, lds);
+    const Operand A = make_operand(a.XT, a.ldxt, a.D, a.ldxt);
+    const Operand Bo = make_operand(a.dZ, a.ldz, a.Bpad, a.ldz);
+    const auto tile_at = [&](int round) {
+        const int tile = share.tile(round);
+        return StreamTile{(tile % a.nDT) * TILE_M, (tile / a.nDT) * TILE_N, (round & 1) != 0};
+    };
+    gemm_stream<KS, RATE, PREFETCH>(A, Bo, a.k_steps, share.count, tile_at, PrefetchShare(share.first % a.nDT, a.nDT), epi, lds);
+}
+
 __global__ __launch_bounds__(NTHREADS) void bwd_dw_traced(DwArgs a, FinishArgs fin, unsigned long long* trace) {
     __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
     if ((int)blockIdx.x >= fin.first_block) {
@@ -963,6 +1017,13 @@ static TilePlan plan_tiles(int n_tiles, bool allow_thin) {
 // Shortest contraction (k-steps of 64 batch rows) for which the dW kernel cuts the tiles of a ragged last round
 // into thin ones: measured slower at 16 k-steps (the last round is mostly output there), faster at 128.
 static const int DW_THIN_MIN_K_STEPS = 48;
+// The dW stream prefetches dz if bwd_dx, which runs in between, has read more than the 256 MiB Infinity Cache holds
+// (dz and W: B = 1024 and C = 12 500, 76 MB: 66.8 us without, 68.0 with; C = 100 000, 615 MB: 372 and 345) and
+// unless its tiles are so long that writes are rare (B = 8192, 128 k-steps: 624 us without, 639 with).
+static const int64_t DW_PREFETCH_MIN_BYTES = (int64_t)256 << 20;
+static const int DW_PREFETCH_MAX_K_STEPS = 64;
+// Row pitch (elements) below which 256 rows of a store tile stay within 32-bit byte offsets.
+static const int64_t STREAM_MAX_LD = (int64_t)1 << 22;
 // Workgroups appended to a GEMM launch for its small side job (X^T, the final reductions).
 static const int SIDE_BLOCKS = 128;
 
@@ -1264,6 +1325,14 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     f.n_blocks = (f.parts || f.db_part) ? SIDE_BLOCKS : 0;
     if (g_dw_trace != nullptr) {
         WS_LAUNCH(KID_DW, bwd_dw_traced, dim3(f.first_block + f.n_blocks), dim3(NTHREADS), s, w, f, g_dw_trace);
+    } else if (w.k_steps >= STREAM_MIN_K_STEPS && !sgd && lddw < STREAM_MAX_LD) {
+        w.plan.thin_first = w.plan.n_full > 0 ? STREAM_WGS : 0;
+        f.first_block = w.plan.thin_first + w.plan.n_thin;
+        const bool far = 2 * (p.Bpad * p.Cpad + (int64_t)C_shard * D) > DW_PREFETCH_MIN_BYTES && w.k_steps <= DW_PREFETCH_MAX_K_STEPS;
+        const int rate = stream_rate(w.k_steps);
+        auto kernel = far ? (rate == 1 ? bwd_dw_stream<1, PREFETCH_B> : rate == 2 ? bwd_dw_stream<2, PREFETCH_B> : bwd_dw_stream<4, PREFETCH_B>)
+                          : (rate == 1 ? bwd_dw_stream<1, PREFETCH_NONE> : rate == 2 ? bwd_dw_stream<2, PREFETCH_NONE> : bwd_dw_stream<4, PREFETCH_NONE>);
+        WS_LAUNCH(KID_DW, kernel, dim3(f.first_block + f.n_blocks), dim3(NTHREADS), s, w, f);
     } else {
         WS_LAUNCH(KID_DW, bwd_dw, dim3(f.first_block + f.n_blocks), dim3(NTHREADS), s, w, f);
     }
