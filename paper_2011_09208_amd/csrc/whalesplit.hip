@@ -379,18 +379,46 @@ __global__ __launch_bounds__(1024) void merge_class_tiles(const float* __restric
     }
 }
 
-__global__ void combine_partials_kernel(const float* __restrict__ row_max, const float* __restrict__ row_sumexp,
-                                        const float* __restrict__ label_logit, int S, int B, int64_t stride,
-                                        float* __restrict__ logsumexp, float* __restrict__ loss_rows) {
+// Bound by the latency of its loads.  The statistics of eight shards are loaded at once; taken one after the other, with
+// the largest maximum first and the sums in a second walk, 8 shards took 7.2 us at B = 1024 and 9.3 at 8192.
+constexpr int COMBINE_BATCH = 8;
+__device__ __forceinline__ void load_shards(float (&v)[COMBINE_BATCH], const float* __restrict__ p, int s0, int S, int64_t stride) {
+#pragma unroll
+    for (int k = 0; k < COMBINE_BATCH; ++k) v[k] = p[(int64_t)(s0 + k < S ? s0 + k : S - 1) * stride];
+}
+__global__ __launch_bounds__(64) void combine_partials_kernel(const float* __restrict__ row_max,
+                                                              const float* __restrict__ row_sumexp,
+                                                              const float* __restrict__ label_logit, int S, int B,
+                                                              int64_t stride, float* __restrict__ logsumexp,
+                                                              float* __restrict__ loss_rows) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= B) return;
+    float vm[COMBINE_BATCH], vs[COMBINE_BATCH], vt[COMBINE_BATCH];
+    load_shards(vm, row_max + i, 0, S, stride);
+    load_shards(vs, row_sumexp + i, 0, S, stride);
+    load_shards(vt, label_logit + i, 0, S, stride);
     float m = NEG_INF;
-    for (int s = 0; s < S; ++s) m = fmaxf(m, row_max[s * stride + i]);
+#pragma unroll
+    for (int k = 0; k < COMBINE_BATCH; ++k) m = fmaxf(m, vm[k]);            // the last shard again beyond S
+    for (int s0 = COMBINE_BATCH; s0 < S; s0 += COMBINE_BATCH) {
+        float more[COMBINE_BATCH];
+        load_shards(more, row_max + i, s0, S, stride);
+#pragma unroll
+        for (int k = 0; k < COMBINE_BATCH; ++k) m = fmaxf(m, more[k]);
+    }
     float tot = 0.0f, t = 0.0f;
-    for (int s = 0; s < S; ++s) {
-        const float ms = row_max[s * stride + i];
-        if (ms != NEG_INF) tot += row_sumexp[s * stride + i] * __expf(ms - m);
-        t += label_logit[s * stride + i];
+    for (int s0 = 0;;) {
+#pragma unroll
+        for (int k = 0; k < COMBINE_BATCH; ++k)
+            if (s0 + k < S) {
+                if (vm[k] != NEG_INF) tot += vs[k] * __expf(vm[k] - m);
+                t += vt[k];
+            }
+        s0 += COMBINE_BATCH;
+        if (s0 >= S) break;
+        load_shards(vm, row_max + i, s0, S, stride);
+        load_shards(vs, row_sumexp + i, s0, S, stride);
+        load_shards(vt, label_logit + i, s0, S, stride);
     }
     const float lse = m + __logf(tot);
     logsumexp[i] = lse;
@@ -695,18 +723,36 @@ __global__ __launch_bounds__(NTHREADS) void top1_logits(FcArgs a, float* __restr
     }
 }
 
-// Merges candidates of one row: n candidates `stride` apart; `base` is added to the winning class.
-// One thread per row (the candidate lists are a few hundred entries of a few MB in total).
-__global__ __launch_bounds__(256) void merge_top1(const float* __restrict__ val, const int* __restrict__ cls, int n,
-                                                  int64_t stride, int B, int base, float* __restrict__ out_val,
-                                                  int* __restrict__ out_cls) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= B) return;
+// Merges n candidates per row, `stride` apart; `base` is added to the winning class.  One workgroup takes 16 rows:
+// thread (r, q) folds candidates q, q + 64, ... of row r, then the 64 winners of a row are merged through LDS (the better
+// of two is an order, so the grouping does not matter).  With one thread per row the loads of a row followed each
+// other: 391 candidates took 129 us, now 5 us.
+__global__ __launch_bounds__(1024) void merge_top1(const float* __restrict__ val, const int* __restrict__ cls, int n,
+                                                   int64_t stride, int B, int base, float* __restrict__ out_val,
+                                                   int* __restrict__ out_cls) {
+    __shared__ float sv[64][16];
+    __shared__ int sc[64][16];
+    const int r = threadIdx.x & 15, q = threadIdx.x >> 4;
+    const int i = blockIdx.x * 16 + r;
     float v = NEG_INF;
     int c = INT_MAX;
-    for (int t = 0; t < n; ++t) better_of(v, c, val[t * stride + i], cls[t * stride + i]);
-    out_val[i] = v;
-    out_cls[i] = c == INT_MAX ? c : c + base;
+    if (i < B)
+        for (int t = q; t < n; t += 64) better_of(v, c, val[t * stride + i], cls[t * stride + i]);
+    sv[q][r] = v;
+    sc[q][r] = c;
+    __syncthreads();
+    for (int w = 32; w > 0; w >>= 1) {
+        if (q < w) {
+            better_of(v, c, sv[q + w][r], sc[q + w][r]);
+            sv[q][r] = v;
+            sc[q][r] = c;
+        }
+        __syncthreads();
+    }
+    if (q == 0 && i < B) {
+        out_val[i] = v;
+        out_cls[i] = c == INT_MAX ? c : c + base;
+    }
 }
 
 struct DxArgs {
@@ -1249,7 +1295,7 @@ int ws_combine_partials(const float* row_max, const float* row_sumexp, const flo
         !aligned(loss_rows, 4) || (loss_mean && !aligned(loss_mean, 4)))
         return WS_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    WS_LAUNCH(KID_COMBINE, combine_partials_kernel, dim3((B + 255) / 256), dim3(256), s, row_max, row_sumexp,
+    WS_LAUNCH(KID_COMBINE, combine_partials_kernel, dim3((B + 63) / 64), dim3(64), s, row_max, row_sumexp,
                        label_logit, S, B, shard_stride, logsumexp, loss_rows);
     if (loss_mean) WS_LAUNCH(KID_MEAN, mean_loss_kernel, dim3(1), dim3(1024), s, loss_rows, B, loss_mean);
     return launch_status();
@@ -1409,7 +1455,7 @@ int ws_split_fc_top1(const void* X, int64_t ldx, const void* W_shard, int64_t ld
     int* part_cls = reinterpret_cast<int*>(part_val + (size_t)a.nCT * a.Bpad);
     hipStream_t s = static_cast<hipStream_t>(stream);
     WS_LAUNCH(KID_TOP1, top1_logits, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, part_val, part_cls);
-    WS_LAUNCH(KID_TOP1_MERGE, merge_top1, dim3((B + 255) / 256), dim3(256), s, part_val, part_cls, a.nCT,
+    WS_LAUNCH(KID_TOP1_MERGE, merge_top1, dim3((B + 15) / 16), dim3(1024), s, part_val, part_cls, a.nCT,
               (int64_t)a.Bpad, B, class_offset, top_logit, top_class);
     return launch_status();
 }
@@ -1422,7 +1468,7 @@ int ws_combine_top1(const float* top_logit, const int32_t* top_class, int32_t S,
     if (!aligned(top_logit, 4) || !aligned(top_class, 4) || !aligned(best_logit, 4) || !aligned(best_class, 4))
         return WS_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    WS_LAUNCH(KID_TOP1_MERGE, merge_top1, dim3((B + 255) / 256), dim3(256), s, top_logit, top_class, S, shard_stride,
+    WS_LAUNCH(KID_TOP1_MERGE, merge_top1, dim3((B + 15) / 16), dim3(1024), s, top_logit, top_class, S, shard_stride,
               B, 0, best_logit, best_class);
     return launch_status();
 }

@@ -1,0 +1,53 @@
+"""GPU parity of the kernels that merge statistics across shards, at the batch and workgroup edges of their loops:
+combine_partials loads eight shards at a time, merge_top1 deals candidates to 64 threads per row and 16 rows per
+workgroup."""
+import numpy as np
+import pytest
+
+from oracle import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ws():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU; there is no CPU fallback")
+    from paper_2011_09208_amd import binding
+    return binding
+
+
+@pytest.mark.parametrize("S,B", [(1, 1), (7, 63), (8, 64), (9, 65), (16, 200), (17, 130)])
+def test_combine_partials_batches_of_shards(ws, S, B):
+    import torch
+    rng = np.random.default_rng(100 * S + B)
+    m = rng.normal(0, 4, (S, B)).astype(np.float32)
+    s = rng.uniform(1, 500, (S, B)).astype(np.float32)
+    t = np.zeros((S, B), np.float32)
+    t[rng.integers(0, S, B), np.arange(B)] = rng.normal(0, 4, B)
+    if S > 1:
+        m[S - 1, ::3], s[S - 1, ::3] = -np.inf, 0.0                # a shard without classes for these rows
+    dm, ds, dt = (torch.from_numpy(x).cuda() for x in (m, s, t))
+    lse, loss = torch.empty(B, device="cuda"), torch.empty(B, device="cuda")
+    ws.combine_partials(dm, ds, dt, lse, loss, None)
+    m64 = m.astype(np.float64)
+    ref = np.log((s * np.exp(m64 - m64.max(0))).sum(0)) + m64.max(0)
+    # fp32: the sum of S terms (each an exp of 2 ulp), a log, one add; loss subtracts t
+    tol = 2.0 ** -23 * (S + 6) + 2.0 ** -23 * np.maximum(np.abs(ref), np.abs(t.sum(0)))
+    assert (np.abs(lse.cpu().numpy() - ref) <= tol).all()
+    assert (np.abs(loss.cpu().numpy() - (ref - t.sum(0))) <= 2 * tol).all()
+
+
+@pytest.mark.parametrize("S,B", [(1, 1), (2, 15), (63, 16), (64, 17), (65, 33), (391, 2)])
+def test_combine_top1_groups_of_candidates(ws, S, B):
+    import torch
+    rng = np.random.default_rng(100 * S + B)
+    v = rng.integers(-3, 4, (S, B)).astype(np.float32)             # many ties: the lowest class id wins
+    c = np.stack([rng.permutation(10 * S)[:S] for _ in range(B)], 1).astype(np.int32)
+    v[:, B // 2] = -np.inf                                         # all candidates of one row alike
+    dv, dc = torch.from_numpy(v).cuda(), torch.from_numpy(c).cuda()
+    bv, bc = torch.empty(B, device="cuda"), torch.empty(B, device="cuda", dtype=torch.int32)
+    ws.combine_top1(dv, dc, bv, bc)
+    rv, rc = oracle.combine_top1(list(v.astype(np.float64)), list(c.astype(np.int64)))
+    assert (bv.cpu().numpy() == rv).all() and (bc.cpu().numpy() == rc).all()
