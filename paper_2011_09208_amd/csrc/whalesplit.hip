@@ -10,6 +10,7 @@
 //                      write X^T for the dW contraction
 //   predict_probs      softmax probabilities of the shard's classes, exp(z - lse), bf16
 //   top1_logits        the shard's arg-max class and its logit per row (+ merge_top1, also used across shards)
+//   *_small            the logits kernels for up to 64 rows (gemm_small.h)
 //   bwd_dx             dX_partial = dz . W_s, split along the class contraction; partial sums
 //   bwd_dw             dW_s = dz^T . X; its surplus workgroups sum the split-K partials of dX
 //                      (optionally accumulating into the caller's dX) and the db partials
@@ -29,6 +30,7 @@
 
 #include "../../include/whalesplit.h"
 #include "gemm_core.h"
+#include "gemm_small.h"
 #include "gemm_stream.h"
 
 namespace ws {
@@ -344,6 +346,9 @@ __global__ __launch_bounds__(NTHREADS) void fwd_logits_stats(FcArgs a, float* __
     }
 }
 
+// Loads of a merge kernel's thread in flight: a chain of them, one per 64 tiles, is what bounds these kernels.
+constexpr int MERGE_BATCH = 8;
+
 // One workgroup merges the class-tile partials of 16 rows: thread (r, q) folds tiles q, q + 64, ...
 // of row r online, then the 64 partial pairs of a row are merged through LDS in a fixed order
 // (8 groups of 8, then the 8 group results).
@@ -355,7 +360,18 @@ __global__ __launch_bounds__(1024) void merge_class_tiles(const float* __restric
     const int r = threadIdx.x & 15, q = threadIdx.x >> 4;
     const int i = blockIdx.x * 16 + r;          // < Bpad: the partial arrays are padded to whole tiles
     float m = NEG_INF, s = 0.0f;
-    for (int t = q; t < nCT; t += 64) merge_ms(m, s, part_max[(int64_t)t * Bpad + i], part_sum[(int64_t)t * Bpad + i]);
+    for (int t0 = q; t0 < nCT; t0 += 64 * MERGE_BATCH) {
+        float vm[MERGE_BATCH], vs[MERGE_BATCH];
+#pragma unroll
+        for (int k = 0; k < MERGE_BATCH; ++k) {                     // beyond the end: a tile read again, not merged
+            const int t = t0 + 64 * k < nCT ? t0 + 64 * k : t0;
+            vm[k] = part_max[(int64_t)t * Bpad + i];
+            vs[k] = part_sum[(int64_t)t * Bpad + i];
+        }
+#pragma unroll
+        for (int k = 0; k < MERGE_BATCH; ++k)
+            if (t0 + 64 * k < nCT) merge_ms(m, s, vm[k], vs[k]);
+    }
     sm[q][r] = m;
     ss[q][r] = s;
     __syncthreads();
@@ -448,16 +464,17 @@ struct XtArgs {
     int first_block, n_blocks;           // workgroups [first_block, first_block + n_blocks) transpose
 };
 
+template <int THREADS>
 __device__ __forceinline__ void transpose_x_tiles(const FcArgs& a, const XtArgs& x, int worker, char* lds) {
     uint16_t (*tile)[66] = reinterpret_cast<uint16_t (*)[66]>(lds);
-    const int nb = a.Bpad / 64, n_tiles = nb * (a.D / 64);
+    const int nb = (a.B + 63) / 64, n_tiles = nb * (a.D / 64);
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     for (int t = worker; t < n_tiles; t += x.n_blocks) {
         const int b0 = (t % nb) * 64, d0 = (t / nb) * 64;
-        for (int r = ty; r < 64; r += NTHREADS / 64)
+        for (int r = ty; r < 64; r += THREADS / 64)
             tile[r][tx] = (b0 + r < a.B) ? a.X[(int64_t)(b0 + r) * a.ldx + d0 + tx] : (uint16_t)0;
         __syncthreads();
-        for (int r = ty; r < 64; r += NTHREADS / 64) x.XT[(int64_t)(d0 + r) * x.ldxt + b0 + tx] = tile[tx][r];
+        for (int r = ty; r < 64; r += THREADS / 64) x.XT[(int64_t)(d0 + r) * x.ldxt + b0 + tx] = tile[tx][r];
         __syncthreads();
     }
 }
@@ -549,7 +566,7 @@ __global__ __launch_bounds__(NTHREADS) void bwd_recompute_dz(FcArgs a, const flo
     __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
     float* sbias = reinterpret_cast<float*>(lds);
     if ((int)blockIdx.x >= xt.first_block) {
-        transpose_x_tiles(a, xt, (int)blockIdx.x - xt.first_block, lds);
+        transpose_x_tiles<NTHREADS>(a, xt, (int)blockIdx.x - xt.first_block, lds);
         return;
     }
     const TileRef ref = logits_tile_ref(a);
@@ -737,7 +754,18 @@ __global__ __launch_bounds__(1024) void merge_top1(const float* __restrict__ val
     float v = NEG_INF;
     int c = INT_MAX;
     if (i < B)
-        for (int t = q; t < n; t += 64) better_of(v, c, val[t * stride + i], cls[t * stride + i]);
+        for (int t0 = q; t0 < n; t0 += 64 * MERGE_BATCH) {
+            float tv[MERGE_BATCH];
+            int tc[MERGE_BATCH];
+#pragma unroll
+            for (int k = 0; k < MERGE_BATCH; ++k) {                 // beyond the end: a candidate once more
+                const int t = t0 + 64 * k < n ? t0 + 64 * k : t0;
+                tv[k] = val[t * stride + i];
+                tc[k] = cls[t * stride + i];
+            }
+#pragma unroll
+            for (int k = 0; k < MERGE_BATCH; ++k) better_of(v, c, tv[k], tc[k]);
+        }
     sv[q][r] = v;
     sc[q][r] = c;
     __syncthreads();
@@ -755,11 +783,163 @@ __global__ __launch_bounds__(1024) void merge_top1(const float* __restrict__ val
     }
 }
 
+// ---- small batches --------------------------------------------------------------------------------
+// The logits kernels for up to 64 rows (gemm_small.h): workgroup w takes the classes [w * range, (w + 1) * range) and
+// reports one partial result per row.
+// Bound by reading W.  W of 100 000 x 2048, B = 1, arg-max: 87 us on the wide tiles, 71 here (5.8 TB/s); W of 12 500 x 2048,
+// B = 32: statistics 31.5 and 14.8 us, probabilities 37.4 and 15.2 (196 of 256 units have work, two turns of 32 classes each).
+template <int NB, class Body>
+__device__ __forceinline__ void small_range(const FcArgs& a, int range, int wg, int classes, float* lds, Body body) {
+    const int c_begin = wg * range, c_end = c_begin + range < classes ? c_begin + range : classes;
+    small_logits<NB>(a.X, a.ldx, a.B, a.W, a.ldw, a.C, a.D, a.bias, c_begin, c_end, lds, [&](int c, float (&z)[SmallShape<NB>::CPT]) {
+#pragma unroll
+        for (int e = 0; e < SmallShape<NB>::CPT; ++e)
+            if (c + e >= c_end) z[e] = NEG_INF;                        // the next workgroup's
+        body(c, c_end - c, z);
+    });
+}
+
+template <int NB>
+__global__ __launch_bounds__(SmallShape<NB>::THREADS) void fwd_stats_small(FcArgs a, int range, float* __restrict__ part_max,
+                                                                           float* __restrict__ part_sum,
+                                                                           float* __restrict__ label_logit) {
+    typedef SmallShape<NB> S;
+    __shared__ __attribute__((aligned(16))) float lds[S::LDS_FLOATS];
+    const int row = (int)threadIdx.x / S::TPR, j = (int)threadIdx.x % S::TPR;
+    const bool row_ok = row < a.B;
+    int local = row_ok ? a.labels[row] - a.class_offset : -1;
+    const bool in_shard = local >= 0 && local < a.C;
+    if (!in_shard) local = -1;
+    float mx = NEG_INF, sum = 0.0f, label = 0.0f;
+    bool found = false;
+    small_range<NB>(a, range, blockIdx.x, a.C, lds, [&](int c, int left, const float (&z)[S::CPT]) {
+        float m = NEG_INF, s = 0.0f;
+#pragma unroll
+        for (int e = 0; e < S::CPT; ++e) m = fmaxf(m, z[e]);
+        const float shift = m == NEG_INF ? 0.0f : -m * LOG2E;
+#pragma unroll
+        for (int e = 0; e < S::CPT; ++e) s += __builtin_amdgcn_exp2f(fmaf(z[e], LOG2E, shift));
+        merge_ms(mx, sum, m, s);
+#pragma unroll
+        for (int e = 0; e < S::CPT; ++e)
+            if (local == c + e && e < left) {
+                label = z[e];
+                found = true;
+            }
+    });
+#pragma unroll
+    for (int w = S::TPR / 2; w > 0; w >>= 1) merge_ms(mx, sum, lane_xor(mx, w), lane_xor(sum, w));
+    if (j == 0) {
+        part_max[(int)blockIdx.x * S::ROWS + row] = mx;
+        part_sum[(int)blockIdx.x * S::ROWS + row] = sum;
+    }
+    if (found || (blockIdx.x == 0 && j == 0 && row_ok && !in_shard)) label_logit[row] = label;
+}
+
+// The N classes of a thread as bf16, in one store where the matrix is that wide (`left` classes are).
+template <int N>
+__device__ __forceinline__ void small_store(uint16_t* out, const float (&v)[N], int left) {
+    if constexpr (N > 1) {
+        uint32_t pk[N / 2];
+#pragma unroll
+        for (int e = 0; e < N / 2; ++e) pk[e] = pack_bf16(v[2 * e], v[2 * e + 1]);
+        if (left >= N) {
+            if constexpr (N == 8) *reinterpret_cast<u32x4*>(out) = u32x4{pk[0], pk[1], pk[2], pk[3]};
+            else *reinterpret_cast<uint32_t*>(out) = pk[0];
+            return;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < N; ++e)
+        if (e < left) out[e] = (uint16_t)pack_bf16(v[e], 0.0f);
+}
+
+// dz of the batch's rows (the contractions that read it bound their operand at the batch), up to whole k-steps of
+// classes (zeros beyond the shard: bwd_dx reads those); one db partial.
+template <int NB>
+__global__ __launch_bounds__(SmallShape<NB>::THREADS) void dz_small(FcArgs a, int range, const float* __restrict__ logsumexp,
+                                                                    float grad_scale, uint16_t* __restrict__ dZ, int64_t ldz,
+                                                                    float* __restrict__ db_part, XtArgs xt) {
+    typedef SmallShape<NB> S;
+    __shared__ __attribute__((aligned(16))) float lds[S::LDS_FLOATS + S::SLOT_FLOATS];
+    if ((int)blockIdx.x >= xt.first_block) {
+        transpose_x_tiles<S::THREADS>(a, xt, (int)blockIdx.x - xt.first_block, reinterpret_cast<char*>(lds));
+        return;
+    }
+    const int row = (int)threadIdx.x / S::TPR, j = (int)threadIdx.x % S::TPR;
+    const bool row_ok = row < a.B;
+    const float gs = row_ok ? grad_scale : 0.0f;
+    const float shift = __log2f(fabsf(gs)) - (row_ok ? logsumexp[row] : 0.0f) * LOG2E;
+    const int local = row_ok ? a.labels[row] - a.class_offset : -1;
+    const int classes = (a.C + TILE_K - 1) / TILE_K * TILE_K;
+    float* tile_f32 = lds + S::LDS_FLOATS;
+    small_range<NB>(a, range, blockIdx.x, classes, lds, [&](int c, int left, float (&z)[S::CPT]) {
+#pragma unroll
+        for (int e = 0; e < S::CPT; ++e) {
+            z[e] = __builtin_amdgcn_exp2f(fmaf(z[e], LOG2E, shift));
+            if (grad_scale < 0.0f) z[e] = -z[e];
+            if (local == c + e && c + e < a.C) z[e] -= gs;
+        }
+        if (row_ok) small_store<S::CPT>(dZ + (int64_t)row * ldz + c, z, left);
+        if (db_part != nullptr) {
+#pragma unroll
+            for (int e = 0; e < S::CPT; ++e) tile_f32[row * SMALL_PITCH + S::CPT * j + e] = z[e];
+            wait_counts<NO_VM_WAIT, 0>();
+            raw_barrier();                             // and the barrier of the next 32 classes comes before the next write
+            const int first = c - S::CPT * j;          // of the 32
+            if ((int)threadIdx.x < SMALL_C && (int)threadIdx.x < left + S::CPT * j) {
+                float s = 0.0f;
+#pragma unroll 8
+                for (int r = 0; r < S::ROWS; ++r) s += tile_f32[r * SMALL_PITCH + threadIdx.x];
+                db_part[first + (int)threadIdx.x] = s;
+            }
+        }
+    });
+}
+
+template <int NB>
+__global__ __launch_bounds__(SmallShape<NB>::THREADS) void predict_small(FcArgs a, int range, const float* __restrict__ logsumexp,
+                                                                         uint16_t* __restrict__ P, int64_t ldp) {
+    typedef SmallShape<NB> S;
+    __shared__ __attribute__((aligned(16))) float lds[S::LDS_FLOATS];
+    const int row = (int)threadIdx.x / S::TPR;
+    const bool row_ok = row < a.B;
+    const float shift = row_ok ? -logsumexp[row] * LOG2E : 0.0f;
+    small_range<NB>(a, range, blockIdx.x, a.C, lds, [&](int c, int left, float (&z)[S::CPT]) {
+#pragma unroll
+        for (int e = 0; e < S::CPT; ++e) z[e] = __builtin_amdgcn_exp2f(fmaf(z[e], LOG2E, shift));
+        if (row_ok) small_store<S::CPT>(P + (int64_t)row * ldp + c, z, left);
+    });
+}
+
+template <int NB>
+__global__ __launch_bounds__(SmallShape<NB>::THREADS) void top1_small(FcArgs a, int range, float* __restrict__ part_val,
+                                                                      int* __restrict__ part_cls) {
+    typedef SmallShape<NB> S;
+    __shared__ __attribute__((aligned(16))) float lds[S::LDS_FLOATS];
+    const int row = (int)threadIdx.x / S::TPR, j = (int)threadIdx.x % S::TPR;
+    float best = NEG_INF;
+    int cls = INT_MAX;
+    small_range<NB>(a, range, blockIdx.x, a.C, lds, [&](int c, int, const float (&z)[S::CPT]) {
+#pragma unroll
+        for (int e = 0; e < S::CPT; ++e)
+            if (z[e] > best) {                                   // a thread's classes come in increasing order
+                best = z[e];
+                cls = c + e;
+            }
+    });
+#pragma unroll
+    for (int w = S::TPR / 2; w > 0; w >>= 1) better_of(best, cls, lane_xor(best, w), __shfl_xor(cls, w, 64));
+    if (j == 0) {
+        part_val[(int)blockIdx.x * S::ROWS + row] = best;
+        part_cls[(int)blockIdx.x * S::ROWS + row] = cls;
+    }
+}
+
 struct DxArgs {
     const uint16_t* dZ; int64_t ldz;     // [Bpad][Cpad]
     const uint16_t* W; int64_t ldw;      // [C][D]
     int B, D, C;
-    int Bpad;
     int nDT, nBT, splits, steps_per_split, steps_total;
     float* out; int64_t ldo; int64_t split_stride;   // out[split][b][d]
 };
@@ -783,7 +963,7 @@ __global__ __launch_bounds__(NTHREADS) void bwd_dx(DxArgs a) {
 
     acc_t acc;
     zero_acc(acc);
-    const Operand A = make_operand(a.dZ, a.ldz, a.Bpad, a.ldz);
+    const Operand A = make_operand(a.dZ, a.ldz, a.B, a.ldz);      // rows beyond the batch read as zeros
     const Operand Bo = make_operand(a.W, a.ldw, a.C, a.D);          // classes beyond the shard read as zeros
     gemm_mainloop<KS>(acc, A, Bo, bt * TILE_M, dt * TILE_N, s0 * TILE_K, ns, lds);
 
@@ -874,7 +1054,7 @@ __device__ __forceinline__ void finish_bwd(const FinishArgs& f, int worker) {
 struct DwArgs {
     const uint16_t* XT; int64_t ldxt;    // [D][Bpad]
     const uint16_t* dZ; int64_t ldz;     // [Bpad][Cpad]
-    int D, C, Bpad;
+    int D, C, B;
     int nDT, nCT, k_steps;
     uint16_t* dW; int64_t lddw;          // sgd: the weights themselves, updated in place
     int sgd; float lr;
@@ -896,7 +1076,7 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, char* lds, unsigned lon
     acc_t acc;
     zero_acc(acc);
     const Operand A = make_operand(a.XT, a.ldxt, a.D, a.ldxt);
-    const Operand Bo = make_operand(a.dZ, a.ldz, a.Bpad, a.ldz);
+    const Operand Bo = make_operand(a.dZ, a.ldz, a.B, a.ldz);      // rows beyond the batch read as zeros
     if (TRACE) stamp[1] = __builtin_readcyclecounter();
     // workgroups are dealt out 256 at a time, 32 to each XCD: alternate the direction round by round, so that a
     // compute unit's next tile finds the end of the X^T panels, which it has just read, still in the L2
@@ -943,7 +1123,7 @@ __device__ __forceinline__ void dw_thin(const DwArgs& a, int q, char* lds) {
 #pragma unroll
         for (int j = 0; j < THIN_NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const Operand A = make_operand(a.XT, a.ldxt, a.D, a.ldxt);
-    const Operand Bo = make_operand(a.dZ, a.ldz, a.Bpad, a.ldz);
+    const Operand Bo = make_operand(a.dZ, a.ldz, a.B, a.ldz);      // rows beyond the batch read as zeros
     thin_mainloop<KS>(acc, A, Bo, dt * TILE_M, c0, 0, a.k_steps, lds);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, jl = lane & 15;
 #pragma unroll
@@ -1022,7 +1202,7 @@ __global__ __launch_bounds__(NTHREADS) void bwd_dw_stream(DwArgs a, FinishArgs f
     if (share.count == 0) return;
     DwEpilogue<RATE> epi(a, share, lds);
     const Operand A = make_operand(a.XT, a.ldxt, a.D, a.ldxt);
-    const Operand Bo = make_operand(a.dZ, a.ldz, a.Bpad, a.ldz);
+    const Operand Bo = make_operand(a.dZ, a.ldz, a.B, a.ldz);      // rows beyond the batch read as zeros
     const auto tile_at = [&](int round) {
         const int tile = share.tile(round);
         return StreamTile{(tile % a.nDT) * TILE_M, (tile / a.nDT) * TILE_N, (round & 1) != 0};
@@ -1072,6 +1252,28 @@ static const int DW_PREFETCH_MAX_K_STEPS = 64;
 static const int64_t STREAM_MAX_LD = (int64_t)1 << 22;
 // Workgroups appended to a GEMM launch for its small side job (X^T, the final reductions).
 static const int SIDE_BLOCKS = 128;
+
+// Small batches: rows that fit the registers of gemm_small.h.  Its kernels are as fast as the
+// 256 x 256 and 256 x 64 tiles or faster up to their last row.  Forward and combine, us, tiles and here: B = 32, C = 100 000,
+// D = 2048: 101 and 81, D = 512: 39 and 25; C = 12 500, D = 2048: 36.5 and 20; B = 64, C = 100 000, D = 2048: 103 and 91, D = 512:
+// 39 and 39; C = 12 500, D = 2048: 37 and 28.  More features than the registers hold take the tiles.
+struct SmallPlan {
+    int rows, range, ranges, threads;
+    SmallPlan(int32_t B, int32_t C) {
+        rows = B <= 16 ? 16 : B <= 32 ? 32 : 64;
+        threads = rows == 64 ? SmallShape<4>::THREADS : SmallShape<2>::THREADS;
+        const int even = (int)round_up((C + SMALL_MAX_RANGES - 1) / SMALL_MAX_RANGES, 8);   // whole 16-byte stores
+        range = std::max(even, rows == 64 ? SmallShape<4>::MIN_RANGE : SmallShape<2>::MIN_RANGE);
+        ranges = (C + range - 1) / range;
+    }
+};
+static inline bool small_batch(int32_t B, int32_t D) { return B <= SMALL_MAX_ROWS && D <= SMALL_MAX_STEPS * TILE_K; }
+#define WS_LAUNCH_SMALL(kid, name, plan, grid, stream, ...)                                                   \
+    do {                                                                                                      \
+        if ((plan).rows == 16) WS_LAUNCH(kid, name<1>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__); \
+        else if ((plan).rows == 32) WS_LAUNCH(kid, name<2>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__); \
+        else WS_LAUNCH(kid, name<4>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__);                  \
+    } while (0)
 
 struct BwdPlan {
     int64_t Bpad, Cpad;
@@ -1249,11 +1451,19 @@ static int launch_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t l
     float* part_max = static_cast<float*>(workspace);
     float* part_sum = part_max + (size_t)a.nCT * a.Bpad;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    a.plan = plan_tiles(a.nBT * a.nCT, true);
-    WS_LAUNCH(KID_FWD, fwd_logits_stats, dim3(a.plan.thin_first + a.plan.n_thin), dim3(NTHREADS), s, a, part_max,
-                       part_sum, label_logit);
-    WS_LAUNCH(KID_MERGE, merge_class_tiles, dim3((B + 15) / 16), dim3(1024), s, part_max, part_sum, a.nCT,
-                       a.Bpad, B, row_max, row_sumexp);
+    int parts = a.nCT, pitch = a.Bpad;
+    if (small_batch(B, D)) {
+        const SmallPlan p(B, C_shard);
+        parts = p.ranges;
+        pitch = p.rows;
+        WS_LAUNCH_SMALL(KID_FWD, fwd_stats_small, p, p.ranges, s, a, p.range, part_max, part_sum, label_logit);
+    } else {
+        a.plan = plan_tiles(a.nBT * a.nCT, true);
+        WS_LAUNCH(KID_FWD, fwd_logits_stats, dim3(a.plan.thin_first + a.plan.n_thin), dim3(NTHREADS), s, a, part_max,
+                  part_sum, label_logit);
+    }
+    WS_LAUNCH(KID_MERGE, merge_class_tiles, dim3((B + 15) / 16), dim3(1024), s, part_max, part_sum, parts, pitch, B, row_max,
+              row_sumexp);
     return launch_status();
 }
 
@@ -1337,15 +1547,23 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     a.Bpad = (int)p.Bpad; a.nBT = p.nBT; a.nCT = p.nCT;
     XtArgs xt;
     xt.XT = XT; xt.ldxt = p.Bpad;
-    a.plan = plan_tiles(p.nBT * p.nCT, true);
-    xt.first_block = a.plan.thin_first + a.plan.n_thin;
-    xt.n_blocks = (int)std::min<int64_t>((p.Bpad / 64) * (D / 64), SIDE_BLOCKS);
-    WS_LAUNCH(KID_DZ, bwd_recompute_dz, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s, a, logsumexp,
-              grad_scale, dZ, p.Cpad, db_shard ? db_part : nullptr, xt);
+    xt.n_blocks = (int)std::min<int64_t>(((B + 63) / 64) * (int64_t)(D / 64), SIDE_BLOCKS);
+    const bool small = small_batch(B, D);
+    if (small) {
+        const SmallPlan sp(B, (int32_t)round_up(C_shard, TILE_K));
+        xt.first_block = sp.ranges;
+        WS_LAUNCH_SMALL(KID_DZ, dz_small, sp, xt.first_block + xt.n_blocks, s, a, sp.range, logsumexp, grad_scale, dZ, p.Cpad,
+                        db_shard ? db_part : nullptr, xt);
+    } else {
+        a.plan = plan_tiles(p.nBT * p.nCT, true);
+        xt.first_block = a.plan.thin_first + a.plan.n_thin;
+        WS_LAUNCH(KID_DZ, bwd_recompute_dz, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s, a, logsumexp,
+                  grad_scale, dZ, p.Cpad, db_shard ? db_part : nullptr, xt);
+    }
 
     DxArgs x;
     x.dZ = dZ; x.ldz = p.Cpad; x.W = a.W; x.ldw = ldw;
-    x.B = B; x.D = D; x.C = C_shard; x.Bpad = (int)p.Bpad;
+    x.B = B; x.D = D; x.C = C_shard;
     x.nDT = p.nDT; x.nBT = p.nBT; x.splits = p.splits; x.steps_per_split = p.steps_per_split;
     x.steps_total = p.steps_total;
     const bool direct = p.splits == 1 && !accumulate_dx;
@@ -1355,7 +1573,7 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     WS_LAUNCH(KID_DX, bwd_dx, dim3(xcd_grid(p.nDT * p.nBT * p.splits)), dim3(NTHREADS), s, x);
     DwArgs w;
     w.XT = XT; w.ldxt = p.Bpad; w.dZ = dZ; w.ldz = p.Cpad;
-    w.D = D; w.C = C_shard; w.Bpad = (int)p.Bpad;
+    w.D = D; w.C = C_shard; w.B = B;
     w.nDT = p.nDT; w.nCT = p.nCT; w.k_steps = (B + TILE_K - 1) / TILE_K;
     w.dW = static_cast<uint16_t*>(dW_shard); w.lddw = lddw;
     w.sgd = sgd; w.lr = lr;
@@ -1364,7 +1582,7 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     FinishArgs f;
     f.parts = direct ? nullptr : parts; f.splits = p.splits; f.split_stride = (int64_t)B * D;
     f.B = B; f.D = D; f.dX = dX_partial; f.lddx = lddx; f.accumulate = accumulate_dx;
-    f.db_part = db_shard ? db_part : nullptr; f.n_db_parts = 4 * p.nBT; f.db_stride = p.Cpad;
+    f.db_part = db_shard ? db_part : nullptr; f.n_db_parts = small ? 1 : 4 * p.nBT; f.db_stride = p.Cpad;
     f.C = C_shard; f.db = db_shard;
     f.sgd = sgd; f.lr = lr;
     f.first_block = w.plan.thin_first + w.plan.n_thin;
@@ -1422,10 +1640,14 @@ int ws_split_fc_predict(const void* X, int64_t ldx, const void* W_shard, int64_t
     a.Bpad = (int)round_up(B, 256);
     a.nBT = a.Bpad / 256;
     a.nCT = (int)(round_up(C_shard, 256) / 256);
-    a.plan = plan_tiles(a.nBT * a.nCT, false);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    WS_LAUNCH(KID_PREDICT, predict_probs, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, logsumexp,
-              static_cast<uint16_t*>(P), ldp);
+    if (small_batch(B, D)) {
+        const SmallPlan p(B, C_shard);
+        WS_LAUNCH_SMALL(KID_PREDICT, predict_small, p, p.ranges, s, a, p.range, logsumexp, static_cast<uint16_t*>(P), ldp);
+    } else {
+        WS_LAUNCH(KID_PREDICT, predict_probs, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, logsumexp,
+                  static_cast<uint16_t*>(P), ldp);
+    }
     return launch_status();
 }
 
@@ -1450,13 +1672,20 @@ int ws_split_fc_top1(const void* X, int64_t ldx, const void* W_shard, int64_t ld
     a.Bpad = (int)round_up(B, 256);
     a.nBT = a.Bpad / 256;
     a.nCT = (int)(round_up(C_shard, 256) / 256);
-    a.plan = plan_tiles(a.nBT * a.nCT, false);
     float* part_val = static_cast<float*>(workspace);
     int* part_cls = reinterpret_cast<int*>(part_val + (size_t)a.nCT * a.Bpad);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    WS_LAUNCH(KID_TOP1, top1_logits, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, part_val, part_cls);
-    WS_LAUNCH(KID_TOP1_MERGE, merge_top1, dim3((B + 15) / 16), dim3(1024), s, part_val, part_cls, a.nCT,
-              (int64_t)a.Bpad, B, class_offset, top_logit, top_class);
+    int parts = a.nCT, pitch = a.Bpad;
+    if (small_batch(B, D)) {
+        const SmallPlan p(B, C_shard);
+        parts = p.ranges;
+        pitch = p.rows;
+        WS_LAUNCH_SMALL(KID_TOP1, top1_small, p, p.ranges, s, a, p.range, part_val, part_cls);
+    } else {
+        WS_LAUNCH(KID_TOP1, top1_logits, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, part_val, part_cls);
+    }
+    WS_LAUNCH(KID_TOP1_MERGE, merge_top1, dim3((B + 15) / 16), dim3(1024), s, part_val, part_cls, parts, (int64_t)pitch, B,
+              class_offset, top_logit, top_class);
     return launch_status();
 }
 
