@@ -1084,13 +1084,16 @@ __device__ __forceinline__ void dw_tile(const DwArgs& a, char* lds, unsigned lon
     if (TRACE) stamp[2] = __builtin_readcyclecounter();
 
     // [class][feature] tile through LDS, then whole 512-byte rows of dW
-    acc_to_lds_bf16<KS>(acc, lds);
-    __syncthreads();
-    if (TRACE) stamp[3] = __builtin_readcyclecounter();
     const int c_left = a.C - ct * TILE_N, d_left = a.D - dt * TILE_M;
     uint16_t* out = a.dW + (int64_t)ct * TILE_N * a.lddw + dt * TILE_M;
     const int n_valid = c_left < TILE_N ? c_left : TILE_N, m_valid = d_left < TILE_M ? d_left : TILE_M;
-    if (a.sgd) lds_tile_update_rows(lds, out, a.lddw, n_valid, m_valid, a.lr);
+    u32x4 weights[UPDATE_CHUNKS];
+    if (a.sgd) tile_update_load(weights, out, a.lddw, n_valid, m_valid);
+    acc_to_lds_bf16<KS>(acc, lds);
+    wait_counts<NO_VM_WAIT, 0>();
+    raw_barrier();                                       // the weights may still be on their way
+    if (TRACE) stamp[3] = __builtin_readcyclecounter();
+    if (a.sgd) lds_tile_update_rows(lds, weights, out, a.lddw, n_valid, m_valid, a.lr);
     else lds_tile_store_rows(lds, out, a.lddw, n_valid, m_valid);
     if (TRACE) {
         stamp[4] = __builtin_readcyclecounter();
@@ -1141,8 +1144,13 @@ __device__ __forceinline__ void dw_thin(const DwArgs& a, int q, char* lds) {
     const int c_left = a.C - c0, d_left = a.D - dt * TILE_M;
     uint16_t* out = a.dW + (int64_t)c0 * a.lddw + dt * TILE_M;
     const int n_valid = c_left < THIN_N ? c_left : THIN_N, m_valid = d_left < TILE_M ? d_left : TILE_M;
-    if (a.sgd) lds_tile_update_rows(lds, out, a.lddw, n_valid, m_valid, a.lr);
-    else lds_tile_store_rows(lds, out, a.lddw, n_valid, m_valid);
+    if (a.sgd) {
+        u32x4 weights[UPDATE_CHUNKS];
+        tile_update_load(weights, out, a.lddw, n_valid, m_valid);
+        lds_tile_update_rows(lds, weights, out, a.lddw, n_valid, m_valid, a.lr);
+    } else {
+        lds_tile_store_rows(lds, out, a.lddw, n_valid, m_valid);
+    }
 }
 
 __global__ __launch_bounds__(NTHREADS) void bwd_dw(DwArgs a, FinishArgs fin) {
