@@ -324,8 +324,7 @@ __device__ __forceinline__ void zero_acc(acc_t& acc) {
 // A launch whose tile count is not a multiple of the 256 compute units ends with a round in which
 // most of them idle.  The tiles of that last round can instead be cut into four "thin" tiles of
 // 256 x 64 (one wave column of a full tile each) and handed to four times as many workgroups.  A thin
-// tile does a quarter of the MFMA work for 5/8 of the staging traffic, about a quarter to a third of a full
-// tile's time.
+// tile does a quarter of the MFMA work for 5/8 of the staging traffic in about half of a full tile's time.
 constexpr int THIN_N = WAVE_N;                         // 64 columns
 constexpr int THIN_WAVE_M = TILE_M / 8;                // a wave of a thin tile: 32 rows x 64 columns
 constexpr int THIN_MT = THIN_WAVE_M / 16, THIN_NT = THIN_N / 16;
@@ -424,7 +423,7 @@ __device__ __forceinline__ void thin_mainloop(thin_acc_t& acc, const Operand& A,
 }
 
 // How a launch of n_tiles full tiles is cut: the tiles of the last, partial round become thin tiles
-// when that round would leave at least half of the compute units idle.
+// when those fit one round of the compute units.
 struct TilePlan {
     int n_full;      // full tiles, logical ids 0 .. n_full - 1 (workgroups 0 .. 8 * ceil(n_full / 8) - 1)
     int n_thin;      // thin tiles: 4 per remaining full tile, workgroups thin_first .. thin_first + n_thin - 1
