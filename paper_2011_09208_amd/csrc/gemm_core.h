@@ -83,6 +83,14 @@ __device__ __forceinline__ void load_to_lds(const Operand& op, uint32_t voff, ui
                  :: "s"(lds_off), "v"(voff), "s"(op.rsrc), "s"(soff) : "memory");
 }
 
+// Brings a line into the L2: 4 bytes per lane, to LDS byte lds_off + 4 * lane, where nobody reads them.  To LDS because a
+// load in inline assembly may not have a register for its result: the compiler takes an output as written at once, and
+// moves other values into its register while the load is still on its way.
+__device__ __forceinline__ void touch_line(const Operand& op, uint32_t voff, uint32_t soff, uint32_t lds_off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+                 :: "s"(lds_off), "v"(voff), "s"(op.rsrc), "s"(soff) : "memory");
+}
+
 // LDS byte offset of a pointer into a __shared__ array.
 __device__ __forceinline__ uint32_t lds_offset(const char* lds) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)lds;

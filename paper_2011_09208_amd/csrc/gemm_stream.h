@@ -155,7 +155,7 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
     // The prefetch cursor runs PREFETCH_STEPS k-steps ahead of the loads.  Line L of the 256 lines of a tile's k-step:
     // row L (KC), or columns 64 (L % 4) .. + 63 of k-row L / 4 (KS).  This workgroup touches one of `shares` parts of
     // them, wave w an eighth of that, one load of 4 bytes for all (lanes share lines).
-    uint32_t p_src = 0, p_inc = 0, p_lane = 0, touched = 0;
+    uint32_t p_src = 0, p_inc = 0, p_lane = 0;
     int p_round = 0, p_left = 0;
     auto prefetch_tile = [&](int round) {
         const StreamTile t = tile_at(round);
@@ -181,11 +181,11 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
         prefetch_tile(0);
         for (int j = 0; j < 2 + PREFETCH_STEPS; ++j) prefetch_next();
     }
-    auto prefetch = [&]() {
+    // The bytes go to the part of A half 1 that this wave's next load_a(1, stage) overwrites: a wave's loads return in the
+    // order in which they were issued.
+    auto prefetch = [&](int stage) {
         if (PREFETCH == PREFETCH_NONE) return;
-        // "+v": the register is written when the line arrives, so it must stay reserved
-        asm volatile("buffer_load_dword %0, %1, %2, %3 offen"
-                     : "+v"(touched) : "v"(p_lane), "s"(PREFETCH == PREFETCH_A ? A.rsrc : Bop.rsrc), "s"(p_src) : "memory");
+        touch_line(PREFETCH == PREFETCH_A ? A : Bop, p_lane, p_src, lds_wave + stage + HALF_TILE_BYTES);
         prefetch_next();
     };
 
@@ -256,7 +256,7 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
         stores(std::integral_constant<int, 3>());
         if constexpr (LAST) epi.template finish<2>(acc);
         if constexpr (V == FETCH_STEP) epi.template fetch<3>();
-        prefetch();
+        prefetch(cur);
         load_a(1, cur);
         cursor_next();
         wait_counts<12 + 2 * P + stream_window_stores(RATE, V, 3) + (FIRST ? E : 0), 0>();
@@ -285,7 +285,6 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
     epi.template fetch<3>();
 #pragma unroll
     for (int n = 0; n < (RATE == 4 ? 8 : 4); ++n) epi.template store<9>();
-    asm volatile("" :: "v"(touched));
     wait_counts<0, 0>();                                 // the loads past the last tile write LDS
 }
 
