@@ -1,5 +1,5 @@
-// Persistent form of the GEMM main loop (gemm_core.h): one workgroup per compute unit walks a list of output tiles
-// as ONE stream of k-steps.  The loads run two k-steps ahead across tile boundaries, so a tile starts on operands
+// Persistent form of the GEMM main loop (gemm_core.h) with a k-strided B operand: one workgroup per compute unit walks a
+// list of output tiles as ONE stream of k-steps.  The loads run two k-steps ahead across tile boundaries, so a tile starts on operands
 // that are already in LDS; the epilogue of a tile sits in the LOAD slots around the boundary, where the other wave
 // of the SIMD feeds the matrix core; and the stores of a tile are spread over the k-steps of the next one.
 #pragma once
@@ -67,12 +67,11 @@ constexpr int stream_window_stores(int rate, int step, int phase) {
     }
     return n;
 }
-// Prefetch of one operand's lines into the L2, for an operand that comes from HBM while the kernel writes much: with
+// Prefetch of B's lines into the L2, for an operand that comes from HBM while the kernel writes much: with
 // writes in flight a few of a k-step's 256 lines arrive late, and all eight waves wait for the last one.  A load that
 // brings a line into the L2 three k-steps before its tile's loads hides that (dW, B = 1024, D = 2048, C = 100 000: 372 ->
 // 345 us; B = 256: 165 -> 141); further ahead changes nothing.  Where the lines are near anyway it costs 2 %.
 // Workgroups of an XCD that run tiles with the same panel share the work: this one is `index` of `count` (1, 2, 4, 8).
-enum { PREFETCH_NONE, PREFETCH_A, PREFETCH_B };
 constexpr int PREFETCH_STEPS = 3;
 struct PrefetchShare {
     int index, count;
@@ -93,12 +92,9 @@ constexpr int stream_rate(int k_steps) { return k_steps >= 10 ? 1 : k_steps >= 6
 //   store<n>()        issue exactly one vector-memory store, of the oldest of the at most n values that are fetched
 //                     and not stored (called 16 times between fetch<0> of one tile and of the next, and more often:
 //                     then, and before the first tile is finished, the store must have no effect)
-//   LOADS             vector-memory loads that load_extra() issues
-//   load_extra()      called once per tile, in its first k-step, after finish<3> of the tile before; its loads are
-//                     complete before finish<0>
 // Loads and stores count in one order, so the wait of a phase allows the 12 loads of the main loop plus the stores
-// and extra loads (and the prefetch, in phase 3) issued in the last six phases.
-template <int BKIND, int RATE, int PREFETCH, class TileAt, class Epi>
+// (and the prefetch, in phase 3) issued in the last six phases.
+template <int RATE, bool PREFETCH, class TileAt, class Epi>
 __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop, int k_steps, int rounds,
                                             TileAt tile_at, PrefetchShare share, Epi& epi, char* lds) {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -112,12 +108,8 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
     const uint32_t a_lane = ((uint32_t)a_row * A.ld + (uint32_t)(8 * kc_chunk)) * 2u;
     const uint32_t a_half = 128u * A.ld, a_second = 256u * A.ld;
     const int k4 = 4 * wave + (lane >> 4);
-    const uint32_t b_lane = BKIND == KC
-        ? ((uint32_t)(64 * (wave >> 2) + 8 * (wave & 3) + r8) * Bop.ld + (uint32_t)(8 * kc_chunk)) * 2u
-        : ((uint32_t)k4 * Bop.ld + (uint32_t)(8 * ((lane & 15) ^ ks_swizzle(k4)))) * 2u;
-    const uint32_t b_half = BKIND == KC ? 64u * Bop.ld : 256u;
-    const uint32_t b_second = BKIND == KC ? 256u * Bop.ld : 64u * Bop.ld;
-    const uint32_t b_step = BKIND == KC ? 128u : 128u * Bop.ld;
+    const uint32_t b_lane = ((uint32_t)k4 * Bop.ld + (uint32_t)(8 * ((lane & 15) ^ ks_swizzle(k4)))) * 2u;
+    const uint32_t b_second = 64u * Bop.ld, b_step = 128u * Bop.ld;
     const uint32_t lds_wave = lds_offset(lds) + 1024u * (uint32_t)wave;
 
     // The load cursor: a k-step of some tile, two k-steps ahead of the MFMAs.  Past the last tile it starts that tile
@@ -128,7 +120,7 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
         const StreamTile t = tile_at(round);
         const uint32_t k = t.descending ? (uint32_t)(k_steps - 1) : 0u;
         a_src = (uint32_t)t.m0 * A.ld * 2u + k * 128u;
-        b_src = (BKIND == KC ? (uint32_t)t.n0 * Bop.ld * 2u : (uint32_t)t.n0 * 2u) + k * b_step;
+        b_src = (uint32_t)t.n0 * 2u + k * b_step;
         a_inc = t.descending ? 0u - 128u : 128u;
         b_inc = t.descending ? 0u - b_step : b_step;
         load_left = k_steps;
@@ -147,23 +139,21 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
         load_to_lds(A, a_lane, src + a_second, dst + HALF_TILE_BYTES / 2);
     };
     auto load_b = [&](int half, int stage) {
-        const uint32_t src = b_src + half * b_half, dst = lds_wave + stage + OPERAND_TILE_BYTES + half * HALF_TILE_BYTES;
+        const uint32_t src = b_src + half * 256u, dst = lds_wave + stage + OPERAND_TILE_BYTES + half * HALF_TILE_BYTES;
         load_to_lds(Bop, b_lane, src, dst);
         load_to_lds(Bop, b_lane, src + b_second, dst + HALF_TILE_BYTES / 2);
     };
 
     // The prefetch cursor runs PREFETCH_STEPS k-steps ahead of the loads.  Line L of the 256 lines of a tile's k-step:
-    // row L (KC), or columns 64 (L % 4) .. + 63 of k-row L / 4 (KS).  This workgroup touches one of `shares` parts of
-    // them, wave w an eighth of that, one load of 4 bytes for all (lanes share lines).
+    // columns 64 (L % 4) .. + 63 of k-row L / 4.  This workgroup touches one of `share.count` parts of them, wave w an
+    // eighth of that, one load of 4 bytes for all (lanes share lines).
     uint32_t p_src = 0, p_inc = 0, p_lane = 0;
     int p_round = 0, p_left = 0;
     auto prefetch_tile = [&](int round) {
         const StreamTile t = tile_at(round);
         const uint32_t k = t.descending ? (uint32_t)(k_steps - 1) : 0u;
-        const uint32_t step_bytes = PREFETCH == PREFETCH_A ? 128u : b_step;
-        p_src = (PREFETCH == PREFETCH_A ? (uint32_t)t.m0 * A.ld * 2u : BKIND == KC ? (uint32_t)t.n0 * Bop.ld * 2u : (uint32_t)t.n0 * 2u) +
-                k * step_bytes;
-        p_inc = t.descending ? 0u - step_bytes : step_bytes;
+        p_src = (uint32_t)t.n0 * 2u + k * b_step;
+        p_inc = t.descending ? 0u - b_step : b_step;
         p_left = k_steps;
     };
     auto prefetch_next = [&]() {
@@ -173,23 +163,22 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
             prefetch_tile(p_round);
         }
     };
-    if (PREFETCH != PREFETCH_NONE) {
+    if (PREFETCH) {
         const int per_wave = 32 / share.count;
         const int line = (8 * share.index + wave) * per_wave + (lane & (per_wave - 1));
-        if (PREFETCH == PREFETCH_B && BKIND == KS) p_lane = ((uint32_t)(line >> 2) * Bop.ld + (uint32_t)(64 * (line & 3))) * 2u;
-        else p_lane = (uint32_t)line * (PREFETCH == PREFETCH_A ? A.ld : Bop.ld) * 2u;
+        p_lane = ((uint32_t)(line >> 2) * Bop.ld + (uint32_t)(64 * (line & 3))) * 2u;
         prefetch_tile(0);
         for (int j = 0; j < 2 + PREFETCH_STEPS; ++j) prefetch_next();
     }
     // The bytes go to the part of A half 1 that this wave's next load_a(1, stage) overwrites: a wave's loads return in the
     // order in which they were issued.
     auto prefetch = [&](int stage) {
-        if (PREFETCH == PREFETCH_NONE) return;
-        touch_line(PREFETCH == PREFETCH_A ? A : Bop, p_lane, p_src, lds_wave + stage + HALF_TILE_BYTES);
+        if (!PREFETCH) return;
+        touch_line(Bop, p_lane, p_src, lds_wave + stage + HALF_TILE_BYTES);
         prefetch_next();
     };
 
-    const FragReader<BKIND> frag(wm, wn, i, g);
+    const FragReader<KS> frag(wm, wn, i, g);
     bf16x8 af[MT / 2][2], bf0[NT / 2][2], bf1[NT / 2][2];
     acc_t acc;
 
@@ -208,8 +197,8 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
 
     auto step = [&](auto which) {
         constexpr int V = decltype(which)::value;
-        constexpr bool FIRST = V == FIRST_STEP, LAST = V == LAST_STEP, SECOND = V == SECOND_STEP;
-        constexpr int E = Epi::LOADS, P = PREFETCH != PREFETCH_NONE;
+        constexpr bool FIRST = V == FIRST_STEP, LAST = V == LAST_STEP;
+        constexpr int P = PREFETCH;
         constexpr int WAITING = FIRST || LAST ? 9 : 4;
         const int nxt = STAGE_BYTES - cur;
         auto stores = [&](auto phase) {
@@ -222,21 +211,18 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
         stores(std::integral_constant<int, 0>());
         if constexpr (FIRST) epi.template finish<3>(acc);
         load_b(0, cur);
-        wait_counts<12 + 2 * P + stream_window_stores(RATE, V, 0) + (SECOND ? E : 0), 0>();
+        wait_counts<12 + 2 * P + stream_window_stores(RATE, V, 0), 0>();
         raw_barrier();
         quadrant_mfmas<0, FIRST>(acc, af, bf0);
         raw_barrier();
         // phase 1
         frag.read_b(bf1, lds, 1, cur);
-        if constexpr (FIRST) {
-            epi.begin_next();
-            epi.load_extra();
-        }
+        if constexpr (FIRST) epi.begin_next();
         stores(std::integral_constant<int, 1>());
         if constexpr (LAST) epi.template finish<0>(acc);
         if constexpr (FIRST && RATE == 4) epi.template fetch<3>();
         load_a(0, cur);
-        wait_counts<12 + P + stream_window_stores(RATE, V, 1) + (FIRST || SECOND ? E : 0), 0>();
+        wait_counts<12 + P + stream_window_stores(RATE, V, 1), 0>();
         raw_barrier();
         quadrant_mfmas<1, FIRST>(acc, af, bf1);
         raw_barrier();
@@ -246,7 +232,7 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
         stores(std::integral_constant<int, 2>());
         if constexpr (LAST) epi.template finish<1>(acc);
         load_b(1, cur);
-        wait_counts<12 + P + stream_window_stores(RATE, V, 2) + (FIRST || SECOND ? E : 0), 0>();
+        wait_counts<12 + P + stream_window_stores(RATE, V, 2), 0>();
         raw_barrier();
         quadrant_mfmas<2, FIRST>(acc, af, bf0);
         raw_barrier();
@@ -259,7 +245,7 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
         prefetch(cur);
         load_a(1, cur);
         cursor_next();
-        wait_counts<12 + 2 * P + stream_window_stores(RATE, V, 3) + (FIRST ? E : 0), 0>();
+        wait_counts<12 + 2 * P + stream_window_stores(RATE, V, 3), 0>();
         raw_barrier();
         quadrant_mfmas<3, FIRST>(acc, af, bf1);
         raw_barrier();
@@ -299,7 +285,7 @@ struct RowStoreTile {
     uint32_t records;                    // bytes from there to the end of the matrix: rows beyond it are dropped
     int m_valid;                         // columns of the matrix from there (a multiple of 64)
 };
-template <int BKIND, int RATE>
+template <int RATE>
 struct RowStore {
     static constexpr int QUEUE = 9;
     u32x4 queue[QUEUE];                  // fetched values, oldest first
@@ -320,7 +306,7 @@ struct RowStore {
         for (int k = 0; k < QUEUE; ++k) queue[k] = u32x4{0, 0, 0, 0};
         const int n = lane >> 3, chunk = lane & 7;       // row of the eight, 16-byte chunk of the line
         rd = scratch + n * 128 + ((chunk ^ n) << 4);
-        lane_off = ((uint32_t)(wave_col<BKIND>(wave & 3, 0) + n) * ld + (uint32_t)(WAVE_M * wm + 8 * chunk)) * 2u;
+        lane_off = ((uint32_t)(wave_col<KS>(wave & 3, 0) + n) * ld + (uint32_t)(WAVE_M * wm + 8 * chunk)) * 2u;
 #pragma unroll
         for (int u = 0; u < 2; ++u) wr[u] = scratch + (lane & 15) * 128 + (((4 * u + (lane >> 4)) ^ (lane & 7)) << 4);
     }
@@ -348,7 +334,7 @@ struct RowStore {
     template <int WAITING>
     __device__ __forceinline__ void store() {
         const int q = next >> 2;
-        const uint32_t soff = ((uint32_t)(wave_col<BKIND>(0, 2 * (q & 1)) + 8 * (next & 3)) * ld + (uint32_t)(64 * (q >> 1))) * 2u;
+        const uint32_t soff = ((uint32_t)(wave_col<KS>(0, 2 * (q & 1)) + 8 * (next & 3)) * ld + (uint32_t)(64 * (q >> 1))) * 2u;
         const bool live = next < 16 && WAVE_M * wm + 64 * (q >> 1) < at.m_valid;
         __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(at.base, 0, live ? (int)at.records : 0, 0x00020000);
         __builtin_amdgcn_raw_buffer_store_b128(queue[0], r, (int)lane_off, (int)soff, 2);      // non-temporal

@@ -1171,16 +1171,14 @@ __global__ __launch_bounds__(NTHREADS) void bwd_dw(DwArgs a, FinishArgs fin) {
 // 69 -> 67 us (1.5 tiles per compute unit).  Feature tiles fastest and the direction of the contraction
 // alternating round by round as in dw_tile.
 template <int RATE>
-struct DwEpilogue : RowStore<KS, RATE> {
+struct DwEpilogue : RowStore<RATE> {
     const DwArgs& a;
     const StreamShare& share;
     int round = -1;
-    static constexpr int LOADS = 0;
     __device__ __forceinline__ DwEpilogue(const DwArgs& args, const StreamShare& s, char* lds) : a(args), share(s) {
         this->init(a.lddw, lds);
     }
     __device__ __forceinline__ void begin_next() { ++round; }
-    __device__ __forceinline__ void load_extra() {}
     template <int Q>
     __device__ __forceinline__ void finish(const acc_t& acc) {
         if (Q == 0) {
@@ -1195,7 +1193,7 @@ struct DwEpilogue : RowStore<KS, RATE> {
     }
 };
 
-template <int RATE, int PREFETCH>
+template <int RATE, bool PREFETCH>
 __global__ __launch_bounds__(NTHREADS) void bwd_dw_stream(DwArgs a, FinishArgs fin) {
     __shared__ __attribute__((aligned(16))) char lds[STREAM_LDS_BYTES];
     if ((int)blockIdx.x >= fin.first_block) {
@@ -1215,7 +1213,7 @@ __global__ __launch_bounds__(NTHREADS) void bwd_dw_stream(DwArgs a, FinishArgs f
         const int tile = share.tile(round);
         return StreamTile{(tile % a.nDT) * TILE_M, (tile / a.nDT) * TILE_N, (round & 1) != 0};
     };
-    gemm_stream<KS, RATE, PREFETCH>(A, Bo, a.k_steps, share.count, tile_at, PrefetchShare(share.first % a.nDT, a.nDT), epi, lds);
+    gemm_stream<RATE, PREFETCH>(A, Bo, a.k_steps, share.count, tile_at, PrefetchShare(share.first % a.nDT, a.nDT), epi, lds);
 }
 
 __global__ __launch_bounds__(NTHREADS) void bwd_dw_traced(DwArgs a, FinishArgs fin, unsigned long long* trace) {
@@ -1604,8 +1602,8 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
         f.first_block = w.plan.thin_first + w.plan.n_thin;
         const bool far = 2 * (p.Bpad * p.Cpad + (int64_t)C_shard * D) > DW_PREFETCH_MIN_BYTES && w.k_steps <= DW_PREFETCH_MAX_K_STEPS;
         const int rate = stream_rate(w.k_steps);
-        auto kernel = far ? (rate == 1 ? bwd_dw_stream<1, PREFETCH_B> : rate == 2 ? bwd_dw_stream<2, PREFETCH_B> : bwd_dw_stream<4, PREFETCH_B>)
-                          : (rate == 1 ? bwd_dw_stream<1, PREFETCH_NONE> : rate == 2 ? bwd_dw_stream<2, PREFETCH_NONE> : bwd_dw_stream<4, PREFETCH_NONE>);
+        auto kernel = far ? (rate == 1 ? bwd_dw_stream<1, true> : rate == 2 ? bwd_dw_stream<2, true> : bwd_dw_stream<4, true>)
+                          : (rate == 1 ? bwd_dw_stream<1, false> : rate == 2 ? bwd_dw_stream<2, false> : bwd_dw_stream<4, false>);
         WS_LAUNCH(KID_DW, kernel, dim3(f.first_block + f.n_blocks), dim3(NTHREADS), s, w, f);
     } else {
         WS_LAUNCH(KID_DW, bwd_dw, dim3(f.first_block + f.n_blocks), dim3(NTHREADS), s, w, f);
