@@ -1251,13 +1251,21 @@ static TilePlan plan_tiles(int n_tiles, bool allow_thin) {
 // Shortest contraction (k-steps of 64 batch rows) for which the dW kernel cuts the tiles of a ragged last round
 // into thin ones: measured slower at 16 k-steps (the last round is mostly output there), faster at 128.
 static const int DW_THIN_MIN_K_STEPS = 48;
-// The dW stream prefetches dz if bwd_dx, which runs in between, has read more than the 256 MiB Infinity Cache holds
-// (dz and W: B = 1024 and C = 12 500, 76 MB: 66.8 us without, 68.0 with; C = 100 000, 615 MB: 372 and 345) and
-// unless its tiles are so long that writes are rare (B = 8192, 128 k-steps: 624 us without, 639 with).
-static const int64_t DW_PREFETCH_MIN_BYTES = (int64_t)256 << 20;
-static const int DW_PREFETCH_MAX_K_STEPS = 64;
-// Row pitch (elements) below which 256 rows of a store tile stay within 32-bit byte offsets.
-static const int64_t STREAM_MAX_LD = (int64_t)1 << 22;
+// dW runs as a stream where a workgroup has a second tile to overlap with the first and neighbouring tiles share a dz
+// panel (more than 256 features).  Whole backward calls, one workgroup per tile and stream, us: up to 256 tiles (B = 384,
+// D = 256, C = 50 000) 88.2 and 99.3; one feature tile (B = 4096, D = 256, C = 100 000) 817 and 835; more than one round of
+// tiles, geometric means over 34 shapes of up to 16 k-steps 1.01 to 1.04 faster as a stream, the same beyond.
+static bool dw_streams(int nDT, int n_full, int k_steps, int64_t lddw) {
+    return nDT > 1 && n_full > STREAM_WGS && k_steps >= STREAM_MIN_K_STEPS && lddw < ((int64_t)1 << 22);   // 256 rows of a
+}                                                                          // store tile stay within 32-bit byte offsets
+// It prefetches dz if bwd_dx, which runs in between, has read more than the 256 MiB Infinity Cache holds (dz and W: B =
+// 1024 and C = 12 500, 76 MB: 66.8 us without, 68.0 with; C = 100 000, 615 MB: 372 and 345), unless its tiles are so
+// long that writes are rare, and where at least four workgroups share the work.  Backward calls without / with, by feature
+// tiles: 8: 1.06 at 4 k-steps, 1.02 at 16, 1.006 at 24, 0.98 at 32, 0.99 at 64; 5: 1.04 at 6, 1.01 at 16, 1.005 at 24, 0.99 at 32;
+// 3: 1.00 at 10 to 16; 2: 0.98 to 1.00; 1: 0.91 to 0.94.
+static bool dw_prefetches(int nDT, int64_t dz_and_w_bytes, int k_steps) {
+    return nDT >= 4 && k_steps <= 24 && dz_and_w_bytes > ((int64_t)256 << 20);
+}
 // Workgroups appended to a GEMM launch for its small side job (X^T, the final reductions).
 static const int SIDE_BLOCKS = 128;
 
@@ -1597,10 +1605,10 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     f.n_blocks = (f.parts || f.db_part) ? SIDE_BLOCKS : 0;
     if (g_dw_trace != nullptr) {
         WS_LAUNCH(KID_DW, bwd_dw_traced, dim3(f.first_block + f.n_blocks), dim3(NTHREADS), s, w, f, g_dw_trace);
-    } else if (w.k_steps >= STREAM_MIN_K_STEPS && !sgd && lddw < STREAM_MAX_LD) {
-        w.plan.thin_first = w.plan.n_full > 0 ? STREAM_WGS : 0;
+    } else if (!sgd && dw_streams(p.nDT, w.plan.n_full, w.k_steps, lddw)) {
+        w.plan.thin_first = STREAM_WGS;
         f.first_block = w.plan.thin_first + w.plan.n_thin;
-        const bool far = 2 * (p.Bpad * p.Cpad + (int64_t)C_shard * D) > DW_PREFETCH_MIN_BYTES && w.k_steps <= DW_PREFETCH_MAX_K_STEPS;
+        const bool far = dw_prefetches(p.nDT, 2 * (p.Bpad * p.Cpad + (int64_t)C_shard * D), w.k_steps);
         const int rate = stream_rate(w.k_steps);
         auto kernel = far ? (rate == 1 ? bwd_dw_stream<1, true> : rate == 2 ? bwd_dw_stream<2, true> : bwd_dw_stream<4, true>)
                           : (rate == 1 ? bwd_dw_stream<1, false> : rate == 2 ? bwd_dw_stream<2, false> : bwd_dw_stream<4, false>);

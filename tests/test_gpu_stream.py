@@ -1,6 +1,7 @@
-"""GPU parity of the dW kernel's tile stream at the sizes where it can go wrong: the shortest contractions of each of
-its store schedules (4, 6 and 10 k-steps of 64 rows), one more and one less, ragged row counts, feature tiles that
-hang over the edge (D = 64, 320), ragged class edges, workgroups with one tile, with two, and with none."""
+"""GPU parity of the dW kernel at the sizes where its tile stream can go wrong: the shortest contractions of each of
+its store schedules (4, 6 and 10 k-steps of 64 rows), ragged row counts, feature tiles that hang over the edge (D = 320,
+576), ragged class edges, workgroups with two tiles, with one and with none; and at the sizes next to them that take one
+workgroup per tile (three k-steps, one feature tile, up to 256 tiles)."""
 import pytest
 
 from paper_2011_09208_amd import inputs
@@ -19,10 +20,16 @@ def H():
 
 @pytest.mark.parametrize("B,D,C", [
     (192, 64, 300),                  # 3 k-steps: one short of a stream
-    (193, 320, 700),                 # 4: two feature tiles, the second 64 wide
-    (256, 64, 256 * 258 + 9),        # 4: 259 tiles, three workgroups with a second one
+    (192, 320, 256 * 128 + 1),       # 3: 258 tiles
+    (193, 320, 700),                 # 4: two feature tiles, the second 64 wide; six tiles
+    (193, 320, 256 * 128),           # 4: 256 tiles, one short of a stream
+    (193, 320, 256 * 128 + 1),       # 4: 258 tiles, two workgroups with a second one
+    (256, 64, 256 * 258 + 9),        # 4: 259 tiles of one feature tile
+    (256, 576, 256 * 91 - 3),        # 4: 273 tiles, three feature tiles; 35 to an XCD, 28 on the last: workgroups with none
     (321, 128, 256 * 256),           # 6: exactly one tile each
-    (384, 64, 256 * 257 - 250),      # 6: the last class tile 6 wide
+    (321, 320, 256 * 130 - 250),     # 6: 260 tiles, the last class tile 6 wide
+    (384, 64, 256 * 257 - 250),      # 6: the same with one feature tile
+    (576, 320, 256 * 129),           # 9: the longest of its schedule
     (577, 320, 256 * 140 + 1),       # 10: 282 tiles, ragged in rows, features and classes
     (639, 576, 256 * 100 - 7),       # 10: three feature tiles, the last 64 wide
     (1025, 64, 40),                  # 17: a single ragged tile
