@@ -160,8 +160,11 @@ __device__ __forceinline__ int wave_col(int wn, int nt) {
     return BKIND == KC ? WAVE_N * wn + 16 * nt : 128 * (nt >> 1) + 32 * wn + 16 * (nt & 1);
 }
 
-// LDS -> fragments: af[tile of the half][k-substep], bf the same for half a B.
-template <int BKIND>
+// LDS -> fragments: af[tile of the half][k-substep], bf the same for half a B.  LEAN keeps one offset per operand: chunk
+// numbers are XOR-ed with the swizzle, so the second k-substep (KC, chunk bit 2) and the second 16-wide tile (KS, bit 1)
+// are an XOR away.  For a loop that has no register left: two variants of the tile stream spilled 1 and 6 without it; the
+// others lose 1 % by its two instructions a phase.
+template <int BKIND, bool LEAN = false>
 struct FragReader {
     int a_frag[2], b_frag[2];
     __device__ __forceinline__ FragReader(int wm, int wn, int i, int g) {
@@ -177,23 +180,34 @@ struct FragReader {
             }
         }
     }
+    // Both offsets of an operand; `bit` is where they differ.  The empty assembly keeps the compiler from holding the
+    // second one between calls all the same.
+    static __device__ __forceinline__ void offsets(int (&o)[2], const int (&f)[2], int bit) {
+        o[0] = f[0];
+        if (LEAN) asm volatile("" : "+v"(o[0]));
+        o[1] = LEAN ? o[0] ^ bit : f[1];
+    }
     __device__ __forceinline__ void read_a(bf16x8 (&af)[MT / 2][2], const char* lds, int half, int stage) const {
+        int o[2];
+        offsets(o, a_frag, 64);
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
             for (int t = 0; t < MT / 2; ++t)
-                af[t][s] = *reinterpret_cast<const bf16x8*>(lds + (a_frag[s] + stage) + half * HALF_TILE_BYTES + t * 2048);
+                af[t][s] = *reinterpret_cast<const bf16x8*>(lds + (o[s] + stage) + half * HALF_TILE_BYTES + t * 2048);
     }
     __device__ __forceinline__ void read_b(bf16x8 (&bf)[NT / 2][2], const char* lds, int half, int stage) const {
+        int o[2];
+        offsets(o, b_frag, BKIND == KC ? 64 : 32);
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
             for (int t = 0; t < NT / 2; ++t) {
                 if (BKIND == KC) {
-                    bf[t][s] = *reinterpret_cast<const bf16x8*>(lds + (b_frag[s] + stage) + half * HALF_TILE_BYTES + t * 2048);
+                    bf[t][s] = *reinterpret_cast<const bf16x8*>(lds + (o[s] + stage) + half * HALF_TILE_BYTES + t * 2048);
                 } else {
                     typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
-                    const char* p = lds + (b_frag[t] + stage) + half * HALF_TILE_BYTES + s * (32 * 256);
+                    const char* p = lds + (o[t] + stage) + half * HALF_TILE_BYTES + s * (32 * 256);
                     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
                     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * 256));
                     bf[t][s] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));

@@ -178,7 +178,7 @@ __device__ __forceinline__ void gemm_stream(const Operand& A, const Operand& Bop
         prefetch_next();
     };
 
-    const FragReader<KS> frag(wm, wn, i, g);
+    const FragReader<KS, RATE == 2> frag(wm, wn, i, g);
     bf16x8 af[MT / 2][2], bf0[NT / 2][2], bf1[NT / 2][2];
     acc_t acc;
 

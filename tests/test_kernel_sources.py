@@ -1,10 +1,15 @@
-"""Host checks on the kernel sources: rules that a run of the kernels does not reliably show when they are broken."""
+"""Host checks on the kernel sources and on what they compile to: rules that a run of the kernels does not reliably
+show when they are broken."""
 import glob
 import os
 import re
+import subprocess
 
 import pytest
 
+from paper_2011_09208_amd import buildlib
+
+READELF = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2011_09208_amd", "csrc")
 
 
@@ -38,3 +43,32 @@ def test_no_load_in_flight_has_an_output_register(path):
     for template, outputs in asm_statements(open(path).read()):
         if re.search(r"\b(buffer|global|flat|scratch|ds|s)_load|\bds_read", template) and outputs:
             assert "s_waitcnt" in template.rsplit("load", 1)[1], (os.path.basename(path), template)
+
+
+def kernel_notes(lib, tmp_path):
+    """{kernel: {field: value}} from the metadata of the gfx950 code objects inside the built library."""
+    data, out, n = open(lib, "rb").read(), {}, 0
+    at = data.find(b"\x7fELF", 4)
+    while at >= 0:
+        if int.from_bytes(data[at + 18:at + 20], "little") == 224:                  # EM_AMDGPU
+            nxt = data.find(b"__CLANG_OFFLOAD_BUNDLE__", at)
+            part = tmp_path / f"{n}.co"
+            part.write_bytes(data[at:nxt if nxt > 0 else len(data)])
+            text = subprocess.run([READELF, "--notes", str(part)], check=True, capture_output=True, text=True).stdout
+            for kernel in text.split("- .agpr_count:")[1:]:
+                fields = dict(re.findall(r"^\s+\.(\w+):\s+(\S+)$", kernel, re.M))
+                out[fields["symbol"]] = fields
+            n += 1
+        at = data.find(b"\x7fELF", at + 4)
+    return out
+
+
+def test_no_kernel_spills_registers(tmp_path):
+    """A spilled register that is reloaded inside a main loop makes the wave wait for all of its loads in flight."""
+    if buildlib.is_stale():
+        buildlib.build()
+    kernels = kernel_notes(buildlib.LIB, tmp_path)
+    assert len(kernels) > 30 and sum("bwd_dw_stream" in k for k in kernels) >= 4
+    spilling = {k: v["vgpr_spill_count"] for k, v in kernels.items()
+                if v["vgpr_spill_count"] != "0" or v["sgpr_spill_count"] != "0" or v["private_segment_fixed_size"] != "0"}
+    assert not spilling, spilling
