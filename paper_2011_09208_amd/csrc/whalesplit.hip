@@ -363,11 +363,11 @@ __global__ __launch_bounds__(1024) void merge_class_tiles(const float* __restric
     for (int t0 = q; t0 < nCT; t0 += 64 * MERGE_BATCH) {
         float vm[MERGE_BATCH], vs[MERGE_BATCH];
 #pragma unroll
-        for (int k = 0; k < MERGE_BATCH; ++k) {                     // beyond the end: a tile read again, not merged
-            const int t = t0 + 64 * k < nCT ? t0 + 64 * k : t0;
-            vm[k] = part_max[(int64_t)t * Bpad + i];
-            vs[k] = part_sum[(int64_t)t * Bpad + i];
-        }
+        for (int k = 0; k < MERGE_BATCH; ++k)
+            if (t0 + 64 * k < nCT) {
+                vm[k] = part_max[(int64_t)(t0 + 64 * k) * Bpad + i];
+                vs[k] = part_sum[(int64_t)(t0 + 64 * k) * Bpad + i];
+            }
 #pragma unroll
         for (int k = 0; k < MERGE_BATCH; ++k)
             if (t0 + 64 * k < nCT) merge_ms(m, s, vm[k], vs[k]);
@@ -758,13 +758,14 @@ __global__ __launch_bounds__(1024) void merge_top1(const float* __restrict__ val
             float tv[MERGE_BATCH];
             int tc[MERGE_BATCH];
 #pragma unroll
-            for (int k = 0; k < MERGE_BATCH; ++k) {                 // beyond the end: a candidate once more
-                const int t = t0 + 64 * k < n ? t0 + 64 * k : t0;
-                tv[k] = val[t * stride + i];
-                tc[k] = cls[t * stride + i];
-            }
+            for (int k = 0; k < MERGE_BATCH; ++k)
+                if (t0 + 64 * k < n) {
+                    tv[k] = val[(t0 + 64 * k) * stride + i];
+                    tc[k] = cls[(t0 + 64 * k) * stride + i];
+                }
 #pragma unroll
-            for (int k = 0; k < MERGE_BATCH; ++k) better_of(v, c, tv[k], tc[k]);
+            for (int k = 0; k < MERGE_BATCH; ++k)
+                if (t0 + 64 * k < n) better_of(v, c, tv[k], tc[k]);
         }
     sv[q][r] = v;
     sc[q][r] = c;
@@ -781,6 +782,34 @@ __global__ __launch_bounds__(1024) void merge_top1(const float* __restrict__ val
         out_val[i] = v;
         out_cls[i] = c == INT_MAX ? c : c + base;
     }
+}
+
+// The same for a few candidates, one thread per row with its loads side by side: the tree of the kernel above costs more
+// than it saves.  B = 1024, us, here and above: 1 candidate 1.9 and 2.8, 8: 2.2 and 2.7, 12: 2.7 and 2.8, 16: 2.9 and 2.8, 64: 7.4
+// and 3.2 (B = 8192: 12: 2.8 and 3.3, 64: 7.4 and 4.1).
+constexpr int MERGE_FEW = 12;
+__global__ __launch_bounds__(64) void merge_top1_few(const float* __restrict__ val, const int* __restrict__ cls, int n,
+                                                     int64_t stride, int B, int base, float* __restrict__ out_val,
+                                                     int* __restrict__ out_cls) {
+    const int i = blockIdx.x * 64 + threadIdx.x;
+    if (i >= B) return;
+    float v = NEG_INF;
+    int c = INT_MAX;
+    for (int t0 = 0; t0 < n; t0 += MERGE_BATCH) {
+        float tv[MERGE_BATCH];
+        int tc[MERGE_BATCH];
+#pragma unroll
+        for (int k = 0; k < MERGE_BATCH; ++k)
+            if (t0 + k < n) {
+                tv[k] = val[(t0 + k) * stride + i];
+                tc[k] = cls[(t0 + k) * stride + i];
+            }
+#pragma unroll
+        for (int k = 0; k < MERGE_BATCH; ++k)
+            if (t0 + k < n) better_of(v, c, tv[k], tc[k]);
+    }
+    out_val[i] = v;
+    out_cls[i] = c == INT_MAX ? c : c + base;
 }
 
 // ---- small batches --------------------------------------------------------------------------------
@@ -1638,6 +1667,14 @@ int ws_split_fc_bwd_sgd(const void* X, int64_t ldx, void* W_shard, int64_t ldw, 
                    dX_partial, lddx, accumulate_dx, W_shard, ldw, b_shard, workspace, workspace_bytes, stream, 1, lr);
 }
 
+static void launch_merge_top1(const float* val, const int* cls, int n, int64_t stride, int B, int base, float* out_val,
+                              int* out_cls, hipStream_t s) {
+    if (n <= MERGE_FEW)
+        WS_LAUNCH(KID_TOP1_MERGE, merge_top1_few, dim3((B + 63) / 64), dim3(64), s, val, cls, n, stride, B, base, out_val, out_cls);
+    else
+        WS_LAUNCH(KID_TOP1_MERGE, merge_top1, dim3((B + 15) / 16), dim3(1024), s, val, cls, n, stride, B, base, out_val, out_cls);
+}
+
 int ws_split_fc_predict(const void* X, int64_t ldx, const void* W_shard, int64_t ldw, const float* b_shard,
                         const float* logsumexp, int32_t B, int32_t D, int32_t C_shard, void* P, int64_t ldp,
                         void* stream) {
@@ -1700,8 +1737,7 @@ int ws_split_fc_top1(const void* X, int64_t ldx, const void* W_shard, int64_t ld
     } else {
         WS_LAUNCH(KID_TOP1, top1_logits, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, part_val, part_cls);
     }
-    WS_LAUNCH(KID_TOP1_MERGE, merge_top1, dim3((B + 15) / 16), dim3(1024), s, part_val, part_cls, parts, (int64_t)pitch, B,
-              class_offset, top_logit, top_class);
+    launch_merge_top1(part_val, part_cls, parts, pitch, B, class_offset, top_logit, top_class, s);
     return launch_status();
 }
 
@@ -1713,8 +1749,7 @@ int ws_combine_top1(const float* top_logit, const int32_t* top_class, int32_t S,
     if (!aligned(top_logit, 4) || !aligned(top_class, 4) || !aligned(best_logit, 4) || !aligned(best_class, 4))
         return WS_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    WS_LAUNCH(KID_TOP1_MERGE, merge_top1, dim3((B + 15) / 16), dim3(1024), s, top_logit, top_class, S, shard_stride,
-              B, 0, best_logit, best_class);
+    launch_merge_top1(top_logit, top_class, S, shard_stride, B, 0, best_logit, best_class, s);
     return launch_status();
 }
 

@@ -1,6 +1,6 @@
 """GPU parity of the kernels that merge statistics across shards, at the batch and workgroup edges of their loops:
 combine_partials loads eight shards at a time, merge_top1 deals candidates to 64 threads per row and 16 rows per
-workgroup."""
+workgroup, or one thread to a row for up to twelve candidates."""
 import numpy as np
 import pytest
 
@@ -39,7 +39,8 @@ def test_combine_partials_batches_of_shards(ws, S, B):
     assert (np.abs(loss.cpu().numpy() - (ref - t.sum(0))) <= 2 * tol).all()
 
 
-@pytest.mark.parametrize("S,B", [(1, 1), (2, 15), (63, 16), (64, 17), (65, 33), (391, 2)])
+@pytest.mark.parametrize("S,B", [(1, 1), (2, 15), (8, 63), (9, 64), (12, 65), (13, 65), (63, 16), (64, 17), (65, 33), (391, 2),
+                                 (513, 16)])
 def test_combine_top1_groups_of_candidates(ws, S, B):
     import torch
     rng = np.random.default_rng(100 * S + B)
