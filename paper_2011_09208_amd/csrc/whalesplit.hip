@@ -1298,10 +1298,7 @@ static bool dw_prefetches(int nDT, int64_t dz_and_w_bytes, int k_steps) {
 // Workgroups appended to a GEMM launch for its small side job (X^T, the final reductions).
 static const int SIDE_BLOCKS = 128;
 
-// Small batches: rows that fit the registers of gemm_small.h.  Its kernels are as fast as the
-// 256 x 256 and 256 x 64 tiles or faster up to their last row.  Forward and combine, us, tiles and here: B = 32, C = 100 000,
-// D = 2048: 101 and 81, D = 512: 39 and 25; C = 12 500, D = 2048: 36.5 and 20; B = 64, C = 100 000, D = 2048: 103 and 91, D = 512:
-// 39 and 39; C = 12 500, D = 2048: 37 and 28.  More features than the registers hold take the tiles.
+// Small batches: rows that fit the registers of gemm_small.h.
 struct SmallPlan {
     int rows, range, ranges, threads;
     SmallPlan(int32_t B, int32_t C) {
@@ -1312,7 +1309,30 @@ struct SmallPlan {
         ranges = (C + range - 1) / range;
     }
 };
-static inline bool small_batch(int32_t B, int32_t D) { return B <= SMALL_MAX_ROWS && D <= SMALL_MAX_STEPS * TILE_K; }
+// Whether a call takes them instead of the 256 x 256 and 256 x 64 tiles.  A workgroup's turns of 32 classes follow each
+// other, so wide shards take longer here, while the tiles take the same time until they fill another round of the 256 units.
+// Measured over 11 feature and 20 class counts up to 125 000, us of a call on the tiles and here:
+//   up to 16 rows: faster everywhere (forward, C = 14 000, D = 2048: 39 and 17; C = 125 000, D = 64: 18 and 13).
+//   up to 32: forward and arg-max of the same kind; probabilities of one or two k-steps only up to 7 turns per round of tiles
+//     (B = 32, D = 64: C = 40 000: 7.7 and 6.5, 65 536: 7.6 and 9.2, 125 000: 13.7 and 16.5).
+//   up to 64 (one wave per SIMD, half as many threads to share a turn): the step where W has a size that a few dozen tiles do
+//     not read quickly, up to 3 turns, or 4 of many features (forward + backward, B = 64: C = 14 000, D = 512: 16 + 57 and 12 + 56,
+//     D = 64: 8.3 + 79 and 9.3 + 81; C = 9000, D = 2048: 28 + 61 and 24 + 57; C = 3000: 23 + 42 and 23 + 46; C = 28 000, D = 512:
+//     18 + 65 and 17 + 70), and where the tiles have a second, thin round (C = 80 000, D = 2048: 92 + 250 and 75 + 233);
+//     probabilities and arg-max, whose tiles have no thin round, as long as the turns are few (D = 512, probabilities:
+//     C = 14 000: 14.7 and 8.8, 32 768: 15.4 and 14.3, 65 536: 17 and 25, 80 000: 30 and 29).
+// The forward and the backward call of a shard decide alike: the backward call's logits are the forward call's.
+enum SmallUse { SMALL_STEP, SMALL_PROBS, SMALL_TOP1 };
+static bool small_batch(int32_t B, int32_t D, int32_t C, SmallUse use) {
+    if (B > SMALL_MAX_ROWS || D > SMALL_MAX_STEPS * TILE_K) return false;
+    const SmallPlan p(B, C);
+    const int tiles = (C + TILE_M - 1) / TILE_M, rounds = (tiles + 255) / 256, turns = (p.range + SMALL_C - 1) / SMALL_C;
+    if (p.rows <= 16) return true;
+    if (p.rows == 32) return use != SMALL_PROBS || D > 2 * TILE_K || turns <= 7 * rounds;
+    if (use != SMALL_STEP) return turns <= rounds * (D < 256 ? 3 : rounds == 1 ? 4 : 5);
+    if (tiles > 256) return tiles <= 256 + 64 && D >= 768;
+    return C > 6144 && turns <= (D < 1536 ? 3 : 4) && (int64_t)C * D >= 4200000;
+}
 #define WS_LAUNCH_SMALL(kid, name, plan, grid, stream, ...)                                                   \
     do {                                                                                                      \
         if ((plan).rows == 16) WS_LAUNCH(kid, name<1>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__); \
@@ -1497,7 +1517,7 @@ static int launch_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t l
     float* part_sum = part_max + (size_t)a.nCT * a.Bpad;
     hipStream_t s = static_cast<hipStream_t>(stream);
     int parts = a.nCT, pitch = a.Bpad;
-    if (small_batch(B, D)) {
+    if (small_batch(B, D, C_shard, SMALL_STEP)) {
         const SmallPlan p(B, C_shard);
         parts = p.ranges;
         pitch = p.rows;
@@ -1593,7 +1613,7 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     XtArgs xt;
     xt.XT = XT; xt.ldxt = p.Bpad;
     xt.n_blocks = (int)std::min<int64_t>(((B + 63) / 64) * (int64_t)(D / 64), SIDE_BLOCKS);
-    const bool small = small_batch(B, D);
+    const bool small = small_batch(B, D, C_shard, SMALL_STEP);
     if (small) {
         const SmallPlan sp(B, (int32_t)round_up(C_shard, TILE_K));
         xt.first_block = sp.ranges;
@@ -1694,7 +1714,7 @@ int ws_split_fc_predict(const void* X, int64_t ldx, const void* W_shard, int64_t
     a.nBT = a.Bpad / 256;
     a.nCT = (int)(round_up(C_shard, 256) / 256);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (small_batch(B, D)) {
+    if (small_batch(B, D, C_shard, SMALL_PROBS)) {
         const SmallPlan p(B, C_shard);
         WS_LAUNCH_SMALL(KID_PREDICT, predict_small, p, p.ranges, s, a, p.range, logsumexp, static_cast<uint16_t*>(P), ldp);
     } else {
@@ -1729,7 +1749,7 @@ int ws_split_fc_top1(const void* X, int64_t ldx, const void* W_shard, int64_t ld
     int* part_cls = reinterpret_cast<int*>(part_val + (size_t)a.nCT * a.Bpad);
     hipStream_t s = static_cast<hipStream_t>(stream);
     int parts = a.nCT, pitch = a.Bpad;
-    if (small_batch(B, D)) {
+    if (small_batch(B, D, C_shard, SMALL_TOP1)) {
         const SmallPlan p(B, C_shard);
         parts = p.ranges;
         pitch = p.rows;

@@ -22,6 +22,13 @@ SHAPES = [                               # B, D, widths
     (64, 2048, [256 * 64 + 1]),          # all registers full; ranges of 72: 32, 32, 8
     (65, 192, [1000]),                   # one row too many: the wide tiles
     (40, 2112, [300]),                   # one k-step too many
+    # either side of the lines between these kernels and the tiles (33 rows or more: by classes and features)
+    (40, 704, [6000, 6150]),             # the step on tiles and here, probabilities and arg-max here
+    (64, 1024, [24576, 24577]),          # 3 turns of 32 classes to a workgroup; 4: the step on tiles
+    (33, 192, [24576, 24577]),           # 3 turns; 4: all on tiles
+    (50, 64, [256 * 48, 256 * 97]),      # probabilities and arg-max here, the step on tiles; all on tiles
+    (36, 768, [256 * 256 + 9]),          # 257 tiles: a thin round
+    (20, 128, [256 * 224, 256 * 224 + 1]),   # probabilities: 7 turns of 32 classes, and 8 on tiles
 ]
 
 
