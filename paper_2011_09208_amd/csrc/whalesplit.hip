@@ -1265,21 +1265,25 @@ static inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<u
 static inline int xcd_grid(int n_tiles) { return 8 * ((n_tiles + 7) / 8); }
 
 // Full tiles fill whole rounds of the 256 compute units; the tiles of a last round are run as thin ones (four per full
-// tile) if those fit one round.  A thin tile takes about half as long as a full one, so two rounds of them are no faster:
-// forward, B = 256, D = 2048, 256 tiles and a tail of 32, 64, 65, 128 tiles: thin 79, 101, 120, 138 us; full, whatever
-// the tail, 101-108.
-static TilePlan plan_tiles(int n_tiles, bool allow_thin) {
+// tile) if they are at most `max_thin_tail`.
+static TilePlan plan_tiles(int n_tiles, int max_thin_tail) {
     TilePlan t;
     const int tail = n_tiles % 256;
-    const bool thin = allow_thin && tail > 0 && tail <= 64;
+    const bool thin = tail > 0 && tail <= max_thin_tail;
     t.n_full = thin ? n_tiles - tail : n_tiles;
     t.n_thin = thin ? 4 * tail : 0;
     t.thin_first = xcd_grid(t.n_full);
     return t;
 }
-// Shortest contraction (k-steps of 64 batch rows) for which the dW kernel cuts the tiles of a ragged last round
-// into thin ones: measured slower at 16 k-steps (the last round is mostly output there), faster at 128.
-static const int DW_THIN_MIN_K_STEPS = 48;
+// Logits: as many as fit one round.  A thin tile takes about half as long as a full one, so two rounds of them are no
+// faster: forward, B = 256, D = 2048, 256 tiles and a tail of 32, 64, 65, 128 tiles: thin 79, 101, 120, 138 us; full, whatever
+// the tail, 101-108.
+static const int LOGITS_MAX_THIN_TAIL = 64;
+// dW: fewer, as its tiles read more per multiplication (dz across its rows) the more of them run, and none where the
+// contraction is short and the last round mostly output.  Backward calls, speed of thin over full last rounds, tails up to
+// 32 / 48 / 64 / 80 / 128: 48 k-steps 1.01, 0.99, 0.97, 0.97, 0.93; 64: 1.02, 1.00, 0.97, 0.97, 0.93; 128: 1.05, 1.03, 0.99, 0.98,
+// 0.94; 32: 1.01, 0.98, 0.96; 16 and 24: 1.00, 0.98, 0.96 (six shapes each, D = 256, 1024, 2048).
+static int dw_max_thin_tail(int k_steps) { return k_steps < 48 ? 0 : k_steps < 96 ? 32 : 48; }
 // dW runs as a stream where a workgroup has a second tile to overlap with the first and neighbouring tiles share a dz
 // panel (more than 256 features).  Whole backward calls, one workgroup per tile and stream, us: up to 256 tiles (B = 384,
 // D = 256, C = 50 000) 88.2 and 99.3; one feature tile (B = 4096, D = 256, C = 100 000) 817 and 835; more than one round of
@@ -1523,7 +1527,7 @@ static int launch_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t l
         pitch = p.rows;
         WS_LAUNCH_SMALL(KID_FWD, fwd_stats_small, p, p.ranges, s, a, p.range, part_max, part_sum, label_logit);
     } else {
-        a.plan = plan_tiles(a.nBT * a.nCT, true);
+        a.plan = plan_tiles(a.nBT * a.nCT, LOGITS_MAX_THIN_TAIL);
         WS_LAUNCH(KID_FWD, fwd_logits_stats, dim3(a.plan.thin_first + a.plan.n_thin), dim3(NTHREADS), s, a, part_max,
                   part_sum, label_logit);
     }
@@ -1620,7 +1624,7 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
         WS_LAUNCH_SMALL(KID_DZ, dz_small, sp, xt.first_block + xt.n_blocks, s, a, sp.range, logsumexp, grad_scale, dZ, p.Cpad,
                         db_shard ? db_part : nullptr, xt);
     } else {
-        a.plan = plan_tiles(p.nBT * p.nCT, true);
+        a.plan = plan_tiles(p.nBT * p.nCT, LOGITS_MAX_THIN_TAIL);
         xt.first_block = a.plan.thin_first + a.plan.n_thin;
         WS_LAUNCH(KID_DZ, bwd_recompute_dz, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s, a, logsumexp,
                   grad_scale, dZ, p.Cpad, db_shard ? db_part : nullptr, xt);
@@ -1642,8 +1646,7 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     w.nDT = p.nDT; w.nCT = p.nCT; w.k_steps = (B + TILE_K - 1) / TILE_K;
     w.dW = static_cast<uint16_t*>(dW_shard); w.lddw = lddw;
     w.sgd = sgd; w.lr = lr;
-    // thin tiles pay off only where a tile is long: with few k-steps the last round is mostly output
-    w.plan = plan_tiles(p.nDT * p.nCT, w.k_steps >= DW_THIN_MIN_K_STEPS);
+    w.plan = plan_tiles(p.nDT * p.nCT, dw_max_thin_tail(w.k_steps));
     FinishArgs f;
     f.parts = direct ? nullptr : parts; f.splits = p.splits; f.split_stride = (int64_t)B * D;
     f.B = B; f.D = D; f.dX = dX_partial; f.lddx = lddx; f.accumulate = accumulate_dx;
