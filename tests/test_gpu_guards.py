@@ -5,7 +5,7 @@ whose surroundings, and the padding columns of pitched matrices, hold a byte pat
 the pattern must be intact everywhere outside the payload, and the payload must equal, bit for bit,
 what the same calls produce into plain buffers.  The shapes cover launches of thin tiles only, of
 full tiles only and of both, with ragged row and class counts (where a tile hangs over the edge of
-its output)."""
+its output), and the small-batch kernels of each number of rows."""
 import numpy as np
 import pytest
 
@@ -40,6 +40,12 @@ SHAPES = [
     ("five batch tiles", 1100, 128, 14000),
     ("dW in full and thin tiles", 300, 1024, 17925),
     ("dW in thin tiles, long contraction", 3100, 320, 600),
+    ("dW stream", 257, 320, 33111),
+    ("two rows", 2, 64, 777),
+    ("16 rows", 16, 192, 1001),
+    ("20 rows", 20, 576, 4099),
+    ("64 rows", 64, 448, 9999),
+    ("64 rows, step on tiles", 61, 64, 777),
 ]
 
 
@@ -94,11 +100,11 @@ def test_step_writes_only_its_outputs(H, tag, B, D, C):
         assert torch.equal(_bits(plain[name]), _bits(pitched[name])), f"{tag}: `{name}` differs with a pitch / guard bands"
 
 
-def test_fused_sgd_writes_only_its_outputs(H):
+@pytest.mark.parametrize("B,D,C", [(513, 64, 23057), (20, 576, 4099), (64, 448, 9999)])
+def test_fused_sgd_writes_only_its_outputs(H, B, D, C):
     """The backward call that updates W and b in place: the weights sit in a pitched, guarded buffer."""
     import torch
     from paper_2011_09208_amd import binding as ws
-    B, D, C = 513, 64, 23057
     p = inputs.make_inputs("guards-sgd", B, D, C, x_sigma=1.0, w_sigma=0.2, bias_sigma=0.5, seed=7)
     H.say(f"[guards] fused SGD: B={B} D={D} C={C}")
     X, W0 = H.dev_bf16(p.X_bits), H.dev_bf16(p.W_bits)

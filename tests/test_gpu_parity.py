@@ -63,16 +63,16 @@ def test_ragged_shapes_with_bias(H, B, D, widths):
     _full_parity(H, p, shards, g=1.0 / B, tag=f"ragged B={B} D={D} widths={widths}")
 
 
-# Shapes chosen by how the launch is cut into tiles (a tile is 256 classes x 256 rows; a launch of at most 128
-# tiles, or the last partial round of a longer one when it fills at most half of the 256 compute units, runs
-# as four 256 x 64 "thin" tiles per tile).  The shapes above all have fewer than 128 tiles, i.e. only thin ones.
+# Shapes chosen by how the launch is cut into tiles (a tile is 256 classes x 256 rows; a launch of at most 64
+# tiles, or the last partial round of a longer one when it has at most 64, runs as four 256 x 64 "thin" tiles
+# per tile).  The shapes above all have fewer than 64 tiles, i.e. only thin ones.
 FULL_TILES_RAGGED = dict(B=300, D=64, C=256 * 70 + 5)      # 2 x 71 = 142 tiles: all full; ragged batch and class edge
 MIXED_TILES_RAGGED = dict(B=513, D=64, C=256 * 90 + 17)    # 3 x 91 = 273 tiles: 256 full + 17 x 4 thin, ragged edges
 MIXED_FIVE_BATCH_TILES = dict(B=1100, D=128, C=14000)      # 5 x 55 = 275 tiles: 256 full + 19 x 4 thin
 # the dW kernel tiles features x classes: 4 x 71 = 284 tiles, more than one round of the 256 compute units
 MIXED_DW_TILES = dict(B=300, D=1024, C=256 * 70 + 5)
-# long contractions in the dW kernel (B >= 3072 rows: 48 k-steps), where it cuts a ragged last round into thin
-# tiles too; 13 batch tiles (logits tiles numbered in blocks of 8 class x 4 batch tiles, the last block 1 wide)
+# long contractions in the dW kernel (more than 3008 rows: 48 k-steps), where it cuts a ragged last round of up to
+# 32 tiles into thin ones too; 13 batch tiles (logits tiles numbered in blocks of 8 class x 4 batch tiles, the last block 1 wide)
 LONG_K_DW_ALL_THIN = dict(B=3100, D=320, C=600)              # dW: 2 x 3 = 6 tiles, all thin; ragged feature tile
 LONG_K_DW_MIXED = dict(B=3100, D=2304, C=256 * 29 - 7)       # dW: 9 x 29 = 261 tiles: 256 full + 5 x 4 thin
 
@@ -211,8 +211,10 @@ def test_run_twice_bit_identical(H):
         assert np.array_equal(a["dW"][i], b["dW"][i]) and np.array_equal(a["db"][i], b["db"][i])
 
 
-@pytest.mark.parametrize("C", [4096 + 37, 256 * 272 + 37], ids=["thin-tiles", "mixed-tiles"])
-def test_recomputed_logits_are_the_forward_logits_bit_for_bit(H, C):
+@pytest.mark.parametrize("B,D,C", [(256, 1024, 4096 + 37), (256, 1024, 256 * 272 + 37), (16, 1024, 4096 + 37),
+                                   (32, 576, 8192 + 37), (64, 1024, 9001)],
+                         ids=["thin-tiles", "mixed-tiles", "16-rows", "32-rows", "64-rows"])
+def test_recomputed_logits_are_the_forward_logits_bit_for_bit(H, B, D, C):
     """The backward call recomputes the logits; they must be the forward call's, bit for bit, whichever
     kind of tile computed them.  Two chains of exact comparisons, all through the C ABI:
 
@@ -225,10 +227,11 @@ def test_recomputed_logits_are_the_forward_logits_bit_for_bit(H, C):
     the prediction exp(z - lse) that the predictions call (full tiles only) writes for the same lse.  The
     other D / 2 features are random, so the logits are sums whose rounding depends on the order of the
     contraction: one differing fp32 bit flips a bf16 rounding once in ~2^16 elements, and there are 1e6
-    (thin) or 1.8e7 (mixed) of them."""
+    (thin) or 1.8e7 (mixed) of them.
+
+    The small batches here have shapes for which all four calls take the small-batch kernels."""
     import torch
     from paper_2011_09208_amd import binding as ws
-    B, D = 256, 1024
     p = inputs.make_inputs("recompute", B, D, C, x_sigma=1.0, w_sigma=0.05, bias_sigma=0.5, seed=C)
     X = inputs.bf16_bits_to_f32(p.X_bits).copy()
     X[:, D // 2:] = 0.0
@@ -266,7 +269,7 @@ def test_recomputed_logits_are_the_forward_logits_bit_for_bit(H, C):
     # at the label dz = p - 1 <= 0
     at_label = dW[tc.long(), D // 2 + torch.arange(B, device=dev)].float()
     assert bool((at_label <= 0).all()) and bool((at_label >= -1).all())
-    H.record(f"recompute == forward C={C}", f"B={B} D={D} C={C}", {"off_label_dz_elements_differing": differing})
+    H.record(f"recompute == forward B={B} C={C}", f"B={B} D={D} C={C}", {"off_label_dz_elements_differing": differing})
 
 
 @pytest.mark.parametrize("name", ["cfg2", "cfg3", "cfg4", "headline"])
@@ -385,14 +388,14 @@ def test_widest_shard_the_32bit_offsets_allow(H):
         assert rep[k] <= H.GRAD_REL_TO_MAX, (k, rep)
 
 
-def test_padded_pitches_stream_and_accumulate(H):
+@pytest.mark.parametrize("B,D,C", [(200, 128, 700), (5, 192, 701), (32, 128, 700), (64, 640, 7001)])
+def test_padded_pitches_stream_and_accumulate(H, B, D, C):
     """Row pitches larger than the row length for every matrix argument, a side stream, loss_mean, and
     accumulate_dx on top of a pre-filled dX: the library must honour pitches, touch nothing in the padding,
     enqueue on the stream it is given, and add to (not overwrite) dX when asked."""
     import torch
     from oracle import oracle
     from paper_2011_09208_amd import binding as ws
-    B, D, C = 200, 128, 700
     p = inputs.make_inputs("pitch", B, D, C, w_sigma=0.3, bias_sigma=0.7, seed=21)
     H.say(f"[parity] padded pitches on a side stream: B={B} D={D} C={C}")
     dev = torch.device("cuda")
@@ -615,7 +618,9 @@ def _fused_sgd_parity(H, p, shards, lr, g, tag):
     (513, 64, [256 * 90 + 17], 63),             # 256 full + 68 thin tiles
     (300, 1024, [256 * 70 + 5], 64),            # dW kernel: 284 tiles, more than one round
     (3100, 320, [600], 65),                     # dW kernel: long contraction, thin tiles
-], ids=["thin", "full-tiles", "mixed-tiles", "mixed-dw-tiles", "long-k-dw-thin"])
+    (32, 256, [700, 800], 66),                  # the small-batch kernels
+    (64, 640, [7001], 67),                      # those for 64 rows
+], ids=["thin", "full-tiles", "mixed-tiles", "mixed-dw-tiles", "long-k-dw-thin", "32-rows", "64-rows"])
 def test_backward_with_fused_sgd_update(H, B, D, widths, seed):
     C = sum(widths)
     p = inputs.make_inputs("sgd", B, D, C, w_sigma=0.3, bias_sigma=0.5, seed=seed)
