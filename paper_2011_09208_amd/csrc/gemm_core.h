@@ -59,6 +59,12 @@ enum { KC = 0, KS = 1 };
 // class counts, the last k-step of a contraction) and the overhang reads as zeros, as the hardware
 // bounds check returns 0 beyond the resource.  Offsets are 32-bit: (rows + 256) * ld * 2 bytes must stay
 // below 4 GiB (checked on the host).
+// The rule of that check, for loads and stores: an access is in range if lane offset + scalar offset lies within the
+// records, as a sum that does not wrap; with a scalar offset alone beyond the records, or no records, nothing is in range.
+// (Measured on 324 combinations of records, lane and scalar offsets inside one allocation, loads and stores.)  The
+// tests that fail if it were not so: a batch of fewer than 32 rows in dW, whose second 32 rows of dz start beyond the
+// records, in a workspace of NaNs (test_gpu_small.py); the dW stream with D = 320 and 576, where the stores of the last
+// feature tile's missing quadrants have no records and would land in the next row (test_gpu_stream.py, test_gpu_guards.py).
 struct Operand {
     u32x4 rsrc;
     uint32_t ld;        // row pitch in elements

@@ -48,8 +48,7 @@ __device__ __forceinline__ void small_logits(const uint16_t* X, int64_t ldx, int
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W), 0, (int)(uint32_t)w_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t*>(X), 0, (int)(uint32_t)((((int64_t)B - 1) * ldx + D) * 2), 0x00020000);
-    // All in the per-lane offset: the hardware compares it with (records - scalar offset), which must not wrap around
-    // where a range lies beyond the shard and has no records.
+    // all in the per-lane offset, one register
     const uint32_t a_lane = ((uint32_t)i * (uint32_t)ldw + 8u * g) * 2u + 128u * (uint32_t)wave;
     const uint32_t b_lane = ((uint32_t)i * (uint32_t)ldx + 8u * g) * 2u + 128u * (uint32_t)wave;
     const int c_mine = S::CPT * (tid % S::TPR);

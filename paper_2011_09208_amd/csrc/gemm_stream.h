@@ -335,6 +335,7 @@ struct RowStore {
     __device__ __forceinline__ void store() {
         const int q = next >> 2;
         const uint32_t soff = ((uint32_t)(wave_col<KS>(0, 2 * (q & 1)) + 8 * (next & 3)) * ld + (uint32_t)(64 * (q >> 1))) * 2u;
+        // no records, nothing in range whatever the offsets (make_operand): a store without effect
         const bool live = next < 16 && WAVE_M * wm + 64 * (q >> 1) < at.m_valid;
         __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(at.base, 0, live ? (int)at.records : 0, 0x00020000);
         __builtin_amdgcn_raw_buffer_store_b128(queue[0], r, (int)lane_off, (int)soff, 2);      // non-temporal
