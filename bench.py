@@ -62,8 +62,9 @@ def main():
                          "loop and the library's main loop as a plain GEMM, on constant and on random operands, "
                          "with torch.matmul beside them as context; prints one JSON line")
     ap.add_argument("--trace-dw", action="store_true",
-                    help="instead of timing the step, run it with the instrumented copy of the dW kernel and print "
-                         "where a workgroup's cycles go (per-tile shader-clock stamps), one JSON line")
+                    help="instead of timing the step, run it with the fused SGD update and print where a workgroup of "
+                         "its dW kernel (bwd_dw, one workgroup per tile) spends its cycles (per-tile shader-clock "
+                         "stamps), one JSON line")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run one 1 GiB device-to-device copy (a kernel of known traffic for scaling "
                          "rocprofv3's FETCH_SIZE / WRITE_SIZE counters)")
@@ -114,6 +115,13 @@ def main():
             ws.split_fc_bwd(X, W[off:off + c], None, lse, y, off, 1.0, dX, i > 0, dW[off:off + c],
                             db[off:off + c], work)
 
+    def sgd_step():                                       # lr = 0: the weights stay as they are
+        for i, (off, c) in enumerate(shards):
+            ws.split_fc_fwd(X, W[off:off + c], None, y, off, m[i], s[i], t[i], work)
+        ws.combine_partials(m, s, t, lse, loss, None)
+        for i, (off, c) in enumerate(shards):
+            ws.split_fc_bwd_sgd(X, W[off:off + c], None, lse, y, off, 1.0, 0.0, dX, i > 0, work)
+
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
@@ -126,7 +134,7 @@ def main():
         del src, dst
 
     if args.trace_dw:
-        print(json.dumps(trace_dw(ws, torch, np, step, args.workload, B, D, shards)), flush=True)
+        print(json.dumps(trace_dw(ws, torch, np, sgd_step, args.workload, B, D, shards)), flush=True)
         return
 
     sustained = None
@@ -353,9 +361,10 @@ def measure_extras(args, result, ws, torch, dev, X, W, y, B, D, C, work, lse, lo
 
 
 def trace_dw(ws, torch, np, step, workload, B, D, shards):
-    """Where the cycles of a dW workgroup go: the step is run with the instrumented copy of the kernel (same
-    arithmetic and stores; thread 0 of every workgroup stamps the shader clock at six points and notes its compute
-    unit).  The trace kept is the one of the last shard's launch of the last step."""
+    """Where the cycles of a workgroup of bwd_dw go, the dW kernel with one workgroup per tile, which is that of the
+    fused update (the plain call runs a stream of tiles, which is not traced): the fused step is run with the instrumented
+    copy of the kernel (same arithmetic and stores; thread 0 of every workgroup stamps the shader clock at six points and
+    notes its compute unit).  The trace kept is the one of the last shard's launch of the last step."""
     n_dt = D // 256
     tiles = max(n_dt * -(-c // 256) for _, c in shards)
     trace = torch.zeros((tiles, 8), dtype=torch.int64, device="cuda:0")
@@ -373,7 +382,7 @@ def trace_dw(ws, torch, np, step, workload, B, D, shards):
     tr = trace[:n].cpu().numpy()
     tr = tr[tr[:, 0] > 0]            # tiles of a last round that ran as thin tiles are not traced
     names = ["entry -> main loop starts", "main loop (%d k-steps)" % (-(-B // 64)), "accumulators -> LDS tile, barrier",
-             "row stores issued", "row stores acknowledged"]
+             "row updates issued", "row stores acknowledged"]
     ph = np.diff(tr[:, :6], axis=1)
     phases = [{"phase": nm, "mean": round(float(ph[:, i].mean()), 1), "median": float(np.median(ph[:, i])),
                "p90": float(np.percentile(ph[:, i], 90))} for i, nm in enumerate(names)]
@@ -389,7 +398,7 @@ def trace_dw(ws, torch, np, step, workload, B, D, shards):
         gaps.extend((rows[1:, 0] - rows[:-1, 5]).tolist())
         busy.append(int(rows[-1, 5] - rows[0, 0]))
     gaps = np.array(gaps if gaps else [0])
-    return {"what": "dW kernel, per-tile shader-clock stamps of thread 0 (cycles)", "workload": workload,
+    return {"what": "bwd_dw with the fused update, per-tile shader-clock stamps of thread 0 (cycles)", "workload": workload,
             "library_version": ws.version(), "tiles": int(n), "tiles_traced": int(len(tr)), "phases": phases,
             "tile_total": {"mean": round(float(total.mean()), 1), "median": float(np.median(total))},
             "compute_units_seen": int(len(per_unit)),

@@ -304,8 +304,11 @@ int ws_probe_gemm(const void* A, int64_t lda, const void* B, int64_t ldb, int32_
  *
  * ws_profile_trace_dw(trace, tiles): while `trace` (DEVICE, 8-byte aligned, uint64 [tiles][8], owned by the
  * caller, who keeps it alive until tracing is switched off and the last traced call has finished) is set,
- * the dW kernel of every backward call runs as an instrumented copy with the same arithmetic and stores;
- * for its output tile t (class tile t / (D / 256), feature tile t % (D / 256)) thread 0 of the workgroup
+ * every backward call runs the dW kernel that has one workgroup per output tile, as an instrumented copy with the
+ * same arithmetic and stores.  That is the dW kernel of ws_split_fc_bwd_sgd, and of ws_split_fc_bwd where it does
+ * not run the tiles as a stream per compute unit (fewer than four 64-row steps of the batch, one feature tile, or
+ * up to 256 tiles); the stream itself is not traced, its outputs are the same bit for bit.
+ * For output tile t (class tile t / (D / 256), feature tile t % (D / 256)) thread 0 of the workgroup
  * writes trace[t][0..5] = shader clock at: kernel entry, start of the main loop, end of the main loop, output
  * tile staged in LDS, row stores issued, row stores acknowledged; [6] = workgroup id; [7] = XCC_ID << 32 |
  * HW_ID (which compute unit).  A backward call with more than `tiles` output tiles returns WS_ERR_WORKSPACE

@@ -744,13 +744,14 @@ def test_ceiling_probes_compute_what_they_time(H):
     assert torch.equal(sink, torch.full_like(sink, 16 * 4 * rounds * 8 * 32.0))
 
 
-def test_traced_dw_kernel_writes_the_same_gradients(H):
+@pytest.mark.parametrize("C", [17925, 256 * 140 - 7], ids=["tiles", "stream"])
+def test_traced_dw_kernel_writes_the_same_gradients(H, C):
     """The instrumented copy of the dW kernel (per-tile clock stamps for the benchmark's trace) must leave
-    every output bit for bit as the plain kernel does, stamp every tile once with clocks that never run
+    every output bit for bit as the plain kernel does (the same one, or the stream of tiles), stamp every tile once with clocks that never run
     backwards, and refuse a trace buffer that is too small before launching anything."""
     import torch
     from paper_2011_09208_amd import binding as ws
-    B, D, C = 300, 512, 17925            # 2 feature tiles x 71 class tiles, ragged in rows and classes
+    B, D = 300, 512                      # 2 feature tiles x 71 or 140 class tiles, ragged in rows and classes
     p = inputs.make_inputs("trace", B, D, C, x_sigma=1.0, w_sigma=0.2, bias_sigma=0.5, seed=17)
     H.say(f"[parity] traced dW kernel: B={B} D={D} C={C}")
     X, W = H.dev_bf16(p.X_bits), H.dev_bf16(p.W_bits)
