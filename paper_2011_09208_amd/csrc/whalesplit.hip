@@ -10,14 +10,14 @@
 //                      write X^T for the dW contraction
 //   predict_probs      softmax probabilities of the shard's classes, exp(z - lse), bf16
 //   top1_logits        the shard's arg-max class and its logit per row (+ merge_top1, also used across shards)
-//   *_small            the logits kernels for up to 64 rows (gemm_small.h)
+//   *_small            the logits kernels for up to 64 rows (gemm_small.h; small_batch on the host)
 //   bwd_dx             dX_partial = dz . W_s, split along the class contraction; partial sums
 //   bwd_dw             dW_s = dz^T . X; its surplus workgroups sum the split-K partials of dX
 //                      (optionally accumulating into the caller's dX) and the db partials
 // fwd_logits_stats and bwd_recompute_dz run the tiles of a ragged last round (256 compute units) as
 // four thin 256 x 64 tiles each (logits_thin, fwd_stats_thin, dz_thin; plan_tiles on the host); bwd_dw
-// does the same where the contraction is long (dw_thin).  From four k-steps on dW runs as a stream of tiles per
-// compute unit (bwd_dw_stream, gemm_stream.h), except where it updates the weights in place or is traced.
+// does the same where the contraction is long (dw_thin).  A plain call with several feature tiles and more than one round
+// of tiles runs dW as a stream of tiles per compute unit (bwd_dw_stream, gemm_stream.h; dw_streams on the host).
 // Tile orders and cache reuse: each XCD walks a contiguous range of tiles whose neighbours share operand
 // panels (logits_tile_coords, bwd_dx, dw_tile); every other round of tiles walks the contraction backwards
 // (logits_descending, dw_tile) and bwd_recompute_dz starts with the tiles that fwd_logits_stats ended on.
@@ -816,7 +816,7 @@ __global__ __launch_bounds__(64) void merge_top1_few(const float* __restrict__ v
 // The logits kernels for up to 64 rows (gemm_small.h): workgroup w takes the classes [w * range, (w + 1) * range) and
 // reports one partial result per row.
 // Bound by reading W.  W of 100 000 x 2048, B = 1, arg-max: 87 us on the wide tiles, 71 here (5.8 TB/s); W of 12 500 x 2048,
-// B = 32: statistics 31.5 and 14.8 us, probabilities 37.4 and 15.2 (196 of 256 units have work, two turns of 32 classes each).
+// B = 32: statistics 31.5 and 14.8 us, probabilities 37.4 and 15.2 (224 of 256 units have work, turns of 32 and 24 classes).
 template <int NB, class Body>
 __device__ __forceinline__ void small_range(const FcArgs& a, int range, int wg, int classes, float* lds, Body body) {
     const int c_begin = wg * range, c_end = c_begin + range < classes ? c_begin + range : classes;
@@ -1279,11 +1279,12 @@ static TilePlan plan_tiles(int n_tiles, int max_thin_tail) {
 // faster: forward, B = 256, D = 2048, 256 tiles and a tail of 32, 64, 65, 128 tiles: thin 79, 101, 120, 138 us; full, whatever
 // the tail, 101-108.
 static const int LOGITS_MAX_THIN_TAIL = 64;
-// dW: fewer, as its tiles read more per multiplication (dz across its rows) the more of them run, and none where the
-// contraction is short and the last round mostly output.  Backward calls, speed of thin over full last rounds, tails up to
+// dW: none where the contraction is short and the last round mostly output; else as many as fit one round if there is no
+// round before (B = 4096, D = 64, C = 12 500, 49 tiles: backward 115 us, on full tiles 143), and fewer behind full rounds, where
+// the first of them share the chip with the last full tiles.  Backward calls of 1 and 3 full rounds, speed of thin over full last rounds, tails up to
 // 32 / 48 / 64 / 80 / 128: 48 k-steps 1.01, 0.99, 0.97, 0.97, 0.93; 64: 1.02, 1.00, 0.97, 0.97, 0.93; 128: 1.05, 1.03, 0.99, 0.98,
 // 0.94; 32: 1.01, 0.98, 0.96; 16 and 24: 1.00, 0.98, 0.96 (six shapes each, D = 256, 1024, 2048).
-static int dw_max_thin_tail(int k_steps) { return k_steps < 48 ? 0 : k_steps < 96 ? 32 : 48; }
+static int dw_max_thin_tail(int n_tiles, int k_steps) { return k_steps < 48 ? 0 : n_tiles < 256 ? 64 : k_steps < 96 ? 32 : 48; }
 // dW runs as a stream where a workgroup has a second tile to overlap with the first and neighbouring tiles share a dz
 // panel (more than 256 features).  Whole backward calls, one workgroup per tile and stream, us: up to 256 tiles (B = 384,
 // D = 256, C = 50 000) 88.2 and 99.3; one feature tile (B = 4096, D = 256, C = 100 000) 817 and 835; more than one round of
@@ -1481,7 +1482,7 @@ const char* ws_status_string(int status) {
     }
 }
 
-int ws_version(void) { return 1216; }
+int ws_version(void) { return 1217; }
 
 size_t ws_fwd_workspace_bytes(int32_t B, int32_t D, int32_t C_shard) {
     return shape_ok(B, D, C_shard) ? fwd_bytes(B, C_shard) : 0;
@@ -1646,7 +1647,7 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     w.nDT = p.nDT; w.nCT = p.nCT; w.k_steps = (B + TILE_K - 1) / TILE_K;
     w.dW = static_cast<uint16_t*>(dW_shard); w.lddw = lddw;
     w.sgd = sgd; w.lr = lr;
-    w.plan = plan_tiles(p.nDT * p.nCT, dw_max_thin_tail(w.k_steps));
+    w.plan = plan_tiles(p.nDT * p.nCT, dw_max_thin_tail(p.nDT * p.nCT, w.k_steps));
     FinishArgs f;
     f.parts = direct ? nullptr : parts; f.splits = p.splits; f.split_stride = (int64_t)B * D;
     f.B = B; f.D = D; f.dX = dX_partial; f.lddx = lddx; f.accumulate = accumulate_dx;
