@@ -1352,6 +1352,27 @@ struct BwdPlan {
     size_t dz_bytes, xt_bytes, dbp_bytes, parts_bytes;
 };
 
+// dX: the splits of the contraction.  Up to as many as fill the 256 compute units once, rounded up; of those the count whose
+// rounds of workgroups take the fewest k-steps, a workgroup's start and its partial tile counted as DX_TILE_STEPS of them,
+// and the fewest partial sums among equals.  Rounded up alone a split too many
+// costs a second round; bwd_dx, us, rounded up / by this rule: B = 777, D = 1088 (20 tiles), C = 14 450, 13 splits (260 workgroups)
+// 56.8, 12 splits 36.3; B = 1200, D = 1536, C = 30 000 (30 tiles), 9: 136.8, 8: 86.0; B = 2300, D = 2048, C = 12 500 (72
+// tiles), 4: 131.9, 3: 94.3; B = 5000, D = 1024, C = 20 000 (80 tiles), 4: 212.7, 3: 154.9.
+constexpr int DX_TILE_STEPS = 4;
+static void dx_splits(BwdPlan& p) {
+    const int tiles = p.nDT * p.nBT;
+    const int most = std::min(tiles >= 256 ? 1 : (256 + tiles - 1) / tiles, p.steps_total);
+    int64_t best = -1;
+    for (int want = 1; want <= most; ++want) {
+        const int steps = (p.steps_total + want - 1) / want, splits = (p.steps_total + steps - 1) / steps;
+        const int64_t cost = (int64_t)(((int64_t)tiles * splits + 255) / 256) * (steps + DX_TILE_STEPS);
+        if (best >= 0 && cost >= best) continue;
+        best = cost;
+        p.steps_per_split = steps;
+        p.splits = splits;
+    }
+}
+
 static bool shape_ok(int32_t B, int32_t D, int32_t C) { return B > 0 && D > 0 && C > 0 && D % 64 == 0; }
 
 // The kernels address an operand with 32-bit byte offsets, tiles may hang 256 rows over its end.
@@ -1365,11 +1386,7 @@ static BwdPlan plan_bwd(int32_t B, int32_t D, int32_t C) {
     p.nCT = (int)(p.Cpad / 256);
     p.nDT = (int)(round_up(D, 256) / 256);
     p.steps_total = (int)(round_up(C, TILE_K) / TILE_K);
-    const int tiles = p.nDT * p.nBT;
-    int want = tiles >= 256 ? 1 : (256 + tiles - 1) / tiles;     // fill the 256 CUs once
-    if (want > p.steps_total) want = p.steps_total;
-    p.steps_per_split = (p.steps_total + want - 1) / want;
-    p.splits = (p.steps_total + p.steps_per_split - 1) / p.steps_per_split;
+    dx_splits(p);
     p.dz_bytes = (size_t)p.Bpad * p.Cpad * 2;
     p.xt_bytes = (size_t)D * p.Bpad * 2;
     p.dbp_bytes = (size_t)4 * p.nBT * p.Cpad * 4;        // one db partial per 64-row wave column
