@@ -456,26 +456,53 @@ __global__ __launch_bounds__(1024) void mean_loss_kernel(const float* __restrict
     if (threadIdx.x == 0) *loss_mean = red[0] / (float)B;
 }
 
-// XT[d][b] = X[b][d], zero for b >= B (the dW contraction reads whole 64-row k-steps), in 64 x 64
-// tiles through LDS.  Run by the workgroups of bwd_recompute_dz beyond its GEMM tiles: they are handed
-// out last, onto compute units the final, partial round of GEMM tiles leaves idle.
+// XT[d][b] = X[b][d], zero for b >= B (the dW contraction reads whole 64-row k-steps), in 64 x 64 tiles through LDS.  Run by
+// the workgroups of bwd_recompute_dz beyond its GEMM tiles: they are handed out last, onto compute units the final,
+// partial round of GEMM tiles leaves idle.  Bound by the latency of its loads: a thread has 16 bytes of the next tile on their
+// way while this one passes through LDS.  (The launch, us, with two bytes per lane of one tile at a time, and so: B = 4000, D =
+// 2048, C = 600 76.5 and 29.1; B = 1024, D = 2048, C = 12 500 51.9 and 48.2; B = 8192, D = 1024, C = 50 000 797 and 786.)
 struct XtArgs {
     uint16_t* XT; int64_t ldxt;          // [D][Bpad]
     int first_block, n_blocks;           // workgroups [first_block, first_block + n_blocks) transpose
 };
+constexpr int XT_PITCH = 72;             // elements of a row of the transposed tile in LDS
 
+// `lds`: two tiles of 64 x XT_PITCH.
 template <int THREADS>
 __device__ __forceinline__ void transpose_x_tiles(const FcArgs& a, const XtArgs& x, int worker, char* lds) {
-    uint16_t (*tile)[66] = reinterpret_cast<uint16_t (*)[66]>(lds);
+    constexpr int PARTS = 512 / THREADS;                 // a tile is 512 16-byte chunks
     const int nb = (a.B + 63) / 64, n_tiles = nb * (a.D / 64);
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    const int row = threadIdx.x >> 3, chunk = threadIdx.x & 7;
+    u32x4 v[PARTS];
+    auto load = [&](int t) {
+        const int b0 = (t % nb) * 64, d0 = (t / nb) * 64;
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p) {
+            const int b = b0 + row + p * (THREADS / 8);
+            v[p] = u32x4{0, 0, 0, 0};
+            if (t < n_tiles && b < a.B) v[p] = *reinterpret_cast<const u32x4*>(a.X + (int64_t)b * a.ldx + d0 + 8 * chunk);
+        }
+    };
+    load(worker);
+    int buffer = 0;
     for (int t = worker; t < n_tiles; t += x.n_blocks) {
         const int b0 = (t % nb) * 64, d0 = (t / nb) * 64;
-        for (int r = ty; r < 64; r += THREADS / 64)
-            tile[r][tx] = (b0 + r < a.B) ? a.X[(int64_t)(b0 + r) * a.ldx + d0 + tx] : (uint16_t)0;
-        __syncthreads();
-        for (int r = ty; r < 64; r += THREADS / 64) x.XT[(int64_t)(d0 + r) * x.ldxt + b0 + tx] = tile[tx][r];
-        __syncthreads();
+        uint16_t* tile = reinterpret_cast<uint16_t*>(lds) + buffer * (64 * XT_PITCH);
+        buffer ^= 1;                                     // read two tiles ago, a barrier ago
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                tile[(8 * chunk + e) * XT_PITCH + row + p * (THREADS / 8)] = (uint16_t)(v[p][e >> 1] >> (16 * (e & 1)));
+        load(t + x.n_blocks);
+        wait_counts<NO_VM_WAIT, 0>();
+        raw_barrier();
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p) {
+            const int d = row + p * (THREADS / 8);
+            *reinterpret_cast<u32x4*>(x.XT + (int64_t)(d0 + d) * x.ldxt + b0 + 8 * chunk) =
+                *reinterpret_cast<const u32x4*>(tile + d * XT_PITCH + 8 * chunk);
+        }
     }
 }
 
@@ -1050,6 +1077,10 @@ struct FinishArgs {
     int first_block, n_blocks;
 };
 
+// Bound by the latency of its loads: FINISH_BATCH of them are in flight.  (One after the other they took longer than dW itself;
+// the launch, us, one after the other and so: B = 200, D = 512, C = 16 000 (125 splits) 42.6 and 18.5; B = 1024, D = 2048, C =
+// 12 500 (8 splits) 63.5 and 51.0; B = 256, D = 2048, C = 100 000 (32 splits) 140.3 and 135.5.)
+constexpr int FINISH_BATCH = 16;
 __device__ __forceinline__ void finish_bwd(const FinishArgs& f, int worker) {
     const int64_t stride = (int64_t)f.n_blocks * NTHREADS;
     const int64_t me = (int64_t)worker * NTHREADS + threadIdx.x;
@@ -1059,8 +1090,16 @@ __device__ __forceinline__ void finish_bwd(const FinishArgs& f, int worker) {
         for (int64_t i = me; i < n4; i += stride) {
             const int row = (int)(i / d4), d = (int)(i % d4) * 4;
             f32x4 s = {0.f, 0.f, 0.f, 0.f};
-            for (int p = 0; p < f.splits; ++p)
-                s += *reinterpret_cast<const f32x4*>(f.parts + p * f.split_stride + (int64_t)row * f.D + d);
+            const float* at = f.parts + (int64_t)row * f.D + d;
+            for (int p0 = 0; p0 < f.splits; p0 += FINISH_BATCH) {
+                f32x4 v[FINISH_BATCH];
+#pragma unroll
+                for (int k = 0; k < FINISH_BATCH; ++k)
+                    if (p0 + k < f.splits) v[k] = *reinterpret_cast<const f32x4*>(at + (p0 + k) * f.split_stride);
+#pragma unroll
+                for (int k = 0; k < FINISH_BATCH; ++k)
+                    if (p0 + k < f.splits) s += v[k];
+            }
             float* o = f.dX + (int64_t)row * f.lddx + d;
             if (f.accumulate) {
 #pragma unroll
@@ -1074,7 +1113,15 @@ __device__ __forceinline__ void finish_bwd(const FinishArgs& f, int worker) {
     if (f.db_part != nullptr) {
         for (int64_t c = me; c < f.C; c += stride) {
             float s = 0.0f;
-            for (int t = 0; t < f.n_db_parts; ++t) s += f.db_part[t * f.db_stride + c];
+            for (int t0 = 0; t0 < f.n_db_parts; t0 += FINISH_BATCH) {
+                float v[FINISH_BATCH];
+#pragma unroll
+                for (int k = 0; k < FINISH_BATCH; ++k)
+                    if (t0 + k < f.n_db_parts) v[k] = f.db_part[(t0 + k) * f.db_stride + c];
+#pragma unroll
+                for (int k = 0; k < FINISH_BATCH; ++k)
+                    if (t0 + k < f.n_db_parts) s += v[k];
+            }
             f.db[c] = f.sgd ? fmaf(-f.lr, s, f.db[c]) : s;
         }
     }
