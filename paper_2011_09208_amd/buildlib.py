@@ -10,7 +10,7 @@ SP2_SRC = os.path.join(PKG, "csrc", "sp2.hip")
 PROBE_SRC = os.path.join(PKG, "csrc", "probe.hip")
 HOST_SRC = os.path.join(PKG, "csrc", "balance.cpp")
 DEPS = [SRC, BRIDGE_SRC, SP2_SRC, PROBE_SRC, HOST_SRC, os.path.join(PKG, "csrc", "gemm_core.h"), os.path.join(PKG, "csrc", "gemm_stream.h"),
-        os.path.join(PKG, "csrc", "gemm_small.h"),
+        os.path.join(PKG, "csrc", "gemm_small.h"), os.path.join(PKG, "csrc", "gemm_block.h"),
         os.path.join(os.path.dirname(PKG), "include", "whalesplit.h")]
 LIB = os.path.join(PKG, "libwhalesplit.so")
 

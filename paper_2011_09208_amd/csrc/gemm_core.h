@@ -542,6 +542,18 @@ __device__ __forceinline__ void lds_tile_store_rows(const char* lds, uint16_t* o
     }
 }
 
+// bf16(w - lr * g), eight weights w and gradients g (bf16), in fp32.
+__device__ __forceinline__ u32x4 updated_weights(u32x4 w, u32x4 g, float lr) {
+    u32x4 r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float w0 = __uint_as_float(w[e] << 16), w1 = __uint_as_float(w[e] & 0xffff0000u);
+        const float g0 = __uint_as_float(g[e] << 16), g1 = __uint_as_float(g[e] & 0xffff0000u);
+        r[e] = pack_bf16(fmaf(-lr, g0, w0), fmaf(-lr, g1, w1));
+    }
+    return r;
+}
+
 // The LDS tile holds a gradient; out[n][m] <- bf16(out[n][m] - lr * tile[n][m]) for rows n < n_valid and columns
 // m < m_valid (a multiple of 8), each 16-byte chunk read, updated in fp32 and written back.  All of a thread's chunks are
 // read by tile_update_load, called while the accumulators are on their way to LDS: read four at a time between the
@@ -568,14 +580,7 @@ __device__ __forceinline__ void lds_tile_update_rows(const char* lds, u32x4 (&w)
             const int g = out_tile_swizzle(n);
             u32x4 gr = *reinterpret_cast<const u32x4*>(lds + n * 512 + ((cq ^ (g >> 1)) << 4));
             if (g & 1) gr = __builtin_shufflevector(gr, gr, 2, 3, 0, 1);
-            u32x4 r;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float w0 = __uint_as_float(w[i][e] << 16), w1 = __uint_as_float(w[i][e] & 0xffff0000u);
-                const float g0 = __uint_as_float(gr[e] << 16), g1 = __uint_as_float(gr[e] & 0xffff0000u);
-                r[e] = pack_bf16(fmaf(-lr, g0, w0), fmaf(-lr, g1, w1));
-            }
-            __builtin_nontemporal_store(r, reinterpret_cast<u32x4*>(out + (int64_t)n * ld + cq * 8));
+            __builtin_nontemporal_store(updated_weights(w[i], gr, lr), reinterpret_cast<u32x4*>(out + (int64_t)n * ld + cq * 8));
         }
     }
 }

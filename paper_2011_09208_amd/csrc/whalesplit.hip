@@ -29,6 +29,7 @@
 #include <stdint.h>
 
 #include "../../include/whalesplit.h"
+#include "gemm_block.h"
 #include "gemm_core.h"
 #include "gemm_small.h"
 #include "gemm_stream.h"
@@ -1229,6 +1230,30 @@ __device__ __forceinline__ void dw_thin(const DwArgs& a, int q, char* lds) {
     }
 }
 
+// dW in tiles of 64 features x 64 classes, two workgroups to a compute unit (gemm_block.h): for layers whose 256 x 256
+// tiles would leave most of the chip idle while each walks a long contraction.
+__global__ __launch_bounds__(NTHREADS, 4) void bwd_dw_block(DwArgs a, FinishArgs fin) {
+    __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
+    if ((int)blockIdx.x >= fin.first_block) {
+        finish_bwd(fin, (int)blockIdx.x - fin.first_block);
+        return;
+    }
+    const int nDT = a.D / BLOCK, tile = xcd_logical_tile(nDT * ((a.C + BLOCK - 1) / BLOCK));
+    if (tile < 0) return;
+    const int d0 = (tile % nDT) * BLOCK, c0 = (tile / nDT) * BLOCK;    // feature tiles fastest: neighbours share the dz panel
+    const Operand A = make_operand(a.XT, a.ldxt, a.D, a.ldxt);
+    const Operand Bo = make_operand(a.dZ, a.ldz, a.B, a.ldz);          // rows beyond the batch read as zeros
+    // one 16-byte chunk of the output per thread: class c0 + tid / 8, features d0 + 8 * (tid % 8)
+    const int row = (int)threadIdx.x >> 3, chunk = (int)threadIdx.x & 7;
+    uint16_t* out = a.dW + (int64_t)(c0 + row) * a.lddw + d0 + 8 * chunk;
+    const bool live = c0 + row < a.C;
+    u32x4 w = {0, 0, 0, 0};
+    if (a.sgd && live) w = *reinterpret_cast<const u32x4*>(out);
+    u32x4 g = block_gemm(A, Bo, d0, c0, a.k_steps, lds);
+    if (a.sgd) g = updated_weights(w, g, a.lr);
+    if (live) __builtin_nontemporal_store(g, reinterpret_cast<u32x4*>(out));
+}
+
 __global__ __launch_bounds__(NTHREADS) void bwd_dw(DwArgs a, FinishArgs fin) {
     __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
     if ((int)blockIdx.x >= fin.first_block) {
@@ -1326,12 +1351,24 @@ static TilePlan plan_tiles(int n_tiles, int max_thin_tail) {
 // faster: forward, B = 256, D = 2048, 256 tiles and a tail of 32, 64, 65, 128 tiles: thin 79, 101, 120, 138 us; full, whatever
 // the tail, 101-108.
 static const int LOGITS_MAX_THIN_TAIL = 64;
-// dW: none where the contraction is short and the last round mostly output; else as many as fit one round if there is no
-// round before (B = 4096, D = 64, C = 12 500, 49 tiles: backward 115 us, on full tiles 143), and fewer behind full rounds, where
-// the first of them share the chip with the last full tiles.  Backward calls of 1 and 3 full rounds, speed of thin over full last rounds, tails up to
-// 32 / 48 / 64 / 80 / 128: 48 k-steps 1.01, 0.99, 0.97, 0.97, 0.93; 64: 1.02, 1.00, 0.97, 0.97, 0.93; 128: 1.05, 1.03, 0.99, 0.98,
-// 0.94; 32: 1.01, 0.98, 0.96; 16 and 24: 1.00, 0.98, 0.96 (six shapes each, D = 256, 1024, 2048).
-static int dw_max_thin_tail(int n_tiles, int k_steps) { return k_steps < 48 ? 0 : n_tiles < 256 ? 64 : k_steps < 96 ? 32 : 48; }
+// dW: as many as fit one round if there is no round before (fewer if they are short: they then wait for the side jobs' compute
+// units), and behind full rounds, where the first of them share the chip with the last full tiles, fewer, and none if they
+// are short.  A single round, us of the launch on full and thin tiles: 30 tiles (D = 256, C = 7600): 11 k-steps 21.5 and 14.7, 40: 52
+// and 33; 40: 5: 13.9 and 12.5, 24: 34 and 23; 52 (D = 1024, C = 3300): 2: 10.7 and 12.5, 11: 22.3 and 20.1, 40: 51 and 39; 64
+// (C = 4000): 2: 11.2 and 15.0, 11: 23.3 and 23.7, 24: 35.7 and 30.0.  Backward calls of 1 and 3 full rounds, speed of thin
+// over full last rounds, tails up to 32 / 48 / 64 / 80 / 128: 48 k-steps 1.01, 0.99, 0.97, 0.97, 0.93; 64: 1.02, 1.00, 0.97, 0.97,
+// 0.93; 128: 1.05, 1.03, 0.99, 0.98, 0.94; 32: 1.01, 0.98, 0.96; 16 and 24: 1.00, 0.98, 0.96 (six shapes each, D = 256, 1024, 2048).
+static int dw_max_thin_tail(int n_tiles, int k_steps) { return n_tiles < 256 ? (k_steps < 12 ? 40 : 64) : k_steps < 48 ? 0 : k_steps < 96 ? 32 : 48; }
+// dW in 64 x 64 tiles: as long as they are few enough for the two that a compute unit holds, and the contraction long enough to
+// pay for their traffic once there is more than one.  us of the launch, 256-wide tiles (thin ones where that is
+// allowed) and these: 8 of them (D = 64, C = 500): 24 k-steps 17.6 and 10.0, 125: 66 and 30; 128 (D = 256, C = 2000): 5: 8.8 and
+// 8.2, 24: 21.6 and 14.8, 125: 72 and 36; 252 (D = 256, C = 4000): 11: 13.7 and 14.4, 24: 22.1 and 17.5, 125: 71 and 40; 384 (D = 1024, C =
+// 1500): 5: 11.9 and 12.3, 24: 22.6 and 20.1, 125: 67.6 and 63.0; 476 (D = 256, C = 7600): 11: 14.4 and 17.9, 24: 23.5 and 23.0,
+// 63: 43 and 35; 640 (D = 1024, C = 2500): 24: 22.5 and 27.2, 63: 38 and 50.
+static bool dw_blocks(int D, int C, int k_steps) {
+    const int64_t n = (int64_t)(D / BLOCK) * ((C + BLOCK - 1) / BLOCK);
+    return n <= 192 || (n <= 512 && k_steps >= 20);
+}
 // dW runs as a stream where a workgroup has a second tile to overlap with the first and neighbouring tiles share a dz
 // panel (more than 256 features).  Whole backward calls, one workgroup per tile and stream, us: up to 256 tiles (B = 384,
 // D = 256, C = 50 000) 88.2 and 99.3; one feature tile (B = 4096, D = 256, C = 100 000) 817 and 835; more than one round of
@@ -1399,20 +1436,23 @@ struct BwdPlan {
     size_t dz_bytes, xt_bytes, dbp_bytes, parts_bytes;
 };
 
-// dX: the splits of the contraction.  Up to as many as fill the 256 compute units once, rounded up; of those the count whose
-// rounds of workgroups take the fewest k-steps, a workgroup's start and its partial tile counted as DX_TILE_STEPS of them,
-// and the fewest partial sums among equals.  Rounded up alone a split too many
+// dX: the splits of the contraction.  Up to as many as fill the 256 compute units once, rounded up; of those the count that
+// takes the shortest time, in sixteenths of a k-step: the rounds of workgroups, a workgroup's start and its partial tile counted as
+// DX_TILE_STEPS k-steps, and the later sum of the partial tiles, of which a side job takes 16 in the time of a k-step.  Rounded up alone a split too many
 // costs a second round; bwd_dx, us, rounded up / by this rule: B = 777, D = 1088 (20 tiles), C = 14 450, 13 splits (260 workgroups)
 // 56.8, 12 splits 36.3; B = 1200, D = 1536, C = 30 000 (30 tiles), 9: 136.8, 8: 86.0; B = 2300, D = 2048, C = 12 500 (72
-// tiles), 4: 131.9, 3: 94.3; B = 5000, D = 1024, C = 20 000 (80 tiles), 4: 212.7, 3: 154.9.
+// tiles), 4: 131.9, 3: 94.3; B = 5000, D = 1024, C = 20 000 (80 tiles), 4: 212.7, 3: 154.9.  And a split for
+// every k-step or two leaves the sum more to do than it saves: step, us, B = 100, D = 64, C = 30 000: 235 splits 61.2, 59 50.3; B = 200,
+// D = 512, C = 16 000: 125 66.5, 63 60.6.
 constexpr int DX_TILE_STEPS = 4;
-static void dx_splits(BwdPlan& p) {
+static void dx_splits(BwdPlan& p, int32_t B, int32_t D) {
+    const int64_t sum_turns = ((int64_t)B * (D / 4) + SIDE_BLOCKS * NTHREADS - 1) / (SIDE_BLOCKS * NTHREADS);   // of the side job's threads
     const int tiles = p.nDT * p.nBT;
     const int most = std::min(tiles >= 256 ? 1 : (256 + tiles - 1) / tiles, p.steps_total);
     int64_t best = -1;
     for (int want = 1; want <= most; ++want) {
         const int steps = (p.steps_total + want - 1) / want, splits = (p.steps_total + steps - 1) / steps;
-        const int64_t cost = (int64_t)(((int64_t)tiles * splits + 255) / 256) * (steps + DX_TILE_STEPS);
+        const int64_t cost = ((int64_t)tiles * splits + 255) / 256 * 16 * (steps + DX_TILE_STEPS) + splits * sum_turns;
         if (best >= 0 && cost >= best) continue;
         best = cost;
         p.steps_per_split = steps;
@@ -1433,7 +1473,7 @@ static BwdPlan plan_bwd(int32_t B, int32_t D, int32_t C) {
     p.nCT = (int)(p.Cpad / 256);
     p.nDT = (int)(round_up(D, 256) / 256);
     p.steps_total = (int)(round_up(C, TILE_K) / TILE_K);
-    dx_splits(p);
+    dx_splits(p, B, D);
     p.dz_bytes = (size_t)p.Bpad * p.Cpad * 2;
     p.xt_bytes = (size_t)D * p.Bpad * 2;
     p.dbp_bytes = (size_t)4 * p.nBT * p.Cpad * 4;        // one db partial per 64-row wave column
@@ -1720,7 +1760,10 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     f.sgd = sgd; f.lr = lr;
     f.first_block = w.plan.thin_first + w.plan.n_thin;
     f.n_blocks = (f.parts || f.db_part) ? SIDE_BLOCKS : 0;
-    if (g_dw_trace != nullptr) {
+    if (g_dw_trace == nullptr && dw_blocks(D, C_shard, w.k_steps)) {
+        f.first_block = xcd_grid((D / BLOCK) * ((C_shard + BLOCK - 1) / BLOCK));
+        WS_LAUNCH(KID_DW, bwd_dw_block, dim3(f.first_block + f.n_blocks), dim3(NTHREADS), s, w, f);
+    } else if (g_dw_trace != nullptr) {
         WS_LAUNCH(KID_DW, bwd_dw_traced, dim3(f.first_block + f.n_blocks), dim3(NTHREADS), s, w, f, g_dw_trace);
     } else if (!sgd && dw_streams(p.nDT, w.plan.n_full, w.k_steps, lddw)) {
         w.plan.thin_first = STREAM_WGS;
