@@ -66,7 +66,8 @@ const char* ws_status_string(int status);
 /* Library version, major * 1000 + minor. */
 int ws_version(void);
 
-/* Bytes of scratch ws_split_fc_fwd needs for this shape (0 on invalid shape). */
+/* Bytes of scratch for ws_split_fc_fwd and this shape (0 on invalid shape).  The call also accepts a workspace of
+ * 2 * ceil(C_shard / 256) * roundup(B, 256) floats where this is more, and may then be slower and sum in another order. */
 size_t ws_fwd_workspace_bytes(int32_t B, int32_t D, int32_t C_shard);
 
 /* Forward call of one shard (Section 2.1 split matmul; Section 3.1.2 FC + Softmax
@@ -94,7 +95,7 @@ int ws_split_fc_fwd(const void* X, int64_t ldx,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and kernels as
  * ws_split_fc_fwd (bit-identical outputs), but the per-class-tile partials live in a fixed array built
  * into the library's device code instead of a caller workspace; the call allocates and frees nothing.
- *   Limit: ws_fwd_workspace_bytes(B, D, C_shard) <= WS_STATIC_SCRATCH_BYTES, else WS_ERR_LIMIT (checked on
+ *   Limit: 2 * ceil(C_shard / 256) * roundup(B, 256) floats <= WS_STATIC_SCRATCH_BYTES, else WS_ERR_LIMIT (checked on
  *   the host with the other arguments, before any HIP call).  16 MiB covers one shard of every workload
  *   this library is measured on (headline 3.2 MB; B = 8192 x 50 000 classes 12.8 MB).
  *   Every GPU the library runs on holds its own 16 MiB copy of the array until the process ends.

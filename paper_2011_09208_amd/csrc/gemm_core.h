@@ -193,13 +193,14 @@ struct FragReader {
         if (LEAN) asm volatile("" : "+v"(o[0]));
         o[1] = LEAN ? o[0] ^ bit : f[1];
     }
+    template <int UNITS = MT / 4>                          // the first 2 * UNITS tiles of the half
     __device__ __forceinline__ void read_a(bf16x8 (&af)[MT / 2][2], const char* lds, int half, int stage) const {
         int o[2];
         offsets(o, a_frag, 64);
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int t = 0; t < MT / 2; ++t)
+            for (int t = 0; t < 2 * UNITS; ++t)
                 af[t][s] = *reinterpret_cast<const bf16x8*>(lds + (o[s] + stage) + half * HALF_TILE_BYTES + t * 2048);
     }
     __device__ __forceinline__ void read_b(bf16x8 (&bf)[NT / 2][2], const char* lds, int half, int stage) const {

@@ -14,9 +14,11 @@
 //   bwd_dx             dX_partial = dz . W_s, split along the class contraction; partial sums
 //   bwd_dw             dW_s = dz^T . X; its surplus workgroups sum the split-K partials of dX
 //                      (optionally accumulating into the caller's dX) and the db partials
+//   fwd_logits_list, bwd_dz_list   the same logits and dz, tiles of any height in even lists, one per compute unit
+//                      (gemm_tiles.h; logits_list on the host)
 // fwd_logits_stats and bwd_recompute_dz run the tiles of a ragged last round (256 compute units) as
 // four thin 256 x 64 tiles each (logits_thin, fwd_stats_thin, dz_thin; plan_tiles on the host); bwd_dw
-// does the same where the contraction is long (dw_thin).  A plain call with several feature tiles and more than one round
+// does the same where the contraction is long (dw_thin), and takes small outputs in 64 x 64 tiles (bwd_dw_block, dw_blocks).  A plain call with several feature tiles and more than one round
 // of tiles runs dW as a stream of tiles per compute unit (bwd_dw_stream, gemm_stream.h; dw_streams on the host).
 // Tile orders and cache reuse: each XCD walks a contiguous range of tiles whose neighbours share operand
 // panels (logits_tile_coords, bwd_dx, dw_tile); every other round of tiles walks the contraction backwards
@@ -33,6 +35,7 @@
 #include "gemm_core.h"
 #include "gemm_small.h"
 #include "gemm_stream.h"
+#include "gemm_tiles.h"
 
 namespace ws {
 
@@ -78,6 +81,16 @@ __device__ __forceinline__ void add_bias_and_mask(acc_t& acc, const float* sbias
     }
 }
 
+// How the list kernels cut the logits: each of `ranges` columns of workgroups (one for every batch tile) takes every ranges-th of
+// the first full * ranges whole class tiles and one part of the rest, `per` units of 32 classes, the first `more` of them one more
+// (whole k-steps of the dX contraction in all).  The divisions that number the workgroups are the host's: n / d = n * inv
+// >> 32 as long as n * d < 2^32.
+struct RangePlan {
+    int ranges, full, per, more;
+    uint32_t inv_block, inv_rest;        // of a block of batch tiles (`ranges` times four of them), of the batch tiles of the last block
+    uint32_t inv_ranges;
+};
+
 struct FcArgs {
     const uint16_t* X; int64_t ldx;
     const uint16_t* W; int64_t ldw;
@@ -86,6 +99,8 @@ struct FcArgs {
     int B, D, C, class_offset;
     int Bpad;        // B rounded up to 256
     int nBT, nCT;    // tiles along the batch and class dimensions
+    RangePlan ranges;
+    bool on_lists;   // the step runs as lists (logits_list), whatever this launch does
     TilePlan plan;   // which of the nBT * nCT tiles run as full tiles and which as four thin tiles each
     int last_tile_first;   // walk the full tiles from the last to the first
 };
@@ -144,8 +159,10 @@ __device__ __forceinline__ TileRef logits_tile_ref(const FcArgs& a) {
 // same class tiles (more); alternating the direction between such groups lets it find the end of the panels
 // that the two tiles share, which it has just read, still in the L2 (launches of one round have nothing to gain
 // and keep one direction).  A function of the tile's coordinates and the launch shape alone, so that every
-// kernel (and the thin and the full version of a tile) adds the products of a logit in the same order.
+// kernel (and the thin and the full version of a tile) adds the products of a logit in the same order.  Where the step runs
+// as lists, a workgroup's whole tiles alternate, `ranges` class tiles apart, and the rest is ascending.
 __device__ __forceinline__ bool logits_descending(const FcArgs& a, int ct, int bt) {
+    if (a.on_lists) return ct < a.ranges.full * a.ranges.ranges && (__umulhi((uint32_t)ct, a.ranges.inv_ranges) & 1) != 0;
     if (a.nBT * a.nCT <= 256) return false;
     if (a.nBT <= 4) return (((ct * a.nBT) >> 5) & 1) != 0;
     return (((ct >> 3) ^ (bt >> 2)) & 1) != 0;
@@ -271,6 +288,243 @@ __device__ __forceinline__ void fwd_stats_thin(const FcArgs& a, const TileRef& r
         part_max[o] = m;
         part_sum[o] = s;
     }
+}
+
+// ---- logits as lists of tiles (gemm_tiles.h) ---------------------------------------------------------
+// A workgroup's list: its class tiles x 256 rows, walked from the first to the last (`backwards`: from the last to the first).  Workgroups are numbered batch tiles fastest in blocks of four of them, all ranges of a block one after
+// the other, so that the 32 of an XCD have up to four X panels and the fewest of W that leaves.
+struct LogitsList {
+    int range, n0, rounds;               // n0: first row
+    int ranges, full, rest, rest_units;  // whole tiles, then rest_units units from class `rest` on
+    bool backwards;
+    __device__ __forceinline__ LogitsList(const FcArgs& a, bool back) : backwards(back) {
+        ranges = a.ranges.ranges;
+        const int it = xcd_logical_tile(ranges * a.nBT), block = (int)__umulhi((uint32_t)it, a.ranges.inv_block);
+        const int r = it - block * 4 * ranges, left = a.nBT - 4 * block;
+        range = left >= 4 ? r >> 2 : left == 1 ? r : (int)__umulhi((uint32_t)r, a.ranges.inv_rest);
+        n0 = TILE_N * (4 * block + r - range * (left >= 4 ? 4 : left));
+        full = a.ranges.full;
+        rest = TILE_M * full * ranges + UNIT * (range * a.ranges.per + (range < a.ranges.more ? range : a.ranges.more));
+        rest_units = a.ranges.per + (range < a.ranges.more);
+        rounds = it < 0 ? 0 : full + (rest_units > 0);
+    }
+    __device__ __forceinline__ ListTile tile(int round) const {
+        const int q = backwards ? rounds - 1 - round : round;
+        return ListTile{q < full ? TILE_M * (q * ranges + range) : rest, n0, q < full ? MAX_UNITS : rest_units, q < full && (q & 1) != 0};
+    }
+};
+
+// LDS of a wave for what its epilogues need: the bias of its up to 128 classes, the labels of its 64 rows and one fp32 value of each.
+// All of it is loaded straight into LDS: a load into registers would make the compiler wait for every load in flight.
+constexpr int LIST_LABELS = 512, LIST_ROWS = 768, LIST_WAVE_BYTES = 1024;
+constexpr int LIST_EXTRA_OFFSET = LDS_BYTES + 8 * LIST_WAVE_BYTES;
+__device__ __forceinline__ Operand make_vector_operand(const void* base, int n) {      // of n 32-bit elements
+    const uint64_t p = reinterpret_cast<uint64_t>(base);
+    return Operand{u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, 4u * (uint32_t)n, 0x00020000u}, 0u};
+}
+
+// The kernel's arguments, read afresh: what an epilogue takes from here is not held in scalar registers (there are not enough of
+// them) over the main loop.
+#define WS_CONSTANT const __attribute__((address_space(4)))
+template <class Args>
+__device__ __forceinline__ WS_CONSTANT Args* fresh_args() {
+    WS_CONSTANT Args* p = (WS_CONSTANT Args*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+// The lane's number, read afresh likewise.
+__device__ __forceinline__ int fresh_lane() {
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+// What the epilogues of the list kernels share: the wave's classes and rows, and their logits.  Positions: unit_row plus 64 in
+// half 1, whatever the units of half 0.  Args begins with an FcArgs a.
+template <class Args>
+struct LogitsEpilogue {
+    const LogitsList& list;
+    char* lds;
+    int c0;                  // the wave's first class (shard-local)
+    __device__ __forceinline__ LogitsEpilogue(const LogitsList& l, char* lds_base) : list(l), lds(lds_base) {}
+    __device__ __forceinline__ int wave() const { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+    __device__ __forceinline__ int row0() const { return list.n0 + WAVE_N * (wave() & 3); }      // the wave's first row
+    __device__ __forceinline__ void begin_tile(int round) {
+        const ListTile t = list.tile(round);
+        const int wm = wave() >> 2, units = wave_row_units(t.units, wm);
+        c0 = t.m0 + (wm == 0 ? 0 : UNIT * wave_row_units(t.units, 0));
+        WS_CONSTANT Args* p = fresh_args<Args>();
+        if (p->a.bias != nullptr) {                      // classes beyond the shard read as zeros
+            wait_counts<NO_VM_WAIT, 0>();                // the bias of the tile before has been read
+            const Operand bias = make_vector_operand(p->a.bias, p->a.C);
+            const uint32_t lane4 = 4u * (uint32_t)fresh_lane();
+            touch_line(bias, lane4, 4u * (uint32_t)c0, lds_offset(lds) + scratch());
+            touch_line(bias, lane4, 4u * (uint32_t)(c0 + UNIT * half_units(units, 0)), lds_offset(lds) + scratch() + 256);
+        }
+    }
+    __device__ __forceinline__ int scratch() const { return LDS_BYTES + LIST_WAVE_BYTES * wave(); }
+    // Labels of the wave's rows, and from[row] if given (anything beyond the batch).
+    __device__ __forceinline__ void load_rows(const float* from) {
+        WS_CONSTANT Args* p = fresh_args<Args>();
+        const uint32_t lane4 = 4u * (uint32_t)fresh_lane();
+        touch_line(make_vector_operand(p->a.labels, p->a.B), lane4, 4u * (uint32_t)row0(), lds_offset(lds) + scratch() + LIST_LABELS);
+        if (from != nullptr) touch_line(make_vector_operand(from, p->a.B), lane4, 4u * (uint32_t)row0(), lds_offset(lds) + scratch() + LIST_ROWS);
+    }
+    // z = acc + bias, classes beyond the shard -inf
+    __device__ __forceinline__ void logits(acc_t& acc, const int (&units)[2], int g) const {
+        WS_CONSTANT Args* p = fresh_args<Args>();
+        wait_counts<8, NO_LG_WAIT>();                    // at least so many loads have followed those of the bias and the rows
+        if (p->a.bias != nullptr) {
+            const float* b = reinterpret_cast<const float*>(lds + scratch());
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if ((u & 1) < units[u >> 1]) {
+#pragma unroll
+                    for (int mt = 2 * u; mt < 2 * u + 2; ++mt) {
+                        const f32x4 b4 = *reinterpret_cast<const f32x4*>(b + 64 * (mt >> 2) + unit_row(mt, g));
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += b4;
+                    }
+                }
+        }
+        const int C = p->a.C;
+        if (c0 + UNIT * (units[0] + units[1]) > C) {     // the last tile of the last range
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (c0 + (mt >= MT / 2 ? UNIT * units[0] : 0) + unit_row(mt, g) + v >= C) {
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) acc[mt][nt][v] = NEG_INF;
+                    }
+        }
+    }
+    // Shard-local label of row nt of the lane, -1 if it is not in the shard or the row not in the batch.
+    __device__ __forceinline__ int label(int nt, int jl, WS_CONSTANT Args* p) const {
+        const int l = *reinterpret_cast<const int*>(lds + scratch() + LIST_LABELS + 4 * (16 * nt + jl)) - p->a.class_offset;
+        return row0() + 16 * nt + jl < p->a.B && l >= 0 && l < p->a.C ? l : -1;
+    }
+    // The accumulator register 4 * mt + v of this lane that holds the logit of a row's label, -1 if none does.
+    __device__ __forceinline__ int label_register(int label, const int (&units)[2], int g) const {
+        int rel = label - c0;
+        if (label < 0 || rel < 0 || rel >= UNIT * (units[0] + units[1]) || ((rel >> 3) & 3) != g) return -1;
+        if (rel >= UNIT * units[0]) rel += 64 - UNIT * units[0];
+        return 8 * (rel >> 5) + (rel & 7);               // unit_row: two M tiles to a unit of 32
+    }
+};
+
+struct FwdArgs {
+    FcArgs a;
+    float* part_max;
+    float* part_sum;
+    float* label_logit;
+};
+
+// Row statistics: a lane keeps (max, sum-exp) of its four rows over its classes of the whole list; the four lanes of a row and the
+// two wave rows meet once, at its end.
+struct FwdEpilogue : LogitsEpilogue<FwdArgs> {
+    float mx[NT], sum[NT];
+    __device__ __forceinline__ FwdEpilogue(const LogitsList& l, char* lds_base) : LogitsEpilogue(l, lds_base) {}
+    __device__ __forceinline__ void begin(int round) {
+        begin_tile(round);
+        if (round != 0) return;
+        load_rows(nullptr);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            mx[nt] = NEG_INF;
+            sum[nt] = 0.0f;
+        }
+    }
+    __device__ __forceinline__ void end(acc_t& acc, int round, const int (&units)[2]) {
+        const int lane = fresh_lane(), g = lane >> 4, jl = lane & 15;
+        logits(acc, units, g);
+        float top[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) top[nt] = mx[nt];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if ((u & 1) < units[u >> 1]) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) top[nt] = fmaxf(fmaxf(top[nt], acc[2 * u][nt][v]), acc[2 * u + 1][nt][v]);
+            }
+        float shift[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const float m = top[nt] == NEG_INF ? 0.0f : top[nt];
+            shift[nt] = -m * LOG2E;                      // exp(z - m) = exp2(z * log2 e - m * log2 e)
+            sum[nt] *= mx[nt] == NEG_INF ? 0.0f : __expf(mx[nt] - m);
+            mx[nt] = top[nt];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if ((u & 1) < units[u >> 1]) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    float s = 0.0f;
+#pragma unroll
+                    for (int mt = 2 * u; mt < 2 * u + 2; ++mt)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) s += __builtin_amdgcn_exp2f(fmaf(acc[mt][nt][v], LOG2E, shift[nt]));
+                    sum[nt] += s;
+                }
+            }
+        // Exactly one lane of the whole grid holds z[row][label - offset] when the label lies in the shard; rows whose label
+        // lies outside get 0 from the first range.
+        WS_CONSTANT FwdArgs* p = fresh_args<FwdArgs>();
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int at = label_register(label(nt, jl, p), units, g);
+            if (__any(at >= 0)) {
+                float t = 0.0f;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (4 * mt + v == at) t = acc[mt][nt][v];
+                if (at >= 0) p->label_logit[row0() + 16 * nt + jl] = t;
+            }
+        }
+        if (round == list.rounds - 1) end_list(g, jl);
+    }
+    __device__ __forceinline__ void end_list(int g, int jl) {
+        const int wm = wave() >> 2, wn = wave() & 3;
+        float* red = reinterpret_cast<float*>(lds + LIST_EXTRA_OFFSET);      // [max, sum][256 rows] of wave row 1
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int row = WAVE_N * wn + 16 * nt + jl;
+            merge_ms(mx[nt], sum[nt], lane_xor(mx[nt], 16), lane_xor(sum[nt], 16));
+            merge_ms(mx[nt], sum[nt], lane_xor(mx[nt], 32), lane_xor(sum[nt], 32));
+            if (wm == 1 && g == 0) {
+                red[row] = mx[nt];
+                red[256 + row] = sum[nt];
+            }
+        }
+        wait_counts<NO_VM_WAIT, 0>();
+        raw_barrier();
+        WS_CONSTANT FwdArgs* p = fresh_args<FwdArgs>();
+        if (wm == 0 && g == 0) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const int row = WAVE_N * wn + 16 * nt + jl;
+                merge_ms(mx[nt], sum[nt], red[row], red[256 + row]);
+                const int64_t o = (int64_t)list.range * p->a.Bpad + list.n0 + row;
+                p->part_max[o] = mx[nt];
+                p->part_sum[o] = sum[nt];
+                if (list.range == 0 && row0() + 16 * nt + jl < p->a.B && label(nt, jl, p) < 0) p->label_logit[row0() + 16 * nt + jl] = 0.0f;
+            }
+        }
+    }
+};
+
+__global__ __launch_bounds__(NTHREADS) void fwd_logits_list(FwdArgs f) {
+    __shared__ __attribute__((aligned(16))) char lds[LIST_EXTRA_OFFSET + 2048];
+    const FcArgs& a = f.a;
+    const LogitsList list(a, false);
+    if (list.rounds == 0) return;
+    FwdEpilogue epi(list, lds);
+    gemm_tiles<KC, 0>(make_operand(a.W, a.ldw, a.C, a.D), make_operand(a.X, a.ldx, a.B, a.D), a.D / TILE_K, list, epi, lds);
 }
 
 __global__ __launch_bounds__(NTHREADS) void fwd_logits_stats(FcArgs a, float* __restrict__ part_max,
@@ -678,6 +932,145 @@ __global__ __launch_bounds__(NTHREADS) void bwd_recompute_dz(FcArgs a, const flo
     acc_to_lds_bf16<KC>(acc, lds);
     __syncthreads();
     lds_tile_store_rows(lds, dZ + (int64_t)bt * TILE_N * ldz + ct * TILE_M, ldz, TILE_N, TILE_M);
+}
+
+// One step of a reduce-scatter over lanes MASK apart: 2 H sums become H.
+template <int H, int MASK, int N>
+__device__ __forceinline__ void exchange_half(float (&val)[N], int jl) {
+    const bool up = (jl & MASK) != 0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        const float keep = up ? val[i + H] : val[i];
+        const float send = up ? val[i] : val[i + H];
+        val[i] = keep + lane_xor(send, MASK);
+    }
+}
+
+// dz of the list kernels.  A wave's 64 rows x 64 classes of a half leave through its own 2 KiB of LDS, 16 rows at a time, so that
+// eight consecutive lanes store one whole 128-byte line (16-byte chunks are XOR-ed with row & 7); nobody waits for the
+// stores.  16 of them per tile and wave, whatever its units: those without classes have no records.
+struct DzArgs {
+    FcArgs a;
+    const float* logsumexp;
+    float grad_scale;
+    uint16_t* dZ; int64_t ldz;
+    float* db_part;
+    XtArgs xt;
+};
+struct DzEpilogue : LogitsEpilogue<DzArgs> {
+    static constexpr int SCRATCH_BYTES = 2048;
+    static constexpr int STORES = 16;
+    __device__ __forceinline__ DzEpilogue(const LogitsList& l, char* lds_base) : LogitsEpilogue(l, lds_base) {}
+    __device__ __forceinline__ void begin(int round) {
+        begin_tile(round);
+        if (round != 0) return;
+        load_rows(fresh_args<DzArgs>()->logsumexp);
+        // the waits of the first tile count the stores of a tile before: stores without effect
+        __amdgpu_buffer_rsrc_t none = __builtin_amdgcn_make_buffer_rsrc(fresh_args<DzArgs>()->dZ, 0, 0, 0x00020000);
+#pragma unroll
+        for (int n = 0; n < STORES; ++n) __builtin_amdgcn_raw_buffer_store_b32(0u, none, 0, 0, 0);
+    }
+    __device__ __forceinline__ void end(acc_t& acc, int, const int (&units)[2]) {
+        const int lane = fresh_lane(), g = lane >> 4, jl = lane & 15;
+        logits(acc, units, g);
+        WS_CONSTANT DzArgs* p = fresh_args<DzArgs>();
+        const float grad_scale = p->grad_scale;
+        float shift[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            // |g| * exp(z - lse) = exp2(z * log2 e + (log2 |g| - lse * log2 e)): one FMA and one exp2 per element; g = 0 (rows
+            // beyond the batch) gives a shift of -inf and exact zeros, as does z = -inf on padded classes.
+            const bool row_ok = row0() + 16 * nt + jl < p->a.B;
+            const float lse = *reinterpret_cast<const float*>(lds + scratch() + LIST_ROWS + 4 * (16 * nt + jl));
+            shift[nt] = __log2f(row_ok ? fabsf(grad_scale) : 0.0f) - (row_ok ? lse : 0.0f) * LOG2E;
+        }
+        const bool negative = grad_scale < 0.0f;                            // uniform; the usual scales are positive
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if ((u & 1) < units[u >> 1]) {
+#pragma unroll
+                for (int mt = 2 * u; mt < 2 * u + 2; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[mt][nt][v] = __builtin_amdgcn_exp2f(fmaf(acc[mt][nt][v], LOG2E, shift[nt]));
+                        if (negative) acc[mt][nt] = -acc[mt][nt];
+                    }
+            }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int at = label_register(label(nt, jl, p), units, g);
+            if (__any(at >= 0)) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        acc[mt][nt][v] -= 4 * mt + v == at ? grad_scale : 0.0f;      // (as a branch the compiler makes 12 of it)
+            }
+        }
+        // db: the tile's column sums over its batch rows, taken from the fp32 values.  A lane first adds its four N-tiles, then
+        // the 16 lanes that hold the same classes reduce-scatter their 32 sums in four exchange steps (16, 8, 4, 2 values
+        // sent), which leaves lane jl the sums of accumulator rows 2 jl and 2 jl + 1 (row index = 4 * M-tile + register).
+        // One partial per wave column: db_part[row / 64][class].
+        p = fresh_args<DzArgs>();
+        if (p->db_part != nullptr) {
+            float val[4 * MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    val[4 * mt + v] = ((mt >> 1) & 1) < units[mt >> 2] ? (acc[mt][0][v] + acc[mt][1][v]) + (acc[mt][2][v] + acc[mt][3][v]) : 0.0f;
+            exchange_half<2 * MT, 8>(val, jl);
+            exchange_half<MT, 4>(val, jl);
+            exchange_half<MT / 2, 2>(val, jl);
+            exchange_half<MT / 4, 1>(val, jl);
+            const int mt = jl >> 1;
+            if (((mt >> 1) & 1) < (mt >= MT / 2 ? units[1] : units[0])) {
+                const int cls = c0 + (mt >= MT / 2 ? UNIT * units[0] : 0) + unit_row(mt, g) + 2 * (jl & 1);
+                f32x2 two = {val[0], val[1]};
+                *reinterpret_cast<f32x2*>(p->db_part + (int64_t)(row0() >> 6) * p->ldz + cls) = two;
+            }
+        }
+        p = fresh_args<DzArgs>();
+        uint16_t* dZ = p->dZ;
+        const uint32_t ldz = (uint32_t)p->ldz;
+        const int n = lane >> 3, chunk = lane & 7, scratch = LIST_EXTRA_OFFSET + SCRATCH_BYTES * wave();
+        const int wr = scratch + jl * 128 + ((g ^ (jl & 7)) << 4), rd = scratch + n * 128 + ((chunk ^ n) << 4);
+        const uint32_t records = (uint32_t)p->a.Bpad * ldz * 2u, lane_off = ((uint32_t)n * ldz + 8u * (uint32_t)chunk) * 2u;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t col = (uint32_t)(c0 + (h == 0 ? 0 : UNIT * units[0])) * 2u;
+            __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(dZ, 0, units[h] > 0 ? (int)records : 0, 0x00020000);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const f32x4 lo = acc[4 * h + 2 * u][nt], hi = acc[4 * h + 2 * u + 1][nt];
+                    *reinterpret_cast<u32x4*>(lds + (wr ^ (64 * u))) =
+                        u32x4{pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3]), pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3])};
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const u32x4 v = *reinterpret_cast<const u32x4*>(lds + rd + 1024 * k);
+                    const uint32_t soff = (uint32_t)(row0() + 16 * nt + 8 * k) * ldz * 2u + col;
+                    if (units[h] != 1 || chunk < 4) __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)lane_off, (int)soff, 2);   // non-temporal
+                }
+            }
+        }
+    }
+};
+
+__global__ __launch_bounds__(NTHREADS) void bwd_dz_list(DzArgs z) {
+    __shared__ __attribute__((aligned(16))) char lds[LIST_EXTRA_OFFSET + 8 * DzEpilogue::SCRATCH_BYTES];
+    const FcArgs& a = z.a;
+    if ((int)blockIdx.x >= z.xt.first_block) {
+        transpose_x_tiles<NTHREADS>(a, z.xt, (int)blockIdx.x - z.xt.first_block, lds);
+        return;
+    }
+    const LogitsList list(a, true);
+    if (list.rounds == 0) return;
+    DzEpilogue epi(list, lds);
+    gemm_tiles<KC, DzEpilogue::STORES>(make_operand(a.W, a.ldw, a.C, a.D), make_operand(a.X, a.ldx, a.B, a.D), a.D / TILE_K, list, epi, lds);
 }
 
 // Predictions of the shard: P[i][c] = exp(z[i][c] - lse[i]) as bf16, the same GEMM and staging as
@@ -1481,8 +1874,64 @@ static BwdPlan plan_bwd(int32_t B, int32_t D, int32_t C) {
     return p;
 }
 
-static size_t fwd_bytes(int32_t B, int32_t C) {
-    return (size_t)2 * (round_up(C, 256) / 256) * round_up(B, 256) * sizeof(float);
+// The list kernels' cut: the number of ranges (and with it of workgroups per compute unit, m) that takes the shortest time, in
+// cycles: a k-step of a whole tile is bound by its matrix instructions, one of a lower tile by the slots of its loads, too.
+constexpr int LIST_MAX_ITEMS = 4;
+static RangePlan plan_ranges(int32_t D, int32_t C, int nBT) {
+    const int units = (int)(2 * ((C + TILE_K - 1) / TILE_K)), k_steps = D / TILE_K;
+    RangePlan best = {1, 0, 0, 0, 0, 0, 0};
+    int64_t best_cost = -1;
+    for (int m = 1; m <= LIST_MAX_ITEMS; ++m) {
+        const int ranges = std::min(std::max(1, LIST_WGS * m / nBT), (units + 1) / 2);
+        const int per_item = (units + ranges - 1) / ranges;
+        const int64_t items = ((int64_t)ranges * nBT + LIST_WGS - 1) / LIST_WGS, full = per_item / MAX_UNITS, u = per_item % MAX_UNITS;
+        const int64_t cost = items * (full * (k_steps * 2700 + 10000) + (u > 0 ? k_steps * (1200 + 180 * u) + 3000 + 1000 * u : 0));
+        if (best_cost >= 0 && cost >= best_cost) continue;
+        best_cost = cost;
+        best.ranges = ranges;
+    }
+    best.full = units / (MAX_UNITS * best.ranges);
+    const int rest = units - best.full * MAX_UNITS * best.ranges;
+    best.per = rest / best.ranges;
+    best.more = rest - best.per * best.ranges;
+    best.inv_block = (uint32_t)((((uint64_t)1 << 32) + 4 * best.ranges - 1) / (4 * best.ranges));
+    best.inv_ranges = best.ranges > 1 ? (uint32_t)((((uint64_t)1 << 32) + best.ranges - 1) / best.ranges) : 0xffffffffu;
+    best.inv_rest = nBT % 4 > 1 ? (uint32_t)((((uint64_t)1 << 32) + nBT % 4 - 1) / (nBT % 4)) : 0;
+    return best;
+}
+// Whether the logits of a step (more than a small batch) run as lists or as a workgroup per tile, us of forward and dz:
+//   up to 64 tiles of 256 x 256 thin tiles fill more of the chip (B = 300, D = 1024, C = 800: tiles 15.1 + 16.2, lists 21.0 + 22.0);
+//   a single round: lists while they halve a tile or better (81 tiles, B = 2300, D = 2048, C = 2117: 40.4 + 45.0 and 35.7 + 44.0; 94,
+//     B = 300, D = 2048, C = 12 000: 39.6 + 43.1 and 35.3 + 37.9; 144, B = 777, D = 1088, C = 9001: 26.4 + 30.0 and 26.3 + 29.6; 196,
+//     B = 1024, D = 2048, C = 12 500: 43.2 + 48.2 and 47.5 + 52.6);
+//   more: short contractions, whose tiles are mostly epilogue (B = 3000, D = 128, C = 20 000: 40.3 + 58.9 and 34.7 + 48.9), and longer ones if
+//     the rest is half a tile or less (B = 700, D = 1024, C = 50 000: 80.5 + 93.6 and 75.1 + 85.4; B = 1024, D = 2048, C = 37 500:
+//     140 + 152 and 131 + 140; B = 8192, D = 1024, C = 50 000: 691 + 794 and 662 + 744; against a rest of five units, B = 256, D = 2048,
+//     C = 100 000: 120 + 121, dX 94.5 and 117 + 121, 99.0), except that long tiles over many rounds, where a workgroup that is
+//     done early takes the next tile, lose nothing (B = 4096, D = 2048, C = 37 500: 460 + 507 and 469 + 509; C = 12 500: 158.9 + 174.6
+//     and 159.2 + 177.4).
+// Every way adds the products of a logit in the same order.
+static bool logits_list(const RangePlan& p, int nBT, int nCT, int k_steps) {
+    const int64_t tiles = (int64_t)nBT * nCT;
+    const int rest = p.per + (p.more > 0);
+    if (tiles <= 64) return false;
+    if (tiles <= 256) return p.full == 0 && rest <= MAX_UNITS / 2;
+    return k_steps <= 8 || (rest <= MAX_UNITS / 2 && (k_steps <= 16 || tiles <= 3 * LIST_WGS));
+}
+// How the logits of a call are cut, and with it the order of their sums.
+static void set_order(FcArgs& a) {
+    a.ranges = plan_ranges(a.D, a.C, a.nBT);
+    a.on_lists = logits_list(a.ranges, a.nBT, a.nCT, a.D / TILE_K);
+}
+static int list_grid(const RangePlan& p, int nBT) { return xcd_grid(p.ranges * nBT); }
+
+// The forward call's partial results: one per class tile or range, and row.
+static size_t fwd_bytes(int32_t B, int32_t parts) { return (size_t)2 * parts * round_up(B, 256) * sizeof(float); }
+static int class_tiles(int32_t C) { return (int)(round_up(C, 256) / 256); }
+static int fwd_parts(int32_t B, int32_t D, int32_t C) {
+    const int nBT = (int)(round_up(B, 256) / 256), nCT = class_tiles(C);
+    const RangePlan p = plan_ranges(D, C, nBT);
+    return logits_list(p, nBT, nCT, D / TILE_K) ? std::max(nCT, p.ranges) : nCT;
 }
 
 static int check_fc_common(const void* X, int64_t ldx, const void* W, int64_t ldw, const float* bias,
@@ -1589,7 +2038,7 @@ const char* ws_status_string(int status) {
 int ws_version(void) { return 1217; }
 
 size_t ws_fwd_workspace_bytes(int32_t B, int32_t D, int32_t C_shard) {
-    return shape_ok(B, D, C_shard) ? fwd_bytes(B, C_shard) : 0;
+    return shape_ok(B, D, C_shard) ? fwd_bytes(B, fwd_parts(B, D, C_shard)) : 0;
 }
 
 size_t ws_bwd_workspace_bytes(int32_t B, int32_t D, int32_t C_shard) {
@@ -1609,10 +2058,11 @@ static int check_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t ld
     return WS_OK;
 }
 
-// Launches of the forward call; `workspace` holds fwd_bytes(B, C_shard) bytes, 16-byte aligned.
+// Launches of the forward call; `workspace` holds a partial result per class tile at least, 16-byte aligned.
 static int launch_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw, const float* b_shard,
                       const int32_t* labels, int32_t B, int32_t D, int32_t C_shard, int32_t class_offset,
-                      float* row_max, float* row_sumexp, float* label_logit, void* workspace, void* stream) {
+                      float* row_max, float* row_sumexp, float* label_logit, void* workspace, size_t workspace_bytes,
+                      void* stream) {
     FcArgs a;
     a.last_tile_first = 0;
     a.X = static_cast<const uint16_t*>(X); a.ldx = ldx;
@@ -1632,9 +2082,18 @@ static int launch_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t l
         pitch = p.rows;
         WS_LAUNCH_SMALL(KID_FWD, fwd_stats_small, p, p.ranges, s, a, p.range, part_max, part_sum, label_logit);
     } else {
-        a.plan = plan_tiles(a.nBT * a.nCT, LOGITS_MAX_THIN_TAIL);
-        WS_LAUNCH(KID_FWD, fwd_logits_stats, dim3(a.plan.thin_first + a.plan.n_thin), dim3(NTHREADS), s, a, part_max,
-                  part_sum, label_logit);
+        set_order(a);
+        // a workspace of one partial result per class tile is enough for the tiles
+        if (a.on_lists && workspace_bytes >= fwd_bytes(B, a.ranges.ranges)) {
+            parts = a.ranges.ranges;
+            part_sum = part_max + (size_t)parts * pitch;
+            WS_LAUNCH(KID_FWD, fwd_logits_list, dim3(list_grid(a.ranges, a.nBT)), dim3(NTHREADS), s,
+                      (FwdArgs{a, part_max, part_sum, label_logit}));
+        } else {
+            a.plan = plan_tiles(a.nBT * a.nCT, LOGITS_MAX_THIN_TAIL);
+            WS_LAUNCH(KID_FWD, fwd_logits_stats, dim3(a.plan.thin_first + a.plan.n_thin), dim3(NTHREADS), s, a, part_max,
+                      part_sum, label_logit);
+        }
     }
     WS_LAUNCH(KID_MERGE, merge_class_tiles, dim3((B + 15) / 16), dim3(1024), s, part_max, part_sum, parts, pitch, B, row_max,
               row_sumexp);
@@ -1648,10 +2107,10 @@ int ws_split_fc_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw
     int st = check_fwd(X, ldx, W_shard, ldw, b_shard, labels, B, D, C_shard, class_offset, row_max, row_sumexp,
                        label_logit);
     if (st != WS_OK) return st;
-    if (!workspace || workspace_bytes < fwd_bytes(B, C_shard)) return WS_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < fwd_bytes(B, class_tiles(C_shard))) return WS_ERR_WORKSPACE;
     if (!aligned(workspace, 16)) return WS_ERR_ALIGN;
     return launch_fwd(X, ldx, W_shard, ldw, b_shard, labels, B, D, C_shard, class_offset, row_max, row_sumexp,
-                      label_logit, workspace, stream);
+                      label_logit, workspace, workspace_bytes, stream);
 }
 
 int ws_split_fc_fwd_static(const void* X, int64_t ldx, const void* W_shard, int64_t ldw, const float* b_shard,
@@ -1660,13 +2119,13 @@ int ws_split_fc_fwd_static(const void* X, int64_t ldx, const void* W_shard, int6
     int st = check_fwd(X, ldx, W_shard, ldw, b_shard, labels, B, D, C_shard, class_offset, row_max, row_sumexp,
                        label_logit);
     if (st != WS_OK) return st;
-    if (fwd_bytes(B, C_shard) > (size_t)WS_STATIC_SCRATCH_BYTES) return WS_ERR_LIMIT;
+    if (fwd_bytes(B, class_tiles(C_shard)) > (size_t)WS_STATIC_SCRATCH_BYTES) return WS_ERR_LIMIT;
     void* ws_ptr = nullptr;
     st = static_scratch(&ws_ptr);
     if (st != WS_OK) return st;
     // every partial the merge reads is written by the logits kernel of the same call: nothing to clear
     return launch_fwd(X, ldx, W_shard, ldw, b_shard, labels, B, D, C_shard, class_offset, row_max, row_sumexp,
-                      label_logit, ws_ptr, stream);
+                      label_logit, ws_ptr, (size_t)WS_STATIC_SCRATCH_BYTES, stream);
 }
 
 int ws_combine_partials(const float* row_max, const float* row_sumexp, const float* label_logit, int32_t S,
@@ -1729,10 +2188,17 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
         WS_LAUNCH_SMALL(KID_DZ, dz_small, sp, xt.first_block + xt.n_blocks, s, a, sp.range, logsumexp, grad_scale, dZ, p.Cpad,
                         db_shard ? db_part : nullptr, xt);
     } else {
-        a.plan = plan_tiles(p.nBT * p.nCT, LOGITS_MAX_THIN_TAIL);
-        xt.first_block = a.plan.thin_first + a.plan.n_thin;
-        WS_LAUNCH(KID_DZ, bwd_recompute_dz, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s, a, logsumexp,
-                  grad_scale, dZ, p.Cpad, db_shard ? db_part : nullptr, xt);
+        set_order(a);
+        if (a.on_lists) {
+            xt.first_block = list_grid(a.ranges, a.nBT);
+            WS_LAUNCH(KID_DZ, bwd_dz_list, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s,
+                      (DzArgs{a, logsumexp, grad_scale, dZ, p.Cpad, db_shard ? db_part : nullptr, xt}));
+        } else {
+            a.plan = plan_tiles(p.nBT * p.nCT, LOGITS_MAX_THIN_TAIL);
+            xt.first_block = a.plan.thin_first + a.plan.n_thin;
+            WS_LAUNCH(KID_DZ, bwd_recompute_dz, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s, a, logsumexp,
+                      grad_scale, dZ, p.Cpad, db_shard ? db_part : nullptr, xt);
+        }
     }
 
     DxArgs x;
@@ -1829,6 +2295,7 @@ int ws_split_fc_predict(const void* X, int64_t ldx, const void* W_shard, int64_t
         const SmallPlan p(B, C_shard);
         WS_LAUNCH_SMALL(KID_PREDICT, predict_small, p, p.ranges, s, a, p.range, logsumexp, static_cast<uint16_t*>(P), ldp);
     } else {
+        set_order(a);
         WS_LAUNCH(KID_PREDICT, predict_probs, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, logsumexp,
                   static_cast<uint16_t*>(P), ldp);
     }
@@ -1845,7 +2312,7 @@ int ws_split_fc_top1(const void* X, int64_t ldx, const void* W_shard, int64_t ld
     if (class_offset < 0 || (int64_t)class_offset + C_shard > INT32_MAX) return WS_ERR_RANGE;
     if (!aligned(X, 16) || !aligned(W_shard, 16) || ldx % 8 || ldw % 8) return WS_ERR_ALIGN;
     if (!aligned(top_logit, 4) || !aligned(top_class, 4) || (b_shard && !aligned(b_shard, 4))) return WS_ERR_ALIGN;
-    if (!workspace || workspace_bytes < fwd_bytes(B, C_shard)) return WS_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < fwd_bytes(B, class_tiles(C_shard))) return WS_ERR_WORKSPACE;
     if (!aligned(workspace, 16)) return WS_ERR_ALIGN;
     FcArgs a;
     a.last_tile_first = 0;
@@ -1866,6 +2333,7 @@ int ws_split_fc_top1(const void* X, int64_t ldx, const void* W_shard, int64_t ld
         pitch = p.rows;
         WS_LAUNCH_SMALL(KID_TOP1, top1_small, p, p.ranges, s, a, p.range, part_val, part_cls);
     } else {
+        set_order(a);
         WS_LAUNCH(KID_TOP1, top1_logits, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, part_val, part_cls);
     }
     launch_merge_top1(part_val, part_cls, parts, pitch, B, class_offset, top_logit, top_class, s);
