@@ -1,4 +1,4 @@
-// GEMM of small output tiles: 64 (M) x 64 (N), A k-contiguous, B k-strided, bf16 out.
+// GEMM of small output tiles: 64 (M) x 64 (N), A k-contiguous, B k-strided.
 //
 // A 256 x 256 tile (gemm_core.h) takes a compute unit 2048 matrix cycles per k-step; an output of a few dozen of them leaves
 // the rest of the chip idle for the length of the contraction.  A 64 x 64 tile moves four times the operand bytes per
@@ -17,9 +17,12 @@ constexpr int BLOCK_STAGE_BYTES = 2 * BLOCK_OPERAND_BYTES;
 constexpr int BLOCK_STAGES = 5;
 constexpr int BLOCK_LDS_BYTES = BLOCK_STAGES * BLOCK_STAGE_BYTES;
 
-// Returns 16-byte chunk tid % 8 (elements m0 + 8 * (tid % 8) ..) of row n0 + tid / 8 of the tile as bf16 out[n][m]: sums over
-// k < 64 * k_steps of A(m, k) * B(k, n).  All 512 threads call it together.
-__device__ __forceinline__ u32x4 block_gemm(const Operand& A, const Operand& Bop, int m0, int n0, int k_steps, char* lds) {
+typedef f32x4 block_acc_t[2][2];
+
+// Sums over k in [k_begin, k_begin + 64 * k_steps) of A(m, k) * B(k, n): waves 0 .. 3 end with quarter (pm, pn) = (wave % 2, wave
+// / 2) of the tile, acc[x][y] M tile x and N tile y of it.  All 512 threads call it together.
+__device__ __forceinline__ void block_gemm(block_acc_t& acc, const Operand& A, const Operand& Bop, int m0, int n0, int k_begin,
+                                           int k_steps, char* lds) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, g = lane >> 4;
@@ -31,8 +34,9 @@ __device__ __forceinline__ u32x4 block_gemm(const Operand& A, const Operand& Bop
     const uint32_t b_lane = ((uint32_t)row * Bop.ld + (uint32_t)(n0 + 8 * ((lane & 7) ^ thin_ks_swizzle(row)))) * 2u;
     const uint32_t lds_wave = lds_offset(lds) + 1024u * (uint32_t)wave;
     auto load = [&](int step, int stage) {
-        load_to_lds(A, a_lane, (uint32_t)step * 128u, lds_wave + (uint32_t)stage);
-        load_to_lds(Bop, b_lane, (uint32_t)step * 128u * Bop.ld, lds_wave + (uint32_t)stage + BLOCK_OPERAND_BYTES);
+        const uint32_t k = (uint32_t)(k_begin + step * TILE_K);
+        load_to_lds(A, a_lane, 2u * k, lds_wave + (uint32_t)stage);
+        load_to_lds(Bop, b_lane, 2u * k * Bop.ld, lds_wave + (uint32_t)stage + BLOCK_OPERAND_BYTES);
     };
     const int a_frag = (32 * pm + i) * 128 + (((4 * half + g) ^ (i >> 1)) << 4);
     int b_frag[2];
@@ -41,7 +45,6 @@ __device__ __forceinline__ u32x4 block_gemm(const Operand& A, const Operand& Bop
         const int krow = 8 * g + (i >> 2), col = 32 * pn + 16 * t + 4 * (i & 3);
         b_frag[t] = BLOCK_OPERAND_BYTES + (32 * half + krow) * 128 + (((col >> 3) ^ thin_ks_swizzle(krow)) << 4) + ((col & 7) << 1);
     }
-    f32x4 acc[2][2];
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -77,22 +80,32 @@ __device__ __forceinline__ u32x4 block_gemm(const Operand& A, const Operand& Bop
     }
     wait_counts<NO_VM_WAIT, 0>();
     raw_barrier();
-    // the second half's sums as [quarter][x, y][lane], then the tile as [n][m], 128 bytes per n, 8-byte slots XOR-ed with n & 15
-    f32x4* other = reinterpret_cast<f32x4*>(lds) + (wave & 3) * 256 + lane;
+    f32x4* other = reinterpret_cast<f32x4*>(lds) + (wave & 3) * 256 + lane;        // [quarter][x, y][lane]
     if (half == 1) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) other[64 * q] = acc[q >> 1][q & 1];
     }
     wait_counts<NO_VM_WAIT, 0>();
     raw_barrier();
-    char* tile = lds + 4 * 4096;
     if (half == 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q >> 1][q & 1] += other[64 * q];
+    }
+}
+constexpr int BLOCK_TILE_OFFSET = 4 * 4096;             // LDS behind the sums of the second half
+
+// The tile as bf16 [n][m]: 16-byte chunk tid % 8 (elements 8 * (tid % 8) ..) of row tid / 8.  It passes through LDS, 128 bytes per
+// n, 8-byte slots XOR-ed with n & 15.
+__device__ __forceinline__ u32x4 block_rows_bf16(const block_acc_t& acc, char* lds) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), i = lane & 15, g = lane >> 4;
+    char* tile = lds + BLOCK_TILE_OFFSET;
+    if (wave < 4) {
 #pragma unroll
         for (int x = 0; x < 2; ++x)
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
-                const f32x4 v = acc[x][y] + other[64 * (2 * x + y)];
-                const int n = 32 * pn + 16 * y + i, slot = (32 * pm + 16 * x + 4 * g) >> 2;
+                const f32x4 v = acc[x][y];
+                const int n = 32 * (wave >> 1) + 16 * y + i, slot = (32 * (wave & 1) + 16 * x + 4 * g) >> 2;
                 *reinterpret_cast<u32x2*>(tile + n * 128 + ((slot ^ (n & 15)) << 3)) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
             }
     }
@@ -101,6 +114,29 @@ __device__ __forceinline__ u32x4 block_gemm(const Operand& A, const Operand& Bop
     const int n = tid >> 3, c = tid & 7;                 // chunk c is slots 2 c and 2 c + 1, side by side, swapped when n is odd
     u32x4 v = *reinterpret_cast<const u32x4*>(tile + n * 128 + ((c ^ ((n & 15) >> 1)) << 4));
     return n & 1 ? __builtin_shufflevector(v, v, 2, 3, 0, 1) : v;
+}
+
+// The tile as fp32 [m][n]: out[half] is elements 4 * (tid % 16) .. + 3 of row 32 * half + tid / 16.  256 bytes per m in LDS, 16-float
+// chunks XOR-ed with (m >> 2) & 3, which spreads the four row groups of a wave's store over the banks.
+__device__ __forceinline__ void block_rows_f32(f32x4 (&out)[2], const block_acc_t& acc, char* lds) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), i = lane & 15, g = lane >> 4;
+    float* tile = reinterpret_cast<float*>(lds + BLOCK_TILE_OFFSET);
+    if (wave < 4) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)              // row m = .. + 4 g + v: (m >> 2) & 3 = g
+                    tile[(32 * (wave & 1) + 16 * x + 4 * g + v) * 64 + 16 * ((2 * (wave >> 1) + y) ^ g) + i] = acc[x][y][v];
+    }
+    wait_counts<NO_VM_WAIT, 0>();
+    raw_barrier();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int m = 32 * h + (tid >> 4), c = tid & 15;
+        out[h] = *reinterpret_cast<const f32x4*>(tile + m * 64 + 16 * ((c >> 2) ^ ((m >> 2) & 3)) + 4 * (c & 3));
+    }
 }
 
 }  // namespace ws

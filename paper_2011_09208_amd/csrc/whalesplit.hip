@@ -1457,6 +1457,27 @@ __global__ __launch_bounds__(NTHREADS) void bwd_dx(DxArgs a) {
     }
 }
 
+// dX in tiles of 64 rows x 64 features (gemm_block.h), for batches and features that 256 x 256 tiles would fill poorly.
+__global__ __launch_bounds__(NTHREADS, 4) void bwd_dx_block(DxArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
+    const int nDT = a.D / BLOCK, tiles = nDT * ((a.B + BLOCK - 1) / BLOCK), tile = xcd_logical_tile(tiles * a.splits);
+    if (tile < 0) return;
+    const int sp = tile / tiles, td = tile - sp * tiles, d0 = (td % nDT) * BLOCK, b0 = (td / nDT) * BLOCK;   // feature tiles fastest
+    const int s0 = sp * a.steps_per_split, left = a.steps_total - s0;
+    const Operand A = make_operand(a.dZ, a.ldz, a.B, a.ldz);      // rows beyond the batch read as zeros
+    const Operand Bo = make_operand(a.W, a.ldw, a.C, a.D);          // classes beyond the shard read as zeros
+    block_acc_t acc;
+    block_gemm(acc, A, Bo, b0, d0, s0 * TILE_K, left < a.steps_per_split ? left : a.steps_per_split, lds);
+    f32x4 v[2];
+    block_rows_f32(v, acc, lds);
+    float* out = a.out + sp * a.split_stride + d0 + 4 * ((int)threadIdx.x & 15);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int row = b0 + 32 * h + ((int)threadIdx.x >> 4);
+        if (row < a.B) *reinterpret_cast<f32x4*>(out + (int64_t)row * a.ldo) = v[h];
+    }
+}
+
 // The two small reductions that finish the backward call: the split-K partials of dX are summed in a
 // fixed order (one float4 per thread and turn; optionally accumulating into the caller's dX), and the
 // per-row-tile column sums into db.  Run by the workgroups of bwd_dw beyond its GEMM tiles (handed out
@@ -1642,7 +1663,9 @@ __global__ __launch_bounds__(NTHREADS, 4) void bwd_dw_block(DwArgs a, FinishArgs
     const bool live = c0 + row < a.C;
     u32x4 w = {0, 0, 0, 0};
     if (a.sgd && live) w = *reinterpret_cast<const u32x4*>(out);
-    u32x4 g = block_gemm(A, Bo, d0, c0, a.k_steps, lds);
+    block_acc_t acc;
+    block_gemm(acc, A, Bo, d0, c0, 0, a.k_steps, lds);
+    u32x4 g = block_rows_bf16(acc, lds);
     if (a.sgd) g = updated_weights(w, g, a.lr);
     if (live) __builtin_nontemporal_store(g, reinterpret_cast<u32x4*>(out));
 }
@@ -1826,30 +1849,39 @@ struct BwdPlan {
     int64_t Bpad, Cpad;
     int nBT, nCT, nDT;
     int steps_total, splits, steps_per_split;
+    bool dx_small;                       // dX in 64 x 64 tiles
     size_t dz_bytes, xt_bytes, dbp_bytes, parts_bytes;
 };
 
-// dX: the splits of the contraction.  Up to as many as fill the 256 compute units once, rounded up; of those the count that
-// takes the shortest time, in sixteenths of a k-step: the rounds of workgroups, a workgroup's start and its partial tile counted as
-// DX_TILE_STEPS k-steps, and the later sum of the partial tiles, of which a side job takes 16 in the time of a k-step.  Rounded up alone a split too many
-// costs a second round; bwd_dx, us, rounded up / by this rule: B = 777, D = 1088 (20 tiles), C = 14 450, 13 splits (260 workgroups)
-// 56.8, 12 splits 36.3; B = 1200, D = 1536, C = 30 000 (30 tiles), 9: 136.8, 8: 86.0; B = 2300, D = 2048, C = 12 500 (72
-// tiles), 4: 131.9, 3: 94.3; B = 5000, D = 1024, C = 20 000 (80 tiles), 4: 212.7, 3: 154.9.  And a split for
-// every k-step or two leaves the sum more to do than it saves: step, us, B = 100, D = 64, C = 30 000: 235 splits 61.2, 59 50.3; B = 200,
-// D = 512, C = 16 000: 125 66.5, 63 60.6.
-constexpr int DX_TILE_STEPS = 4;
+// dX: its tiles, 256 x 256 or 64 x 64, and the splits of its contraction: what takes the shortest time, in ns, of up to as many
+// splits as fill the compute units once (two workgroups each of the small tiles), rounded up.
+//   A wide tile takes 1.3 us per k-step and 6 for its start and its end, whatever part of it is there; a small one 0.32 for each
+//   of those that share a compute unit.  The partial sums are written and read once (4.5 TB/s), and the side job takes 16 splits
+//   per us and turn of its threads.
+// Rounded up alone a split too many costs a second round; bwd_dx, us, rounded up / one round: B = 777, D = 1088 (20 tiles), C =
+// 14 450, 13 splits (260 workgroups) 56.8, 12 splits 36.3; B = 5000, D = 1024, C = 20 000 (80 tiles), 4: 212.7, 3: 154.9.  A split for
+// every k-step or two leaves the sum more to do than it saves: step, us, B = 100, D = 64, C = 30 000: 235 splits 61.2, 59 50.3.
+// Wide and small tiles, dX / step: B = 32, D = 256, C = 8000 12.4 / 30.6 and 7.0 / 27.3; B = 400, D = 128, C = 12 000 17.8 / 56.3 and
+// 9.2 / 47.6; B = 1500, D = 256, C = 8000 20.2 / 75.8 and 19.3 / 67.3; B = 3000, D = 256, C = 8000 28.0 / 118.5 and 38.1 / 116.2; B = 800, D =
+// 2048, C = 3000 22.6 / 93.4 and 29.8 / 94.7; B = 800, D = 256, C = 40 000 30.0 / 134.2 and 45.2 / 143.3.
 static void dx_splits(BwdPlan& p, int32_t B, int32_t D) {
     const int64_t sum_turns = ((int64_t)B * (D / 4) + SIDE_BLOCKS * NTHREADS - 1) / (SIDE_BLOCKS * NTHREADS);   // of the side job's threads
-    const int tiles = p.nDT * p.nBT;
-    const int most = std::min(tiles >= 256 ? 1 : (256 + tiles - 1) / tiles, p.steps_total);
+    const int64_t bytes = (int64_t)B * D * 4;
     int64_t best = -1;
-    for (int want = 1; want <= most; ++want) {
-        const int steps = (p.steps_total + want - 1) / want, splits = (p.steps_total + steps - 1) / steps;
-        const int64_t cost = ((int64_t)tiles * splits + 255) / 256 * 16 * (steps + DX_TILE_STEPS) + splits * sum_turns;
-        if (best >= 0 && cost >= best) continue;
-        best = cost;
-        p.steps_per_split = steps;
-        p.splits = splits;
+    for (int small = 0; small < 2; ++small) {
+        const int64_t tiles = small ? (int64_t)(D / BLOCK) * ((B + BLOCK - 1) / BLOCK) : (int64_t)p.nDT * p.nBT;
+        const int room = small ? 512 : 256, most = std::min(tiles >= room ? 1 : (int)((room + tiles - 1) / tiles), p.steps_total);
+        for (int want = 1; want <= most; ++want) {
+            const int steps = (p.steps_total + want - 1) / want, splits = (p.steps_total + steps - 1) / steps;
+            const int64_t turns = (tiles * splits + 255) / 256;
+            const int64_t cost = (small ? turns * 320 * steps + 1500 : turns * (1300 * steps + 6000)) +
+                                 splits * (2 * bytes / 4500 + sum_turns * 1000 / 16);
+            if (best >= 0 && cost >= best) continue;
+            best = cost;
+            p.steps_per_split = steps;
+            p.splits = splits;
+            p.dx_small = small;
+        }
     }
 }
 
@@ -2210,7 +2242,10 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     x.out = direct ? dX_partial : parts;
     x.ldo = direct ? lddx : D;
     x.split_stride = (int64_t)B * D;
-    WS_LAUNCH(KID_DX, bwd_dx, dim3(xcd_grid(p.nDT * p.nBT * p.splits)), dim3(NTHREADS), s, x);
+    if (p.dx_small)
+        WS_LAUNCH(KID_DX, bwd_dx_block, dim3(xcd_grid((D / BLOCK) * ((B + BLOCK - 1) / BLOCK) * p.splits)), dim3(NTHREADS), s, x);
+    else
+        WS_LAUNCH(KID_DX, bwd_dx, dim3(xcd_grid(p.nDT * p.nBT * p.splits)), dim3(NTHREADS), s, x);
     DwArgs w;
     w.XT = XT; w.ldxt = p.Bpad; w.dZ = dZ; w.ldz = p.Cpad;
     w.D = D; w.C = C_shard; w.B = B;

@@ -1,6 +1,6 @@
-"""GPU parity of dX where its contraction is cut so that the workgroups fit one round of the 256 compute units: tile counts
-that do not divide 256 (20, 27, 72, 132 tiles), more splits than k-steps, last splits shorter than the others, one split
-written straight to the output and one that is added to it."""
+"""GPU parity of dX where its contraction is cut: wide tiles whose number does not divide 256 (20, 44, 72 of them), last splits
+shorter than the others, one split written straight to the output and one that is added to it; the 64 x 64 tiles with one
+row, one tile, ragged rows and classes, and more than 256 workgroups."""
 import pytest
 
 from paper_2011_09208_amd import inputs
@@ -18,11 +18,18 @@ def H():
 
 
 @pytest.mark.parametrize("B,D,widths", [
-    (1100, 1024, [64 * 141 - 5]),        # 20 tiles, 141 k-steps: 12 splits of 12, the last of 9
-    (1100, 1024, [64 * 3]),         # 3 k-steps: as many splits
-    (2300, 576, [64 * 19 + 1]),          # 27 tiles, 20 k-steps: 7 splits of 3, the last of 2
-    (2100, 1984, [64 * 10]),             # 72 tiles: 2 splits
-    (2700, 2880, [300, 64 * 7 + 9]),     # 132 tiles: one split, the second shard added to the first
+    (1100, 1024, [64 * 141 - 5]),        # 20 wide tiles, 141 k-steps: 9 splits of 16, the last of 13
+    (2600, 1024, [64 * 30 + 7]),         # 44: 3 splits of 11, the last of 9
+    (2300, 2048, [64 * 40 - 3]),         # 72: 2 splits
+    (1000, 2048, [5000]),                # 32: 5 splits of 16, the last of 15
+    (1, 64, [1, 40]),                    # one small tile
+    (64, 64, [64 * 70 + 1]),             # 1: 18 splits of 4 k-steps, the last of 3
+    (65, 128, [64 * 200]),               # 4, one row in the second: 29 splits of 7, the last of 4
+    (130, 64, [2561]),                   # 3: 14 splits of 3, the last of 2
+    (700, 192, [64 * 21]),               # 33
+    (2300, 576, [64 * 19 + 1]),          # 324: 2 splits
+    (1100, 1024, [64 * 3, 64 * 2 + 9]),  # 288: one split, the second shard added to the first
+    (4500, 64, [130]),                   # 71, 3 k-steps
 ])
 def test_dx_splits(H, B, D, widths):
     C = sum(widths)
