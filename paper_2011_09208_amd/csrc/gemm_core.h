@@ -463,9 +463,8 @@ struct TilePlan {
 // Map the hardware id to a logical tile id so that each XCD walks one contiguous range of
 // logical tiles (tiles that share an operand panel are numbered next to each other).
 // The grid must hold 8 * ceil(n_tiles / 8) workgroups; returns -1 for the surplus ones.
-__device__ __forceinline__ int xcd_logical_tile(int n_tiles) {
+__device__ __forceinline__ int xcd_logical_tile(int n_tiles, int bid = blockIdx.x) {
     const int per = (n_tiles + 7) >> 3;
-    const int bid = blockIdx.x;
     const int t = (bid & 7) * per + (bid >> 3);
     return t < n_tiles ? t : -1;
 }

@@ -657,13 +657,9 @@ __device__ __forceinline__ void load_shards(float (&v)[COMBINE_BATCH], const flo
 #pragma unroll
     for (int k = 0; k < COMBINE_BATCH; ++k) v[k] = p[(int64_t)(s0 + k < S ? s0 + k : S - 1) * stride];
 }
-__global__ __launch_bounds__(64) void combine_partials_kernel(const float* __restrict__ row_max,
-                                                              const float* __restrict__ row_sumexp,
-                                                              const float* __restrict__ label_logit, int S, int B,
-                                                              int64_t stride, float* __restrict__ logsumexp,
-                                                              float* __restrict__ loss_rows) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= B) return;
+__device__ __forceinline__ float combine_row(const float* __restrict__ row_max, const float* __restrict__ row_sumexp,
+                                             const float* __restrict__ label_logit, int S, int64_t stride, int i,
+                                             float* __restrict__ logsumexp, float* __restrict__ loss_rows) {
     float vm[COMBINE_BATCH], vs[COMBINE_BATCH], vt[COMBINE_BATCH];
     load_shards(vm, row_max + i, 0, S, stride);
     load_shards(vs, row_sumexp + i, 0, S, stride);
@@ -694,14 +690,20 @@ __global__ __launch_bounds__(64) void combine_partials_kernel(const float* __res
     const float lse = m + __logf(tot);
     logsumexp[i] = lse;
     loss_rows[i] = lse - t;
+    return lse - t;
+}
+__global__ __launch_bounds__(64) void combine_partials_kernel(const float* __restrict__ row_max,
+                                                              const float* __restrict__ row_sumexp,
+                                                              const float* __restrict__ label_logit, int S, int B,
+                                                              int64_t stride, float* __restrict__ logsumexp,
+                                                              float* __restrict__ loss_rows) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < B) combine_row(row_max, row_sumexp, label_logit, S, stride, i, logsumexp, loss_rows);
 }
 
-// Mean of loss_rows in a fixed summation order (one workgroup).
-__global__ __launch_bounds__(1024) void mean_loss_kernel(const float* __restrict__ loss_rows, int B,
-                                                          float* __restrict__ loss_mean) {
+// Mean of the threads' sums of loss_rows in a fixed order (one workgroup; thread t has added rows t, t + 1024, ..).
+__device__ __forceinline__ void mean_of_sums(float acc, int B, float* __restrict__ loss_mean) {
     __shared__ float red[1024];
-    float acc = 0.0f;
-    for (int i = threadIdx.x; i < B; i += 1024) acc += loss_rows[i];
     red[threadIdx.x] = acc;
     __syncthreads();
     for (int w = 512; w > 0; w >>= 1) {
@@ -709,6 +711,24 @@ __global__ __launch_bounds__(1024) void mean_loss_kernel(const float* __restrict
         __syncthreads();
     }
     if (threadIdx.x == 0) *loss_mean = red[0] / (float)B;
+}
+__global__ __launch_bounds__(1024) void mean_loss_kernel(const float* __restrict__ loss_rows, int B,
+                                                          float* __restrict__ loss_mean) {
+    float acc = 0.0f;
+    for (int i = threadIdx.x; i < B; i += 1024) acc += loss_rows[i];
+    mean_of_sums(acc, B, loss_mean);
+}
+// Both in one workgroup (COMBINE_MEAN_ROWS on the host).
+__global__ __launch_bounds__(1024) void combine_mean_kernel(const float* __restrict__ row_max,
+                                                            const float* __restrict__ row_sumexp,
+                                                            const float* __restrict__ label_logit, int S, int B,
+                                                            int64_t stride, float* __restrict__ logsumexp,
+                                                            float* __restrict__ loss_rows, float* __restrict__ loss_mean) {
+    float acc = 0.0f;
+#pragma unroll 2
+    for (int i = threadIdx.x; i < B; i += 1024)
+        acc += combine_row(row_max, row_sumexp, label_logit, S, stride, i, logsumexp, loss_rows);
+    mean_of_sums(acc, B, loss_mean);
 }
 
 // XT[d][b] = X[b][d], zero for b >= B (the dW contraction reads whole 64-row k-steps), in 64 x 64 tiles through LDS.  Run by
@@ -1457,25 +1477,38 @@ __global__ __launch_bounds__(NTHREADS) void bwd_dx(DxArgs a) {
     }
 }
 
-// dX in tiles of 64 rows x 64 features (gemm_block.h), for batches and features that 256 x 256 tiles would fill poorly.
+// dX in tiles of 64 rows x 64 features (gemm_block.h), for batches and features that 256 x 256 tiles would fill poorly.  A
+// tile's place in the output, and the two chunks of each thread: 4 floats of rows row() and row() + 32.
+struct DxBlock {
+    int split, tile, b0, d0;
+    __device__ __forceinline__ DxBlock(const DxArgs& a, int logical) {
+        const int nDT = a.D / BLOCK, tiles = nDT * ((a.B + BLOCK - 1) / BLOCK);
+        split = logical / tiles;
+        tile = logical - split * tiles;
+        d0 = (tile % nDT) * BLOCK;                       // feature tiles fastest
+        b0 = (tile / nDT) * BLOCK;
+    }
+    __device__ __forceinline__ int row() const { return b0 + ((int)threadIdx.x >> 4); }
+    __device__ __forceinline__ int64_t offset(int h, int64_t ld) const { return (int64_t)(row() + 32 * h) * ld + d0 + 4 * ((int)threadIdx.x & 15); }
+    __device__ __forceinline__ void compute(f32x4 (&v)[2], const DxArgs& a, char* lds) const {
+        const int s0 = split * a.steps_per_split, left = a.steps_total - s0;
+        const Operand A = make_operand(a.dZ, a.ldz, a.B, a.ldz);      // rows beyond the batch read as zeros
+        const Operand Bo = make_operand(a.W, a.ldw, a.C, a.D);          // classes beyond the shard read as zeros
+        block_acc_t acc;
+        block_gemm(acc, A, Bo, b0, d0, s0 * TILE_K, left < a.steps_per_split ? left : a.steps_per_split, lds);
+        block_rows_f32(v, acc, lds);
+    }
+};
 __global__ __launch_bounds__(NTHREADS, 4) void bwd_dx_block(DxArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
-    const int nDT = a.D / BLOCK, tiles = nDT * ((a.B + BLOCK - 1) / BLOCK), tile = xcd_logical_tile(tiles * a.splits);
-    if (tile < 0) return;
-    const int sp = tile / tiles, td = tile - sp * tiles, d0 = (td % nDT) * BLOCK, b0 = (td / nDT) * BLOCK;   // feature tiles fastest
-    const int s0 = sp * a.steps_per_split, left = a.steps_total - s0;
-    const Operand A = make_operand(a.dZ, a.ldz, a.B, a.ldz);      // rows beyond the batch read as zeros
-    const Operand Bo = make_operand(a.W, a.ldw, a.C, a.D);          // classes beyond the shard read as zeros
-    block_acc_t acc;
-    block_gemm(acc, A, Bo, b0, d0, s0 * TILE_K, left < a.steps_per_split ? left : a.steps_per_split, lds);
+    const int logical = xcd_logical_tile(a.D / BLOCK * ((a.B + BLOCK - 1) / BLOCK) * a.splits);
+    if (logical < 0) return;
+    const DxBlock t(a, logical);
     f32x4 v[2];
-    block_rows_f32(v, acc, lds);
-    float* out = a.out + sp * a.split_stride + d0 + 4 * ((int)threadIdx.x & 15);
+    t.compute(v, a, lds);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int row = b0 + 32 * h + ((int)threadIdx.x >> 4);
-        if (row < a.B) *reinterpret_cast<f32x4*>(out + (int64_t)row * a.ldo) = v[h];
-    }
+    for (int h = 0; h < 2; ++h)
+        if (t.row() + 32 * h < a.B) *reinterpret_cast<f32x4*>(a.out + t.split * a.split_stride + t.offset(h, a.ldo)) = v[h];
 }
 
 // The two small reductions that finish the backward call: the split-K partials of dX are summed in a
@@ -1645,16 +1678,9 @@ __device__ __forceinline__ void dw_thin(const DwArgs& a, int q, char* lds) {
 }
 
 // dW in tiles of 64 features x 64 classes, two workgroups to a compute unit (gemm_block.h): for layers whose 256 x 256
-// tiles would leave most of the chip idle while each walks a long contraction.
-__global__ __launch_bounds__(NTHREADS, 4) void bwd_dw_block(DwArgs a, FinishArgs fin) {
-    __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
-    if ((int)blockIdx.x >= fin.first_block) {
-        finish_bwd(fin, (int)blockIdx.x - fin.first_block);
-        return;
-    }
-    const int nDT = a.D / BLOCK, tile = xcd_logical_tile(nDT * ((a.C + BLOCK - 1) / BLOCK));
-    if (tile < 0) return;
-    const int d0 = (tile % nDT) * BLOCK, c0 = (tile / nDT) * BLOCK;    // feature tiles fastest: neighbours share the dz panel
+// tiles would leave most of the chip idle while each walks the contraction.
+__device__ __forceinline__ void dw_block(const DwArgs& a, int tile, char* lds) {
+    const int nDT = a.D / BLOCK, d0 = (tile % nDT) * BLOCK, c0 = (tile / nDT) * BLOCK;   // feature tiles fastest: neighbours share the dz panel
     const Operand A = make_operand(a.XT, a.ldxt, a.D, a.ldxt);
     const Operand Bo = make_operand(a.dZ, a.ldz, a.B, a.ldz);          // rows beyond the batch read as zeros
     // one 16-byte chunk of the output per thread: class c0 + tid / 8, features d0 + 8 * (tid % 8)
@@ -1668,6 +1694,47 @@ __global__ __launch_bounds__(NTHREADS, 4) void bwd_dw_block(DwArgs a, FinishArgs
     u32x4 g = block_rows_bf16(acc, lds);
     if (a.sgd) g = updated_weights(w, g, a.lr);
     if (live) __builtin_nontemporal_store(g, reinterpret_cast<u32x4*>(out));
+}
+__global__ __launch_bounds__(NTHREADS, 4) void bwd_dw_block(DwArgs a, FinishArgs fin) {
+    __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
+    if ((int)blockIdx.x >= fin.first_block) {
+        finish_bwd(fin, (int)blockIdx.x - fin.first_block);
+        return;
+    }
+    const int tile = xcd_logical_tile(a.D / BLOCK * ((a.C + BLOCK - 1) / BLOCK));
+    if (tile >= 0) dw_block(a, tile, lds);
+}
+
+// dX of whole contractions and dW in one launch, both in 64 x 64 tiles (neither reads what the other writes: no fused update).
+// (With splits, whose last workgroup added the partial sums: correct, but what one XCD's L2 wrote has to reach the others
+// first, and that took 10 to 100 us.)
+struct DxTail {
+    float* dX; int64_t lddx; int accumulate;
+    int dw_first_block;
+};
+__global__ __launch_bounds__(NTHREADS, 4) void bwd_dx_dw_block(DxArgs x, DxTail tail, DwArgs w, FinishArgs fin) {
+    __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
+    const int bid = blockIdx.x;
+    if (bid >= fin.first_block) {
+        finish_bwd(fin, bid - fin.first_block);
+        return;
+    }
+    if (bid >= tail.dw_first_block) {
+        const int tile = xcd_logical_tile(w.D / BLOCK * ((w.C + BLOCK - 1) / BLOCK), bid - tail.dw_first_block);
+        if (tile >= 0) dw_block(w, tile, lds);
+        return;
+    }
+    const int logical = xcd_logical_tile(x.D / BLOCK * ((x.B + BLOCK - 1) / BLOCK));
+    if (logical < 0) return;
+    const DxBlock t(x, logical);
+    f32x4 v[2];
+    t.compute(v, x, lds);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        if (t.row() + 32 * h < x.B) {
+            f32x4* o = reinterpret_cast<f32x4*>(tail.dX + t.offset(h, tail.lddx));
+            *o = tail.accumulate ? *o + v[h] : v[h];
+        }
 }
 
 __global__ __launch_bounds__(NTHREADS) void bwd_dw(DwArgs a, FinishArgs fin) {
@@ -1767,6 +1834,10 @@ static TilePlan plan_tiles(int n_tiles, int max_thin_tail) {
 // faster: forward, B = 256, D = 2048, 256 tiles and a tail of 32, 64, 65, 128 tiles: thin 79, 101, 120, 138 us; full, whatever
 // the tail, 101-108.
 static const int LOGITS_MAX_THIN_TAIL = 64;
+// The mean is taken by the combine launch itself while one workgroup is as quick as two launches; us, two launches and one: B = 32,
+// 8 shards 3.5 and 2.5 (and a launch less on the host, 3.7); B = 1024 4.1 and 3.2; B = 2048 4.5 and 4.3, 16 shards 5.1 and 7.6; B =
+// 4096 4.8 and 6.3.
+constexpr int COMBINE_MEAN_ROWS = 2048;
 // dW: as many as fit one round if there is no round before (fewer if they are short: they then wait for the side jobs' compute
 // units), and behind full rounds, where the first of them share the chip with the last full tiles, fewer, and none if they
 // are short.  A single round, us of the launch on full and thin tiles: 30 tiles (D = 256, C = 7600): 11 k-steps 21.5 and 14.7, 40: 52
@@ -1849,8 +1920,10 @@ struct BwdPlan {
     int64_t Bpad, Cpad;
     int nBT, nCT, nDT;
     int steps_total, splits, steps_per_split;
-    bool dx_small;                       // dX in 64 x 64 tiles
+    bool dx_small, dw_small;             // dX, dW in 64 x 64 tiles
     size_t dz_bytes, xt_bytes, dbp_bytes, parts_bytes;
+    bool one_launch() const { return dx_small && dw_small && splits == 1; }      // for dX and dW (not with the fused update)
+    size_t bytes() const { return dz_bytes + xt_bytes + dbp_bytes + parts_bytes; }
 };
 
 // dX: its tiles, 256 x 256 or 64 x 64, and the splits of its contraction: what takes the shortest time, in ns, of up to as many
@@ -1861,9 +1934,12 @@ struct BwdPlan {
 // Rounded up alone a split too many costs a second round; bwd_dx, us, rounded up / one round: B = 777, D = 1088 (20 tiles), C =
 // 14 450, 13 splits (260 workgroups) 56.8, 12 splits 36.3; B = 5000, D = 1024, C = 20 000 (80 tiles), 4: 212.7, 3: 154.9.  A split for
 // every k-step or two leaves the sum more to do than it saves: step, us, B = 100, D = 64, C = 30 000: 235 splits 61.2, 59 50.3.
+// Without splits small tiles run in the launch of a dW of small tiles, which is worth ONE_LAUNCH_NS (step, two launches and one: B = 32,
+// D = 256, C = 500 27.9 and 25.6; B = 900, D = 128, C = 700 29.9 and 26.4; B = 8000, D = 64, C = 500 55.7 and 51.3).
 // Wide and small tiles, dX / step: B = 32, D = 256, C = 8000 12.4 / 30.6 and 7.0 / 27.3; B = 400, D = 128, C = 12 000 17.8 / 56.3 and
 // 9.2 / 47.6; B = 1500, D = 256, C = 8000 20.2 / 75.8 and 19.3 / 67.3; B = 3000, D = 256, C = 8000 28.0 / 118.5 and 38.1 / 116.2; B = 800, D =
 // 2048, C = 3000 22.6 / 93.4 and 29.8 / 94.7; B = 800, D = 256, C = 40 000 30.0 / 134.2 and 45.2 / 143.3.
+constexpr int ONE_LAUNCH_NS = 4000;
 static void dx_splits(BwdPlan& p, int32_t B, int32_t D) {
     const int64_t sum_turns = ((int64_t)B * (D / 4) + SIDE_BLOCKS * NTHREADS - 1) / (SIDE_BLOCKS * NTHREADS);   // of the side job's threads
     const int64_t bytes = (int64_t)B * D * 4;
@@ -1875,7 +1951,8 @@ static void dx_splits(BwdPlan& p, int32_t B, int32_t D) {
             const int steps = (p.steps_total + want - 1) / want, splits = (p.steps_total + steps - 1) / steps;
             const int64_t turns = (tiles * splits + 255) / 256;
             const int64_t cost = (small ? turns * 320 * steps + 1500 : turns * (1300 * steps + 6000)) +
-                                 splits * (2 * bytes / 4500 + sum_turns * 1000 / 16);
+                                 splits * (2 * bytes / 4500 + sum_turns * 1000 / 16) -
+                                 (small && splits == 1 && p.dw_small ? ONE_LAUNCH_NS : 0);
             if (best >= 0 && cost >= best) continue;
             best = cost;
             p.steps_per_split = steps;
@@ -1898,6 +1975,7 @@ static BwdPlan plan_bwd(int32_t B, int32_t D, int32_t C) {
     p.nCT = (int)(p.Cpad / 256);
     p.nDT = (int)(round_up(D, 256) / 256);
     p.steps_total = (int)(round_up(C, TILE_K) / TILE_K);
+    p.dw_small = dw_blocks(D, C, (B + TILE_K - 1) / TILE_K);
     dx_splits(p, B, D);
     p.dz_bytes = (size_t)p.Bpad * p.Cpad * 2;
     p.xt_bytes = (size_t)D * p.Bpad * 2;
@@ -2007,10 +2085,10 @@ static int static_scratch(void** out) {
 // When enabled, every kernel launch is bracketed by a pair of events recorded on the launch stream.
 // The pairs come from a pool created by ws_profile_enable; when the pool is used up, launches go
 // untimed.  Not thread safe; meant for benchmarks.
-enum KernelId { KID_FWD = 0, KID_MERGE, KID_COMBINE, KID_MEAN, KID_DZ, KID_DX, KID_DW, KID_PREDICT, KID_TOP1, KID_TOP1_MERGE, KID_COUNT };
+enum KernelId { KID_FWD = 0, KID_MERGE, KID_COMBINE, KID_MEAN, KID_DZ, KID_DX, KID_DW, KID_PREDICT, KID_TOP1, KID_TOP1_MERGE, KID_DX_DW, KID_COUNT };
 static const char* const kKernelNames[KID_COUNT] = {"fwd_logits_stats", "merge_class_tiles", "combine_partials",
                                                     "mean_loss", "bwd_recompute_dz", "bwd_dx", "bwd_dw",
-                                                    "predict_probs", "top1_logits", "merge_top1"};
+                                                    "predict_probs", "top1_logits", "merge_top1", "bwd_dx_dw"};
 struct ProfState {
     bool on = false;
     bool paused = false;
@@ -2076,7 +2154,7 @@ size_t ws_fwd_workspace_bytes(int32_t B, int32_t D, int32_t C_shard) {
 size_t ws_bwd_workspace_bytes(int32_t B, int32_t D, int32_t C_shard) {
     if (!shape_ok(B, D, C_shard)) return 0;
     const BwdPlan p = plan_bwd(B, D, C_shard);
-    return p.dz_bytes + p.xt_bytes + p.dbp_bytes + p.parts_bytes;
+    return p.bytes();
 }
 
 // Argument checks of the forward call that do not concern the workspace.
@@ -2170,6 +2248,11 @@ int ws_combine_partials(const float* row_max, const float* row_sumexp, const flo
         !aligned(loss_rows, 4) || (loss_mean && !aligned(loss_mean, 4)))
         return WS_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (loss_mean && B <= COMBINE_MEAN_ROWS && S <= COMBINE_BATCH) {
+        WS_LAUNCH(KID_COMBINE, combine_mean_kernel, dim3(1), dim3(1024), s, row_max, row_sumexp, label_logit, S, B, shard_stride,
+                  logsumexp, loss_rows, loss_mean);
+        return launch_status();
+    }
     WS_LAUNCH(KID_COMBINE, combine_partials_kernel, dim3((B + 63) / 64), dim3(64), s, row_max, row_sumexp,
                        label_logit, S, B, shard_stride, logsumexp, loss_rows);
     if (loss_mean) WS_LAUNCH(KID_MEAN, mean_loss_kernel, dim3(1), dim3(1024), s, loss_rows, B, loss_mean);
@@ -2193,7 +2276,7 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     const BwdPlan p = plan_bwd(B, D, C_shard);
     if (!fits_32bit_offsets(p.Bpad, p.Cpad) || !fits_32bit_offsets(D, p.Bpad))
         return WS_ERR_SHAPE;
-    if (!workspace || workspace_bytes < p.dz_bytes + p.xt_bytes + p.dbp_bytes + p.parts_bytes) return WS_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < p.bytes()) return WS_ERR_WORKSPACE;
     if (!aligned(workspace, 16)) return WS_ERR_ALIGN;
     if (g_dw_trace != nullptr && (int64_t)p.nDT * p.nCT > g_dw_trace_tiles) return WS_ERR_WORKSPACE;
 
@@ -2210,6 +2293,7 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     a.bias = b_shard; a.labels = labels;
     a.B = B; a.D = D; a.C = C_shard; a.class_offset = class_offset;
     a.Bpad = (int)p.Bpad; a.nBT = p.nBT; a.nCT = p.nCT;
+    const bool one_launch = p.one_launch() && !sgd && g_dw_trace == nullptr;
     XtArgs xt;
     xt.XT = XT; xt.ldxt = p.Bpad;
     xt.n_blocks = (int)std::min<int64_t>(((B + 63) / 64) * (int64_t)(D / 64), SIDE_BLOCKS);
@@ -2242,10 +2326,13 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     x.out = direct ? dX_partial : parts;
     x.ldo = direct ? lddx : D;
     x.split_stride = (int64_t)B * D;
-    if (p.dx_small)
+    if (one_launch) {
+        // with dW, below
+    } else if (p.dx_small) {
         WS_LAUNCH(KID_DX, bwd_dx_block, dim3(xcd_grid((D / BLOCK) * ((B + BLOCK - 1) / BLOCK) * p.splits)), dim3(NTHREADS), s, x);
-    else
+    } else {
         WS_LAUNCH(KID_DX, bwd_dx, dim3(xcd_grid(p.nDT * p.nBT * p.splits)), dim3(NTHREADS), s, x);
+    }
     DwArgs w;
     w.XT = XT; w.ldxt = p.Bpad; w.dZ = dZ; w.ldz = p.Cpad;
     w.D = D; w.C = C_shard; w.B = B;
@@ -2261,7 +2348,13 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     f.sgd = sgd; f.lr = lr;
     f.first_block = w.plan.thin_first + w.plan.n_thin;
     f.n_blocks = (f.parts || f.db_part) ? SIDE_BLOCKS : 0;
-    if (g_dw_trace == nullptr && dw_blocks(D, C_shard, w.k_steps)) {
+    if (one_launch) {
+        const DxTail t = {dX_partial, lddx, accumulate_dx, xcd_grid((D / BLOCK) * ((B + BLOCK - 1) / BLOCK))};
+        f.parts = nullptr;
+        f.first_block = t.dw_first_block + xcd_grid((D / BLOCK) * ((C_shard + BLOCK - 1) / BLOCK));
+        f.n_blocks = f.db_part ? std::min((C_shard + NTHREADS - 1) / NTHREADS, SIDE_BLOCKS) : 0;
+        WS_LAUNCH(KID_DX_DW, bwd_dx_dw_block, dim3(f.first_block + f.n_blocks), dim3(NTHREADS), s, x, t, w, f);
+    } else if (g_dw_trace == nullptr && p.dw_small) {
         f.first_block = xcd_grid((D / BLOCK) * ((C_shard + BLOCK - 1) / BLOCK));
         WS_LAUNCH(KID_DW, bwd_dw_block, dim3(f.first_block + f.n_blocks), dim3(NTHREADS), s, w, f);
     } else if (g_dw_trace != nullptr) {

@@ -30,6 +30,8 @@ def H():
     (2300, 576, [64 * 19 + 1]),          # 324: 2 splits
     (1100, 1024, [64 * 3, 64 * 2 + 9]),  # 288: one split, the second shard added to the first
     (4500, 64, [130]),                   # 71, 3 k-steps
+    (300, 128, [500, 130]),              # in one launch with dW, the second shard added to the first
+    (90, 320, [64 * 16, 64 * 16 + 1]),   # 16 k-steps in one launch with dW, 17 in splits of their own
 ])
 def test_dx_splits(H, B, D, widths):
     C = sum(widths)

@@ -52,3 +52,26 @@ def test_combine_top1_groups_of_candidates(ws, S, B):
     ws.combine_top1(dv, dc, bv, bc)
     rv, rc = oracle.combine_top1(list(v.astype(np.float64)), list(c.astype(np.int64)))
     assert (bv.cpu().numpy() == rv).all() and (bc.cpu().numpy() == rc).all()
+
+
+@pytest.mark.parametrize("B", [1, 1023, 1025, 2048, 2049])
+@pytest.mark.parametrize("S", [1, 8, 9])
+def test_mean_in_the_combine_launch(B, S):
+    """Up to 2048 rows and 8 shards one workgroup does it all: rows bit for bit as without the mean, the mean within the
+    rounding of its B fp32 additions."""
+    import torch
+    from paper_2011_09208_amd import binding as ws
+    g = torch.Generator(device="cuda").manual_seed(B + S)
+    m, t = (torch.empty((S, B), device="cuda").normal_(0.0, 3.0, generator=g) for _ in range(2))
+    s = torch.empty((S, B), device="cuda").uniform_(1.0, 9.0, generator=g)
+    m[0, 0] = float("-inf")                                        # an empty shard
+    s[0, 0] = 0.0 if S > 1 else 1.0
+    if S == 1:
+        m[0, 0] = 0.0
+    out = [torch.empty(B, device="cuda") for _ in range(4)]
+    mean = torch.empty(1, device="cuda")
+    ws.combine_partials(m, s, t, out[0], out[1], None)
+    ws.combine_partials(m, s, t, out[2], out[3], mean)
+    assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
+    loss = out[1].double()
+    assert (mean.double() - loss.mean()).abs() <= 2.0 ** -24 * (12 + B / 1024) * loss.abs().mean()
