@@ -139,4 +139,80 @@ __device__ __forceinline__ void block_rows_f32(f32x4 (&out)[2], const block_acc_
     }
 }
 
+// ---- logits ---------------------------------------------------------------------------------------------
+// 64 classes (M, rows of A) x 64 batch rows (N, rows of B), both k-contiguous.  Eight waves: 2 (M) x 4 (N), each 32 classes x 16
+// rows and the whole contraction, so that a logit's products are added in the order of the wide tiles.
+typedef f32x4 block_logits_t[2];
+
+// acc[x][v] is class 32 * wm + 16 * x + 4 * g + v of row 16 * wn + i of the tile (wave 4 * wm + wn, lane 16 * g + i).  All 512
+// threads call it together; ends with a workgroup barrier.
+__device__ __forceinline__ void block_logits(block_logits_t& acc, const Operand& A, const Operand& Bop, int m0, int n0, int k_steps,
+                                             char* lds) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3, i = lane & 15, g = lane >> 4;
+    const int last = k_steps - 1;
+    // wave w loads rows 8 w .. + 7 of either operand: one load of 1 KiB each
+    const int row = 8 * wave + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
+    const uint32_t a_lane = ((uint32_t)(m0 + row) * A.ld + (uint32_t)(8 * chunk)) * 2u;
+    const uint32_t b_lane = ((uint32_t)(n0 + row) * Bop.ld + (uint32_t)(8 * chunk)) * 2u;
+    const uint32_t lds_wave = lds_offset(lds) + 1024u * (uint32_t)wave;
+    auto load = [&](int step, int stage) {
+        load_to_lds(A, a_lane, (uint32_t)step * 128u, lds_wave + (uint32_t)stage);
+        load_to_lds(Bop, b_lane, (uint32_t)step * 128u, lds_wave + (uint32_t)stage + BLOCK_OPERAND_BYTES);
+    };
+    int a_frag[2], b_frag[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int at = i * 128 + (((4 * s + g) ^ (i >> 1)) << 4);
+        a_frag[s] = 32 * wm * 128 + at;
+        b_frag[s] = BLOCK_OPERAND_BYTES + 16 * wn * 128 + at;
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x) acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < BLOCK_STAGES - 1 && j <= last; ++j) load(j, j * BLOCK_STAGE_BYTES);
+    int cur = 0, nxt = (BLOCK_STAGES - 1) * BLOCK_STAGE_BYTES;        // stages of k-steps j and j + 4
+    for (int j = 0; j <= last; ++j) {
+        // k-steps j + 1 .. j + 3 may still be on their way
+        if (j + 3 <= last) wait_counts<6, NO_LG_WAIT>();
+        else if (j + 2 <= last) wait_counts<4, NO_LG_WAIT>();
+        else if (j + 1 <= last) wait_counts<2, NO_LG_WAIT>();
+        else wait_counts<0, NO_LG_WAIT>();
+        raw_barrier();                                   // every wave has read k-step j - 1, whose stage is refilled
+        if (j + BLOCK_STAGES - 1 <= last) load(j + BLOCK_STAGES - 1, nxt);
+        bf16x8 af[2][2], bf[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            bf[s] = *reinterpret_cast<const bf16x8*>(lds + (b_frag[s] + cur));
+#pragma unroll
+            for (int x = 0; x < 2; ++x) af[x][s] = *reinterpret_cast<const bf16x8*>(lds + (a_frag[s] + cur) + x * 2048);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[x][s], bf[s], acc[x], 0, 0, 0);
+        cur += BLOCK_STAGE_BYTES;
+        if (cur == BLOCK_LDS_BYTES) cur = 0;
+        nxt += BLOCK_STAGE_BYTES;
+        if (nxt == BLOCK_LDS_BYTES) nxt = 0;
+    }
+    wait_counts<NO_VM_WAIT, 0>();
+    raw_barrier();
+}
+
+// The tile as bf16 [row][class]: 16-byte chunk tid % 8 of row tid / 8.  Through LDS as in block_rows_bf16.
+__device__ __forceinline__ u32x4 block_logits_rows(const block_logits_t& acc, char* lds) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), i = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const int n = 16 * (wave & 3) + i, slot = (32 * (wave >> 2) + 16 * x + 4 * g) >> 2;
+        *reinterpret_cast<u32x2*>(lds + n * 128 + ((slot ^ (n & 15)) << 3)) = u32x2{pack_bf16(acc[x][0], acc[x][1]), pack_bf16(acc[x][2], acc[x][3])};
+    }
+    wait_counts<NO_VM_WAIT, 0>();
+    raw_barrier();
+    const int n = tid >> 3, c = tid & 7;
+    u32x4 v = *reinterpret_cast<const u32x4*>(lds + n * 128 + ((c ^ ((n & 15) >> 1)) << 4));
+    return n & 1 ? __builtin_shufflevector(v, v, 2, 3, 0, 1) : v;
+}
+
 }  // namespace ws

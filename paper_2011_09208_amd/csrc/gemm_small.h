@@ -1,34 +1,33 @@
-// Logits of small batches (up to 64 rows, up to 2048 features), bound by reading W once.
+// Logits of small batches (up to 32 rows, up to 2048 features), bound by reading W once.
 //
 // A 256-row tile (gemm_core.h) computes 256 rows whatever the batch, and 256 classes per workgroup leave most of the
 // chip idle on a narrow shard.  Here the classes are dealt out evenly, one range per compute unit, walked 32 classes at
 // a time.  The waves of a workgroup share out the contraction (wave w the k-steps w, w + WAVES, ..) and keep their part of
 // X in registers for the whole range, so that the loop reads nothing but W: 128 KiB per 32 classes at 2048 features, all
 // of it in flight while the waves' partial sums of the 32 classes before meet in LDS.  One barrier per 32 classes.
-// (With X read again for every 32 or 64 classes, W of 100 000 x 2048: 76 us for 16 rows, 113 for 32, 137 for 64.)
+// (With X read again for every 32 or 64 classes, W of 100 000 x 2048: 76 us for 16 rows, 113 for 32.)
 #pragma once
 #include "gemm_core.h"
 
 namespace ws {
 
-constexpr int SMALL_MAX_ROWS = 64;
+constexpr int SMALL_MAX_ROWS = 32;
 constexpr int SMALL_MAX_STEPS = 32;          // k-steps of X that the registers of a workgroup hold
 constexpr int SMALL_C = 32;                  // classes at a time
 constexpr int SMALL_PITCH = SMALL_C + 4;     // floats per row of a partial sum
 
-// NB = 16-row blocks of the batch (1, 2 or 4).  The finished logits are dealt out CPT classes of one row per thread,
+// NB = 16-row blocks of the batch (1 or 2).  The finished logits are dealt out CPT classes of one row per thread,
 // the TPR threads of a row side by side in one wave.
 template <int NB> struct SmallShape {
     static constexpr int ROWS = 16 * NB;
-    static constexpr int WAVES = NB == 4 ? 4 : 8;            // 64 rows of X take 256 registers of four waves
+    static constexpr int WAVES = 8;
     static constexpr int THREADS = 64 * WAVES;
     static constexpr int STEPS = SMALL_MAX_STEPS / WAVES;    // k-steps per wave
-    static constexpr int CPT = SMALL_C * ROWS / THREADS;     // classes per thread: 1, 2 or 8
-    static constexpr int TPR = SMALL_C / CPT;                // threads per row: 32, 16 or 4
+    static constexpr int CPT = SMALL_C * ROWS / THREADS;     // classes per thread: 1 or 2
+    static constexpr int TPR = SMALL_C / CPT;                // threads per row: 32 or 16
     static constexpr int SLOT_FLOATS = ROWS * SMALL_PITCH;
     static constexpr int LDS_FLOATS = 2 * WAVES * SLOT_FLOATS;
-    // Shortest range: one partial result per range, and the workspace has room for one of 64 rows per 64 classes
-    static constexpr int MIN_RANGE = NB == 4 ? 64 : 32;
+    static constexpr int MIN_RANGE = 32;
 };
 constexpr int SMALL_MAX_RANGES = 256;        // one per compute unit
 

@@ -10,7 +10,8 @@
 //                      write X^T for the dW contraction
 //   predict_probs      softmax probabilities of the shard's classes, exp(z - lse), bf16
 //   top1_logits        the shard's arg-max class and its logit per row (+ merge_top1, also used across shards)
-//   *_small            the logits kernels for up to 64 rows (gemm_small.h; small_batch on the host)
+//   *_small            the logits kernels for up to 32 rows (gemm_small.h; small_batch on the host)
+//   *_block            the logits, dX and dW of small layers in 64 x 64 tiles (gemm_block.h; logits_blocks, dx_splits, dw_blocks)
 //   bwd_dx             dX_partial = dz . W_s, split along the class contraction; partial sums
 //   bwd_dw             dW_s = dz^T . X; its surplus workgroups sum the split-K partials of dX
 //                      (optionally accumulating into the caller's dX) and the db partials
@@ -1254,7 +1255,7 @@ __global__ __launch_bounds__(64) void merge_top1_few(const float* __restrict__ v
 }
 
 // ---- small batches --------------------------------------------------------------------------------
-// The logits kernels for up to 64 rows (gemm_small.h): workgroup w takes the classes [w * range, (w + 1) * range) and
+// The logits kernels for up to 32 rows (gemm_small.h): workgroup w takes the classes [w * range, (w + 1) * range) and
 // reports one partial result per row.
 // Bound by reading W.  W of 100 000 x 2048, B = 1, arg-max: 87 us on the wide tiles, 71 here (5.8 TB/s); W of 12 500 x 2048,
 // B = 32: statistics 31.5 and 14.8 us, probabilities 37.4 and 15.2 (224 of 256 units have work, turns of 32 and 24 classes).
@@ -1314,8 +1315,8 @@ __device__ __forceinline__ void small_store(uint16_t* out, const float (&v)[N], 
 #pragma unroll
         for (int e = 0; e < N / 2; ++e) pk[e] = pack_bf16(v[2 * e], v[2 * e + 1]);
         if (left >= N) {
-            if constexpr (N == 8) *reinterpret_cast<u32x4*>(out) = u32x4{pk[0], pk[1], pk[2], pk[3]};
-            else *reinterpret_cast<uint32_t*>(out) = pk[0];
+            static_assert(N == 2, "");
+            *reinterpret_cast<uint32_t*>(out) = pk[0];
             return;
         }
     }
@@ -1403,6 +1404,185 @@ __global__ __launch_bounds__(SmallShape<NB>::THREADS) void top1_small(FcArgs a, 
     if (j == 0) {
         part_val[(int)blockIdx.x * S::ROWS + row] = best;
         part_cls[(int)blockIdx.x * S::ROWS + row] = cls;
+    }
+}
+
+// ---- small layers ---------------------------------------------------------------------------------
+// The logits kernels in tiles of 64 classes x 64 rows (gemm_block.h).  Workgroups are numbered row blocks fastest.
+struct LogitsBlock {
+    int cb, rb, c0, row;                 // class and row block; the lane's first class (4 * g of M tile 0), its row
+    int wave, g, i;
+    __device__ __forceinline__ explicit LogitsBlock(const FcArgs& a) {
+        const int nRB = (a.B + BLOCK - 1) / BLOCK, tile = xcd_logical_tile(nRB * ((a.C + BLOCK - 1) / BLOCK));
+        cb = tile < 0 ? -1 : tile / nRB;
+        rb = tile - cb * nRB;
+        const int lane = threadIdx.x & 63;
+        wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        g = lane >> 4;
+        i = lane & 15;
+        c0 = cb * BLOCK + 32 * (wave >> 2) + 4 * g;
+        row = rb * BLOCK + 16 * (wave & 3) + i;
+    }
+    __device__ __forceinline__ int cls(int x, int v) const { return c0 + 16 * x + v; }
+    // z: bias added, classes beyond the shard -inf
+    __device__ __forceinline__ void logits(block_logits_t& z, const FcArgs& a, char* lds) const {
+        float b[2][4];                                   // on their way during the main loop
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) b[x][v] = a.bias != nullptr && cls(x, v) < a.C ? a.bias[cls(x, v)] : 0.0f;
+        block_logits(z, make_operand(a.W, a.ldw, a.C, a.D), make_operand(a.X, a.ldx, a.B, a.D), cb * BLOCK, rb * BLOCK, a.D / TILE_K, lds);
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) z[x][v] = cls(x, v) < a.C ? (a.bias != nullptr ? z[x][v] + b[x][v] : z[x][v]) : NEG_INF;
+    }
+};
+
+__global__ __launch_bounds__(NTHREADS, 4) void fwd_stats_block(FcArgs a, int pitch, float* __restrict__ part_max,
+                                                               float* __restrict__ part_sum, float* __restrict__ label_logit) {
+    __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
+    const LogitsBlock t(a);
+    if (t.cb < 0) return;
+    const bool row_ok = t.row < a.B;
+    int local = row_ok ? a.labels[t.row] - a.class_offset : -1;
+    const bool in_shard = local >= 0 && local < a.C;
+    block_logits_t z;
+    t.logits(z, a, lds);
+    float mx = NEG_INF, s = 0.0f;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) mx = fmaxf(mx, z[x][v]);
+    const float shift = mx == NEG_INF ? 0.0f : -mx * LOG2E;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            s += __builtin_amdgcn_exp2f(fmaf(z[x][v], LOG2E, shift));
+            if (in_shard && local == t.cls(x, v)) label_logit[t.row] = z[x][v];
+        }
+    if (t.cb == 0 && t.wave < 4 && t.g == 0 && row_ok && !in_shard) label_logit[t.row] = 0.0f;
+    merge_ms(mx, s, lane_xor(mx, 16), lane_xor(s, 16));
+    merge_ms(mx, s, lane_xor(mx, 32), lane_xor(s, 32));
+    float* red = reinterpret_cast<float*>(lds);          // [max, sum][64 rows] of the upper 32 classes
+    const int r = 16 * (t.wave & 3) + t.i;
+    if (t.wave >= 4 && t.g == 0) {
+        red[r] = mx;
+        red[BLOCK + r] = s;
+    }
+    __syncthreads();
+    if (t.wave < 4 && t.g == 0) {
+        merge_ms(mx, s, red[r], red[BLOCK + r]);
+        part_max[(int64_t)t.cb * pitch + t.row] = mx;
+        part_sum[(int64_t)t.cb * pitch + t.row] = s;
+    }
+}
+
+// dz of the batch's rows, up to whole k-steps of classes (zeros beyond the shard); one db partial per row block.
+__global__ __launch_bounds__(NTHREADS, 4) void dz_block(FcArgs a, const float* __restrict__ logsumexp, float grad_scale,
+                                                        uint16_t* __restrict__ dZ, int64_t ldz, float* __restrict__ db_part, XtArgs xt) {
+    __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
+    if ((int)blockIdx.x >= xt.first_block) {
+        transpose_x_tiles<NTHREADS>(a, xt, (int)blockIdx.x - xt.first_block, lds);
+        return;
+    }
+    const LogitsBlock t(a);
+    if (t.cb < 0) return;
+    const bool row_ok = t.row < a.B;
+    const float gs = row_ok ? grad_scale : 0.0f, lse = row_ok ? logsumexp[t.row] : 0.0f;
+    const int local = row_ok ? a.labels[t.row] - a.class_offset : -1;
+    block_logits_t z;
+    t.logits(z, a, lds);
+    const float shift = __log2f(fabsf(gs)) - lse * LOG2E;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float d = __builtin_amdgcn_exp2f(fmaf(z[x][v], LOG2E, shift));
+            if (grad_scale < 0.0f) d = -d;
+            z[x][v] = d - (local == t.cls(x, v) && t.cls(x, v) < a.C ? gs : 0.0f);
+        }
+    float* red = reinterpret_cast<float*>(lds + BLOCK_TILE_OFFSET);        // [4 row quarters][64 classes]
+    if (db_part != nullptr) {
+        float val[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) val[e] = z[e >> 2][e & 3];
+        exchange_half<4, 8>(val, t.i);
+        exchange_half<2, 4>(val, t.i);
+        exchange_half<1, 2>(val, t.i);
+        val[0] += lane_xor(val[0], 1);
+        if ((t.i & 1) == 0) {                            // lane i holds register i / 2
+            const int e = t.i >> 1;
+            red[(t.wave & 3) * BLOCK + 32 * (t.wave >> 2) + 16 * (e >> 2) + 4 * t.g + (e & 3)] = val[0];
+        }
+    }
+    const u32x4 out = block_logits_rows(z, lds);         // with a barrier behind the writes to red
+    const int n = t.rb * BLOCK + ((int)threadIdx.x >> 3);
+    if (n < a.B) *reinterpret_cast<u32x4*>(dZ + (int64_t)n * ldz + t.cb * BLOCK + 8 * ((int)threadIdx.x & 7)) = out;
+    if (db_part != nullptr && (int)threadIdx.x < BLOCK) {
+        float s = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s += red[q * BLOCK + threadIdx.x];
+        db_part[(int64_t)t.rb * ldz + t.cb * BLOCK + threadIdx.x] = s;
+    }
+}
+
+__global__ __launch_bounds__(NTHREADS, 4) void predict_block(FcArgs a, const float* __restrict__ logsumexp, uint16_t* __restrict__ P,
+                                                             int64_t ldp) {
+    __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
+    const LogitsBlock t(a);
+    if (t.cb < 0) return;
+    const float shift = t.row < a.B ? -logsumexp[t.row] * LOG2E : 0.0f;
+    block_logits_t z;
+    t.logits(z, a, lds);
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) z[x][v] = __builtin_amdgcn_exp2f(fmaf(z[x][v], LOG2E, shift));
+    const u32x4 out = block_logits_rows(z, lds);
+    const int n = t.rb * BLOCK + ((int)threadIdx.x >> 3), c = t.cb * BLOCK + 8 * ((int)threadIdx.x & 7);
+    if (n >= a.B) return;
+    uint16_t* o = P + (int64_t)n * ldp + c;
+    if (c + 8 <= a.C) {
+        *reinterpret_cast<u32x4*>(o) = out;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (c + e < a.C) o[e] = (uint16_t)(out[e >> 1] >> (16 * (e & 1)));
+    }
+}
+
+__global__ __launch_bounds__(NTHREADS, 4) void top1_block(FcArgs a, int pitch, float* __restrict__ part_val, int* __restrict__ part_cls) {
+    __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
+    const LogitsBlock t(a);
+    if (t.cb < 0) return;
+    block_logits_t z;
+    t.logits(z, a, lds);
+    float best = NEG_INF;
+    int cls = INT_MAX;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (z[x][v] > best) {                        // a lane's classes come in increasing order
+                best = z[x][v];
+                cls = t.cls(x, v);
+            }
+    better_of(best, cls, lane_xor(best, 16), __shfl_xor(cls, 16, 64));
+    better_of(best, cls, lane_xor(best, 32), __shfl_xor(cls, 32, 64));
+    float* red_v = reinterpret_cast<float*>(lds);        // of the upper 32 classes
+    int* red_c = reinterpret_cast<int*>(red_v + BLOCK);
+    const int r = 16 * (t.wave & 3) + t.i;
+    if (t.wave >= 4 && t.g == 0) {
+        red_v[r] = best;
+        red_c[r] = cls;
+    }
+    __syncthreads();
+    if (t.wave < 4 && t.g == 0) {
+        better_of(best, cls, red_v[r], red_c[r]);
+        part_val[(int64_t)t.cb * pitch + t.row] = best;
+        part_cls[(int64_t)t.cb * pitch + t.row] = cls;
     }
 }
 
@@ -1878,43 +2058,45 @@ static const int SIDE_BLOCKS = 128;
 struct SmallPlan {
     int rows, range, ranges, threads;
     SmallPlan(int32_t B, int32_t C) {
-        rows = B <= 16 ? 16 : B <= 32 ? 32 : 64;
-        threads = rows == 64 ? SmallShape<4>::THREADS : SmallShape<2>::THREADS;
+        rows = B <= 16 ? 16 : 32;
+        threads = SmallShape<2>::THREADS;
         const int even = (int)round_up((C + SMALL_MAX_RANGES - 1) / SMALL_MAX_RANGES, 8);   // whole 16-byte stores
-        range = std::max(even, rows == 64 ? SmallShape<4>::MIN_RANGE : SmallShape<2>::MIN_RANGE);
+        range = std::max(even, SmallShape<2>::MIN_RANGE);
         ranges = (C + range - 1) / range;
     }
 };
-// Whether a call takes them instead of the 256 x 256 and 256 x 64 tiles.  A workgroup's turns of 32 classes follow each
-// other, so wide shards take longer here, while the tiles take the same time until they fill another round of the 256 units.
-// Measured over 11 feature and 20 class counts up to 125 000, us of a call on the tiles and here:
-//   up to 16 rows: faster everywhere (forward, C = 14 000, D = 2048: 39 and 17; C = 125 000, D = 64: 18 and 13).
-//   up to 32: forward and arg-max of the same kind; probabilities of one or two k-steps only up to 7 turns per round of tiles
-//     (B = 32, D = 64: C = 40 000: 7.7 and 6.5, 65 536: 7.6 and 9.2, 125 000: 13.7 and 16.5).
-//   up to 64 (one wave per SIMD, half as many threads to share a turn): the step where W has a size that a few dozen tiles do
-//     not read quickly, up to 3 turns, or 4 of many features (forward + backward, B = 64: C = 14 000, D = 512: 16 + 57 and 12 + 56,
-//     D = 64: 8.3 + 79 and 9.3 + 81; C = 9000, D = 2048: 28 + 61 and 24 + 57; C = 3000: 23 + 42 and 23 + 46; C = 28 000, D = 512:
-//     18 + 65 and 17 + 70), and where the tiles have a second, thin round (C = 80 000, D = 2048: 92 + 250 and 75 + 233);
-//     probabilities and arg-max, whose tiles have no thin round, as long as the turns are few (D = 512, probabilities:
-//     C = 14 000: 14.7 and 8.8, 32 768: 15.4 and 14.3, 65 536: 17 and 25, 80 000: 30 and 29).
+// Whether a call takes them: up to 16 rows always (forward, us, 256-wide tiles and here: C = 14 000, D = 2048: 39 and 17; arg-max, 64 x 64
+// tiles and here: B = 1, D = 2048, C = 4000: 13.3 and 9.9, C = 70 000: 52.4 and 50.7).  Up to 32 where a workgroup has one turn of
+// 32 classes (forward + dz, 64 x 64 tiles and here: B = 24, D = 2048, C = 4000: 12.9 + 13.2 and 12.0 + 12.1; C = 16 000: 13.9 + 14.9 and
+// 17.5 + 18.3; B = 32, D = 256, C = 50 000: 11.5 + 12.2 and 12.4 + 17.3), and the arg-max again where it has four, whose 64 x 64 tiles leave four times
+// as many candidates to merge (B = 24, D = 1024: C = 16 000: 10.9 and 12.0, C = 33 000: 20.3 and 18.9).
 // The forward and the backward call of a shard decide alike: the backward call's logits are the forward call's.
 enum SmallUse { SMALL_STEP, SMALL_PROBS, SMALL_TOP1 };
 static bool small_batch(int32_t B, int32_t D, int32_t C, SmallUse use) {
     if (B > SMALL_MAX_ROWS || D > SMALL_MAX_STEPS * TILE_K) return false;
-    const SmallPlan p(B, C);
-    const int tiles = (C + TILE_M - 1) / TILE_M, rounds = (tiles + 255) / 256, turns = (p.range + SMALL_C - 1) / SMALL_C;
-    if (p.rows <= 16) return true;
-    if (p.rows == 32) return use != SMALL_PROBS || D > 2 * TILE_K || turns <= 7 * rounds;
-    if (use != SMALL_STEP) return turns <= rounds * (D < 256 ? 3 : rounds == 1 ? 4 : 5);
-    if (tiles > 256) return tiles <= 256 + 64 && D >= 768;
-    return C > 6144 && turns <= (D < 1536 ? 3 : 4) && (int64_t)C * D >= 4200000;
+    return B <= 16 || C <= 32 * SMALL_MAX_RANGES || (use == SMALL_TOP1 && C > 128 * SMALL_MAX_RANGES);
 }
 #define WS_LAUNCH_SMALL(kid, name, plan, grid, stream, ...)                                                   \
     do {                                                                                                      \
         if ((plan).rows == 16) WS_LAUNCH(kid, name<1>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__); \
-        else if ((plan).rows == 32) WS_LAUNCH(kid, name<2>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__); \
-        else WS_LAUNCH(kid, name<4>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__);                  \
+        else WS_LAUNCH(kid, name<2>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__);                  \
     } while (0)
+// Small layers, and batches of up to 64 rows that are not small: the logits kernels in 64 x 64 tiles.  The wide tiles need all of a
+// compute unit for 256 rows, the thin ones for 256 classes, and either a barrier's wait per k-step; two of these share one.  us of forward + dz
+// on wide or thin tiles and here, by their number: 16 (B = 40, D = 1408, C = 1000) 17.4 + 18.4 and 10.6 + 10.8; 188 (B = 100, D = 2048, C =
+// 6000) 22.9 + 24.4 and 13.0 + 13.6; 376 (B = 200, C = 6000) 22.5 + 24.4 and 16.9 + 16.9; 470 (B = 100, D = 256, C = 15 000) 11.2 + 11.4 and
+// 7.8 + 9.0; 553 (B = 400, D = 256, C = 5000) 9.7 + 11.8 and 10.3 + 12.2; 611 (B = 800, D = 1408, C = 3000) 18.3 + 20.0 and 20.4 + 20.3.
+// Probabilities and arg-max, which have neither thin tiles nor lists: 782 (B = 80, D = 2048, C = 25 000) 38.4, 40.2 and 25.9, 29.5; 939 (B =
+// 150, D = 256, C = 20 000) 12.2, 13.4 and 8.9, 12.4; 1316 (B = 400, D = 1024, C = 12 000) 24.1, 25.0 and 23.6, 26.6.  Up to 64 rows, forward +
+// dz: 125 (D = 4096, C = 8000) 45.2 + 46.8 and 19.8 + 20.2; 1094 (D = 1024, C = 70 000) 38.9 + 53.1 and 27.5 + 29.5; 1954 (D = 64, C = 125 000)
+// 18.6 + 29.6 and 15.2 + 17.2, D = 2048: 105.7 + 107.9 and 95.3 + 107.5, but D = 3072: 141.9 + 154.6 and 147.5 + 162.7, where two full
+// rounds of wide tiles read W as fast.  Arg-max of the same: D = 1024: 50.2 and 46.4, D = 256: 25.8 and 25.2, but D = 64: 16.6 and 19.8,
+// four times the candidates to merge.
+static bool logits_blocks(int32_t B, int32_t D, int32_t C, SmallUse use) {
+    const int64_t rows = (B + BLOCK - 1) / BLOCK, tiles = rows * ((C + BLOCK - 1) / BLOCK);
+    if (rows == 1) return tiles <= 1280 || (D <= 2048 && (use != SMALL_TOP1 || D >= 256));
+    return tiles <= (use == SMALL_STEP ? 512 : 1024);
+}
 
 struct BwdPlan {
     int64_t Bpad, Cpad;
@@ -2035,13 +2217,16 @@ static void set_order(FcArgs& a) {
 }
 static int list_grid(const RangePlan& p, int nBT) { return xcd_grid(p.ranges * nBT); }
 
-// The forward call's partial results: one per class tile or range, and row.
-static size_t fwd_bytes(int32_t B, int32_t parts) { return (size_t)2 * parts * round_up(B, 256) * sizeof(float); }
-static int class_tiles(int32_t C) { return (int)(round_up(C, 256) / 256); }
-static int fwd_parts(int32_t B, int32_t D, int32_t C) {
-    const int nBT = (int)(round_up(B, 256) / 256), nCT = class_tiles(C);
+// The forward call's partial results: one per class tile, range or class block, and row.  `least`: what any call needs.
+static size_t parts_bytes(int64_t parts, int64_t rows) { return (size_t)(2 * parts * rows) * sizeof(float); }
+static size_t least_fwd_bytes(int32_t B, int32_t C) { return parts_bytes(round_up(C, 256) / 256, round_up(B, 256)); }
+static size_t block_parts_bytes(int32_t B, int32_t C) { return parts_bytes(round_up(C, BLOCK) / BLOCK, round_up(B, BLOCK)); }
+static size_t fwd_bytes(int32_t B, int32_t D, int32_t C) {
+    const size_t least = least_fwd_bytes(B, C);
+    const int nBT = (int)(round_up(B, 256) / 256), nCT = (int)(round_up(C, 256) / 256);
+    if (logits_blocks(B, D, C, SMALL_STEP) || logits_blocks(B, D, C, SMALL_TOP1)) return std::max(least, block_parts_bytes(B, C));
     const RangePlan p = plan_ranges(D, C, nBT);
-    return logits_list(p, nBT, nCT, D / TILE_K) ? std::max(nCT, p.ranges) : nCT;
+    return logits_list(p, nBT, nCT, D / TILE_K) ? std::max(least, parts_bytes(p.ranges, round_up(B, 256))) : least;
 }
 
 static int check_fc_common(const void* X, int64_t ldx, const void* W, int64_t ldw, const float* bias,
@@ -2148,7 +2333,7 @@ const char* ws_status_string(int status) {
 int ws_version(void) { return 1217; }
 
 size_t ws_fwd_workspace_bytes(int32_t B, int32_t D, int32_t C_shard) {
-    return shape_ok(B, D, C_shard) ? fwd_bytes(B, fwd_parts(B, D, C_shard)) : 0;
+    return shape_ok(B, D, C_shard) ? fwd_bytes(B, D, C_shard) : 0;
 }
 
 size_t ws_bwd_workspace_bytes(int32_t B, int32_t D, int32_t C_shard) {
@@ -2194,7 +2379,13 @@ static int launch_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t l
     } else {
         set_order(a);
         // a workspace of one partial result per class tile is enough for the tiles
-        if (a.on_lists && workspace_bytes >= fwd_bytes(B, a.ranges.ranges)) {
+        if (logits_blocks(B, D, C_shard, SMALL_STEP) && workspace_bytes >= block_parts_bytes(B, C_shard)) {
+            parts = (C_shard + BLOCK - 1) / BLOCK;
+            pitch = (int)round_up(B, BLOCK);
+            part_sum = part_max + (size_t)parts * pitch;
+            WS_LAUNCH(KID_FWD, fwd_stats_block, dim3(xcd_grid(parts * (pitch / BLOCK))), dim3(NTHREADS), s, a, pitch, part_max, part_sum,
+                      label_logit);
+        } else if (a.on_lists && workspace_bytes >= parts_bytes(a.ranges.ranges, a.Bpad)) {
             parts = a.ranges.ranges;
             part_sum = part_max + (size_t)parts * pitch;
             WS_LAUNCH(KID_FWD, fwd_logits_list, dim3(list_grid(a.ranges, a.nBT)), dim3(NTHREADS), s,
@@ -2217,7 +2408,7 @@ int ws_split_fc_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw
     int st = check_fwd(X, ldx, W_shard, ldw, b_shard, labels, B, D, C_shard, class_offset, row_max, row_sumexp,
                        label_logit);
     if (st != WS_OK) return st;
-    if (!workspace || workspace_bytes < fwd_bytes(B, class_tiles(C_shard))) return WS_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < least_fwd_bytes(B, C_shard)) return WS_ERR_WORKSPACE;
     if (!aligned(workspace, 16)) return WS_ERR_ALIGN;
     return launch_fwd(X, ldx, W_shard, ldw, b_shard, labels, B, D, C_shard, class_offset, row_max, row_sumexp,
                       label_logit, workspace, workspace_bytes, stream);
@@ -2229,7 +2420,7 @@ int ws_split_fc_fwd_static(const void* X, int64_t ldx, const void* W_shard, int6
     int st = check_fwd(X, ldx, W_shard, ldw, b_shard, labels, B, D, C_shard, class_offset, row_max, row_sumexp,
                        label_logit);
     if (st != WS_OK) return st;
-    if (fwd_bytes(B, class_tiles(C_shard)) > (size_t)WS_STATIC_SCRATCH_BYTES) return WS_ERR_LIMIT;
+    if (least_fwd_bytes(B, C_shard) > (size_t)WS_STATIC_SCRATCH_BYTES) return WS_ERR_LIMIT;
     void* ws_ptr = nullptr;
     st = static_scratch(&ws_ptr);
     if (st != WS_OK) return st;
@@ -2297,7 +2488,7 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     XtArgs xt;
     xt.XT = XT; xt.ldxt = p.Bpad;
     xt.n_blocks = (int)std::min<int64_t>(((B + 63) / 64) * (int64_t)(D / 64), SIDE_BLOCKS);
-    const bool small = small_batch(B, D, C_shard, SMALL_STEP);
+    const bool small = small_batch(B, D, C_shard, SMALL_STEP), blocks = !small && logits_blocks(B, D, C_shard, SMALL_STEP);
     if (small) {
         const SmallPlan sp(B, (int32_t)round_up(C_shard, TILE_K));
         xt.first_block = sp.ranges;
@@ -2305,7 +2496,11 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
                         db_shard ? db_part : nullptr, xt);
     } else {
         set_order(a);
-        if (a.on_lists) {
+        if (blocks) {
+            xt.first_block = xcd_grid(((C_shard + BLOCK - 1) / BLOCK) * ((B + BLOCK - 1) / BLOCK));
+            WS_LAUNCH(KID_DZ, dz_block, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s, a, logsumexp, grad_scale, dZ, p.Cpad,
+                      db_shard ? db_part : nullptr, xt);
+        } else if (a.on_lists) {
             xt.first_block = list_grid(a.ranges, a.nBT);
             WS_LAUNCH(KID_DZ, bwd_dz_list, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s,
                       (DzArgs{a, logsumexp, grad_scale, dZ, p.Cpad, db_shard ? db_part : nullptr, xt}));
@@ -2343,7 +2538,7 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     FinishArgs f;
     f.parts = direct ? nullptr : parts; f.splits = p.splits; f.split_stride = (int64_t)B * D;
     f.B = B; f.D = D; f.dX = dX_partial; f.lddx = lddx; f.accumulate = accumulate_dx;
-    f.db_part = db_shard ? db_part : nullptr; f.n_db_parts = small ? 1 : 4 * p.nBT; f.db_stride = p.Cpad;
+    f.db_part = db_shard ? db_part : nullptr; f.n_db_parts = small ? 1 : blocks ? (B + BLOCK - 1) / BLOCK : 4 * p.nBT; f.db_stride = p.Cpad;
     f.C = C_shard; f.db = db_shard;
     f.sgd = sgd; f.lr = lr;
     f.first_block = w.plan.thin_first + w.plan.n_thin;
@@ -2422,6 +2617,9 @@ int ws_split_fc_predict(const void* X, int64_t ldx, const void* W_shard, int64_t
     if (small_batch(B, D, C_shard, SMALL_PROBS)) {
         const SmallPlan p(B, C_shard);
         WS_LAUNCH_SMALL(KID_PREDICT, predict_small, p, p.ranges, s, a, p.range, logsumexp, static_cast<uint16_t*>(P), ldp);
+    } else if (logits_blocks(B, D, C_shard, SMALL_PROBS)) {
+        WS_LAUNCH(KID_PREDICT, predict_block, dim3(xcd_grid(((C_shard + BLOCK - 1) / BLOCK) * ((B + BLOCK - 1) / BLOCK))), dim3(NTHREADS), s,
+                  a, logsumexp, static_cast<uint16_t*>(P), ldp);
     } else {
         set_order(a);
         WS_LAUNCH(KID_PREDICT, predict_probs, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, logsumexp,
@@ -2440,7 +2638,7 @@ int ws_split_fc_top1(const void* X, int64_t ldx, const void* W_shard, int64_t ld
     if (class_offset < 0 || (int64_t)class_offset + C_shard > INT32_MAX) return WS_ERR_RANGE;
     if (!aligned(X, 16) || !aligned(W_shard, 16) || ldx % 8 || ldw % 8) return WS_ERR_ALIGN;
     if (!aligned(top_logit, 4) || !aligned(top_class, 4) || (b_shard && !aligned(b_shard, 4))) return WS_ERR_ALIGN;
-    if (!workspace || workspace_bytes < fwd_bytes(B, class_tiles(C_shard))) return WS_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < least_fwd_bytes(B, C_shard)) return WS_ERR_WORKSPACE;
     if (!aligned(workspace, 16)) return WS_ERR_ALIGN;
     FcArgs a;
     a.last_tile_first = 0;
@@ -2460,6 +2658,11 @@ int ws_split_fc_top1(const void* X, int64_t ldx, const void* W_shard, int64_t ld
         parts = p.ranges;
         pitch = p.rows;
         WS_LAUNCH_SMALL(KID_TOP1, top1_small, p, p.ranges, s, a, p.range, part_val, part_cls);
+    } else if (logits_blocks(B, D, C_shard, SMALL_TOP1) && workspace_bytes >= block_parts_bytes(B, C_shard)) {
+        parts = (C_shard + BLOCK - 1) / BLOCK;
+        pitch = (int)round_up(B, BLOCK);
+        part_cls = reinterpret_cast<int*>(part_val + (size_t)parts * pitch);
+        WS_LAUNCH(KID_TOP1, top1_block, dim3(xcd_grid(parts * (pitch / BLOCK))), dim3(NTHREADS), s, a, pitch, part_val, part_cls);
     } else {
         set_order(a);
         WS_LAUNCH(KID_TOP1, top1_logits, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, part_val, part_cls);
