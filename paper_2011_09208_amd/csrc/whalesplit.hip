@@ -340,6 +340,18 @@ __device__ __forceinline__ int fresh_lane() {
     return lane;
 }
 
+// N stores that nothing is in range of: the waits of a list's first tile count the stores of a tile before.  The empty assembly keeps
+// them apart, alike as they are: the compiler made one of them, and the first waits let the tile's own loads pass for stores.
+template <int N>
+__device__ __forceinline__ void stores_without_effect(void* base) {
+    __amdgpu_buffer_rsrc_t none = __builtin_amdgcn_make_buffer_rsrc(base, 0, 0, 0x00020000);
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        __builtin_amdgcn_raw_buffer_store_b32(0u, none, 0, 0, 0);
+        asm volatile("" ::: "memory");
+    }
+}
+
 // What the epilogues of the list kernels share: the wave's classes and rows, and their logits.  Positions: unit_row plus 64 in
 // half 1, whatever the units of half 0.  Args begins with an FcArgs a.
 template <class Args>
@@ -986,10 +998,7 @@ struct DzEpilogue : LogitsEpilogue<DzArgs> {
         begin_tile(round);
         if (round != 0) return;
         load_rows(fresh_args<DzArgs>()->logsumexp);
-        // the waits of the first tile count the stores of a tile before: stores without effect
-        __amdgpu_buffer_rsrc_t none = __builtin_amdgcn_make_buffer_rsrc(fresh_args<DzArgs>()->dZ, 0, 0, 0x00020000);
-#pragma unroll
-        for (int n = 0; n < STORES; ++n) __builtin_amdgcn_raw_buffer_store_b32(0u, none, 0, 0, 0);
+        stores_without_effect<STORES>(fresh_args<DzArgs>()->dZ);
     }
     __device__ __forceinline__ void end(acc_t& acc, int, const int (&units)[2]) {
         const int lane = fresh_lane(), g = lane >> 4, jl = lane & 15;

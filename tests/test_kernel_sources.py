@@ -72,3 +72,22 @@ def test_no_kernel_spills_registers(tmp_path):
     spilling = {k: v["vgpr_spill_count"] for k, v in kernels.items()
                 if v["vgpr_spill_count"] != "0" or v["sgpr_spill_count"] != "0" or v["private_segment_fixed_size"] != "0"}
     assert not spilling, spilling
+
+
+OBJDUMP = os.path.join(os.path.dirname(READELF), "llvm-objdump")
+
+
+def test_stores_without_effect_are_not_merged(tmp_path):
+    """The list kernels' first waits count 16 stores per wave that are issued to be counted.  They are alike; merged into fewer, the
+    waits would let loads of the first tile pass for them and its first k-steps be read before they have arrived."""
+    if buildlib.is_stale():
+        buildlib.build()
+    kernel_notes(buildlib.LIB, tmp_path)                                            # writes the code objects
+    text = "".join(subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(p)], check=True, capture_output=True, text=True).stdout
+                   for p in tmp_path.glob("*.co"))
+    count = {}
+    for body in re.split(r"^[0-9a-f]+ <", text, flags=re.M)[1:]:
+        name = body.split(">", 1)[0]
+        if re.search("bwd_d[zw]_list", name):
+            count[name] = len(re.findall(r"\bbuffer_store_dword ", body))
+    assert count and all(n == 16 for n in count.values()), count
