@@ -2210,13 +2210,20 @@ static RangePlan plan_ranges(int32_t D, int32_t C, int nBT) {
 //     140 + 152 and 131 + 140; B = 8192, D = 1024, C = 50 000: 691 + 794 and 662 + 744; against a rest of five units, B = 256, D = 2048,
 //     C = 100 000: 120 + 121, dX 94.5 and 117 + 121, 99.0), except that long tiles over many rounds, where a workgroup that is
 //     done early takes the next tile, lose nothing (B = 4096, D = 2048, C = 37 500: 460 + 507 and 469 + 509; C = 12 500: 158.9 + 174.6
-//     and 159.2 + 177.4).
+//     and 159.2 + 177.4);
+//   behind one or two full rounds a tail that runs as thin tiles ends sooner than the lists' rests: one round from 3 k-steps on (288 tiles, B = 2057, D =
+//     832, C = 8132: 35.7 + 43.9 and 39.1 + 45.1; 264, B = 500, D = 2048: 68.1 + 74.7 and 73.1 + 79.4), two from 17 (531, B = 2057, D = 2048: 110 + 123
+//     and 115 + 131; but 528, 13 k-steps, B = 700: 58.0 + 69.6 and 56.5 + 67.3), or from 9 if it is longer than 32 (560, B = 4000, D = 832:
+//     58.2 + 70.6 and 63.0 + 76.0; 4 k-steps, B = 1000: 32.5 + 45.0 and 31.8 + 42.2).
 // Every way adds the products of a logit in the same order.
 static bool logits_list(const RangePlan& p, int nBT, int nCT, int k_steps) {
     const int64_t tiles = (int64_t)nBT * nCT;
     const int rest = p.per + (p.more > 0);
     if (tiles <= 64) return false;
     if (tiles <= 256) return p.full == 0 && rest <= MAX_UNITS / 2;
+    const int64_t tail = tiles % LIST_WGS;
+    if (tail > 0 && tail <= LOGITS_MAX_THIN_TAIL &&
+        (tiles < 2 * LIST_WGS ? k_steps > 2 : tiles < 3 * LIST_WGS && k_steps > (tail > LOGITS_MAX_THIN_TAIL / 2 ? 8 : 16))) return false;
     return k_steps <= 8 || (rest <= MAX_UNITS / 2 && (k_steps <= 16 || tiles <= 3 * LIST_WGS));
 }
 // How the logits of a call are cut, and with it the order of their sums.

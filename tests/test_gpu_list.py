@@ -16,6 +16,10 @@ SHAPES = [                               # B, D, C
     (513, 1088, 256 * 40),               # 3; 17 k-steps, rests of 3 and 4
     (600, 64, 256 * 170 + 33),           # 3; two whole tiles
     (700, 576, 256 * 86 + 65),           # 3; 9 k-steps, rests of one unit and none
+    (700, 576, 256 * 112 + 65),          # 3; 339 tiles: the same behind a whole one (of 264 the last 8 run as thin tiles)
+    (600, 640, 256 * 170 + 33),          # 3; 513 tiles, 10 k-steps: lists
+    (1000, 576, 256 * 136),              # 4; 544 and a tail of 32: lists
+    (1000, 576, 256 * 137),              # 548, one of 36: tiles
     (1000, 192, 256 * 17 + 1),           # 4; 72 tiles, 3 k-steps
     (1100, 128, 256 * 21 + 1),           # 5: a block of four and one
     (1400, 192, 256 * 13 - 100),         # 6
