@@ -11,7 +11,7 @@ PROBE_SRC = os.path.join(PKG, "csrc", "probe.hip")
 HOST_SRC = os.path.join(PKG, "csrc", "balance.cpp")
 DEPS = [SRC, BRIDGE_SRC, SP2_SRC, PROBE_SRC, HOST_SRC, os.path.join(PKG, "csrc", "gemm_core.h"), os.path.join(PKG, "csrc", "gemm_stream.h"),
         os.path.join(PKG, "csrc", "gemm_small.h"), os.path.join(PKG, "csrc", "gemm_block.h"),
-        os.path.join(PKG, "csrc", "gemm_tiles.h"),
+        os.path.join(PKG, "csrc", "gemm_tiles.h"), os.path.join(PKG, "csrc", "plan.h"),
         os.path.join(os.path.dirname(PKG), "include", "whalesplit.h")]
 LIB = os.path.join(PKG, "libwhalesplit.so")
 

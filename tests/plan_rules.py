@@ -1,0 +1,29 @@
+"""The library's rules (csrc/plan.h) as ctypes functions, compiled for the host alone.  Not collected by pytest (no test_ prefix)."""
+import ctypes
+import os
+import subprocess
+
+from paper_2011_09208_amd import buildlib
+
+PLAN = os.path.join(buildlib.PKG, "csrc", "plan.h")
+SHIM = """#include "%s"
+using namespace ws;
+extern "C" {
+size_t fwd_bytes_(int B, int D, int C) { return fwd_bytes(B, D, C); }
+size_t least_fwd_bytes_(int B, int C) { return least_fwd_bytes(B, C); }
+size_t bwd_bytes_(int B, int D, int C) { return plan_bwd(B, D, C).bytes(); }
+}
+"""
+
+
+def load(folder):
+    """Compiles the rules in `folder` and loads them."""
+    src, lib = os.path.join(folder, "rules.hip"), os.path.join(folder, "rules.so")
+    with open(src, "w") as f:
+        f.write(SHIM % PLAN)
+    subprocess.run([buildlib.HIPCC, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-Wno-unused-function",
+                    src, "-o", lib], check=True)
+    rules = ctypes.CDLL(lib)
+    for name in ("fwd_bytes_", "least_fwd_bytes_", "bwd_bytes_"):
+        getattr(rules, name).restype = ctypes.c_size_t
+    return rules
