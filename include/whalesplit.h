@@ -66,8 +66,9 @@ const char* ws_status_string(int status);
 /* Library version, major * 1000 + minor. */
 int ws_version(void);
 
-/* Bytes of scratch for ws_split_fc_fwd and this shape (0 on invalid shape).  The call also accepts a workspace of
- * 2 * ceil(C_shard / 256) * roundup(B, 256) floats where this is more, and may then be slower and sum in another order. */
+/* Bytes of scratch that the kernels of ws_split_fc_fwd and ws_split_fc_top1 want for this shape (0 on invalid shape).  The
+ * calls also accept a workspace of 2 * ceil(C_shard / 256) * roundup(B, 256) floats where this is more, and may then be slower
+ * and sum in another order. */
 size_t ws_fwd_workspace_bytes(int32_t B, int32_t D, int32_t C_shard);
 
 /* Forward call of one shard (Section 2.1 split matmul; Section 3.1.2 FC + Softmax
@@ -93,8 +94,9 @@ int ws_split_fc_fwd(const void* X, int64_t ldx,
 
 /* The forward call for callers that cannot allocate or pass a workspace: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and kernels as
- * ws_split_fc_fwd (bit-identical outputs), but the per-class-tile partials live in a fixed array built
- * into the library's device code instead of a caller workspace; the call allocates and frees nothing.
+ * ws_split_fc_fwd with a workspace of ws_fwd_workspace_bytes or more (bit-identical outputs), but the partial
+ * results live in a fixed array built into the library's device code instead of a caller workspace; the call
+ * allocates and frees nothing.
  *   Limit: 2 * ceil(C_shard / 256) * roundup(B, 256) floats <= WS_STATIC_SCRATCH_BYTES, else WS_ERR_LIMIT (checked on
  *   the host with the other arguments, before any HIP call).  16 MiB covers one shard of every workload
  *   this library is measured on (headline 3.2 MB; B = 8192 x 50 000 classes 12.8 MB).

@@ -83,9 +83,9 @@ struct SmallPlan {
     SmallPlan(int32_t B, int32_t C) {
         rows = B <= 16 ? 16 : 32;
         threads = SmallShape<2>::THREADS;
-        const int even = (int)round_up((C + SMALL_MAX_RANGES - 1) / SMALL_MAX_RANGES, 8);   // whole 16-byte stores
+        const int even = (int)round_up(round_up(C, SMALL_MAX_RANGES) / SMALL_MAX_RANGES, 8);   // whole 16-byte stores
         range = std::max(even, SmallShape<2>::MIN_RANGE);
-        ranges = (C + range - 1) / range;
+        ranges = (int)(round_up(C, range) / range);
     }
 };
 // Whether a call takes them: up to 16 rows always (forward, us, 256-wide tiles and here: C = 14 000, D = 2048: 39 and 17; arg-max, 64 x 64
@@ -111,7 +111,7 @@ static bool small_batch(int32_t B, int32_t D, int32_t C, SmallUse use) {
 // rounds of wide tiles read W as fast.  Arg-max of the same: D = 1024: 50.2 and 46.4, D = 256: 25.8 and 25.2, but D = 64: 16.6 and 19.8,
 // four times the candidates to merge.
 static bool logits_blocks(int32_t B, int32_t D, int32_t C, SmallUse use) {
-    const int64_t rows = (B + BLOCK - 1) / BLOCK, tiles = rows * ((C + BLOCK - 1) / BLOCK);
+    const int64_t rows = round_up(B, BLOCK) / BLOCK, tiles = rows * (round_up(C, BLOCK) / BLOCK);
     if (rows == 1) return tiles <= 1280 || (D <= 2048 && (use != SMALL_TOP1 || D >= 256));
     return tiles <= (use == SMALL_STEP ? 512 : 1024);
 }
@@ -188,7 +188,7 @@ static BwdPlan plan_bwd(int32_t B, int32_t D, int32_t C) {
 // cycles: a k-step of a whole tile is bound by its matrix instructions, one of a lower tile by the slots of its loads, too.
 constexpr int LIST_MAX_ITEMS = 4;
 static RangePlan plan_ranges(int32_t D, int32_t C, int nBT) {
-    const int units = (int)(2 * ((C + TILE_K - 1) / TILE_K)), k_steps = D / TILE_K;
+    const int units = (int)(2 * (round_up(C, TILE_K) / TILE_K)), k_steps = D / TILE_K;
     RangePlan best = {1, 0, 0, 0, 0, 0, 0};
     int64_t best_cost = -1;
     for (int m = 1; m <= LIST_MAX_ITEMS; ++m) {
@@ -237,16 +237,48 @@ static bool logits_list(const RangePlan& p, int nBT, int nCT, int k_steps) {
 }
 static int list_grid(const RangePlan& p, int nBT) { return xcd_grid(p.ranges * nBT); }
 
-// The forward call's partial results: one per class tile, range or class block, and row.  `least`: what any call needs.
-static size_t parts_bytes(int64_t parts, int64_t rows) { return (size_t)(2 * parts * rows) * sizeof(float); }
-static size_t least_fwd_bytes(int32_t B, int32_t C) { return parts_bytes(round_up(C, 256) / 256, round_up(B, 256)); }
-static size_t block_parts_bytes(int32_t B, int32_t C) { return parts_bytes(round_up(C, BLOCK) / BLOCK, round_up(B, BLOCK)); }
+// The kernels that compute the logits of a call, and the forward call's (the arg-max's) partial results: a pair of numbers for each
+// of `parts` groups of classes and `pitch` rows.
+enum LogitsWay { WAY_SMALL, WAY_BLOCKS, WAY_LISTS, WAY_TILES };
+struct LogitsPlan {
+    LogitsWay way;
+    int64_t parts, pitch;
+    RangePlan ranges;                    // of the lists; not set otherwise
+    size_t bytes() const { return (size_t)(2 * parts * pitch) * sizeof(float); }
+};
+// The wide tiles: what any call can do, and what it does with a workspace that its own kernels find too small.
+static LogitsPlan plan_wide(int32_t B, int32_t C) {
+    LogitsPlan p;
+    p.way = WAY_TILES;
+    p.parts = round_up(C, TILE_M) / TILE_M;
+    p.pitch = round_up(B, TILE_N);
+    return p;
+}
+static LogitsPlan plan_logits(int32_t B, int32_t D, int32_t C, SmallUse use) {
+    LogitsPlan p = plan_wide(B, C);
+    if (small_batch(B, D, C, use)) {
+        const SmallPlan s(B, C);
+        p.way = WAY_SMALL;
+        p.parts = s.ranges;
+        p.pitch = s.rows;
+    } else if (logits_blocks(B, D, C, use)) {
+        p.way = WAY_BLOCKS;
+        p.parts = round_up(C, BLOCK) / BLOCK;
+        p.pitch = round_up(B, BLOCK);
+    } else if (use == SMALL_STEP) {
+        const int nBT = (int)(p.pitch / TILE_N);
+        p.ranges = plan_ranges(D, C, nBT);
+        if (logits_list(p.ranges, nBT, (int)p.parts, D / TILE_K)) {
+            p.way = WAY_LISTS;
+            p.parts = p.ranges.ranges;
+        }
+    }
+    return p;
+}
+// The workspace that the forward call and the arg-max want, and the one that either does with.
+static size_t least_fwd_bytes(int32_t B, int32_t C) { return plan_wide(B, C).bytes(); }
 static size_t fwd_bytes(int32_t B, int32_t D, int32_t C) {
-    const size_t least = least_fwd_bytes(B, C);
-    const int nBT = (int)(round_up(B, 256) / 256), nCT = (int)(round_up(C, 256) / 256);
-    if (logits_blocks(B, D, C, SMALL_STEP) || logits_blocks(B, D, C, SMALL_TOP1)) return std::max(least, block_parts_bytes(B, C));
-    const RangePlan p = plan_ranges(D, C, nBT);
-    return logits_list(p, nBT, nCT, D / TILE_K) ? std::max(least, parts_bytes(p.ranges, round_up(B, 256))) : least;
+    return std::max({least_fwd_bytes(B, C), plan_logits(B, D, C, SMALL_STEP).bytes(), plan_logits(B, D, C, SMALL_TOP1).bytes()});
 }
 
 }  // namespace ws

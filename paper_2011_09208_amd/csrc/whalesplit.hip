@@ -2136,7 +2136,7 @@ static int check_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t ld
     return WS_OK;
 }
 
-// Launches of the forward call; `workspace` holds a partial result per class tile at least, 16-byte aligned.
+// Launches of the forward call; `workspace` holds least_fwd_bytes at least, 16-byte aligned.
 static int launch_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw, const float* b_shard,
                       const int32_t* labels, int32_t B, int32_t D, int32_t C_shard, int32_t class_offset,
                       float* row_max, float* row_sumexp, float* label_logit, void* workspace, size_t workspace_bytes,
@@ -2150,34 +2150,26 @@ static int launch_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t l
     a.Bpad = (int)round_up(B, 256);
     a.nBT = a.Bpad / 256;
     a.nCT = (int)(round_up(C_shard, 256) / 256);
+    LogitsPlan p = plan_logits(B, D, C_shard, SMALL_STEP);
+    if (workspace_bytes < p.bytes()) p = plan_wide(B, C_shard);
     float* part_max = static_cast<float*>(workspace);
-    float* part_sum = part_max + (size_t)a.nCT * a.Bpad;
+    float* part_sum = part_max + p.parts * p.pitch;
+    const int parts = (int)p.parts, pitch = (int)p.pitch;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int parts = a.nCT, pitch = a.Bpad;
-    if (small_batch(B, D, C_shard, SMALL_STEP)) {
-        const SmallPlan p(B, C_shard);
-        parts = p.ranges;
-        pitch = p.rows;
-        WS_LAUNCH_SMALL(KID_FWD, fwd_stats_small, p, p.ranges, s, a, p.range, part_max, part_sum, label_logit);
+    set_order(a);
+    if (p.way == WAY_SMALL) {
+        const SmallPlan sp(B, C_shard);
+        WS_LAUNCH_SMALL(KID_FWD, fwd_stats_small, sp, sp.ranges, s, a, sp.range, part_max, part_sum, label_logit);
+    } else if (p.way == WAY_BLOCKS) {
+        WS_LAUNCH(KID_FWD, fwd_stats_block, dim3(xcd_grid(parts * (pitch / BLOCK))), dim3(NTHREADS), s, a, pitch, part_max, part_sum,
+                  label_logit);
+    } else if (p.way == WAY_LISTS) {
+        WS_LAUNCH(KID_FWD, fwd_logits_list, dim3(list_grid(a.ranges, a.nBT)), dim3(NTHREADS), s,
+                  (FwdArgs{a, part_max, part_sum, label_logit}));
     } else {
-        set_order(a);
-        // a workspace of one partial result per class tile is enough for the tiles
-        if (logits_blocks(B, D, C_shard, SMALL_STEP) && workspace_bytes >= block_parts_bytes(B, C_shard)) {
-            parts = (C_shard + BLOCK - 1) / BLOCK;
-            pitch = (int)round_up(B, BLOCK);
-            part_sum = part_max + (size_t)parts * pitch;
-            WS_LAUNCH(KID_FWD, fwd_stats_block, dim3(xcd_grid(parts * (pitch / BLOCK))), dim3(NTHREADS), s, a, pitch, part_max, part_sum,
-                      label_logit);
-        } else if (a.on_lists && workspace_bytes >= parts_bytes(a.ranges.ranges, a.Bpad)) {
-            parts = a.ranges.ranges;
-            part_sum = part_max + (size_t)parts * pitch;
-            WS_LAUNCH(KID_FWD, fwd_logits_list, dim3(list_grid(a.ranges, a.nBT)), dim3(NTHREADS), s,
-                      (FwdArgs{a, part_max, part_sum, label_logit}));
-        } else {
-            a.plan = plan_tiles(a.nBT * a.nCT, LOGITS_MAX_THIN_TAIL);
-            WS_LAUNCH(KID_FWD, fwd_logits_stats, dim3(a.plan.thin_first + a.plan.n_thin), dim3(NTHREADS), s, a, part_max,
-                      part_sum, label_logit);
-        }
+        a.plan = plan_tiles(a.nBT * a.nCT, LOGITS_MAX_THIN_TAIL);
+        WS_LAUNCH(KID_FWD, fwd_logits_stats, dim3(a.plan.thin_first + a.plan.n_thin), dim3(NTHREADS), s, a, part_max,
+                  part_sum, label_logit);
     }
     WS_LAUNCH(KID_MERGE, merge_class_tiles, dim3((B + 15) / 16), dim3(1024), s, part_max, part_sum, parts, pitch, B, row_max,
               row_sumexp);
@@ -2271,28 +2263,26 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     XtArgs xt;
     xt.XT = XT; xt.ldxt = p.Bpad;
     xt.n_blocks = (int)std::min<int64_t>(((B + 63) / 64) * (int64_t)(D / 64), SIDE_BLOCKS);
-    const bool small = small_batch(B, D, C_shard, SMALL_STEP), blocks = !small && logits_blocks(B, D, C_shard, SMALL_STEP);
-    if (small) {
+    const LogitsPlan lp = plan_logits(B, D, C_shard, SMALL_STEP);
+    set_order(a);
+    if (lp.way == WAY_SMALL) {
         const SmallPlan sp(B, (int32_t)round_up(C_shard, TILE_K));
         xt.first_block = sp.ranges;
         WS_LAUNCH_SMALL(KID_DZ, dz_small, sp, xt.first_block + xt.n_blocks, s, a, sp.range, logsumexp, grad_scale, dZ, p.Cpad,
                         db_shard ? db_part : nullptr, xt);
+    } else if (lp.way == WAY_BLOCKS) {
+        xt.first_block = xcd_grid((int)(lp.parts * (lp.pitch / BLOCK)));
+        WS_LAUNCH(KID_DZ, dz_block, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s, a, logsumexp, grad_scale, dZ, p.Cpad,
+                  db_shard ? db_part : nullptr, xt);
+    } else if (lp.way == WAY_LISTS) {
+        xt.first_block = list_grid(a.ranges, a.nBT);
+        WS_LAUNCH(KID_DZ, bwd_dz_list, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s,
+                  (DzArgs{a, logsumexp, grad_scale, dZ, p.Cpad, db_shard ? db_part : nullptr, xt}));
     } else {
-        set_order(a);
-        if (blocks) {
-            xt.first_block = xcd_grid(((C_shard + BLOCK - 1) / BLOCK) * ((B + BLOCK - 1) / BLOCK));
-            WS_LAUNCH(KID_DZ, dz_block, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s, a, logsumexp, grad_scale, dZ, p.Cpad,
-                      db_shard ? db_part : nullptr, xt);
-        } else if (a.on_lists) {
-            xt.first_block = list_grid(a.ranges, a.nBT);
-            WS_LAUNCH(KID_DZ, bwd_dz_list, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s,
-                      (DzArgs{a, logsumexp, grad_scale, dZ, p.Cpad, db_shard ? db_part : nullptr, xt}));
-        } else {
-            a.plan = plan_tiles(p.nBT * p.nCT, LOGITS_MAX_THIN_TAIL);
-            xt.first_block = a.plan.thin_first + a.plan.n_thin;
-            WS_LAUNCH(KID_DZ, bwd_recompute_dz, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s, a, logsumexp,
-                      grad_scale, dZ, p.Cpad, db_shard ? db_part : nullptr, xt);
-        }
+        a.plan = plan_tiles(p.nBT * p.nCT, LOGITS_MAX_THIN_TAIL);
+        xt.first_block = a.plan.thin_first + a.plan.n_thin;
+        WS_LAUNCH(KID_DZ, bwd_recompute_dz, dim3(xt.first_block + xt.n_blocks), dim3(NTHREADS), s, a, logsumexp,
+                  grad_scale, dZ, p.Cpad, db_shard ? db_part : nullptr, xt);
     }
 
     DxArgs x;
@@ -2321,7 +2311,7 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     FinishArgs f;
     f.parts = direct ? nullptr : parts; f.splits = p.splits; f.split_stride = (int64_t)B * D;
     f.B = B; f.D = D; f.dX = dX_partial; f.lddx = lddx; f.accumulate = accumulate_dx;
-    f.db_part = db_shard ? db_part : nullptr; f.n_db_parts = small ? 1 : blocks ? (B + BLOCK - 1) / BLOCK : 4 * p.nBT; f.db_stride = p.Cpad;
+    f.db_part = db_shard ? db_part : nullptr; f.n_db_parts = lp.way == WAY_SMALL ? 1 : lp.way == WAY_BLOCKS ? (B + BLOCK - 1) / BLOCK : 4 * p.nBT; f.db_stride = p.Cpad;
     f.C = C_shard; f.db = db_shard;
     f.sgd = sgd; f.lr = lr;
     f.first_block = w.plan.thin_first + w.plan.n_thin;
@@ -2397,14 +2387,15 @@ int ws_split_fc_predict(const void* X, int64_t ldx, const void* W_shard, int64_t
     a.nBT = a.Bpad / 256;
     a.nCT = (int)(round_up(C_shard, 256) / 256);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (small_batch(B, D, C_shard, SMALL_PROBS)) {
-        const SmallPlan p(B, C_shard);
-        WS_LAUNCH_SMALL(KID_PREDICT, predict_small, p, p.ranges, s, a, p.range, logsumexp, static_cast<uint16_t*>(P), ldp);
-    } else if (logits_blocks(B, D, C_shard, SMALL_PROBS)) {
-        WS_LAUNCH(KID_PREDICT, predict_block, dim3(xcd_grid(((C_shard + BLOCK - 1) / BLOCK) * ((B + BLOCK - 1) / BLOCK))), dim3(NTHREADS), s,
-                  a, logsumexp, static_cast<uint16_t*>(P), ldp);
+    const LogitsPlan p = plan_logits(B, D, C_shard, SMALL_PROBS);
+    set_order(a);
+    if (p.way == WAY_SMALL) {
+        const SmallPlan sp(B, C_shard);
+        WS_LAUNCH_SMALL(KID_PREDICT, predict_small, sp, sp.ranges, s, a, sp.range, logsumexp, static_cast<uint16_t*>(P), ldp);
+    } else if (p.way == WAY_BLOCKS) {
+        WS_LAUNCH(KID_PREDICT, predict_block, dim3(xcd_grid((int)(p.parts * (p.pitch / BLOCK)))), dim3(NTHREADS), s, a, logsumexp,
+                  static_cast<uint16_t*>(P), ldp);
     } else {
-        set_order(a);
         WS_LAUNCH(KID_PREDICT, predict_probs, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, logsumexp,
                   static_cast<uint16_t*>(P), ldp);
     }
@@ -2432,22 +2423,19 @@ int ws_split_fc_top1(const void* X, int64_t ldx, const void* W_shard, int64_t ld
     a.Bpad = (int)round_up(B, 256);
     a.nBT = a.Bpad / 256;
     a.nCT = (int)(round_up(C_shard, 256) / 256);
+    LogitsPlan p = plan_logits(B, D, C_shard, SMALL_TOP1);
+    if (workspace_bytes < p.bytes()) p = plan_wide(B, C_shard);
     float* part_val = static_cast<float*>(workspace);
-    int* part_cls = reinterpret_cast<int*>(part_val + (size_t)a.nCT * a.Bpad);
+    int* part_cls = reinterpret_cast<int*>(part_val + p.parts * p.pitch);
+    const int parts = (int)p.parts, pitch = (int)p.pitch;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int parts = a.nCT, pitch = a.Bpad;
-    if (small_batch(B, D, C_shard, SMALL_TOP1)) {
-        const SmallPlan p(B, C_shard);
-        parts = p.ranges;
-        pitch = p.rows;
-        WS_LAUNCH_SMALL(KID_TOP1, top1_small, p, p.ranges, s, a, p.range, part_val, part_cls);
-    } else if (logits_blocks(B, D, C_shard, SMALL_TOP1) && workspace_bytes >= block_parts_bytes(B, C_shard)) {
-        parts = (C_shard + BLOCK - 1) / BLOCK;
-        pitch = (int)round_up(B, BLOCK);
-        part_cls = reinterpret_cast<int*>(part_val + (size_t)parts * pitch);
+    set_order(a);
+    if (p.way == WAY_SMALL) {
+        const SmallPlan sp(B, C_shard);
+        WS_LAUNCH_SMALL(KID_TOP1, top1_small, sp, sp.ranges, s, a, sp.range, part_val, part_cls);
+    } else if (p.way == WAY_BLOCKS) {
         WS_LAUNCH(KID_TOP1, top1_block, dim3(xcd_grid(parts * (pitch / BLOCK))), dim3(NTHREADS), s, a, pitch, part_val, part_cls);
     } else {
-        set_order(a);
         WS_LAUNCH(KID_TOP1, top1_logits, dim3(xcd_grid(a.nBT * a.nCT)), dim3(NTHREADS), s, a, part_val, part_cls);
     }
     launch_merge_top1(part_val, part_cls, parts, pitch, B, class_offset, top_logit, top_class, s);

@@ -72,7 +72,7 @@ def run_step(X_bits, W_bits, bias, labels, shards, g=1.0, w_lo=0, want_db=True, 
     for i, (off, c) in enumerate(shards):
         Ws = W[off - w_lo: off - w_lo + c]
         bs = None if b_dev is None else b_dev[off - w_lo: off - w_lo + c]
-        ws.split_fc_fwd(X, Ws, bs, y, off, m[i], s[i], t[i], work)
+        ws.split_fc_fwd(X, Ws, bs, y, off, m[i], s[i], t[i], work[:ws.fwd_workspace_bytes(B, D, c)])      # exactly what it asks for
     ws.combine_partials(m, s, t, lse, loss, mean)
     lse_bwd = lse if lse_override is None else torch.from_numpy(
         np.ascontiguousarray(lse_override, dtype=np.float32)).cuda()

@@ -6,11 +6,16 @@ import subprocess
 from paper_2011_09208_amd import buildlib
 
 PLAN = os.path.join(buildlib.PKG, "csrc", "plan.h")
+STEP, PROBS, TOP1 = 0, 1, 2                              # SmallUse
+SMALL, BLOCKS, LISTS, TILES = 0, 1, 2, 3                 # LogitsWay
 SHIM = """#include "%s"
 using namespace ws;
 extern "C" {
 size_t fwd_bytes_(int B, int D, int C) { return fwd_bytes(B, D, C); }
 size_t least_fwd_bytes_(int B, int C) { return least_fwd_bytes(B, C); }
+size_t way_bytes_(int B, int D, int C, int use) { return plan_logits(B, D, C, (SmallUse)use).bytes(); }
+int way_(int B, int D, int C, int use) { return plan_logits(B, D, C, (SmallUse)use).way; }
+int ranges_(int D, int C, int nBT) { return plan_ranges(D, C, nBT).ranges; }
 size_t bwd_bytes_(int B, int D, int C) { return plan_bwd(B, D, C).bytes(); }
 }
 """
@@ -24,6 +29,6 @@ def load(folder):
     subprocess.run([buildlib.HIPCC, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-Wno-unused-function",
                     src, "-o", lib], check=True)
     rules = ctypes.CDLL(lib)
-    for name in ("fwd_bytes_", "least_fwd_bytes_", "bwd_bytes_"):
+    for name in ("fwd_bytes_", "least_fwd_bytes_", "way_bytes_", "bwd_bytes_"):
         getattr(rules, name).restype = ctypes.c_size_t
     return rules

@@ -5,6 +5,7 @@ import pytest
 
 from paper_2011_09208_amd import buildlib
 from tests import plan_rules
+from tests.plan_rules import LISTS, STEP, TOP1
 
 
 @pytest.fixture(scope="module")
@@ -37,3 +38,23 @@ def test_the_rules_tested_here_are_the_librarys(rules, ws):
     for B, D, C in drawn(2000, seed=1):
         assert rules.fwd_bytes_(B, D, C) == ws.fwd_workspace_bytes(B, D, C), (B, D, C)
         assert rules.bwd_bytes_(B, D, C) == ws.bwd_workspace_bytes(B, D, C), (B, D, C)
+
+
+@pytest.mark.parametrize("B,D,C,want", [(300, 2048, 12000, 2 * 128 * 512 * 4), (257, 64, 8441, 2 * 128 * 512 * 4),
+                                        (100, 2048, 20000, 2 * 256 * 256 * 4), (85, 192, 30922, 2 * 256 * 256 * 4)])
+def test_forward_query_holds_the_lists_where_the_arg_max_takes_blocks(rules, ws, B, D, C, want):
+    assert rules.way_(B, D, C, STEP) == LISTS and ws.fwd_workspace_bytes(B, D, C) == want
+
+
+def test_forward_query_is_what_the_calls_compare_with(rules, ws):
+    """The forward call and the arg-max take their own kernels with a workspace as large as the query, and the former size, a pair
+    per class tile of 256, is never more than that.  Where the former size fits the built-in scratch, so does what the call wants."""
+    lists = 0
+    for B, D, C in [*drawn(30000, seed=2), (2 ** 31 - 1, 64, 2 ** 31 - 1), (1, 64, 2 ** 31 - 1), (20, 64, 2 ** 31 - 1), (2 ** 31 - 1, 64, 1)]:
+        step, top1, least = rules.way_bytes_(B, D, C, STEP), rules.way_bytes_(B, D, C, TOP1), rules.least_fwd_bytes_(B, C)
+        assert least == 2 * ((C + 255) // 256) * ((B + 255) // 256 * 256) * 4
+        assert ws.fwd_workspace_bytes(B, D, C) == max(step, top1, least), (B, D, C)
+        if least <= ws.STATIC_SCRATCH_BYTES:
+            assert step <= ws.STATIC_SCRATCH_BYTES, (B, D, C)
+        lists += rules.way_(B, D, C, STEP) == LISTS
+    assert lists > 3000

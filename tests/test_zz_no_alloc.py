@@ -52,8 +52,8 @@ def test_static_scratch_forward_two_calls_second_smaller():
         pytest.fail("GPU tests need a GPU; there is no CPU fallback")
     from tests import gpu_harness as H
     from paper_2011_09208_amd import binding as ws
-    _one_call(H, ws, torch, 1100, 128, 14000, 5000, seed=1)      # 275 tiles: full and thin, 1.4 MB of scratch
-    _one_call(H, ws, torch, 300, 64, 1000, 700, seed=2)          # smaller: thin tiles only, stale partials around it
+    _one_call(H, ws, torch, 1100, 128, 14000, 5000, seed=1)      # lists, 1.5 MB of scratch
+    _one_call(H, ws, torch, 300, 64, 1000, 700, seed=2)          # smaller: 64 x 64 tiles, stale partials around it
     # beyond the built-in scratch: refused on the host, nothing launched
     B, D, C = 8192, 64, 600_000
     assert ws.fwd_workspace_bytes(B, D, C) > ws.STATIC_SCRATCH_BYTES
@@ -64,3 +64,14 @@ def test_static_scratch_forward_two_calls_second_smaller():
     with pytest.raises(ws.WhaleSplitError) as e:
         ws.split_fc_fwd_static(X, W, None, y, 0, *out)
     assert str(e.value) == "WS_ERR_LIMIT"
+
+
+@pytest.mark.parametrize("B,D,C", [(300, 2048, 12000), (85, 192, 30922), (40, 256, 9000), (300, 64, 5001), (1100, 192, 14000)])
+def test_static_scratch_forward_is_the_forward_with_the_queried_workspace(B, D, C):
+    """Lists (the first two where the arg-max takes 64 x 64 tiles), 64 x 64 tiles, full and thin tiles: the plain call's workspace is exactly what the query says."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU; there is no CPU fallback")
+    from tests import gpu_harness as H
+    from paper_2011_09208_amd import binding as ws
+    _one_call(H, ws, torch, B, D, C, 100, seed=B)
