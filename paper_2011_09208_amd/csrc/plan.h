@@ -13,10 +13,13 @@
 
 namespace ws {
 
+// n / d is the high half of n * inverse(d) as long as n * d < 2^32 and d > 1; there is no such number for 1, and 0 stands for it.
+static inline uint32_t inverse(uint32_t d) { return d > 1 ? (uint32_t)((((uint64_t)1 << 32) + d - 1) / d) : 0; }
+__host__ __device__ inline uint32_t quotient(uint32_t n, uint32_t inv) { return inv == 0 ? n : (uint32_t)(((uint64_t)n * inv) >> 32); }
+
 // How the list kernels cut the logits: each of `ranges` columns of workgroups (one for every batch tile) takes every ranges-th of
 // the first full * ranges whole class tiles and one part of the rest, `per` units of 32 classes, the first `more` of them one more
-// (whole k-steps of the dX contraction in all).  The divisions that number the workgroups are the host's: n / d = n * inv
-// >> 32 as long as n * d < 2^32.
+// (whole k-steps of the dX contraction in all).  What the kernels divide by comes as its inverse.
 struct RangePlan {
     int ranges, full, per, more;
     uint32_t inv_block, inv_rest;        // of a block of batch tiles (`ranges` times four of them), of the batch tiles of the last block
@@ -204,9 +207,9 @@ static RangePlan plan_ranges(int32_t D, int32_t C, int nBT) {
     const int rest = units - best.full * MAX_UNITS * best.ranges;
     best.per = rest / best.ranges;
     best.more = rest - best.per * best.ranges;
-    best.inv_block = (uint32_t)((((uint64_t)1 << 32) + 4 * best.ranges - 1) / (4 * best.ranges));
-    best.inv_ranges = best.ranges > 1 ? (uint32_t)((((uint64_t)1 << 32) + best.ranges - 1) / best.ranges) : 0xffffffffu;
-    best.inv_rest = nBT % 4 > 1 ? (uint32_t)((((uint64_t)1 << 32) + nBT % 4 - 1) / (nBT % 4)) : 0;
+    best.inv_block = inverse(4 * best.ranges);
+    best.inv_ranges = inverse(best.ranges);
+    best.inv_rest = inverse(nBT % 4);
     return best;
 }
 // Whether the logits of a step (more than a small batch) run as lists or as a workgroup per tile, us of forward and dz:

@@ -154,7 +154,7 @@ __device__ __forceinline__ TileRef logits_tile_ref(const FcArgs& a) {
 // kernel (and the thin and the full version of a tile) adds the products of a logit in the same order.  Where the step runs
 // as lists, a workgroup's whole tiles alternate, `ranges` class tiles apart, and the rest is ascending.
 __device__ __forceinline__ bool logits_descending(const FcArgs& a, int ct, int bt) {
-    if (a.on_lists) return ct < a.ranges.full * a.ranges.ranges && (__umulhi((uint32_t)ct, a.ranges.inv_ranges) & 1) != 0;
+    if (a.on_lists) return ct < a.ranges.full * a.ranges.ranges && (quotient((uint32_t)ct, a.ranges.inv_ranges) & 1) != 0;
     if (a.nBT * a.nCT <= 256) return false;
     if (a.nBT <= 4) return (((ct * a.nBT) >> 5) & 1) != 0;
     return (((ct >> 3) ^ (bt >> 2)) & 1) != 0;
@@ -291,9 +291,9 @@ struct LogitsList {
     bool backwards;
     __device__ __forceinline__ LogitsList(const FcArgs& a, bool back) : backwards(back) {
         ranges = a.ranges.ranges;
-        const int it = xcd_logical_tile(ranges * a.nBT), block = (int)__umulhi((uint32_t)it, a.ranges.inv_block);
+        const int it = xcd_logical_tile(ranges * a.nBT), block = (int)quotient((uint32_t)it, a.ranges.inv_block);
         const int r = it - block * 4 * ranges, left = a.nBT - 4 * block;
-        range = left >= 4 ? r >> 2 : left == 1 ? r : (int)__umulhi((uint32_t)r, a.ranges.inv_rest);
+        range = left >= 4 ? r >> 2 : (int)quotient((uint32_t)r, a.ranges.inv_rest);
         n0 = TILE_N * (4 * block + r - range * (left >= 4 ? 4 : left));
         full = a.ranges.full;
         rest = TILE_M * full * ranges + UNIT * (range * a.ranges.per + (range < a.ranges.more ? range : a.ranges.more));

@@ -15,6 +15,8 @@ size_t fwd_bytes_(int B, int D, int C) { return fwd_bytes(B, D, C); }
 size_t least_fwd_bytes_(int B, int C) { return least_fwd_bytes(B, C); }
 size_t way_bytes_(int B, int D, int C, int use) { return plan_logits(B, D, C, (SmallUse)use).bytes(); }
 int way_(int B, int D, int C, int use) { return plan_logits(B, D, C, (SmallUse)use).way; }
+unsigned quotient_(unsigned n, unsigned d) { return quotient(n, inverse(d)); }
+unsigned list_quotient_(unsigned n, int D, int C, int nBT) { return quotient(n, plan_ranges(D, C, nBT).inv_ranges); }
 int ranges_(int D, int C, int nBT) { return plan_ranges(D, C, nBT).ranges; }
 size_t bwd_bytes_(int B, int D, int C) { return plan_bwd(B, D, C).bytes(); }
 }
@@ -31,4 +33,5 @@ def load(folder):
     rules = ctypes.CDLL(lib)
     for name in ("fwd_bytes_", "least_fwd_bytes_", "way_bytes_", "bwd_bytes_"):
         getattr(rules, name).restype = ctypes.c_size_t
+    rules.quotient_.restype = rules.list_quotient_.restype = ctypes.c_uint
     return rules

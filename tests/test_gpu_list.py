@@ -73,3 +73,20 @@ def test_forward_with_a_partial_result_per_class_tile(H):
     assert (out[0][1] - out[1][1]).abs().max() <= 2.0 ** -24 * 2 * (33 + 128) * out[0][1].max()
     with pytest.raises(ws.WhaleSplitError):
         ws.split_fc_fwd(X, W, None, y, 0, m, s, t, work[:least - 16])
+
+
+@pytest.mark.parametrize("B,D,C", [(50000, 128, 600), (600, 640, 256 * 170 + 33), (700, 576, 256 * 112 + 65)])
+def test_wide_tiles_add_in_the_order_of_the_lists(H, B, D, C):
+    """Lists of several whole tiles, which alternate their direction, one of them with a single range: the arg-max's logit (wide
+    tiles) is the forward call's maximum, and with that class as the label its label logit, bit for bit."""
+    import torch
+    from paper_2011_09208_amd import binding as ws
+    H.say(f"[parity] lists and wide tiles: B={B} D={D} C={C}")
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    X, W = (torch.randn((n, D), device="cuda", generator=gen).to(torch.bfloat16) for n in (B, C))
+    m, s, t, top = (torch.empty(B, device="cuda") for _ in range(4))
+    y = torch.empty(B, device="cuda", dtype=torch.int32)
+    work = torch.empty(ws.fwd_workspace_bytes(B, D, C), dtype=torch.uint8, device="cuda")
+    ws.split_fc_top1(X, W, None, 0, top, y, work)
+    ws.split_fc_fwd(X, W, None, y, 0, m, s, t, work)
+    assert torch.equal(m, top) and torch.equal(t, top)

@@ -58,3 +58,21 @@ def test_forward_query_is_what_the_calls_compare_with(rules, ws):
             assert step <= ws.STATIC_SCRATCH_BYTES, (B, D, C)
         lists += rules.way_(B, D, C, STEP) == LISTS
     assert lists > 3000
+
+
+def test_quotients_of_the_list_kernels(rules):
+    """By 1 to 1024 ranges, four times as many, and up to three batch tiles: every edge of a quotient below the bound n * d < 2^32."""
+    rng = random.Random(3)
+    for d in [*range(1, 1025), *range(1028, 4097, 4)]:
+        top = (2 ** 32 - 1) // d
+        for q in {1, 2, 3, top // d, *(rng.randint(0, top // d) for _ in range(20))}:
+            for n in (q * d - 1, q * d, q * d + d - 1):
+                if 0 <= n <= top:
+                    assert rules.quotient_(n, d) == n // d, (n, d)
+
+
+@pytest.mark.parametrize("B,D,C,ranges", [(50000, 128, 600, 1), (65536, 512, 1000, 1), (44000, 128, 600, 4), (600, 640, 43553, 85)])
+def test_whole_tiles_of_a_list_are_a_range_apart(rules, B, D, C, ranges):
+    assert rules.way_(B, D, C, STEP) == LISTS and rules.ranges_(D, C, (B + 255) // 256) == ranges
+    for ct in range((C + 255) // 256):
+        assert rules.list_quotient_(ct, D, C, (B + 255) // 256) == ct // ranges
