@@ -227,7 +227,6 @@ static RangePlan plan_ranges(int32_t D, int32_t C, int nBT) {
 //     832, C = 8132: 35.7 + 43.9 and 39.1 + 45.1; 264, B = 500, D = 2048: 68.1 + 74.7 and 73.1 + 79.4), two from 17 (531, B = 2057, D = 2048: 110 + 123
 //     and 115 + 131; but 528, 13 k-steps, B = 700: 58.0 + 69.6 and 56.5 + 67.3), or from 9 if it is longer than 32 (560, B = 4000, D = 832:
 //     58.2 + 70.6 and 63.0 + 76.0; 4 k-steps, B = 1000: 32.5 + 45.0 and 31.8 + 42.2).
-// Every way adds the products of a logit in the same order.
 static bool logits_list(const RangePlan& p, int nBT, int nCT, int k_steps) {
     const int64_t tiles = (int64_t)nBT * nCT;
     const int rest = p.per + (p.more > 0);
@@ -246,12 +245,12 @@ enum LogitsWay { WAY_SMALL, WAY_BLOCKS, WAY_LISTS, WAY_TILES };
 struct LogitsPlan {
     LogitsWay way;
     int64_t parts, pitch;
-    RangePlan ranges;                    // of the lists; not set otherwise
+    RangePlan ranges;                    // of the lists
     size_t bytes() const { return (size_t)(2 * parts * pitch) * sizeof(float); }
 };
 // The wide tiles: what any call can do, and what it does with a workspace that its own kernels find too small.
 static LogitsPlan plan_wide(int32_t B, int32_t C) {
-    LogitsPlan p;
+    LogitsPlan p = {};
     p.way = WAY_TILES;
     p.parts = round_up(C, TILE_M) / TILE_M;
     p.pitch = round_up(B, TILE_N);
@@ -278,6 +277,28 @@ static LogitsPlan plan_logits(int32_t B, int32_t D, int32_t C, SmallUse use) {
     }
     return p;
 }
+// Direction in which the logits of class tile ct and batch tile bt (256 x 256) walk the features, a function of the shard's
+// step and the tile's coordinates alone, so that every kernel (and the thin and the full version of a tile) adds the products
+// of a logit in the same order:
+//   where the step runs in 64 x 64 tiles (or as a small batch, which has an order of its own): ascending;
+//   as lists: a workgroup's whole tiles alternate, `ranges` class tiles apart, and the rest is ascending;
+//   as wide tiles: a compute unit's next tile lies about 32 tile ids further on, in the next group of class tiles (up to four
+//     batch tiles) or the next batch block of the same class tiles (more); alternating the direction between such groups lets it
+//     find the end of the panels that the two tiles share, which it has just read, still in the L2 (launches of one round have
+//     nothing to gain and keep one direction).
+enum LogitsOrder { ORDER_ASCENDING, ORDER_LISTS, ORDER_FEW_BATCH_TILES, ORDER_MANY_BATCH_TILES };
+static LogitsOrder logits_order(const LogitsPlan& step) {
+    const int64_t nBT = step.pitch / TILE_N;
+    if (step.way == WAY_LISTS) return ORDER_LISTS;
+    if (step.way != WAY_TILES || nBT * step.parts <= 256) return ORDER_ASCENDING;
+    return nBT <= 4 ? ORDER_FEW_BATCH_TILES : ORDER_MANY_BATCH_TILES;
+}
+__host__ __device__ inline bool logits_descending(LogitsOrder order, const RangePlan& ranges, int nBT, int ct, int bt) {
+    if (order == ORDER_LISTS) return ct < ranges.full * ranges.ranges && (quotient((uint32_t)ct, ranges.inv_ranges) & 1) != 0;
+    if (order == ORDER_FEW_BATCH_TILES) return (((ct * nBT) >> 5) & 1) != 0;
+    return order == ORDER_MANY_BATCH_TILES && (((ct >> 3) ^ (bt >> 2)) & 1) != 0;
+}
+
 // The workspace that the forward call and the arg-max want, and the one that either does with.
 static size_t least_fwd_bytes(int32_t B, int32_t C) { return plan_wide(B, C).bytes(); }
 static size_t fwd_bytes(int32_t B, int32_t D, int32_t C) {

@@ -91,8 +91,8 @@ struct FcArgs {
     int B, D, C, class_offset;
     int Bpad;        // B rounded up to 256
     int nBT, nCT;    // tiles along the batch and class dimensions
+    LogitsOrder order;
     RangePlan ranges;
-    bool on_lists;   // the step runs as lists (logits_list), whatever this launch does
     TilePlan plan;   // which of the nBT * nCT tiles run as full tiles and which as four thin tiles each
     int last_tile_first;   // walk the full tiles from the last to the first
 };
@@ -146,20 +146,6 @@ __device__ __forceinline__ TileRef logits_tile_ref(const FcArgs& a) {
     return r;
 }
 
-// Direction in which the logits of tile (ct, bt) walk the features.  A compute unit's next tile lies about 32
-// tile ids further on, in the next group of class tiles (up to four batch tiles) or the next batch block of the
-// same class tiles (more); alternating the direction between such groups lets it find the end of the panels
-// that the two tiles share, which it has just read, still in the L2 (launches of one round have nothing to gain
-// and keep one direction).  A function of the tile's coordinates and the launch shape alone, so that every
-// kernel (and the thin and the full version of a tile) adds the products of a logit in the same order.  Where the step runs
-// as lists, a workgroup's whole tiles alternate, `ranges` class tiles apart, and the rest is ascending.
-__device__ __forceinline__ bool logits_descending(const FcArgs& a, int ct, int bt) {
-    if (a.on_lists) return ct < a.ranges.full * a.ranges.ranges && (quotient((uint32_t)ct, a.ranges.inv_ranges) & 1) != 0;
-    if (a.nBT * a.nCT <= 256) return false;
-    if (a.nBT <= 4) return (((ct * a.nBT) >> 5) & 1) != 0;
-    return (((ct >> 3) ^ (bt >> 2)) & 1) != 0;
-}
-
 // Runs the logits GEMM of one 256-class x 256-row tile and leaves z (bias added, padding = -inf)
 // in acc.  M = classes (A = W_s, KC), N = batch rows (B operand = X, KC), K = D.
 __device__ __forceinline__ void logits_tile(acc_t& acc, const FcArgs& a, int ct, int bt, char* lds,
@@ -167,7 +153,7 @@ __device__ __forceinline__ void logits_tile(acc_t& acc, const FcArgs& a, int ct,
     zero_acc(acc);
     const Operand A = make_operand(a.W, a.ldw, a.C, a.D);
     const Operand Bo = make_operand(a.X, a.ldx, a.B, a.D);
-    gemm_mainloop<KC>(acc, A, Bo, ct * TILE_M, bt * TILE_N, 0, a.D / TILE_K, lds, logits_descending(a, ct, bt));
+    gemm_mainloop<KC>(acc, A, Bo, ct * TILE_M, bt * TILE_N, 0, a.D / TILE_K, lds, logits_descending(a.order, a.ranges, a.nBT, ct, bt));
     const int tid = threadIdx.x;
     const bool has_bias = a.bias != nullptr;
     if (has_bias) {
@@ -193,7 +179,7 @@ __device__ __forceinline__ void logits_thin(thin_acc_t& acc, const FcArgs& a, in
         for (int j = 0; j < THIN_NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const Operand A = make_operand(a.W, a.ldw, a.C, a.D);
     const Operand Bo = make_operand(a.X, a.ldx, a.B, a.D);
-    thin_mainloop(acc, A, Bo, ct * TILE_M, bt * TILE_N + piece * THIN_N, 0, a.D / TILE_K, lds, logits_descending(a, ct, bt));
+    thin_mainloop(acc, A, Bo, ct * TILE_M, bt * TILE_N + piece * THIN_N, 0, a.D / TILE_K, lds, logits_descending(a.order, a.ranges, a.nBT, ct, bt));
     const int tid = threadIdx.x, wave = tid >> 6, g = (tid & 63) >> 4;
     if (a.bias != nullptr) {
         if (tid < TILE_M) {
@@ -2006,10 +1992,11 @@ constexpr int COMBINE_MEAN_ROWS = 2048;
         if ((plan).rows == 16) WS_LAUNCH(kid, name<1>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__); \
         else WS_LAUNCH(kid, name<2>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__);                  \
     } while (0)
-// How the logits of a call are cut, and with it the order of their sums.
-static void set_order(FcArgs& a) {
-    a.ranges = plan_ranges(a.D, a.C, a.nBT);
-    a.on_lists = logits_list(a.ranges, a.nBT, a.nCT, a.D / TILE_K);
+// Predictions and arg-max add the products of a logit in the order of the step, whatever kernels the step runs.
+static void set_step_order(FcArgs& a) {
+    const LogitsPlan step = plan_logits(a.B, a.D, a.C, SMALL_STEP);
+    a.order = logits_order(step);
+    a.ranges = step.ranges;
 }
 
 static int check_fc_common(const void* X, int64_t ldx, const void* W, int64_t ldw, const float* bias,
@@ -2151,12 +2138,13 @@ static int launch_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t l
     a.nBT = a.Bpad / 256;
     a.nCT = (int)(round_up(C_shard, 256) / 256);
     LogitsPlan p = plan_logits(B, D, C_shard, SMALL_STEP);
+    a.order = logits_order(p);
+    a.ranges = p.ranges;
     if (workspace_bytes < p.bytes()) p = plan_wide(B, C_shard);
     float* part_max = static_cast<float*>(workspace);
     float* part_sum = part_max + p.parts * p.pitch;
     const int parts = (int)p.parts, pitch = (int)p.pitch;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    set_order(a);
     if (p.way == WAY_SMALL) {
         const SmallPlan sp(B, C_shard);
         WS_LAUNCH_SMALL(KID_FWD, fwd_stats_small, sp, sp.ranges, s, a, sp.range, part_max, part_sum, label_logit);
@@ -2264,7 +2252,8 @@ static int run_bwd(const void* X, int64_t ldx, const void* W_shard, int64_t ldw,
     xt.XT = XT; xt.ldxt = p.Bpad;
     xt.n_blocks = (int)std::min<int64_t>(((B + 63) / 64) * (int64_t)(D / 64), SIDE_BLOCKS);
     const LogitsPlan lp = plan_logits(B, D, C_shard, SMALL_STEP);
-    set_order(a);
+    a.order = logits_order(lp);
+    a.ranges = lp.ranges;
     if (lp.way == WAY_SMALL) {
         const SmallPlan sp(B, (int32_t)round_up(C_shard, TILE_K));
         xt.first_block = sp.ranges;
@@ -2388,7 +2377,7 @@ int ws_split_fc_predict(const void* X, int64_t ldx, const void* W_shard, int64_t
     a.nCT = (int)(round_up(C_shard, 256) / 256);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const LogitsPlan p = plan_logits(B, D, C_shard, SMALL_PROBS);
-    set_order(a);
+    set_step_order(a);
     if (p.way == WAY_SMALL) {
         const SmallPlan sp(B, C_shard);
         WS_LAUNCH_SMALL(KID_PREDICT, predict_small, sp, sp.ranges, s, a, sp.range, logsumexp, static_cast<uint16_t*>(P), ldp);
@@ -2429,7 +2418,7 @@ int ws_split_fc_top1(const void* X, int64_t ldx, const void* W_shard, int64_t ld
     int* part_cls = reinterpret_cast<int*>(part_val + p.parts * p.pitch);
     const int parts = (int)p.parts, pitch = (int)p.pitch;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    set_order(a);
+    set_step_order(a);
     if (p.way == WAY_SMALL) {
         const SmallPlan sp(B, C_shard);
         WS_LAUNCH_SMALL(KID_TOP1, top1_small, sp, sp.ranges, s, a, sp.range, part_val, part_cls);

@@ -17,6 +17,10 @@ size_t way_bytes_(int B, int D, int C, int use) { return plan_logits(B, D, C, (S
 int way_(int B, int D, int C, int use) { return plan_logits(B, D, C, (SmallUse)use).way; }
 unsigned quotient_(unsigned n, unsigned d) { return quotient(n, inverse(d)); }
 unsigned list_quotient_(unsigned n, int D, int C, int nBT) { return quotient(n, plan_ranges(D, C, nBT).inv_ranges); }
+int descending_(int B, int D, int C, int ct, int bt) {
+    const LogitsPlan p = plan_logits(B, D, C, SMALL_STEP);
+    return logits_descending(logits_order(p), p.ranges, (B + 255) / 256, ct, bt);
+}
 int ranges_(int D, int C, int nBT) { return plan_ranges(D, C, nBT).ranges; }
 size_t bwd_bytes_(int B, int D, int C) { return plan_bwd(B, D, C).bytes(); }
 }

@@ -75,10 +75,10 @@ def test_forward_with_a_partial_result_per_class_tile(H):
         ws.split_fc_fwd(X, W, None, y, 0, m, s, t, work[:least - 16])
 
 
-@pytest.mark.parametrize("B,D,C", [(50000, 128, 600), (600, 640, 256 * 170 + 33), (700, 576, 256 * 112 + 65)])
-def test_wide_tiles_add_in_the_order_of_the_lists(H, B, D, C):
-    """Lists of several whole tiles, which alternate their direction, one of them with a single range: the arg-max's logit (wide
-    tiles) is the forward call's maximum, and with that class as the label its label logit, bit for bit."""
+@pytest.mark.parametrize("B,D,C", [(50000, 128, 600), (600, 640, 256 * 170 + 33), (700, 576, 256 * 112 + 65), (64, 192, 140000)])
+def test_wide_tiles_add_in_the_order_of_the_step(H, B, D, C):
+    """Lists of several whole tiles, which alternate their direction, one of them with a single range, and a step of 64 x 64 tiles,
+    which do not: the arg-max's logit (wide tiles) is the forward call's maximum, and with that class as the label its label logit, bit for bit."""
     import torch
     from paper_2011_09208_amd import binding as ws
     H.say(f"[parity] lists and wide tiles: B={B} D={D} C={C}")

@@ -5,7 +5,7 @@ import pytest
 
 from paper_2011_09208_amd import buildlib
 from tests import plan_rules
-from tests.plan_rules import LISTS, STEP, TOP1
+from tests.plan_rules import BLOCKS, LISTS, PROBS, SMALL, STEP, TILES, TOP1
 
 
 @pytest.fixture(scope="module")
@@ -76,3 +76,26 @@ def test_whole_tiles_of_a_list_are_a_range_apart(rules, B, D, C, ranges):
     assert rules.way_(B, D, C, STEP) == LISTS and rules.ranges_(D, C, (B + 255) // 256) == ranges
     for ct in range((C + 255) // 256):
         assert rules.list_quotient_(ct, D, C, (B + 255) // 256) == ct // ranges
+
+
+def test_every_kind_of_tile_walks_the_features_in_one_direction(rules):
+    """A shard's calls may run a logit in 64 x 64 tiles (always ascending), in a list (which alternates its whole tiles) or in a
+    wide tile, which asks the rule: the rule must say what the others do.  Small batches have an order of their own."""
+    seen = set()
+    for B, D, C in [*drawn(20000, seed=4), (64, 192, 140000), (17, 128, 150000)]:
+        ways = {use: rules.way_(B, D, C, use) for use in (STEP, PROBS, TOP1)}
+        nBT, nCT = (B + 255) // 256, (C + 255) // 256
+        tiles = [(ct, bt) for ct in {0, 1, 2, 31, 32, 33, nCT // 2, nCT - 1} for bt in {0, 3, 4, nBT - 1} if 0 <= ct < nCT and bt < nBT]
+        got = {t: rules.descending_(B, D, C, *t) for t in tiles}
+        if BLOCKS in ways.values():
+            assert not any(got.values()), (B, D, C, ways)
+        elif ways[STEP] == LISTS:
+            ranges = rules.ranges_(D, C, nBT)
+            full = 2 * ((C + 63) // 64) // (8 * ranges)
+            assert got == {(ct, bt): int(ct < full * ranges and ct // ranges % 2 == 1) for ct, bt in tiles}, (B, D, C)
+        elif ways[STEP] == TILES and nBT * nCT > 256:
+            assert got == {(ct, bt): (ct * nBT // 32 if nBT <= 4 else ct // 8 ^ bt // 4) % 2 for ct, bt in tiles}, (B, D, C)
+        else:
+            assert not any(got.values()), (B, D, C, ways)
+        seen.add(tuple(ways.values()))
+    assert {(BLOCKS, BLOCKS, TILES), (LISTS, TILES, TILES), (LISTS, BLOCKS, BLOCKS), (TILES, TILES, TILES), (SMALL, SMALL, SMALL)} <= seen
