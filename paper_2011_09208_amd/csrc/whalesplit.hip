@@ -55,6 +55,13 @@ __device__ __forceinline__ void merge_ms(float& m, float& s, float m2, float s2)
     m = M;
 }
 
+// exp(z - m) = exp2(z * log2 e + exp_shift(m)), m the largest logit of a group (-inf: of an empty one, exp2 gives zeros).  The
+// shift is rounded, which the group's sum carries as a factor of up to exp2 of half a unit in its last place: near 1 for any
+// real logits, but from -2^30 on (classes masked by -1e10, -1e30, the lowest float) it would overflow, and an infinite sum times
+// the weight of zero that the group has beside real logits is no number.  There the bound leaves the sum at zero.
+constexpr float EXP_SHIFT_MAX = 0x1p30f * LOG2E;
+__device__ __forceinline__ float exp_shift(float m) { return fminf(-m * LOG2E, EXP_SHIFT_MAX); }
+
 // Class id (relative to the wave's first class) held in accumulator register v of M-tile mt by the
 // lanes of 16-lane group g.
 __device__ __forceinline__ int acc_row(int mt, int v, int g) { return 16 * mt + 4 * g + v; }
@@ -228,8 +235,7 @@ __device__ __forceinline__ void fwd_stats_thin(const FcArgs& a, const TileRef& r
         for (int mt = 0; mt < THIN_MT; ++mt)
 #pragma unroll
             for (int v = 0; v < 4; ++v) mx = fmaxf(mx, acc[mt][nt][v]);
-        const float ms = (mx == NEG_INF) ? 0.0f : mx;
-        const float shift = -ms * LOG2E;
+        const float shift = exp_shift(mx);
         float s = 0.0f;
 #pragma unroll
         for (int mt = 0; mt < THIN_MT; ++mt)
@@ -442,9 +448,8 @@ struct FwdEpilogue : LogitsEpilogue<FwdArgs> {
         float shift[NT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const float m = top[nt] == NEG_INF ? 0.0f : top[nt];
-            shift[nt] = -m * LOG2E;                      // exp(z - m) = exp2(z * log2 e - m * log2 e)
-            sum[nt] *= mx[nt] == NEG_INF ? 0.0f : __expf(mx[nt] - m);
+            shift[nt] = exp_shift(top[nt]);
+            sum[nt] *= mx[nt] == NEG_INF ? 0.0f : __expf(mx[nt] - top[nt]);
             mx[nt] = top[nt];
         }
 #pragma unroll
@@ -549,8 +554,7 @@ __global__ __launch_bounds__(NTHREADS) void fwd_logits_stats(FcArgs a, float* __
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int v = 0; v < 4; ++v) mx = fmaxf(mx, acc[mt][nt][v]);
-        const float ms = (mx == NEG_INF) ? 0.0f : mx;
-        const float shift = -ms * LOG2E;                 // exp(z - m) = exp2(z * log2 e - m * log2 e)
+        const float shift = exp_shift(mx);
         float s = 0.0f;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
@@ -1273,7 +1277,7 @@ __global__ __launch_bounds__(SmallShape<NB>::THREADS) void fwd_stats_small(FcArg
         float m = NEG_INF, s = 0.0f;
 #pragma unroll
         for (int e = 0; e < S::CPT; ++e) m = fmaxf(m, z[e]);
-        const float shift = m == NEG_INF ? 0.0f : -m * LOG2E;
+        const float shift = exp_shift(m);
 #pragma unroll
         for (int e = 0; e < S::CPT; ++e) s += __builtin_amdgcn_exp2f(fmaf(z[e], LOG2E, shift));
         merge_ms(mx, sum, m, s);
@@ -1440,7 +1444,7 @@ __global__ __launch_bounds__(NTHREADS, 4) void fwd_stats_block(FcArgs a, int pit
     for (int x = 0; x < 2; ++x)
 #pragma unroll
         for (int v = 0; v < 4; ++v) mx = fmaxf(mx, z[x][v]);
-    const float shift = mx == NEG_INF ? 0.0f : -mx * LOG2E;
+    const float shift = exp_shift(mx);
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
