@@ -145,22 +145,31 @@ struct BwdPlan {
 constexpr int ONE_LAUNCH_NS = 4000;
 static void dx_splits(BwdPlan& p, int32_t B, int32_t D) {
     const int64_t sum_turns = ((int64_t)B * (D / 4) + SIDE_BLOCKS * NTHREADS - 1) / (SIDE_BLOCKS * NTHREADS);   // of the side job's threads
-    const int64_t bytes = (int64_t)B * D * 4;
+    const int64_t sum_cost = 2 * ((int64_t)B * D * 4) / 4500 + sum_turns * 1000 / 16;                            // of a split
     int64_t best = -1;
     for (int small = 0; small < 2; ++small) {
-        const int64_t tiles = small ? (int64_t)(D / BLOCK) * ((B + BLOCK - 1) / BLOCK) : (int64_t)p.nDT * p.nBT;
+        const int64_t tiles = small ? (int64_t)(D / BLOCK) * (round_up(B, BLOCK) / BLOCK) : (int64_t)p.nDT * p.nBT;
         const int room = small ? 512 : 256, most = std::min(tiles >= room ? 1 : (int)((room + tiles - 1) / tiles), p.steps_total);
-        for (int want = 1; want <= most; ++want) {
-            const int steps = (p.steps_total + want - 1) / want, splits = (p.steps_total + steps - 1) / steps;
+        // from one number of splits to the next that makes them shorter, as long as their sum alone does not cost more
+        for (int splits = 1, steps = p.steps_total; splits <= most && (splits == 1 || splits * sum_cost < best);) {
             const int64_t turns = (tiles * splits + 255) / 256;
-            const int64_t cost = (small ? turns * 320 * steps + 1500 : turns * (1300 * steps + 6000)) +
-                                 splits * (2 * bytes / 4500 + sum_turns * 1000 / 16) -
+            const int64_t cost = (small ? turns * 320 * steps + 1500 : turns * (1300 * (int64_t)steps + 6000)) + splits * sum_cost -
                                  (small && splits == 1 && p.dw_small ? ONE_LAUNCH_NS : 0);
-            if (best >= 0 && cost >= best) continue;
-            best = cost;
-            p.steps_per_split = steps;
-            p.splits = splits;
-            p.dx_small = small;
+            if (best < 0 || cost < best) {
+                best = cost;
+                p.steps_per_split = steps;
+                p.splits = splits;
+                p.dx_small = small;
+            }
+            // every number of splits up to the root of the k-steps makes them shorter, and every length below it is some number's
+            if ((int64_t)splits * (splits + 1) <= p.steps_total) {
+                ++splits;
+                steps = (p.steps_total + splits - 1) / splits;
+            } else if (--steps > 0) {
+                splits = (p.steps_total + steps - 1) / steps;
+            } else {
+                break;
+            }
         }
     }
 }

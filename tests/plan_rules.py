@@ -22,6 +22,13 @@ int descending_(int B, int D, int C, int ct, int bt) {
     return logits_descending(logits_order(p), p.ranges, (B + 255) / 256, ct, bt);
 }
 int ranges_(int D, int C, int nBT) { return plan_ranges(D, C, nBT).ranges; }
+void dx_splits_(int B, int D, int C, int* out) {
+    const BwdPlan p = plan_bwd(B, D, C);
+    out[0] = p.dx_small;
+    out[1] = p.splits;
+    out[2] = p.steps_per_split;
+    out[3] = p.dw_small;
+}
 size_t bwd_bytes_(int B, int D, int C) { return plan_bwd(B, D, C).bytes(); }
 }
 """

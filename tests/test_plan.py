@@ -1,4 +1,5 @@
 """Host checks of the rules that pick the kernels of a call and size its workspace (csrc/plan.h)."""
+import ctypes
 import random
 
 import pytest
@@ -99,3 +100,24 @@ def test_every_kind_of_tile_walks_the_features_in_one_direction(rules):
             assert not any(got.values()), (B, D, C, ways)
         seen.add(tuple(ways.values()))
     assert {(BLOCKS, BLOCKS, TILES), (LISTS, TILES, TILES), (LISTS, BLOCKS, BLOCKS), (TILES, TILES, TILES), (SMALL, SMALL, SMALL)} <= seen
+
+
+def test_splits_of_dx_are_the_cheapest(rules):
+    """The search skips numbers of splits; trying each of them finds nothing better, and nothing as good that comes earlier."""
+    out = (ctypes.c_int * 4)()
+    for B, D, C in [*drawn(1500, seed=5, max_b=20000), *((1, 64, 64 * t) for t in range(1, 400)), (32, 64, 30000), (64, 64, 100000), (1, 64, 1), (1, 64, 2 ** 31 - 1)]:
+        rules.dx_splits_(B, D, C, out)
+        total, best = (C + 63) // 64, None
+        turns_of_the_sum = -(-B * (D // 4) // (128 * 512))
+        for small in (0, 1):
+            tiles = D // 64 * -(-B // 64) if small else -(-D // 256) * -(-B // 256)
+            room = 512 if small else 256
+            for want in range(1, min(max(1, -(-room // tiles)), total) + 1):
+                steps = -(-total // want)
+                splits, turns = -(-total // steps), -(-tiles * -(-total // steps) // 256)
+                cost = turns * 320 * steps + 1500 if small else turns * (1300 * steps + 6000)
+                cost += splits * (8 * B * D // 4500 + turns_of_the_sum * 1000 // 16) - (4000 if small and splits == 1 and out[3] else 0)
+                if best is None or cost < best[0]:
+                    best = (cost, small, splits, steps)
+        assert (out[0], out[1], out[2]) == best[1:], (B, D, C)
+        assert (out[1] - 1) * out[2] < total <= out[1] * out[2]
