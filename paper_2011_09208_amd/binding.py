@@ -115,11 +115,14 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-_current_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+try:
+    from torch._C import _cuda_getCurrentRawStream, _cuda_getDevice
 
-
-def _stream():
-    return _current_raw_stream(_current_device())
+    def _stream():
+        return _cuda_getCurrentRawStream(_cuda_getDevice())
+except ImportError:                      # PyTorch's own names, which a build without a GPU lacks: the host functions work there, too
+    def _stream():
+        return torch.cuda.current_stream().cuda_stream
 
 
 def status_string(status):

@@ -3,6 +3,8 @@ header declares, and rejects bad arguments before any HIP call."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -25,6 +27,17 @@ def test_header_symbols_are_exported(ws):
     assert declared == set(ws.EXPORTS)
     for name in declared:
         assert getattr(ws.lib, name) is not None
+
+
+def test_binding_loads_without_pytorchs_own_names():
+    """A PyTorch without a GPU build has no raw stream; the functions that run on the host do not ask for one."""
+    code = ("import torch\n"
+            "for n in ('_cuda_getCurrentRawStream', '_cuda_getDevice'): delattr(torch._C, n)\n"
+            "from paper_2011_09208_amd import binding as ws\n"
+            "assert ws.version() >= 1000 and ws.status_string(0) == 'WS_OK' and ws.bwd_workspace_bytes(4, 64, 8) > 0\n"
+            "print(ws.balance_widths(100, [1.0, 1.0], [1e9, 1e9], 1.0, 1.0))\n")
+    out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert out.returncode == 0, out.stderr
 
 
 def test_version_and_status_strings(ws):
