@@ -226,7 +226,11 @@ static RangePlan plan_ranges(int32_t D, int32_t C, int nBT) {
 //   a single round: lists while they halve a tile or better (81 tiles, B = 2300, D = 2048, C = 2117: 40.4 + 45.0 and 35.7 + 44.0; 94,
 //     B = 300, D = 2048, C = 12 000: 39.6 + 43.1 and 35.3 + 37.9; 144, B = 777, D = 1088, C = 9001: 26.4 + 30.0 and 26.3 + 29.6; 196,
 //     B = 1024, D = 2048, C = 12 500: 43.2 + 48.2 and 47.5 + 52.6);
-//   more: short contractions, whose tiles are mostly epilogue (B = 3000, D = 128, C = 20 000: 40.3 + 58.9 and 34.7 + 48.9), and longer ones if
+//   more: not as several lists to a compute unit of less than a tile and a half each, which hardly run on from one tile into the next, and
+//     end and start again instead (forward, tiles and lists, units of a list: B = 1408, D = 64, C = 13 471, 5: 15.8 and 19.4; B = 5409, D = 128, C =
+//     2909, 4: 17.5 and 21.0; B = 1408, D = 256, C = 24 271, 6: 33.1 + 45.3 and 35.8 + 46.7; B = 14 734, D = 192, C = 3268, 8: 34.5 + 53.8 and 38.1 +
+//     50.4; B = 38 406, D = 64, C = 1611, 10: 39.5 + 62.1 and 43.9 + 63.6; 12.8, B = 25 686, C = 1993: 35.8 and 36.7, 14.6, B = 18 464, C = 3220: 37.5 and 36.0);
+//     of these, short contractions, whose tiles are mostly epilogue (B = 3000, D = 128, C = 20 000: 40.3 + 58.9 and 34.7 + 48.9), and longer ones if
 //     the rest is half a tile or less (B = 700, D = 1024, C = 50 000: 80.5 + 93.6 and 75.1 + 85.4; B = 1024, D = 2048, C = 37 500:
 //     140 + 152 and 131 + 140; B = 8192, D = 1024, C = 50 000: 691 + 794 and 662 + 744; against a rest of five units, B = 256, D = 2048,
 //     C = 100 000: 120 + 121, dX 94.5 and 117 + 121, 99.0), except that long tiles over many rounds, where a workgroup that is
@@ -241,6 +245,7 @@ static bool logits_list(const RangePlan& p, int nBT, int nCT, int k_steps) {
     const int rest = p.per + (p.more > 0);
     if (tiles <= 64) return false;
     if (tiles <= 256) return p.full == 0 && rest <= MAX_UNITS / 2;
+    if (p.ranges * nBT > LIST_WGS && MAX_UNITS * p.full + p.per < 3 * MAX_UNITS / 2) return false;
     const int64_t tail = tiles % LIST_WGS;
     if (tail > 0 && tail <= LOGITS_MAX_THIN_TAIL &&
         (tiles < 2 * LIST_WGS ? k_steps > 2 : tiles < 3 * LIST_WGS && k_steps > (tail > LOGITS_MAX_THIN_TAIL / 2 ? 8 : 16))) return false;
@@ -286,6 +291,15 @@ static LogitsPlan plan_logits(int32_t B, int32_t D, int32_t C, SmallUse use) {
     }
     return p;
 }
+// The forward call: as the step, but a single k-step and a single round of wide tiles, or one with a tail of thin ones, are done
+// sooner by the tiles; dz, whose epilogue is longer, is not (forward, us, tiles and lists, D = 64: 114 tiles, B = 94, C = 29 001: 11.2 and
+// 12.0, dz 1.3 less; 297, B = 2303, C = 8376: 15.6 and 16.6; 312, B = 3002, C = 6596: 15.7 and 16.5; but 432, B = 4363, C = 6004: 19.3 and 18.5; two
+// k-steps, 110, B = 1100, C = 5377, and fewer: 12.3 to 13.3 and 11.7 to 12.8).  Both add the products of a logit in one order.
+static LogitsPlan plan_forward(int32_t B, int32_t D, int32_t C, const LogitsPlan& step) {
+    const int64_t tiles = round_up(B, TILE_N) / TILE_N * (round_up(C, TILE_M) / TILE_M);
+    return step.way == WAY_LISTS && D <= TILE_K && tiles <= LIST_WGS + LOGITS_MAX_THIN_TAIL ? plan_wide(B, C) : step;
+}
+
 // Direction in which the logits of class tile ct and batch tile bt (256 x 256) walk the features, a function of the shard's
 // step and the tile's coordinates alone, so that every kernel (and the thin and the full version of a tile) adds the products
 // of a logit in the same order:
@@ -311,7 +325,7 @@ __host__ __device__ inline bool logits_descending(LogitsOrder order, const Range
 // The workspace that the forward call and the arg-max want, and the one that either does with.
 static size_t least_fwd_bytes(int32_t B, int32_t C) { return plan_wide(B, C).bytes(); }
 static size_t fwd_bytes(int32_t B, int32_t D, int32_t C) {
-    return std::max({least_fwd_bytes(B, C), plan_logits(B, D, C, SMALL_STEP).bytes(), plan_logits(B, D, C, SMALL_TOP1).bytes()});
+    return std::max({least_fwd_bytes(B, C), plan_forward(B, D, C, plan_logits(B, D, C, SMALL_STEP)).bytes(), plan_logits(B, D, C, SMALL_TOP1).bytes()});
 }
 
 }  // namespace ws

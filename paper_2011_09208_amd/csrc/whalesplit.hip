@@ -2141,9 +2141,10 @@ static int launch_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t l
     a.Bpad = (int)round_up(B, 256);
     a.nBT = a.Bpad / 256;
     a.nCT = (int)(round_up(C_shard, 256) / 256);
-    LogitsPlan p = plan_logits(B, D, C_shard, SMALL_STEP);
-    a.order = logits_order(p);
-    a.ranges = p.ranges;
+    const LogitsPlan step = plan_logits(B, D, C_shard, SMALL_STEP);
+    a.order = logits_order(step);
+    a.ranges = step.ranges;
+    LogitsPlan p = plan_forward(B, D, C_shard, step);
     if (workspace_bytes < p.bytes()) p = plan_wide(B, C_shard);
     float* part_max = static_cast<float*>(workspace);
     float* part_sum = part_max + p.parts * p.pitch;

@@ -6,15 +6,18 @@ import subprocess
 from paper_2011_09208_amd import buildlib
 
 PLAN = os.path.join(buildlib.PKG, "csrc", "plan.h")
-STEP, PROBS, TOP1 = 0, 1, 2                              # SmallUse
+STEP, PROBS, TOP1, FORWARD = 0, 1, 2, 3                  # SmallUse, and the forward call's own
 SMALL, BLOCKS, LISTS, TILES = 0, 1, 2, 3                 # LogitsWay
 SHIM = """#include "%s"
 using namespace ws;
 extern "C" {
 size_t fwd_bytes_(int B, int D, int C) { return fwd_bytes(B, D, C); }
 size_t least_fwd_bytes_(int B, int C) { return least_fwd_bytes(B, C); }
-size_t way_bytes_(int B, int D, int C, int use) { return plan_logits(B, D, C, (SmallUse)use).bytes(); }
-int way_(int B, int D, int C, int use) { return plan_logits(B, D, C, (SmallUse)use).way; }
+static LogitsPlan plan(int B, int D, int C, int use) {
+    return use == 3 ? plan_forward(B, D, C, plan_logits(B, D, C, SMALL_STEP)) : plan_logits(B, D, C, (SmallUse)use);
+}
+size_t way_bytes_(int B, int D, int C, int use) { return plan(B, D, C, use).bytes(); }
+int way_(int B, int D, int C, int use) { return plan(B, D, C, use).way; }
 unsigned quotient_(unsigned n, unsigned d) { return quotient(n, inverse(d)); }
 unsigned list_quotient_(unsigned n, int D, int C, int nBT) { return quotient(n, plan_ranges(D, C, nBT).inv_ranges); }
 int descending_(int B, int D, int C, int ct, int bt) {

@@ -10,22 +10,26 @@ from paper_2011_09208_amd import inputs
 pytestmark = pytest.mark.gpu
 
 SHAPES = [                               # B, D, C
-    (70, 64, 256 * 65 - 40),             # 1 batch tile, 65 class tiles, 1 k-step; rests of 2 and 3 units
-    (257, 64, 256 * 33 - 7),             # 2; 66 tiles
+    (70, 64, 256 * 65 - 40),             # 1 batch tile, 65 class tiles, 1 k-step; rests of 2 and 3 units; the forward call on tiles
+    (257, 64, 256 * 33 - 7),             # 2; 66 tiles; the same
     (300, 128, 256 * 129),               # 2; a whole tile, 8 workgroups of 128 columns with a rest of one unit
     (513, 1088, 256 * 40),               # 3; 17 k-steps, rests of 3 and 4
     (600, 64, 256 * 170 + 33),           # 3; two whole tiles
-    (700, 576, 256 * 86 + 65),           # 3; 9 k-steps, rests of one unit and none
-    (700, 576, 256 * 112 + 65),          # 3; 339 tiles: the same behind a whole one (of 264 the last 8 run as thin tiles)
+    (700, 576, 256 * 86 + 65),           # 3; 9 k-steps, 261 tiles: wide ones, the last 5 as thin tiles
+    (700, 576, 256 * 112 + 65),          # 3; 339 tiles: a whole one and rests of 2 and 3 units
     (600, 640, 256 * 170 + 33),          # 3; 513 tiles, 10 k-steps: lists
     (1000, 576, 256 * 136),              # 4; 544 and a tail of 32: lists
     (1000, 576, 256 * 137),              # 548, one of 36: tiles
     (1000, 192, 256 * 17 + 1),           # 4; 72 tiles, 3 k-steps
     (1100, 128, 256 * 21 + 1),           # 5: a block of four and one
     (1400, 192, 256 * 13 - 100),         # 6
-    (1700, 64, 2600),                    # 7
+    (1700, 64, 2600),                    # 7; the forward call on tiles
     (2100, 64, 256 * 40 - 31),           # 9: two blocks and one
-    (33000, 64, 500),                    # 129
+    (33000, 64, 500),                    # 129 batch tiles, 258 tiles: wide ones
+    (70, 192, 256 * 65 - 40),            # forward and dz
+    (1100, 192, 256 * 21 + 1),
+    (1700, 192, 2600),
+    (30000, 128, 1500),                  # 118 batch tiles, three whole tiles and no rest
 ]
 
 
@@ -58,7 +62,7 @@ def test_forward_with_a_partial_result_per_class_tile(H):
     the same numbers, the sums differ in their order only (two fp32 roundings per merge of the 33 and 128 partial sums)."""
     import torch
     from paper_2011_09208_amd import binding as ws
-    B, D, C = 257, 64, 256 * 33 - 7
+    B, D, C = 257, 192, 256 * 33 - 7
     p = inputs.make_inputs("list", B, D, C, x_sigma=1.0, w_sigma=0.3, seed=1)
     X, W, y = H.dev_bf16(p.X_bits), H.dev_bf16(p.W_bits), torch.from_numpy(np.ascontiguousarray(p.labels, dtype=np.int32)).cuda()
     least, full = 2 * 33 * 512 * 4, ws.fwd_workspace_bytes(B, D, C)

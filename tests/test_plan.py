@@ -6,7 +6,7 @@ import pytest
 
 from paper_2011_09208_amd import buildlib
 from tests import plan_rules
-from tests.plan_rules import BLOCKS, LISTS, PROBS, SMALL, STEP, TILES, TOP1
+from tests.plan_rules import BLOCKS, FORWARD, LISTS, PROBS, SMALL, STEP, TILES, TOP1
 
 
 @pytest.fixture(scope="module")
@@ -41,10 +41,10 @@ def test_the_rules_tested_here_are_the_librarys(rules, ws):
         assert rules.bwd_bytes_(B, D, C) == ws.bwd_workspace_bytes(B, D, C), (B, D, C)
 
 
-@pytest.mark.parametrize("B,D,C,want", [(300, 2048, 12000, 2 * 128 * 512 * 4), (257, 64, 8441, 2 * 128 * 512 * 4),
+@pytest.mark.parametrize("B,D,C,want", [(300, 2048, 12000, 2 * 128 * 512 * 4), (257, 192, 8441, 2 * 128 * 512 * 4),
                                         (100, 2048, 20000, 2 * 256 * 256 * 4), (85, 192, 30922, 2 * 256 * 256 * 4)])
 def test_forward_query_holds_the_lists_where_the_arg_max_takes_blocks(rules, ws, B, D, C, want):
-    assert rules.way_(B, D, C, STEP) == LISTS and ws.fwd_workspace_bytes(B, D, C) == want
+    assert rules.way_(B, D, C, FORWARD) == LISTS and ws.fwd_workspace_bytes(B, D, C) == want
 
 
 def test_forward_query_is_what_the_calls_compare_with(rules, ws):
@@ -52,12 +52,12 @@ def test_forward_query_is_what_the_calls_compare_with(rules, ws):
     per class tile of 256, is never more than that.  Where the former size fits the built-in scratch, so does what the call wants."""
     lists = 0
     for B, D, C in [*drawn(30000, seed=2), (2 ** 31 - 1, 64, 2 ** 31 - 1), (1, 64, 2 ** 31 - 1), (20, 64, 2 ** 31 - 1), (2 ** 31 - 1, 64, 1)]:
-        step, top1, least = rules.way_bytes_(B, D, C, STEP), rules.way_bytes_(B, D, C, TOP1), rules.least_fwd_bytes_(B, C)
+        step, top1, least = rules.way_bytes_(B, D, C, FORWARD), rules.way_bytes_(B, D, C, TOP1), rules.least_fwd_bytes_(B, C)
         assert least == 2 * ((C + 255) // 256) * ((B + 255) // 256 * 256) * 4
         assert ws.fwd_workspace_bytes(B, D, C) == max(step, top1, least), (B, D, C)
         if least <= ws.STATIC_SCRATCH_BYTES:
             assert step <= ws.STATIC_SCRATCH_BYTES, (B, D, C)
-        lists += rules.way_(B, D, C, STEP) == LISTS
+        lists += rules.way_(B, D, C, FORWARD) == LISTS
     assert lists > 3000
 
 
@@ -72,7 +72,7 @@ def test_quotients_of_the_list_kernels(rules):
                     assert rules.quotient_(n, d) == n // d, (n, d)
 
 
-@pytest.mark.parametrize("B,D,C,ranges", [(50000, 128, 600, 1), (65536, 512, 1000, 1), (44000, 128, 600, 4), (600, 640, 43553, 85)])
+@pytest.mark.parametrize("B,D,C,ranges", [(50000, 128, 600, 1), (65536, 512, 1000, 1), (20000, 128, 2000, 3), (600, 640, 43553, 85)])
 def test_whole_tiles_of_a_list_are_a_range_apart(rules, B, D, C, ranges):
     assert rules.way_(B, D, C, STEP) == LISTS and rules.ranges_(D, C, (B + 255) // 256) == ranges
     for ct in range((C + 255) // 256):
@@ -121,3 +121,34 @@ def test_splits_of_dx_are_the_cheapest(rules):
                     best = (cost, small, splits, steps)
         assert (out[0], out[1], out[2]) == best[1:], (B, D, C)
         assert (out[1] - 1) * out[2] < total <= out[1] * out[2]
+
+
+def test_short_lists_have_a_compute_unit_of_their_own(rules):
+    """More than 256 tiles: several lists on a compute unit are of 12 units of 32 classes (a tile and a half) or more."""
+    for B, D, C in [(1408, 64, 13471), (1408, 256, 24271), (3261, 64, 8679), (5409, 128, 2909), (14734, 192, 3268), (38406, 64, 1611)]:
+        assert rules.way_(B, D, C, STEP) == TILES
+    for B, D, C in drawn(10000, seed=6):
+        nBT, nCT = (B + 255) // 256, (C + 255) // 256
+        ranges = rules.ranges_(D, C, nBT)
+        if rules.way_(B, D, C, STEP) == LISTS and nBT * nCT > 256 < ranges * nBT:
+            assert 2 * ((C + 63) // 64) >= 12 * ranges, (B, D, C)
+
+
+def test_the_forward_call_of_a_short_contraction_runs_a_single_round_on_tiles(rules):
+    for B, D, C, way in [(94, 64, 29001, TILES), (94, 128, 29001, LISTS), (2303, 64, 8376, TILES), (4363, 64, 6004, LISTS)]:
+        assert rules.way_(B, D, C, STEP) == LISTS and rules.way_(B, D, C, FORWARD) == way, (B, D, C)
+    for B, D, C in drawn(10000, seed=7):
+        step, forward = rules.way_(B, D, C, STEP), rules.way_(B, D, C, FORWARD)
+        assert forward == step or (step, forward) == (LISTS, TILES)
+
+
+def test_shapes_of_the_list_tests_run_lists(rules):
+    """Which of the shapes of test_gpu_list.py (a whole shard) run lists, both ways or dz alone: their tests must not lose them unnoticed."""
+    from tests.test_gpu_list import SHAPES
+    tiles = {(700, 576, 22081), (1000, 576, 35072), (33000, 64, 500)}
+    dz_alone = {(70, 64, 16600), (257, 64, 8441), (1700, 64, 2600)}
+    for shape in SHAPES:
+        step, forward = rules.way_(*shape, STEP), rules.way_(*shape, FORWARD)
+        assert step == (TILES if shape in tiles else LISTS), shape
+        assert forward == (TILES if shape in tiles | dz_alone else LISTS), shape
+    assert rules.way_(257, 192, 8441, FORWARD) == LISTS
