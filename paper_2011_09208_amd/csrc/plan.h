@@ -26,6 +26,7 @@ struct RangePlan {
     uint32_t inv_ranges;
 };
 
+constexpr int64_t INFINITY_CACHE_BYTES = (int64_t)256 << 20;
 static inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 static inline int xcd_grid(int n_tiles) { return 8 * ((n_tiles + 7) / 8); }
 
@@ -75,7 +76,7 @@ static bool dw_streams(int nDT, int n_full, int k_steps, int64_t lddw) {
 // tiles: 8: 1.06 at 4 k-steps, 1.02 at 16, 1.006 at 24, 0.98 at 32, 0.99 at 64; 5: 1.04 at 6, 1.01 at 16, 1.005 at 24, 0.99 at 32;
 // 3: 1.00 at 10 to 16; 2: 0.98 to 1.00; 1: 0.91 to 0.94.
 static bool dw_prefetches(int nDT, int64_t dz_and_w_bytes, int k_steps) {
-    return nDT >= 4 && k_steps <= 24 && dz_and_w_bytes > ((int64_t)256 << 20);
+    return nDT >= 4 && k_steps <= 24 && dz_and_w_bytes > INFINITY_CACHE_BYTES;
 }
 // Workgroups appended to a GEMM launch for its small side job (X^T, the final reductions).
 static const int SIDE_BLOCKS = 128;
@@ -142,12 +143,17 @@ struct BwdPlan {
 // Wide and small tiles, dX / step: B = 32, D = 256, C = 8000 12.4 / 30.6 and 7.0 / 27.3; B = 400, D = 128, C = 12 000 17.8 / 56.3 and
 // 9.2 / 47.6; B = 1500, D = 256, C = 8000 20.2 / 75.8 and 19.3 / 67.3; B = 3000, D = 256, C = 8000 28.0 / 118.5 and 38.1 / 116.2; B = 800, D =
 // 2048, C = 3000 22.6 / 93.4 and 29.8 / 94.7; B = 800, D = 256, C = 40 000 30.0 / 134.2 and 45.2 / 143.3.
+// A W that the 256 MiB Infinity Cache does not hold comes from HBM, and the 128 bytes that a small tile takes of each of its rows cost more
+// there: wide tiles (backward call, us, wide and small, D = 2048: B = 64, C = 62 000, 254 MB 158.1 and 152.3, C = 70 000, 287 MB 172.2 and 180.4;
+// B = 24, C = 80 000: 181.7 and 192.7, with the fused update 250.7 and 277.0; D = 1536, B = 32, C = 80 000, 246 MB 136.1 and 133.1, C = 90 000, 276 MB
+// 155.3 and 159.8).
 constexpr int ONE_LAUNCH_NS = 4000;
-static void dx_splits(BwdPlan& p, int32_t B, int32_t D) {
+static void dx_splits(BwdPlan& p, int32_t B, int32_t D, int32_t C) {
     const int64_t sum_turns = ((int64_t)B * (D / 4) + SIDE_BLOCKS * NTHREADS - 1) / (SIDE_BLOCKS * NTHREADS);   // of the side job's threads
     const int64_t sum_cost = 2 * ((int64_t)B * D * 4) / 4500 + sum_turns * 1000 / 16;                            // of a split
+    const bool w_fits_cache = (int64_t)C * D * 2 <= INFINITY_CACHE_BYTES;
     int64_t best = -1;
-    for (int small = 0; small < 2; ++small) {
+    for (int small = 0; small < (w_fits_cache ? 2 : 1); ++small) {
         const int64_t tiles = small ? (int64_t)(D / BLOCK) * (round_up(B, BLOCK) / BLOCK) : (int64_t)p.nDT * p.nBT;
         const int room = small ? 512 : 256, most = std::min(tiles >= room ? 1 : (int)((room + tiles - 1) / tiles), p.steps_total);
         // from one number of splits to the next that makes them shorter, as long as their sum alone does not cost more
@@ -188,7 +194,7 @@ static BwdPlan plan_bwd(int32_t B, int32_t D, int32_t C) {
     p.nDT = (int)(round_up(D, 256) / 256);
     p.steps_total = (int)(round_up(C, TILE_K) / TILE_K);
     p.dw_small = dw_blocks(D, C, (B + TILE_K - 1) / TILE_K);
-    dx_splits(p, B, D);
+    dx_splits(p, B, D, C);
     p.dz_bytes = (size_t)p.Bpad * p.Cpad * 2;
     p.xt_bytes = (size_t)D * p.Bpad * 2;
     p.dbp_bytes = (size_t)4 * p.nBT * p.Cpad * 4;        // one db partial per 64-row wave column

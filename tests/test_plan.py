@@ -105,11 +105,12 @@ def test_every_kind_of_tile_walks_the_features_in_one_direction(rules):
 def test_splits_of_dx_are_the_cheapest(rules):
     """The search skips numbers of splits; trying each of them finds nothing better, and nothing as good that comes earlier."""
     out = (ctypes.c_int * 4)()
-    for B, D, C in [*drawn(1500, seed=5, max_b=20000), *((1, 64, 64 * t) for t in range(1, 400)), (32, 64, 30000), (64, 64, 100000), (1, 64, 1), (1, 64, 2 ** 31 - 1)]:
+    for B, D, C in [*drawn(1500, seed=5, max_b=20000), *((1, 64, 64 * t) for t in range(1, 400)), (32, 64, 30000), (64, 64, 100000), (1, 64, 1), (1, 64, 2 ** 31 - 1),
+                    (64, 2048, 65536), (64, 2048, 65537)]:
         rules.dx_splits_(B, D, C, out)
         total, best = (C + 63) // 64, None
         turns_of_the_sum = -(-B * (D // 4) // (128 * 512))
-        for small in (0, 1):
+        for small in (0, 1) if 2 * C * D <= 2 ** 28 else (0,):
             tiles = D // 64 * -(-B // 64) if small else -(-D // 256) * -(-B // 256)
             room = 512 if small else 256
             for want in range(1, min(max(1, -(-room // tiles)), total) + 1):
