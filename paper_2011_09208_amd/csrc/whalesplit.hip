@@ -1987,10 +1987,10 @@ __global__ __launch_bounds__(NTHREADS) void bwd_dw_traced(DwArgs a, FinishArgs f
 
 static inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
-// The mean is taken by the combine launch itself while one workgroup is as quick as two launches; us, two launches and one: B = 32,
-// 8 shards 3.5 and 2.5 (and a launch less on the host, 3.7); B = 1024 4.1 and 3.2; B = 2048 4.5 and 4.3, 16 shards 5.1 and 7.6; B =
-// 4096 4.8 and 6.3.
-constexpr int COMBINE_MEAN_ROWS = 2048;
+// The mean is taken by the combine launch itself while one workgroup is as quick as two launches; us, two launches and one, 1 to 8 shards
+// (and a launch less on the host, 3.7): B = 32 3.5 and 2.5; B = 1024 4.1 and 3.1; B = 1536 4.1 and 3.6; B = 1792 4.2 and 3.9; B = 1857, where the
+// rows of the second turn end within a wave, 4.2 and 4.7; B = 1920 4.2 and 4.1; B = 4096 4.8 and 6.3; 16 shards, B = 2048 5.1 and 7.6.
+constexpr int COMBINE_MEAN_ROWS = 1792;
 #define WS_LAUNCH_SMALL(kid, name, plan, grid, stream, ...)                                                   \
     do {                                                                                                      \
         if ((plan).rows == 16) WS_LAUNCH(kid, name<1>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__); \

@@ -54,10 +54,10 @@ def test_combine_top1_groups_of_candidates(ws, S, B):
     assert (bv.cpu().numpy() == rv).all() and (bc.cpu().numpy() == rc).all()
 
 
-@pytest.mark.parametrize("B", [1, 1023, 1025, 2048, 2049])
+@pytest.mark.parametrize("B", [1, 1023, 1025, 1792, 1793, 2048, 2049])
 @pytest.mark.parametrize("S", [1, 8, 9])
 def test_mean_in_the_combine_launch(B, S):
-    """Up to 2048 rows and 8 shards one workgroup does it all: rows bit for bit as without the mean, the mean within the
+    """Up to 1792 rows and 8 shards one workgroup does it all: rows bit for bit as without the mean, the mean within the
     rounding of its B fp32 additions."""
     import torch
     from paper_2011_09208_amd import binding as ws
