@@ -113,9 +113,12 @@ static bool small_batch(int32_t B, int32_t D, int32_t C, SmallUse use) {
 // dz: 125 (D = 4096, C = 8000) 45.2 + 46.8 and 19.8 + 20.2; 1094 (D = 1024, C = 70 000) 38.9 + 53.1 and 27.5 + 29.5; 1954 (D = 64, C = 125 000)
 // 18.6 + 29.6 and 15.2 + 17.2, D = 2048: 105.7 + 107.9 and 95.3 + 107.5, but D = 3072: 141.9 + 154.6 and 147.5 + 162.7, where two full
 // rounds of wide tiles read W as fast.  Arg-max of the same: D = 1024: 50.2 and 46.4, D = 256: 25.8 and 25.2, but D = 64: 16.6 and 19.8,
-// four times the candidates to merge.
+// four times the candidates to merge; likewise within one round of wide tiles, from the fourth block of a compute unit on: 64 rows, D =
+// 64, 760 blocks 10.6 and 10.8, 820 10.6 and 11.7, 1024 10.7 and 12.1, but 1150 15.9 and 14.1; D = 192: 900 12.8 and 13.0; D = 256: 13.8 and
+// 13.5; 128 rows, D = 64: 820 10.2 and 10.5, 1024 10.4 and 11.0, D = 128: 11.6 and 11.5.
 static bool logits_blocks(int32_t B, int32_t D, int32_t C, SmallUse use) {
     const int64_t rows = round_up(B, BLOCK) / BLOCK, tiles = rows * (round_up(C, BLOCK) / BLOCK);
+    if (use == SMALL_TOP1 && tiles > 768 && tiles <= 1024 && D < (rows == 1 ? 256 : 128)) return false;
     if (rows == 1) return tiles <= 1280 || (D <= 2048 && (use != SMALL_TOP1 || D >= 256));
     return tiles <= (use == SMALL_STEP ? 512 : 1024);
 }

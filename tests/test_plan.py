@@ -153,3 +153,11 @@ def test_shapes_of_the_list_tests_run_lists(rules):
         assert step == (TILES if shape in tiles else LISTS), shape
         assert forward == (TILES if shape in tiles | dz_alone else LISTS), shape
     assert rules.way_(257, 192, 8441, FORWARD) == LISTS
+
+
+@pytest.mark.parametrize("B,D,tiles,way", [(64, 192, 768, BLOCKS), (64, 192, 769, TILES), (33, 64, 1024, TILES), (64, 192, 1025, BLOCKS), (64, 256, 1024, BLOCKS),
+                                           (128, 64, 768, BLOCKS), (128, 64, 770, TILES), (128, 128, 1024, BLOCKS), (128, 128, 1026, TILES)])
+def test_arg_max_of_short_contractions(rules, B, D, tiles, way):
+    C = 64 * (tiles // ((B + 63) // 64))
+    assert rules.way_(B, D, C, TOP1) == way
+    assert rules.way_(B, D, C, PROBS) == (BLOCKS if tiles <= 1024 or B <= 64 else TILES)
