@@ -14,20 +14,18 @@ namespace ws {
 constexpr int SMALL_MAX_ROWS = 32;
 constexpr int SMALL_MAX_STEPS = 32;          // k-steps of X that the registers of a workgroup hold
 constexpr int SMALL_C = 32;                  // classes at a time
+constexpr int SMALL_WAVES = 8, SMALL_THREADS = 64 * SMALL_WAVES;
 constexpr int SMALL_PITCH = SMALL_C + 4;     // floats per row of a partial sum
 
 // NB = 16-row blocks of the batch (1 or 2).  The finished logits are dealt out CPT classes of one row per thread,
 // the TPR threads of a row side by side in one wave.
 template <int NB> struct SmallShape {
     static constexpr int ROWS = 16 * NB;
-    static constexpr int WAVES = 8;
-    static constexpr int THREADS = 64 * WAVES;
-    static constexpr int STEPS = SMALL_MAX_STEPS / WAVES;    // k-steps per wave
-    static constexpr int CPT = SMALL_C * ROWS / THREADS;     // classes per thread: 1 or 2
+    static constexpr int STEPS = SMALL_MAX_STEPS / SMALL_WAVES;  // k-steps per wave
+    static constexpr int CPT = SMALL_C * ROWS / SMALL_THREADS;   // classes per thread: 1 or 2
     static constexpr int TPR = SMALL_C / CPT;                // threads per row: 32 or 16
     static constexpr int SLOT_FLOATS = ROWS * SMALL_PITCH;
-    static constexpr int LDS_FLOATS = 2 * WAVES * SLOT_FLOATS;
-    static constexpr int MIN_RANGE = 32;
+    static constexpr int LDS_FLOATS = 2 * SMALL_WAVES * SLOT_FLOATS;
 };
 constexpr int SMALL_MAX_RANGES = 256;        // one per compute unit
 
@@ -63,28 +61,28 @@ __device__ __forceinline__ void small_logits(const uint16_t* X, int64_t ldx, int
         const uint32_t row = a_lane + (uint32_t)c0 * (uint32_t)ldw * 2u;
 #pragma unroll
         for (int n = 0; n < S::STEPS; ++n)
-            if (wave + n * S::WAVES < k_steps) {
+            if (wave + n * SMALL_WAVES < k_steps) {
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
                     for (int s = 0; s < 2; ++s)
                         a[n][t][s] = __builtin_amdgcn_raw_buffer_load_b128(
-                            ra, (int)(row + 32u * t * (uint32_t)ldw + (uint32_t)(128 * n * S::WAVES + 64 * s)), 0, 0);
+                            ra, (int)(row + 32u * t * (uint32_t)ldw + (uint32_t)(128 * n * SMALL_WAVES + 64 * s)), 0, 0);
             }
     };
     load(c_begin);
 #pragma unroll
     for (int n = 0; n < S::STEPS; ++n)
-        if (wave + n * S::WAVES < k_steps) {
+        if (wave + n * SMALL_WAVES < k_steps) {
 #pragma unroll
             for (int r = 0; r < NB; ++r)
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
                     x[n][r][s] = __builtin_amdgcn_raw_buffer_load_b128(
-                        rb, (int)(b_lane + 32u * r * (uint32_t)ldx + (uint32_t)(128 * n * S::WAVES + 64 * s)), 0, 0);
+                        rb, (int)(b_lane + 32u * r * (uint32_t)ldx + (uint32_t)(128 * n * SMALL_WAVES + 64 * s)), 0, 0);
         }
     float* slots = lds;                                      // this tile's partial sums; the next one uses the other half
-    float* other = lds + S::WAVES * S::SLOT_FLOATS;
+    float* other = lds + SMALL_WAVES * S::SLOT_FLOATS;
     for (int c0 = c_begin; c0 < c_end; c0 += SMALL_C) {
         f32x4 acc[2][NB];
 #pragma unroll
@@ -93,7 +91,7 @@ __device__ __forceinline__ void small_logits(const uint16_t* X, int64_t ldx, int
             for (int r = 0; r < NB; ++r) acc[t][r] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int n = 0; n < S::STEPS; ++n)
-            if (wave + n * S::WAVES < k_steps) {
+            if (wave + n * SMALL_WAVES < k_steps) {
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -125,7 +123,7 @@ __device__ __forceinline__ void small_logits(const uint16_t* X, int64_t ldx, int
         for (int e = 0; e < S::CPT; ++e) {
             z[e] = mine[e];
 #pragma unroll
-            for (int w = 1; w < S::WAVES; ++w) z[e] += mine[w * S::SLOT_FLOATS + e];
+            for (int w = 1; w < SMALL_WAVES; ++w) z[e] += mine[w * S::SLOT_FLOATS + e];
             z[e] = c0 + c_mine + e < C ? z[e] + bias_now[e] : -INFINITY;
         }
         body(c0 + c_mine, z);

@@ -83,12 +83,11 @@ static const int SIDE_BLOCKS = 128;
 
 // Small batches: rows that fit the registers of gemm_small.h.
 struct SmallPlan {
-    int rows, range, ranges, threads;
+    int rows, range, ranges;
     SmallPlan(int32_t B, int32_t C) {
         rows = B <= 16 ? 16 : 32;
-        threads = SmallShape<2>::THREADS;
         const int even = (int)round_up(round_up(C, SMALL_MAX_RANGES) / SMALL_MAX_RANGES, 8);   // whole 16-byte stores
-        range = std::max(even, SmallShape<2>::MIN_RANGE);
+        range = std::max(even, SMALL_C);
         ranges = (int)(round_up(C, range) / range);
     }
 };

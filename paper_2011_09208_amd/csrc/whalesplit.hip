@@ -736,21 +736,15 @@ struct XtArgs {
 };
 constexpr int XT_PITCH = 72;             // elements of a row of the transposed tile in LDS
 
-// `lds`: two tiles of 64 x XT_PITCH.
-template <int THREADS>
+// `lds`: two tiles of 64 x XT_PITCH.  Workgroups of NTHREADS, a 16-byte chunk of the tile each.
 __device__ __forceinline__ void transpose_x_tiles(const FcArgs& a, const XtArgs& x, int worker, char* lds) {
-    constexpr int PARTS = 512 / THREADS;                 // a tile is 512 16-byte chunks
     const int nb = (a.B + 63) / 64, n_tiles = nb * (a.D / 64);
     const int row = threadIdx.x >> 3, chunk = threadIdx.x & 7;
-    u32x4 v[PARTS];
+    u32x4 v;
     auto load = [&](int t) {
-        const int b0 = (t % nb) * 64, d0 = (t / nb) * 64;
-#pragma unroll
-        for (int p = 0; p < PARTS; ++p) {
-            const int b = b0 + row + p * (THREADS / 8);
-            v[p] = u32x4{0, 0, 0, 0};
-            if (t < n_tiles && b < a.B) v[p] = *reinterpret_cast<const u32x4*>(a.X + (int64_t)b * a.ldx + d0 + 8 * chunk);
-        }
+        const int b = (t % nb) * 64 + row, d0 = (t / nb) * 64;
+        v = u32x4{0, 0, 0, 0};
+        if (t < n_tiles && b < a.B) v = *reinterpret_cast<const u32x4*>(a.X + (int64_t)b * a.ldx + d0 + 8 * chunk);
     };
     load(worker);
     int buffer = 0;
@@ -759,19 +753,12 @@ __device__ __forceinline__ void transpose_x_tiles(const FcArgs& a, const XtArgs&
         uint16_t* tile = reinterpret_cast<uint16_t*>(lds) + buffer * (64 * XT_PITCH);
         buffer ^= 1;                                     // read two tiles ago, a barrier ago
 #pragma unroll
-        for (int p = 0; p < PARTS; ++p)
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                tile[(8 * chunk + e) * XT_PITCH + row + p * (THREADS / 8)] = (uint16_t)(v[p][e >> 1] >> (16 * (e & 1)));
+        for (int e = 0; e < 8; ++e) tile[(8 * chunk + e) * XT_PITCH + row] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
         load(t + x.n_blocks);
         wait_counts<NO_VM_WAIT, 0>();
         raw_barrier();
-#pragma unroll
-        for (int p = 0; p < PARTS; ++p) {
-            const int d = row + p * (THREADS / 8);
-            *reinterpret_cast<u32x4*>(x.XT + (int64_t)(d0 + d) * x.ldxt + b0 + 8 * chunk) =
-                *reinterpret_cast<const u32x4*>(tile + d * XT_PITCH + 8 * chunk);
-        }
+        *reinterpret_cast<u32x4*>(x.XT + (int64_t)(d0 + row) * x.ldxt + b0 + 8 * chunk) =
+            *reinterpret_cast<const u32x4*>(tile + row * XT_PITCH + 8 * chunk);
     }
 }
 
@@ -862,7 +849,7 @@ __global__ __launch_bounds__(NTHREADS) void bwd_recompute_dz(FcArgs a, const flo
     __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
     float* sbias = reinterpret_cast<float*>(lds);
     if ((int)blockIdx.x >= xt.first_block) {
-        transpose_x_tiles<NTHREADS>(a, xt, (int)blockIdx.x - xt.first_block, lds);
+        transpose_x_tiles(a, xt, (int)blockIdx.x - xt.first_block, lds);
         return;
     }
     const TileRef ref = logits_tile_ref(a);
@@ -1075,7 +1062,7 @@ __global__ __launch_bounds__(NTHREADS) void bwd_dz_list(DzArgs z) {
     __shared__ __attribute__((aligned(16))) char lds[LIST_EXTRA_OFFSET + 8 * DzEpilogue::SCRATCH_BYTES];
     const FcArgs& a = z.a;
     if ((int)blockIdx.x >= z.xt.first_block) {
-        transpose_x_tiles<NTHREADS>(a, z.xt, (int)blockIdx.x - z.xt.first_block, lds);
+        transpose_x_tiles(a, z.xt, (int)blockIdx.x - z.xt.first_block, lds);
         return;
     }
     const LogitsList list(a, true);
@@ -1261,7 +1248,7 @@ __device__ __forceinline__ void small_range(const FcArgs& a, int range, int wg, 
 }
 
 template <int NB>
-__global__ __launch_bounds__(SmallShape<NB>::THREADS) void fwd_stats_small(FcArgs a, int range, float* __restrict__ part_max,
+__global__ __launch_bounds__(SMALL_THREADS) void fwd_stats_small(FcArgs a, int range, float* __restrict__ part_max,
                                                                            float* __restrict__ part_sum,
                                                                            float* __restrict__ label_logit) {
     typedef SmallShape<NB> S;
@@ -1318,13 +1305,13 @@ __device__ __forceinline__ void small_store(uint16_t* out, const float (&v)[N], 
 // dz of the batch's rows (the contractions that read it bound their operand at the batch), up to whole k-steps of
 // classes (zeros beyond the shard: bwd_dx reads those); one db partial.
 template <int NB>
-__global__ __launch_bounds__(SmallShape<NB>::THREADS) void dz_small(FcArgs a, int range, const float* __restrict__ logsumexp,
+__global__ __launch_bounds__(SMALL_THREADS) void dz_small(FcArgs a, int range, const float* __restrict__ logsumexp,
                                                                     float grad_scale, uint16_t* __restrict__ dZ, int64_t ldz,
                                                                     float* __restrict__ db_part, XtArgs xt) {
     typedef SmallShape<NB> S;
     __shared__ __attribute__((aligned(16))) float lds[S::LDS_FLOATS + S::SLOT_FLOATS];
     if ((int)blockIdx.x >= xt.first_block) {
-        transpose_x_tiles<S::THREADS>(a, xt, (int)blockIdx.x - xt.first_block, reinterpret_cast<char*>(lds));
+        transpose_x_tiles(a, xt, (int)blockIdx.x - xt.first_block, reinterpret_cast<char*>(lds));
         return;
     }
     const int row = (int)threadIdx.x / S::TPR, j = (int)threadIdx.x % S::TPR;
@@ -1359,7 +1346,7 @@ __global__ __launch_bounds__(SmallShape<NB>::THREADS) void dz_small(FcArgs a, in
 }
 
 template <int NB>
-__global__ __launch_bounds__(SmallShape<NB>::THREADS) void predict_small(FcArgs a, int range, const float* __restrict__ logsumexp,
+__global__ __launch_bounds__(SMALL_THREADS) void predict_small(FcArgs a, int range, const float* __restrict__ logsumexp,
                                                                          uint16_t* __restrict__ P, int64_t ldp) {
     typedef SmallShape<NB> S;
     __shared__ __attribute__((aligned(16))) float lds[S::LDS_FLOATS];
@@ -1374,7 +1361,7 @@ __global__ __launch_bounds__(SmallShape<NB>::THREADS) void predict_small(FcArgs 
 }
 
 template <int NB>
-__global__ __launch_bounds__(SmallShape<NB>::THREADS) void top1_small(FcArgs a, int range, float* __restrict__ part_val,
+__global__ __launch_bounds__(SMALL_THREADS) void top1_small(FcArgs a, int range, float* __restrict__ part_val,
                                                                       int* __restrict__ part_cls) {
     typedef SmallShape<NB> S;
     __shared__ __attribute__((aligned(16))) float lds[S::LDS_FLOATS];
@@ -1474,7 +1461,7 @@ __global__ __launch_bounds__(NTHREADS, 4) void dz_block(FcArgs a, const float* _
                                                         uint16_t* __restrict__ dZ, int64_t ldz, float* __restrict__ db_part, XtArgs xt) {
     __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
     if ((int)blockIdx.x >= xt.first_block) {
-        transpose_x_tiles<NTHREADS>(a, xt, (int)blockIdx.x - xt.first_block, lds);
+        transpose_x_tiles(a, xt, (int)blockIdx.x - xt.first_block, lds);
         return;
     }
     const LogitsBlock t(a);
@@ -1993,8 +1980,8 @@ static inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<u
 constexpr int COMBINE_MEAN_ROWS = 1792;
 #define WS_LAUNCH_SMALL(kid, name, plan, grid, stream, ...)                                                   \
     do {                                                                                                      \
-        if ((plan).rows == 16) WS_LAUNCH(kid, name<1>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__); \
-        else WS_LAUNCH(kid, name<2>, dim3(grid), dim3((plan).threads), stream, __VA_ARGS__);                  \
+        if ((plan).rows == 16) WS_LAUNCH(kid, name<1>, dim3(grid), dim3(SMALL_THREADS), stream, __VA_ARGS__); \
+        else WS_LAUNCH(kid, name<2>, dim3(grid), dim3(SMALL_THREADS), stream, __VA_ARGS__);                  \
     } while (0)
 // Predictions and arg-max add the products of a logit in the order of the step, whatever kernels the step runs.
 static void set_step_order(FcArgs& a) {
