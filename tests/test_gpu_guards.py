@@ -4,8 +4,9 @@ Each output (and the workspace, sized exactly as the size query says) sits insid
 whose surroundings, and the padding columns of pitched matrices, hold a byte pattern.  After the calls
 the pattern must be intact everywhere outside the payload, and the payload must equal, bit for bit,
 what the same calls produce into plain buffers.  The shapes cover launches of thin tiles only, of
-full tiles only and of both, with ragged row and class counts (where a tile hangs over the edge of
-its output), and the small-batch kernels of each number of rows."""
+full tiles only and of both, of lists and of 64 x 64 tiles, with ragged row and class counts (where a tile
+hangs over the edge of its output), and the small-batch kernels of each number of rows; test_plan.py checks
+that they do."""
 import numpy as np
 import pytest
 
@@ -34,18 +35,21 @@ def _bits(t):
 
 
 SHAPES = [
-    ("thin tiles only", 300, 64, 1000),
+    ("64 x 64 tiles", 300, 64, 1000),
+    ("thin tiles only", 300, 192, 7001),
     ("full tiles only", 300, 64, 17925),
-    ("full and thin tiles", 513, 64, 23057),
-    ("five batch tiles", 1100, 128, 14000),
+    ("forward on full and thin tiles, dz in lists", 513, 64, 23057),
+    ("full and thin tiles", 513, 192, 23057),
+    ("lists, five batch tiles", 1100, 128, 14000),
+    ("lists, nine k-steps", 300, 576, 12001),
     ("dW in full and thin tiles", 300, 1024, 17925),
     ("dW in thin tiles, long contraction", 3100, 320, 600),
     ("dW stream", 257, 320, 33111),
     ("two rows", 2, 64, 777),
     ("16 rows", 16, 192, 1001),
     ("20 rows", 20, 576, 4099),
-    ("64 rows", 64, 448, 9999),
-    ("64 rows, step on tiles", 61, 64, 777),
+    ("64 x 64 tiles, 64 rows", 64, 448, 9999),
+    ("64 x 64 tiles, 61 rows", 61, 64, 777),
 ]
 
 

@@ -211,25 +211,34 @@ def test_run_twice_bit_identical(H):
         assert np.array_equal(a["dW"][i], b["dW"][i]) and np.array_equal(a["db"][i], b["db"][i])
 
 
-@pytest.mark.parametrize("B,D,C", [(256, 1024, 4096 + 37), (256, 1024, 256 * 272 + 37), (16, 1024, 4096 + 37),
-                                   (32, 576, 8192 + 37), (64, 1024, 9001)],
-                         ids=["thin-tiles", "mixed-tiles", "16-rows", "32-rows", "64-rows"])
+RECOMPUTE_SHAPES = {                     # forward and backward; predictions and arg-max in 64 x 64 tiles or wide ones
+    "64x64-tiles": (256, 1024, 4096 + 37),
+    "mixed-tiles": (256, 1024, 256 * 272 + 37),
+    "thin-tiles": (256, 1024, 10005),
+    "lists-of-rests": (300, 1024, 12001),
+    "lists-of-whole-tiles": (256, 512, 256 * 340 + 37),
+    "16-rows": (16, 1024, 4096 + 37),
+    "32-rows": (32, 576, 8192 + 37),
+    "32-rows-small-batch": (32, 576, 8192),
+    "64-rows": (64, 1024, 9001),
+}
+
+
+@pytest.mark.parametrize("B,D,C", RECOMPUTE_SHAPES.values(), ids=RECOMPUTE_SHAPES)
 def test_recomputed_logits_are_the_forward_logits_bit_for_bit(H, B, D, C):
     """The backward call recomputes the logits; they must be the forward call's, bit for bit, whichever
     kind of tile computed them.  Two chains of exact comparisons, all through the C ABI:
 
-    fp32, exact: a shard's row_max from the forward call (thin tiles, or full and thin mixed) equals the
-    best logit the arg-max call reports (full tiles only), and with every label set to that arg-max class
-    the label logit equals both.
+    fp32, exact: a shard's row_max from the forward call equals the best logit the arg-max call reports, and
+    with every label set to that arg-max class the label logit equals both.
 
     dz, exact at bf16: with B <= D / 2, features [D/2 + i] = 1 in row i only, dW[c, D/2 + i] is
     dz[i, c] itself (one non-zero term, a bf16 number times 1).  With g = 1 it must equal, off the label,
-    the prediction exp(z - lse) that the predictions call (full tiles only) writes for the same lse.  The
-    other D / 2 features are random, so the logits are sums whose rounding depends on the order of the
-    contraction: one differing fp32 bit flips a bf16 rounding once in ~2^16 elements, and there are 1e6
-    (thin) or 1.8e7 (mixed) of them.
+    the prediction exp(z - lse) that the predictions call writes for the same lse.  The other D / 2 features are random, so the logits are sums whose rounding depends on the order of the
+    contraction: one differing fp32 bit flips a bf16 rounding once in ~2^16 elements, and there are 1e6 to
+    2.2e7 of them in the larger shapes.
 
-    The small batches here have shapes for which all four calls take the small-batch kernels."""
+    Tiles of every kind add in one order, the small-batch kernels in one of their own: all four calls take those or none."""
     import torch
     from paper_2011_09208_amd import binding as ws
     p = inputs.make_inputs("recompute", B, D, C, x_sigma=1.0, w_sigma=0.05, bias_sigma=0.5, seed=C)

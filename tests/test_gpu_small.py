@@ -1,6 +1,6 @@
-"""GPU parity of the logits kernels for small batches (up to 64 rows and 2048 features: statistics, dz, probabilities,
+"""GPU parity of the logits kernels for small batches (up to 32 rows and 2048 features: statistics, dz, probabilities,
 arg-max) at the edges of their 16-row blocks, of the 32 classes they take at a time and of the workgroups' ranges, and
-with contractions shorter and longer than one round of their waves."""
+with contractions shorter and longer than one round of their waves; and of batches of up to 65 rows, which take 64 x 64 tiles."""
 import numpy as np
 import pytest
 
@@ -15,20 +15,22 @@ SHAPES = [                               # B, D, widths
     (17, 576, [31, 64, 1]),              # nine; the second 16-row block has one row
     (31, 128, [97]),
     (32, 1088, [700, 65]),               # seventeen k-steps
-    (33, 1024, [63, 129]),               # sixteen; the 64-row kernels, four waves
+    (33, 1024, [63, 129]),               # sixteen; here and below, with 33 rows or more, 64 x 64 tiles
     (64, 192, [1000]),
     (5, 128, [256 * 32, 256 * 32 + 1]),  # 256 ranges of 32 classes; ranges of 40, walked 32 and 8
-    (20, 64, [256 * 57 + 3]),            # ranges of 64, the last 35 classes
-    (64, 2048, [256 * 64 + 1]),          # all registers full; ranges of 72: 32, 32, 8
-    (65, 192, [1000]),                   # one row too many: the wide tiles
-    (40, 2112, [300]),                   # one k-step too many
-    # either side of the lines between these kernels and the tiles (33 rows or more: by classes and features)
-    (40, 704, [6000, 6150]),             # the step on tiles and here, probabilities and arg-max here
-    (64, 1024, [24576, 24577]),          # 3 turns of 32 classes to a workgroup; 4: the step on tiles
-    (33, 192, [24576, 24577]),           # 3 turns; 4: all on tiles
-    (50, 64, [256 * 48, 256 * 97]),      # probabilities and arg-max here, the step on tiles; all on tiles
-    (36, 768, [256 * 256 + 9]),          # 257 tiles: a thin round
-    (20, 128, [256 * 224, 256 * 224 + 1]),   # probabilities: 7 turns of 32 classes, and 8 on tiles
+    (20, 64, [256 * 57 + 3]),            # too many classes for more than 16 rows: 64 x 64 tiles
+    (12, 64, [256 * 57 + 3]),            # ranges of 64, the last 35 classes
+    (64, 2048, [256 * 64 + 1]),
+    (16, 2048, [256 * 64 + 1]),          # all registers full; ranges of 72: 32, 32, 8
+    (65, 192, [1000]),
+    (40, 2112, [300]),
+    (16, 2112, [300]),                   # one k-step too many: 64 x 64 tiles
+    (40, 704, [6000, 6150]),
+    (64, 1024, [24576, 24577]),
+    (33, 192, [24576, 24577]),
+    (50, 64, [256 * 48, 256 * 97]),
+    (36, 768, [256 * 256 + 9]),
+    (20, 128, [256 * 224, 256 * 224 + 1]),   # the arg-max here, ranges of 224 and 232, the rest in 64 x 64 tiles
 ]
 
 

@@ -161,3 +161,43 @@ def test_arg_max_of_short_contractions(rules, B, D, tiles, way):
     C = 64 * (tiles // ((B + 63) // 64))
     assert rules.way_(B, D, C, TOP1) == way
     assert rules.way_(B, D, C, PROBS) == (BLOCKS if tiles <= 1024 or B <= 64 else TILES)
+
+
+def test_shapes_of_the_guard_band_tests(rules):
+    """The kernels that the tags of test_gpu_guards.py name (the logits; the others are about dW)."""
+    from tests.test_gpu_guards import SHAPES
+    want = {"64 x 64 tiles": (BLOCKS, BLOCKS), "thin tiles only": (TILES, TILES), "full tiles only": (TILES, TILES),
+            "forward on full and thin tiles, dz in lists": (LISTS, TILES), "full and thin tiles": (TILES, TILES),
+            "lists, five batch tiles": (LISTS, LISTS), "lists, nine k-steps": (LISTS, LISTS), "two rows": (SMALL, SMALL),
+            "16 rows": (SMALL, SMALL), "20 rows": (SMALL, SMALL), "64 x 64 tiles, 64 rows": (BLOCKS, BLOCKS),
+            "64 x 64 tiles, 61 rows": (BLOCKS, BLOCKS)}
+    tiles = {"thin tiles only": range(1, 65), "full tiles only": range(65, 257), "full and thin tiles": range(257, 321),
+             "forward on full and thin tiles, dz in lists": range(257, 321)}
+    shapes = {s[0]: s[1:] for s in SHAPES}
+    for tag, ways in want.items():
+        B, D, C = shapes[tag]
+        assert (rules.way_(B, D, C, STEP), rules.way_(B, D, C, FORWARD)) == ways, tag
+        if tag in tiles:
+            assert (B + 255) // 256 * ((C + 255) // 256) in tiles[tag], tag
+
+
+def test_shapes_of_the_recompute_tests(rules):
+    from tests.test_gpu_parity import RECOMPUTE_SHAPES
+    want = {"64x64-tiles": (BLOCKS, BLOCKS, BLOCKS), "mixed-tiles": (TILES, TILES, TILES), "thin-tiles": (TILES, BLOCKS, BLOCKS),
+            "lists-of-rests": (LISTS, BLOCKS, BLOCKS), "lists-of-whole-tiles": (LISTS, TILES, TILES), "16-rows": (SMALL,) * 3,
+            "32-rows": (BLOCKS,) * 3, "32-rows-small-batch": (SMALL,) * 3, "64-rows": (BLOCKS,) * 3}
+    for name, shape in RECOMPUTE_SHAPES.items():
+        assert tuple(rules.way_(*shape, use) for use in (STEP, PROBS, TOP1)) == want[name], name
+        assert rules.way_(*shape, FORWARD) == want[name][0], name
+
+
+def test_shapes_of_the_dx_tests(rules):
+    from tests.test_gpu_dx_splits import SHAPES
+    out, got = (ctypes.c_int * 4)(), set()
+    for B, D, widths in SHAPES:
+        for C in widths:
+            rules.dx_splits_(B, D, C, out)
+            tiles = D // 64 * ((B + 63) // 64) if out[0] else (D + 255) // 256 * ((B + 255) // 256)
+            got.add((out[0], tiles, out[1], out[2], (C + 63) // 64 - (out[1] - 1) * out[2]))
+    assert {(0, 20, 9, 16, 13), (0, 44, 4, 16, 13), (0, 72, 2, 20, 20), (0, 32, 5, 16, 15), (1, 1, 18, 4, 3), (1, 4, 29, 7, 4),
+            (1, 3, 14, 3, 2), (1, 33, 1, 21, 21), (1, 324, 1, 20, 20), (1, 312, 2, 21, 20), (1, 288, 1, 3, 3), (1, 10, 7, 3, 3)} <= got
