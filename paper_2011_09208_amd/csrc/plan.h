@@ -96,7 +96,9 @@ struct SmallPlan {
 // 32 classes (forward + dz, 64 x 64 tiles and here: B = 24, D = 2048, C = 4000: 12.9 + 13.2 and 12.0 + 12.1; C = 16 000: 13.9 + 14.9 and
 // 17.5 + 18.3; B = 32, D = 256, C = 50 000: 11.5 + 12.2 and 12.4 + 17.3), and the arg-max again where it has four, whose 64 x 64 tiles leave four times
 // as many candidates to merge (B = 24, D = 1024: C = 16 000: 10.9 and 12.0, C = 33 000: 20.3 and 18.9).
-// The forward and the backward call of a shard decide alike: the backward call's logits are the forward call's.
+// The forward and the backward call of a shard decide alike: the backward call's logits are the forward call's.  The forward call alone would
+// be quicker here from the second round of 64 x 64 tiles on, but dz loses more (B = 24, D = 256, forward and dz, 64 x 64 tiles against here: C =
+// 33 000: 1.0 slower and 4.0 quicker, C = 100 000: 3.7 and 10.0; D = 2048: 0.9 and 2.4, at 80 000 3.8 and 2.7).
 enum SmallUse { SMALL_STEP, SMALL_PROBS, SMALL_TOP1 };
 static bool small_batch(int32_t B, int32_t D, int32_t C, SmallUse use) {
     if (B > SMALL_MAX_ROWS || D > SMALL_MAX_STEPS * TILE_K) return false;
