@@ -271,13 +271,15 @@ def bridge_gather_args(dim, parts, out):
     other, dtype = out.shape[1 - dim], out.dtype
     ptrs, lds, ext = [], [], []
     for p in parts:
-        rows, cols = p.shape
+        shape = p.shape
+        assert len(shape) == 2 and p.dtype == dtype
+        rows, cols = shape
         ld, unit = p.stride()
-        assert p.dtype == dtype and (rows, cols)[1 - dim] == other
+        assert shape[1 - dim] == other
         assert cols <= 1 or unit == 1
         ptrs.append(p.data_ptr())
         lds.append(ld if rows > 1 else max(cols, ld))
-        ext.append((rows, cols)[dim])
+        ext.append(shape[dim])
     ptrs, lds, ext = (_p * n)(*ptrs), (_i64 * n)(*lds), (_i32 * n)(*ext)
     return (int(dim), ptrs, lds, ext, n, int(other), out.element_size(), _ptr(out), out.stride(0))
 

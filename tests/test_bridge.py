@@ -165,3 +165,13 @@ def test_bridge_argument_validation(ws):
     assert ws.lib.ws_bridge_fusable(-1, 2, a, 0, 2, a, ctypes.byref(ok)) == E["WS_ERR_RANGE"]
     neg = (ctypes.c_int64 * 2)(1, -2)
     assert ws.lib.ws_bridge_fusable(0, 2, neg, 0, 2, a, ctypes.byref(ok)) == E["WS_ERR_SHAPE"]
+
+
+def test_gather_refuses_parts_that_are_not_matrices_of_the_output(ws):
+    import torch
+    out = torch.empty((8, 4))
+    for part in (torch.empty(4), torch.empty((2, 4, 1)), torch.empty((8, 3)), torch.empty((8, 4), dtype=torch.bfloat16), torch.empty((4, 8)).t()):
+        with pytest.raises(AssertionError):
+            ws.bridge_gather_args(0, [part], out)
+    dim, ptrs, lds, ext, n, other, size, _, ld_out = ws.bridge_gather_args(0, [out[:1], out[1:]], out)
+    assert (list(lds), list(ext), n, other, size, ld_out) == ([4, 4], [1, 7], 2, 4, 4, 4)
