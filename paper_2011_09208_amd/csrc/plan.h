@@ -97,8 +97,9 @@ struct SmallPlan {
 // 17.5 + 18.3; B = 32, D = 256, C = 50 000: 11.5 + 12.2 and 12.4 + 17.3), and the arg-max again where it has four, whose 64 x 64 tiles leave four times
 // as many candidates to merge (B = 24, D = 1024: C = 16 000: 10.9 and 12.0, C = 33 000: 20.3 and 18.9).
 // The forward and the backward call of a shard decide alike: the backward call's logits are the forward call's.  The forward call alone would
-// be quicker here from the second round of 64 x 64 tiles on, but dz loses more (B = 24, D = 256, forward and dz, 64 x 64 tiles against here: C =
-// 33 000: 1.0 slower and 4.0 quicker, C = 100 000: 3.7 and 10.0; D = 2048: 0.9 and 2.4, at 80 000 3.8 and 2.7).
+// be quicker here from the second round of 64 x 64 tiles on up to some 1024 features, but dz loses more (B = 24, forward and backward calls, us, 64 x
+// 64 tiles and here, D = 256: C = 33 000: 10.9 + 21.1 and 10.3 + 24.3, C = 100 000: 20.2 + 44.7 and 18.1 + 52.3; D = 512: 26.1 + 71.6 and 22.2 + 78.3;
+// D = 2048: C = 33 000: 31.4 + 87.9 and 30.8 + 88.7, C = 100 000: 79.9 + 239.3 and 79.7 + 248.3).
 enum SmallUse { SMALL_STEP, SMALL_PROBS, SMALL_TOP1 };
 static bool small_batch(int32_t B, int32_t D, int32_t C, SmallUse use) {
     if (B > SMALL_MAX_ROWS || D > SMALL_MAX_STEPS * TILE_K) return false;

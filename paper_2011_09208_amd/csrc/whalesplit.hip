@@ -216,8 +216,7 @@ __device__ __forceinline__ void logits_thin(thin_acc_t& acc, const FcArgs& a, in
 
 // Forward statistics of a thin tile: every wave reduces its 32 classes per row, the eight waves'
 // pairs are merged through LDS in wave order.
-__device__ __forceinline__ void fwd_stats_thin(const FcArgs& a, const TileRef& r, char* lds,
-                                               float* __restrict__ part_max, float* __restrict__ part_sum,
+__device__ __forceinline__ void fwd_stats_thin(const FcArgs& a, const TileRef& r, char* lds, f32x2* __restrict__ parts,
                                                float* __restrict__ label_logit) {
     float* sbias = reinterpret_cast<float*>(lds);
     float* red_m = sbias + 256;            // [8][64]
@@ -268,9 +267,7 @@ __device__ __forceinline__ void fwd_stats_thin(const FcArgs& a, const TileRef& r
         float m = red_m[tid], s = red_s[tid];
 #pragma unroll
         for (int w = 1; w < 8; ++w) merge_ms(m, s, red_m[w * THIN_N + tid], red_s[w * THIN_N + tid]);
-        const int64_t o = (int64_t)r.ct * a.Bpad + row0 + tid;
-        part_max[o] = m;
-        part_sum[o] = s;
+        parts[(int64_t)r.ct * a.Bpad + row0 + tid] = f32x2{m, s};
     }
 }
 
@@ -411,8 +408,7 @@ struct LogitsEpilogue {
 
 struct FwdArgs {
     FcArgs a;
-    float* part_max;
-    float* part_sum;
+    f32x2* parts;
     float* label_logit;
 };
 
@@ -504,9 +500,7 @@ struct FwdEpilogue : LogitsEpilogue<FwdArgs> {
             for (int nt = 0; nt < NT; ++nt) {
                 const int row = WAVE_N * wn + 16 * nt + jl;
                 merge_ms(mx[nt], sum[nt], red[row], red[256 + row]);
-                const int64_t o = (int64_t)list.range * p->a.Bpad + list.n0 + row;
-                p->part_max[o] = mx[nt];
-                p->part_sum[o] = sum[nt];
+                p->parts[(int64_t)list.range * p->a.Bpad + list.n0 + row] = f32x2{mx[nt], sum[nt]};
                 if (list.range == 0 && row0() + 16 * nt + jl < p->a.B && label(nt, jl, p) < 0) p->label_logit[row0() + 16 * nt + jl] = 0.0f;
             }
         }
@@ -522,8 +516,7 @@ __global__ __launch_bounds__(NTHREADS) void fwd_logits_list(FwdArgs f) {
     gemm_tiles<KC, 0>(make_operand(a.W, a.ldw, a.C, a.D), make_operand(a.X, a.ldx, a.B, a.D), a.D / TILE_K, list, epi, lds);
 }
 
-__global__ __launch_bounds__(NTHREADS) void fwd_logits_stats(FcArgs a, float* __restrict__ part_max,
-                                                              float* __restrict__ part_sum,
+__global__ __launch_bounds__(NTHREADS) void fwd_logits_stats(FcArgs a, f32x2* __restrict__ parts,
                                                               float* __restrict__ label_logit) {
     __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
     float* sbias = reinterpret_cast<float*>(lds);          // reused after the main loop
@@ -532,7 +525,7 @@ __global__ __launch_bounds__(NTHREADS) void fwd_logits_stats(FcArgs a, float* __
     const TileRef ref = logits_tile_ref(a);
     if (!ref.valid) return;
     if (ref.piece >= 0) {
-        fwd_stats_thin(a, ref, lds, part_max, part_sum, label_logit);
+        fwd_stats_thin(a, ref, lds, parts, label_logit);
         return;
     }
     const int ct = ref.ct, bt = ref.bt;
@@ -589,37 +582,40 @@ __global__ __launch_bounds__(NTHREADS) void fwd_logits_stats(FcArgs a, float* __
     if (tid < 256) {
         float m = red_m[tid], s = red_s[tid];
         merge_ms(m, s, red_m[256 + tid], red_s[256 + tid]);
-        const int64_t o = (int64_t)ct * a.Bpad + bt * TILE_N + tid;
-        part_max[o] = m;
-        part_sum[o] = s;
+        parts[(int64_t)ct * a.Bpad + bt * TILE_N + tid] = f32x2{m, s};
     }
 }
 
 // Loads of a merge kernel's thread in flight: a chain of them, one per 64 tiles, is what bounds these kernels.
 constexpr int MERGE_BATCH = 8;
 
-// One workgroup merges the class-tile partials of 16 rows: thread (r, q) folds tiles q, q + 64, ...
-// of row r online, then the 64 partial pairs of a row are merged through LDS in a fixed order
+// One workgroup merges the class-tile partials, pairs (max, sum-exp), of MERGE_ROWS rows: thread (r, q) folds tiles q, q + 64, ...
+// of row r, a batch of them at a time, then the 64 partial pairs of a row are merged through LDS in a fixed order
 // (8 groups of 8, then the 8 group results).
-__global__ __launch_bounds__(1024) void merge_class_tiles(const float* __restrict__ part_max,
-                                                           const float* __restrict__ part_sum, int nCT, int Bpad,
-                                                           int B, float* __restrict__ row_max,
-                                                           float* __restrict__ row_sumexp) {
-    __shared__ float sm[64][16], ss[64][16];
-    const int r = threadIdx.x & 15, q = threadIdx.x >> 4;
-    const int i = blockIdx.x * 16 + r;          // < Bpad: the partial arrays are padded to whole tiles
+// Bound by issuing exponentials where few rows have many partials, one for every 64 classes of up to 64 rows: so one for each pair and
+// a batch's sum so far, and eight rows to a workgroup.  With two for each pair and 16 rows 17 to 32 rows x 125 000 classes took
+// 3.9 us in here beyond the cost of a launch, with one 2.5, with one and eight rows 1.1, with four rows 1.4; 64 rows 4.0, 2.5, 1.4
+// and 2.1; 256 rows on more features, whose partials are one for 256 classes, the same either way.
+constexpr int MERGE_ROWS = 8;
+__global__ __launch_bounds__(64 * MERGE_ROWS) void merge_class_tiles(const f32x2* __restrict__ parts, int nCT, int Bpad, int B,
+                                                               float* __restrict__ row_max, float* __restrict__ row_sumexp) {
+    __shared__ float sm[64][MERGE_ROWS], ss[64][MERGE_ROWS];
+    const int r = threadIdx.x % MERGE_ROWS, q = threadIdx.x / MERGE_ROWS;
+    const int i = blockIdx.x * MERGE_ROWS + r;        // < Bpad: the partial arrays are padded to whole tiles
     float m = NEG_INF, s = 0.0f;
     for (int t0 = q; t0 < nCT; t0 += 64 * MERGE_BATCH) {
-        float vm[MERGE_BATCH], vs[MERGE_BATCH];
+        f32x2 v[MERGE_BATCH];
 #pragma unroll
         for (int k = 0; k < MERGE_BATCH; ++k)
-            if (t0 + 64 * k < nCT) {
-                vm[k] = part_max[(int64_t)(t0 + 64 * k) * Bpad + i];
-                vs[k] = part_sum[(int64_t)(t0 + 64 * k) * Bpad + i];
-            }
+            v[k] = t0 + 64 * k < nCT ? parts[(int64_t)(t0 + 64 * k) * Bpad + i] : f32x2{NEG_INF, 0.0f};
+        float top = m;
 #pragma unroll
-        for (int k = 0; k < MERGE_BATCH; ++k)
-            if (t0 + 64 * k < nCT) merge_ms(m, s, vm[k], vs[k]);
+        for (int k = 0; k < MERGE_BATCH; ++k) top = fmaxf(top, v[k][0]);
+        const float from = top == NEG_INF ? 0.0f : top;          // of empty pairs only: their exponentials are zeros
+        s *= __expf(m - from);
+#pragma unroll
+        for (int k = 0; k < MERGE_BATCH; ++k) s += v[k][1] * __expf(v[k][0] - from);
+        m = top;
     }
     sm[q][r] = m;
     ss[q][r] = s;
@@ -1248,8 +1244,7 @@ __device__ __forceinline__ void small_range(const FcArgs& a, int range, int wg, 
 }
 
 template <int NB>
-__global__ __launch_bounds__(SMALL_THREADS) void fwd_stats_small(FcArgs a, int range, float* __restrict__ part_max,
-                                                                           float* __restrict__ part_sum,
+__global__ __launch_bounds__(SMALL_THREADS) void fwd_stats_small(FcArgs a, int range, f32x2* __restrict__ parts,
                                                                            float* __restrict__ label_logit) {
     typedef SmallShape<NB> S;
     __shared__ __attribute__((aligned(16))) float lds[S::LDS_FLOATS];
@@ -1277,10 +1272,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void fwd_stats_small(FcArgs a, int r
     });
 #pragma unroll
     for (int w = S::TPR / 2; w > 0; w >>= 1) merge_ms(mx, sum, lane_xor(mx, w), lane_xor(sum, w));
-    if (j == 0) {
-        part_max[(int)blockIdx.x * S::ROWS + row] = mx;
-        part_sum[(int)blockIdx.x * S::ROWS + row] = sum;
-    }
+    if (j == 0) parts[(int)blockIdx.x * S::ROWS + row] = f32x2{mx, sum};
     if (found || (blockIdx.x == 0 && j == 0 && row_ok && !in_shard)) label_logit[row] = label;
 }
 
@@ -1416,8 +1408,8 @@ struct LogitsBlock {
     }
 };
 
-__global__ __launch_bounds__(NTHREADS, 4) void fwd_stats_block(FcArgs a, int pitch, float* __restrict__ part_max,
-                                                               float* __restrict__ part_sum, float* __restrict__ label_logit) {
+__global__ __launch_bounds__(NTHREADS, 4) void fwd_stats_block(FcArgs a, int pitch, f32x2* __restrict__ parts,
+                                                               float* __restrict__ label_logit) {
     __shared__ __attribute__((aligned(16))) char lds[BLOCK_LDS_BYTES];
     const LogitsBlock t(a);
     if (t.cb < 0) return;
@@ -1451,8 +1443,7 @@ __global__ __launch_bounds__(NTHREADS, 4) void fwd_stats_block(FcArgs a, int pit
     __syncthreads();
     if (t.wave < 4 && t.g == 0) {
         merge_ms(mx, s, red[r], red[BLOCK + r]);
-        part_max[(int64_t)t.cb * pitch + t.row] = mx;
-        part_sum[(int64_t)t.cb * pitch + t.row] = s;
+        parts[(int64_t)t.cb * pitch + t.row] = f32x2{mx, s};
     }
 }
 
@@ -2133,26 +2124,24 @@ static int launch_fwd(const void* X, int64_t ldx, const void* W_shard, int64_t l
     a.ranges = step.ranges;
     LogitsPlan p = plan_forward(B, D, C_shard, step);
     if (workspace_bytes < p.bytes()) p = plan_wide(B, C_shard);
-    float* part_max = static_cast<float*>(workspace);
-    float* part_sum = part_max + p.parts * p.pitch;
-    const int parts = (int)p.parts, pitch = (int)p.pitch;
+    f32x2* parts = static_cast<f32x2*>(workspace);
+    const int n_parts = (int)p.parts, pitch = (int)p.pitch;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (p.way == WAY_SMALL) {
         const SmallPlan sp(B, C_shard);
-        WS_LAUNCH_SMALL(KID_FWD, fwd_stats_small, sp, sp.ranges, s, a, sp.range, part_max, part_sum, label_logit);
+        WS_LAUNCH_SMALL(KID_FWD, fwd_stats_small, sp, sp.ranges, s, a, sp.range, parts, label_logit);
     } else if (p.way == WAY_BLOCKS) {
-        WS_LAUNCH(KID_FWD, fwd_stats_block, dim3(xcd_grid(parts * (pitch / BLOCK))), dim3(NTHREADS), s, a, pitch, part_max, part_sum,
-                  label_logit);
+        WS_LAUNCH(KID_FWD, fwd_stats_block, dim3(xcd_grid(n_parts * (pitch / BLOCK))), dim3(NTHREADS), s, a, pitch, parts, label_logit);
     } else if (p.way == WAY_LISTS) {
         WS_LAUNCH(KID_FWD, fwd_logits_list, dim3(list_grid(a.ranges, a.nBT)), dim3(NTHREADS), s,
-                  (FwdArgs{a, part_max, part_sum, label_logit}));
+                  (FwdArgs{a, parts, label_logit}));
     } else {
         a.plan = plan_tiles(a.nBT * a.nCT, LOGITS_MAX_THIN_TAIL);
-        WS_LAUNCH(KID_FWD, fwd_logits_stats, dim3(a.plan.thin_first + a.plan.n_thin), dim3(NTHREADS), s, a, part_max,
-                  part_sum, label_logit);
+        WS_LAUNCH(KID_FWD, fwd_logits_stats, dim3(a.plan.thin_first + a.plan.n_thin), dim3(NTHREADS), s, a, parts,
+                  label_logit);
     }
-    WS_LAUNCH(KID_MERGE, merge_class_tiles, dim3((B + 15) / 16), dim3(1024), s, part_max, part_sum, parts, pitch, B, row_max,
-              row_sumexp);
+    WS_LAUNCH(KID_MERGE, merge_class_tiles, dim3((B + MERGE_ROWS - 1) / MERGE_ROWS), dim3(64 * MERGE_ROWS), s, parts, n_parts, pitch, B,
+              row_max, row_sumexp);
     return launch_status();
 }
 

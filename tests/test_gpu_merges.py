@@ -1,6 +1,7 @@
 """GPU parity of the kernels that merge statistics across shards, at the batch and workgroup edges of their loops:
-combine_partials loads eight shards at a time, merge_top1 deals candidates to 64 threads per row and 16 rows per
-workgroup, or one thread to a row for up to twelve candidates."""
+combine_partials loads eight shards at a time, merge_class_tiles eight partials for each of 64 threads per row, 8 rows per
+workgroup, merge_top1 deals candidates to 64 threads per row and 16 rows per workgroup, or one thread to a row for up to
+twelve candidates."""
 import numpy as np
 import pytest
 
@@ -75,3 +76,26 @@ def test_mean_in_the_combine_launch(B, S):
     assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
     loss = out[1].double()
     assert (mean.double() - loss.mean()).abs() <= 2.0 ** -24 * (12 + B / 1024) * loss.abs().mean()
+
+
+@pytest.mark.parametrize("B,parts", [(1, 1), (17, 129), (24, 511), (33, 512), (40, 513), (63, 65), (64, 1025), (17, 1100)])
+def test_forward_statistics_of_many_partial_results(ws, B, parts):
+    """64 x 64 tiles (one row: the small-batch kernel): a partial result for every 64 classes, the last of them of three.  Small integers, so the
+    logits are exact; a sum is up to 8 logits of a lane, 3 merges in a tile, 8 of a batch's turns of 8 and 15 merges of 64 threads."""
+    import torch
+    D, C = 64, 64 * parts - 61
+    g = torch.Generator(device="cuda").manual_seed(parts)
+    X = torch.randint(-1, 2, (B, D), device="cuda", generator=g).to(torch.bfloat16)
+    W = torch.randint(-1, 2, (C, D), device="cuda", generator=g).to(torch.bfloat16)
+    bias = torch.zeros(C, device="cuda")
+    bias[64:192] = float("-inf")                                   # whole tiles without a class
+    y = torch.randint(0, min(C, 64), (B,), device="cuda", generator=g, dtype=torch.int32)
+    m, s, t = (torch.empty(B, device="cuda") for _ in range(3))
+    ws.split_fc_fwd(X, W, bias, y, 0, m, s, t, torch.empty(ws.fwd_workspace_bytes(B, D, C), dtype=torch.uint8, device="cuda"))
+    z = X.double() @ W.double().t() + bias.double()
+    top = z.max(1).values
+    assert torch.equal(m.double(), top) and torch.equal(t.double(), z.gather(1, y.long()[:, None])[:, 0])
+    ref = torch.exp(z - top[:, None]).sum(1)
+    # per term: an addition at each of up to 40 places, an exponential and its argument's rounding at each of up to 22
+    tol = 2.0 ** -24 * (40 + 22 * (2 + 2 * z[z > -1e9].abs().max()))
+    assert ((s.double() - ref).abs() <= tol * ref).all()
