@@ -151,14 +151,17 @@ struct BwdPlan {
 // A W that the 256 MiB Infinity Cache does not hold comes from HBM, and the 128 bytes that a small tile takes of each of its rows cost more
 // there: wide tiles (backward call, us, wide and small, D = 2048: B = 64, C = 62 000, 254 MB 158.1 and 152.3, C = 70 000, 287 MB 172.2 and 180.4;
 // B = 24, C = 80 000: 181.7 and 192.7, with the fused update 250.7 and 277.0; D = 1536, B = 32, C = 80 000, 246 MB 136.1 and 133.1, C = 90 000, 276 MB
-// 155.3 and 159.8).
+// 155.3 and 159.8).  Unless more than 1 / 32 of the wide tiles is padding, which cuts their reading short as well (275 to 430 MB, wide over small, backward
+// call and fused update: D = 1088, a fifth tile for 64 features, 1.03 to 1.09 and 1.01 to 1.07; 1600, a seventh, 1.02 to 1.10 and 1.00 to 1.05; 1728, 192
+// of a seventh, 1.00 to 1.08 and 0.99 to 1.04; 1984, 192 of an eighth, 0.97 to 1.05 and 0.93 to 1.00; whole tiles, D = 1024 to 2048, 0.93 to 1.03 and
+// 0.91 to 1.02, but 1280 features, 41 and 64 rows, 275 MB 1.07).
 constexpr int ONE_LAUNCH_NS = 4000;
 static void dx_splits(BwdPlan& p, int32_t B, int32_t D, int32_t C) {
     const int64_t sum_turns = ((int64_t)B * (D / 4) + SIDE_BLOCKS * NTHREADS - 1) / (SIDE_BLOCKS * NTHREADS);   // of the side job's threads
     const int64_t sum_cost = 2 * ((int64_t)B * D * 4) / 4500 + sum_turns * 1000 / 16;                            // of a split
-    const bool w_fits_cache = (int64_t)C * D * 2 <= INFINITY_CACHE_BYTES;
+    const bool wide_only = (int64_t)C * D * 2 > INFINITY_CACHE_BYTES && 32 * (TILE_N * (int64_t)p.nDT - D) <= TILE_N * (int64_t)p.nDT;
     int64_t best = -1;
-    for (int small = 0; small < (w_fits_cache ? 2 : 1); ++small) {
+    for (int small = 0; small < (wide_only ? 1 : 2); ++small) {
         const int64_t tiles = small ? (int64_t)(D / BLOCK) * (round_up(B, BLOCK) / BLOCK) : (int64_t)p.nDT * p.nBT;
         const int room = small ? 512 : 256, most = std::min(tiles >= room ? 1 : (int)((room + tiles - 1) / tiles), p.steps_total);
         // from one number of splits to the next that makes them shorter, as long as their sum alone does not cost more

@@ -110,7 +110,7 @@ def test_splits_of_dx_are_the_cheapest(rules):
         rules.dx_splits_(B, D, C, out)
         total, best = (C + 63) // 64, None
         turns_of_the_sum = -(-B * (D // 4) // (128 * 512))
-        for small in (0, 1) if 2 * C * D <= 2 ** 28 else (0,):
+        for small in (0,) if 2 * C * D > 2 ** 28 and 32 * (-D % 256) <= D + -D % 256 else (0, 1):
             tiles = D // 64 * -(-B // 64) if small else -(-D // 256) * -(-B // 256)
             room = 512 if small else 256
             for want in range(1, min(max(1, -(-room // tiles)), total) + 1):
@@ -122,6 +122,16 @@ def test_splits_of_dx_are_the_cheapest(rules):
                     best = (cost, small, splits, steps)
         assert (out[0], out[1], out[2]) == best[1:], (B, D, C)
         assert (out[1] - 1) * out[2] < total <= out[1] * out[2]
+
+
+def test_dx_of_a_large_w_and_padded_features_runs_in_small_tiles(rules):
+    """W beyond the Infinity Cache: wide tiles, unless more than 1 / 32 of them is padding of the features."""
+    out = (ctypes.c_int * 4)()
+    for B in (24, 64):
+        for D, small in [(1024, 0), (1088, 1), (1280, 0), (1600, 1), (1728, 1), (1920, 1), (1984, 0), (2048, 0), (3008, 0)]:
+            for megabytes in (275, 430):
+                rules.dx_splits_(B, D, megabytes * 500000 // D, out)
+                assert out[0] == small, (B, D, megabytes)
 
 
 def test_short_lists_have_a_compute_unit_of_their_own(rules):
