@@ -305,13 +305,16 @@ static LogitsPlan plan_logits(int32_t B, int32_t D, int32_t C, SmallUse use) {
     }
     return p;
 }
-// The forward call: as the step, but a single k-step and a single round of wide tiles, or one with a tail of thin ones, are done
+// The forward call: as the step, but short contractions of a single round of wide tiles, or one with a tail of thin ones, are done
 // sooner by the tiles; dz, whose epilogue is longer, is not (forward, us, tiles and lists, D = 64: 114 tiles, B = 94, C = 29 001: 11.2 and
 // 12.0, dz 1.3 less; 297, B = 2303, C = 8376: 15.6 and 16.6; 312, B = 3002, C = 6596: 15.7 and 16.5; but 432, B = 4363, C = 6004: 19.3 and 18.5; two
-// k-steps, 110, B = 1100, C = 5377, and fewer: 12.3 to 13.3 and 11.7 to 12.8).  Both add the products of a logit in one order.
+// k-steps from some hundred tiles on: 110, B = 5631, C = 1128: 13.3 and 13.9; 126, B = 3522, C = 2073: 13.2 and 13.6; 300, B = 1410, C = 12 668: 16.9 and
+// 17.7, the backward call 56.8 and 55.4; 272, B = 4084, C = 4127: 17.4 and 19.1, 56.8 and 52.4; but 87, B = 617, C = 7172: 12.5 and 12.3; 429 20.4 and
+// 19.9; three k-steps: 106, B = 467, C = 13 349: 13.6 and 13.4).  Both add the products of a logit in one order.
 static LogitsPlan plan_forward(int32_t B, int32_t D, int32_t C, const LogitsPlan& step) {
     const int64_t tiles = round_up(B, TILE_N) / TILE_N * (round_up(C, TILE_M) / TILE_M);
-    return step.way == WAY_LISTS && D <= TILE_K && tiles <= LIST_WGS + LOGITS_MAX_THIN_TAIL ? plan_wide(B, C) : step;
+    const bool tiles_sooner = tiles <= LIST_WGS + LOGITS_MAX_THIN_TAIL && (D <= TILE_K || (D <= 2 * TILE_K && tiles > 100));
+    return step.way == WAY_LISTS && tiles_sooner ? plan_wide(B, C) : step;
 }
 
 // Direction in which the logits of class tile ct and batch tile bt (256 x 256) walk the features, a function of the shard's

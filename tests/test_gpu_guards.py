@@ -40,7 +40,8 @@ SHAPES = [
     ("full tiles only", 300, 64, 17925),
     ("forward on full and thin tiles, dz in lists", 513, 64, 23057),
     ("full and thin tiles", 513, 192, 23057),
-    ("lists, five batch tiles", 1100, 128, 14000),
+    ("forward on full and thin tiles, dz in lists, five batch tiles", 1100, 128, 14000),
+    ("lists, five batch tiles", 1100, 128, 17000),
     ("lists, nine k-steps", 300, 576, 12001),
     ("dW in full and thin tiles", 300, 1024, 17925),
     ("dW in thin tiles, long contraction", 3100, 320, 600),

@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 SHAPES = [                               # B, D, C
     (70, 64, 256 * 65 - 40),             # 1 batch tile, 65 class tiles, 1 k-step; rests of 2 and 3 units; the forward call on tiles
     (257, 64, 256 * 33 - 7),             # 2; 66 tiles; the same
-    (300, 128, 256 * 129),               # 2; a whole tile, 8 workgroups of 128 columns with a rest of one unit
+    (300, 128, 256 * 129),               # 2; a whole tile, 8 workgroups of 128 columns with a rest of one unit; the forward call on tiles
+    (300, 128, 256 * 161),               # 2; a whole tile and rests of 2 and 3 units
     (513, 1088, 256 * 40),               # 3; 17 k-steps, rests of 3 and 4
     (600, 64, 256 * 170 + 33),           # 3; two whole tiles
     (700, 576, 256 * 86 + 65),           # 3; 9 k-steps, 261 tiles: wide ones, the last 5 as thin tiles
@@ -21,7 +22,7 @@ SHAPES = [                               # B, D, C
     (1000, 576, 256 * 136),              # 4; 544 and a tail of 32: lists
     (1000, 576, 256 * 137),              # 548, one of 36: tiles
     (1000, 192, 256 * 17 + 1),           # 4; 72 tiles, 3 k-steps
-    (1100, 128, 256 * 21 + 1),           # 5: a block of four and one
+    (1100, 128, 256 * 21 + 1),           # 5: a block of four and one; the forward call on tiles
     (1400, 192, 256 * 13 - 100),         # 6
     (1700, 64, 2600),                    # 7; the forward call on tiles
     (2100, 64, 256 * 40 - 31),           # 9: two blocks and one

@@ -146,7 +146,8 @@ def test_short_lists_have_a_compute_unit_of_their_own(rules):
 
 
 def test_the_forward_call_of_a_short_contraction_runs_a_single_round_on_tiles(rules):
-    for B, D, C, way in [(94, 64, 29001, TILES), (94, 128, 29001, LISTS), (2303, 64, 8376, TILES), (4363, 64, 6004, LISTS)]:
+    for B, D, C, way in [(94, 64, 29001, TILES), (94, 128, 25601, TILES), (94, 128, 25600, LISTS), (94, 192, 29001, LISTS), (2303, 64, 8376, TILES),
+                         (4363, 64, 6004, LISTS), (1280, 128, 16384, TILES), (1281, 128, 14000, LISTS)]:
         assert rules.way_(B, D, C, STEP) == LISTS and rules.way_(B, D, C, FORWARD) == way, (B, D, C)
     for B, D, C in drawn(10000, seed=7):
         step, forward = rules.way_(B, D, C, STEP), rules.way_(B, D, C, FORWARD)
@@ -157,7 +158,7 @@ def test_shapes_of_the_list_tests_run_lists(rules):
     """Which of the shapes of test_gpu_list.py (a whole shard) run lists, both ways or dz alone: their tests must not lose them unnoticed."""
     from tests.test_gpu_list import SHAPES
     tiles = {(700, 576, 22081), (1000, 576, 35072), (33000, 64, 500)}
-    dz_alone = {(70, 64, 16600), (257, 64, 8441), (1700, 64, 2600)}
+    dz_alone = {(70, 64, 16600), (257, 64, 8441), (1700, 64, 2600), (300, 128, 33024), (1100, 128, 5377)}
     for shape in SHAPES:
         step, forward = rules.way_(*shape, STEP), rules.way_(*shape, FORWARD)
         assert step == (TILES if shape in tiles else LISTS), shape
@@ -178,11 +179,12 @@ def test_shapes_of_the_guard_band_tests(rules):
     from tests.test_gpu_guards import SHAPES
     want = {"64 x 64 tiles": (BLOCKS, BLOCKS), "thin tiles only": (TILES, TILES), "full tiles only": (TILES, TILES),
             "forward on full and thin tiles, dz in lists": (LISTS, TILES), "full and thin tiles": (TILES, TILES),
-            "lists, five batch tiles": (LISTS, LISTS), "lists, nine k-steps": (LISTS, LISTS), "two rows": (SMALL, SMALL),
+            "forward on full and thin tiles, dz in lists, five batch tiles": (LISTS, TILES), "lists, five batch tiles": (LISTS, LISTS), "lists, nine k-steps": (LISTS, LISTS), "two rows": (SMALL, SMALL),
             "16 rows": (SMALL, SMALL), "20 rows": (SMALL, SMALL), "64 x 64 tiles, 64 rows": (BLOCKS, BLOCKS),
             "64 x 64 tiles, 61 rows": (BLOCKS, BLOCKS)}
     tiles = {"thin tiles only": range(1, 65), "full tiles only": range(65, 257), "full and thin tiles": range(257, 321),
-             "forward on full and thin tiles, dz in lists": range(257, 321)}
+             "forward on full and thin tiles, dz in lists": range(257, 321),
+             "forward on full and thin tiles, dz in lists, five batch tiles": range(257, 321)}
     shapes = {s[0]: s[1:] for s in SHAPES}
     for tag, ways in want.items():
         B, D, C = shapes[tag]

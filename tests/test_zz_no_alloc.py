@@ -52,7 +52,7 @@ def test_static_scratch_forward_two_calls_second_smaller():
         pytest.fail("GPU tests need a GPU; there is no CPU fallback")
     from tests import gpu_harness as H
     from paper_2011_09208_amd import binding as ws
-    _one_call(H, ws, torch, 1100, 128, 14000, 5000, seed=1)      # lists, 1.5 MB of scratch
+    _one_call(H, ws, torch, 1100, 128, 14000, 5000, seed=1)      # full and thin tiles, 1.4 MB of scratch
     _one_call(H, ws, torch, 300, 64, 1000, 700, seed=2)          # smaller: 64 x 64 tiles, stale partials around it
     # beyond the built-in scratch: refused on the host, nothing launched
     B, D, C = 8192, 64, 600_000
